@@ -200,11 +200,9 @@ size_t awq_linear_workspace_bytes(int64_t M, int64_t N, int64_t K, int group);
  *   y[m,n] = fp16( sum_k fp32(x[m,k]) * (q[n,k] - zero[n,k/128]) * scale[n,k/128] )
  * with fp32 accumulation.  x_f16 [M,K] fp16 row-major, already divided by s;
  * qweight/scales/zeros as written by awq_quantize_pack; y_f16 [M,N] fp16 row-major
- * (written).  M <= 16 takes the decode path (streams the packed weights once), 17..128 tokens
- * go through the decode kernels in blocks of 16 (one grouped launch where the shape allows it;
- * the last block is moved back to hold 16 tokens, so a few tokens are computed twice with
- * identical results), larger M the prefill path (MFMA tiles; with the workspace also from 49 tokens on where that
- * is estimated to be faster).  `workspace` may be NULL; if it is given where
+ * (written).  M <= 16 takes the decode path (streams the packed weights once), 17..128 tokens, and
+ * more where that is estimated to be faster, a tile kernel that cuts K over the waves of a workgroup and
+ * uses no workspace, larger M the prefill kernel (with the workspace also over K ranges).  `workspace` may be NULL; if it is given where
  * awq_linear_workspace_bytes() is not 0 it must hold that many bytes (AWQ_ERR_WORKSPACE_TOO_SMALL)
  * and be 16-byte aligned (AWQ_ERR_MISALIGNED); its contents are undefined afterwards.  Results with and without the workspace
  * differ by the order of the fp32 sums only. */
@@ -397,10 +395,9 @@ int awq_w3a16_linear_multi(const awq_linear_desc *descs, int count, int64_t M, i
  *             group t of the block at bits [2t, 2t+2).
  * Arguments, ownership and errors as for the 4-bit calls of the same name.  awq_unpack_w2 returns
  * codes u8[N,K], scales f16[N,K/64], zeros u8[N,K/64] (each optional).
- * awq_w2a16_linear: y = x' * dequant(q)^T with fp32 accumulation, any M >= 1, through the decode
- * kernel: more than 16 rows run as blocks of 16 rows, 128 rows per launch.  There is no 2-bit
- * matrix-matrix kernel, so the time grows with M/128 launches that each read the packed weights
- * again (sized for prompts of a few hundred tokens).  awq_w2a16_linear_multi: as awq_w4a16_linear_multi
+ * awq_w2a16_linear: y = x' * dequant(q)^T with fp32 accumulation, any M >= 1: up to 16 rows
+ * through the decode kernel, more through the tile kernel of awq_w4a16_linear, which reads the packed
+ * weights once per 128 rows at most.  awq_w2a16_linear_multi: as awq_w4a16_linear_multi
  * (1 <= M <= 16, up to AWQ_MULTI_MAX linears, eight per launch). */
 #define AWQ_GROUP_W2 64
 int awq_packed_sizes_w2(int64_t N, int64_t K, int group, size_t *qweight_bytes,

@@ -13,7 +13,7 @@ LIB = os.path.join(HERE, "libawq_mi355x.so")
 # test that runs the other kernel variants); the product is LIB, which reads no environment
 LIB_KNOBS = os.path.join(HERE, "libawq_mi355x_knobs.so")
 SOURCES = ["awq_api.hip", "awq_prep.hip", "awq_quantize.hip", "awq_gemv.hip", "awq_gemv_stream.hip", "awq_gemm.hip",
-           "awq_linear.hip", "awq_search.hip", "awq_w3.hip", "awq_w2.hip", "awq_attention.hip"]
+           "awq_linear.hip", "awq_tile.hip", "awq_search.hip", "awq_w3.hip", "awq_w2.hip", "awq_attention.hip"]
 
 COMMON = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -552,6 +552,13 @@ int awq_gemm_ksplit(int M, int N, int K, double *estimate_us)
     return best;
 }
 
+// The same estimate for the launch that does not cut K.
+double awq_gemm_unsplit_us(int M, int N, int K)
+{
+    const int64_t tiles = (int64_t)((N + BN - 1) / BN) * ((M + BM - 1) / BM);
+    return (double)((tiles + 255) / 256) * (4.0 + 1.4 * (K / AWQ_GROUP));
+}
+
 namespace {
 
 template <bool SPLIT>

@@ -936,7 +936,6 @@ __global__ __launch_bounds__(ROWS_THREADS) void gemv_rows_kernel(const GemvArgs<
     const int M = L.M, K = P.K, N = P.N, G = K >> 7, NRB = P.nrb, NB = (G + 3) >> 2;
     const int iters = P.plan >> 8;
     const bool split = (P.plan & 15) != 0;                 // rows split over the two units
-    const int m_first = (P.plan >> 4) & 15;                // token rows below this one are not written
     const int rows_per_step = split ? ROWS_CW : ROWS_UNITS * ROWS_CW;
     const int rb_first = ((int)blockIdx.x - wg0) * iters * rows_per_step + (split ? 0 : unit * ROWS_CW);
     // the unit's chunks [c0, c0 + NC)
@@ -1143,7 +1142,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void gemv_rows_kernel(const GemvArgs<
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int m = 4 * c4 + v;
-                if (m >= m_first && m < M) py[(size_t)m * N + rbo * 16 + r] = (half_t)acc[it][v];
+                if (m < M) py[(size_t)m * N + rbo * 16 + r] = (half_t)acc[it][v];
             }
         }
     }
@@ -1545,12 +1544,7 @@ int awq_gemv_chain_launch(const GemvProblem *const *problems, const GemvFusedExt
 // the cost of taking a chunk of x out of LDS is shared by that many jobs (measured: 1.5 us per job
 // with one step, 0.9 us with three).  The plan is the one with the smallest largest such estimate
 // among those with at most 256 workgroups.
-//
-// first_row (optional): per linear, the first token row whose outputs are written.  The sums are
-// taken chunk by chunk in an order that differs between workgroups, so two linears that share
-// weights and tokens need not agree in the last bit: a caller that lets token blocks overlap names
-// here the rows that the block in front has already written.
-int awq_gemv_rows_launch(const GemvProblem *problems, int count, int M, hipStream_t stream, const int *first_row)
+int awq_gemv_rows_launch(const GemvProblem *problems, int count, int M, hipStream_t stream)
 {
     if (count < 1 || count > GEMV_MAX_PROBLEMS || M < 1 || M > 16) return AWQ_ERR_BAD_ARGUMENT;
     struct Option {
@@ -1615,8 +1609,7 @@ int awq_gemv_rows_launch(const GemvProblem *problems, int count, int M, hipStrea
     int wg = 0;
     for (int e = 0; e < count; ++e) {
         GemvProblem p = problems[order[e]];
-        const int skip = first_row ? std::max(0, std::min(15, first_row[order[e]])) : 0;
-        p.plan = chosen[order[e]].split | (skip << 4) | (chosen[order[e]].iters << 8);
+        p.plan = chosen[order[e]].split | (chosen[order[e]].iters << 8);
         p.nrb = p.N / 16;
         L.wg_begin[e] = wg;
         L.p[e] = p;

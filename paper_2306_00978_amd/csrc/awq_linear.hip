@@ -1,8 +1,9 @@
-// awq_w4a16_linear: validation and dispatch between the decode (M <= 16) and the
-// prefill (M > 16) kernels.  AWQ Sec. 4.2: the same fused dequantization is used
+// awq_w4a16_linear: validation and dispatch between the decode kernels (M <= 16), the K-split tile kernel
+// (a few dozen to a few hundred tokens) and the prefill kernel.  AWQ Sec. 4.2: the same fused dequantization is used
 // by the matrix-vector and the matrix-matrix kernel.
 #include "awq_common.h"
 #include "awq_gemv_stream.h"
+#include "awq_tile.h"
 
 #include <stdlib.h>
 #include <algorithm>
@@ -18,8 +19,11 @@ int awq_gemm_launch(const void *x, const void *qweight, const void *scales, cons
 int awq_gemm_launch_split(const void *x, const void *qweight, const void *scales, const void *zeros,
                           void *y, int M, int N, int K, void *part, int ksplit, hipStream_t stream);
 int awq_gemm_ksplit(int M, int N, int K, double *estimate_us);
+double awq_gemm_unsplit_us(int M, int N, int K);
 
-// Only the prefill kernel at a few hundred tokens uses scratch: fp32 partial tiles of its K ranges.
+// Only the prefill kernel at a few hundred tokens uses scratch: fp32 partial tiles of its K ranges.  (The
+// tile kernel has taken over part of these shapes and needs none; the figure stays what callers size
+// their buffers by, and what decides which shapes the static entry point refuses.)
 extern "C" size_t awq_linear_workspace_bytes(int64_t M, int64_t N, int64_t K, int group)
 {
     if (awq_check_weight_shape(N, K, group) != AWQ_OK || M <= 48 || M > (int64_t)1 << 22) return 0;
@@ -34,10 +38,6 @@ extern "C" size_t awq_linear_workspace_bytes(int64_t M, int64_t N, int64_t K, in
         if (ks < 2 || split_us > 0.85 * blocked_us) return 0;
     }
     return ks > 1 ? (size_t)ks * (size_t)M * (size_t)N * sizeof(float) : 0;
-}
-
-namespace {
-int grouped_decode(const awq_linear_desc *descs, int count, int64_t M, int group, void *stream, bool token_blocks);
 }
 
 extern "C" int awq_w4a16_linear(const void *x_f16, const void *qweight, const void *scales,
@@ -77,31 +77,22 @@ extern "C" int awq_w4a16_linear(const void *x_f16, const void *qweight, const vo
         return awq_gemv_launch(x_f16, qweight, scales, zeros, y_f16, (int)M, (int)N, (int)K,
                                (hipStream_t)stream);
     }
-    // A few dozen tokens: the matrix-matrix kernel would run ceil(M/128) * N/256 tiles, a handful
-    // of CUs each walking all of K.  The decode kernel on blocks of 16 tokens reads the weights
-    // once per block (the repeats come from cache) but keeps the whole chip busy, all blocks in one
-    // grouped launch where the shape allows it.  The last block is moved back so that it has 16
-    // tokens too; the tokens it shares with its neighbour are computed twice, bit for bit alike.
-    // (4096 x 4096: 43 us -> 9-18 us for 17..128 tokens; 4096 x 11008: 105 us -> 20-43 us; when the
-    // caller brings its workspace, the prefill kernel with K cut into ranges takes over from 49
-    // tokens on: 36 us for that shape.)
-    static const int small_env = awq_knob("AWQ_SMALL_M_MAX", -1);
-    const int64_t small_max = small_env >= 0 ? std::min(small_env, 128) : 128;
-    if (M <= small_max && !split) {
-        const int blocks = (int)((M + 15) / 16);
-        awq_linear_desc d[8];
-        for (int b = 0; b < blocks; ++b) {
-            const int64_t m0 = b + 1 < blocks ? 16 * (int64_t)b : M - 16;
-            d[b].x_f16 = (const half_t *)x_f16 + m0 * K;
-            d[b].qweight = qweight;
-            d[b].scales = scales;
-            d[b].zeros = zeros;
-            d[b].y_f16 = (half_t *)y_f16 + m0 * N;
-            d[b].N = N;
-            d[b].K = K;
-        }
-        return grouped_decode(d, blocks, 16, group, stream, true);
-    }
+    // The prefill kernel's tiles are 128 x 256: at a few hundred tokens there are few of them, each
+    // walking a long K, and cutting K over workgroups costs a second pass over fp32 partial tiles.  The tile
+    // kernel cuts K over the waves of a workgroup and pays with more reads of x (a tile is at most 128 x 48
+    // or 96 x 64), so it wins until the prefill kernel fills the chip.  Up to 128 tokens always
+    // (11008 x 4096 at 77 tokens: 13.8 us against 23.1, 4096 x 11008 at 17: 11.5 against 20.9, 4096 x 4096
+    // at 128: 10.9 against 18.5); beyond, by the two estimates, the tile kernel's with 20 % on top (its
+    // large launches run at a lower clock than the small ones it was fitted to): 4096 x 4096 at 300 / 500
+    // tokens 19.2 / 28.5 us against 26.3 / 31.1; 4096 x 11008 at 300: 41 against 45, at 500: 62 against 55 and
+    // left to the prefill kernel.
+    const TilePlan plan = awq_tile_plan((int)M, (int)N, (int)K);
+    double gemm_us = 0.0;
+    if (split) (void)awq_gemm_ksplit((int)M, (int)N, (int)K, &gemm_us);
+    else gemm_us = awq_gemm_unsplit_us((int)M, (int)N, (int)K);
+    if (M <= 128 || 1.2 * plan.us < gemm_us)
+        return awq_tile_launch(4, plan, x_f16, qweight, scales, zeros, y_f16, (int)M, (int)N, (int)K,
+                               (hipStream_t)stream);
     if (split)
         return awq_gemm_launch_split(x_f16, qweight, scales, zeros, y_f16, (int)M, (int)N, (int)K, workspace,
                                      awq_gemm_ksplit((int)M, (int)N, (int)K, nullptr), (hipStream_t)stream);
@@ -163,15 +154,6 @@ extern "C" int awq_w4a16_linear_multi(const awq_linear_desc *descs, int count, i
                                       void *workspace, size_t workspace_bytes, void *stream)
 {
     (void)workspace; (void)workspace_bytes;
-    return grouped_decode(descs, count, M, group, stream, false);
-}
-
-namespace {
-
-// The grouped decode call.  token_blocks: the linears are blocks of 16 tokens of ONE linear (the
-// call comes from awq_w4a16_linear for 17..128 tokens), so the weights are the same for all.
-int grouped_decode(const awq_linear_desc *descs, int count, int64_t M, int group, void *stream, bool token_blocks)
-{
     if (!descs) return AWQ_ERR_NULL_POINTER;
     if (count < 1 || count > AWQ_MULTI_MAX) return AWQ_ERR_BAD_ARGUMENT;
     if (M <= 0 || M > 16) return AWQ_ERR_BAD_SHAPE;
@@ -196,20 +178,10 @@ int grouped_decode(const awq_linear_desc *descs, int count, int64_t M, int group
     // linears of the call in one launch.  A lone linear goes there only when it has row blocks
     // enough for every CU (measured at N = 32000, K = 4096, 16 tokens: 21.5 us against 41 us); a
     // smaller one stays with the batch kernel, where everything requested at once is the faster way
-    // through a small matrix (N = 4096, K = 11008: 10 us against 20 us).  Token blocks of one linear
-    // go there from 40 M weights on (4096 x 11008 at 128 tokens: 43 us against 70 us; 4096 x 4096 is
-    // faster the other way, 9 us against 11 us at 32 tokens).
+    // through a small matrix (N = 4096, K = 11008: 10 us against 20 us).
     static const int rows_min_count = awq_knob("AWQ_ROWS_MIN_COUNT", 2);
-    const bool rows = token_blocks ? (int64_t)p[0].N * p[0].K >= (int64_t)40 << 20
-                                   : (count >= rows_min_count || p[0].N >= 16384);
-    if (M > 4 && rows) {
-        // the last token block is moved back over its neighbour; the rows they share are written
-        // by the neighbour alone
-        int first_row[GEMV_MAX_PROBLEMS] = {};
-        if (token_blocks && count > 1)
-            first_row[count - 1] = (int)((p[count - 2].y + 16 * (size_t)p[0].N - p[count - 1].y) / p[0].N);
-        return awq_gemv_rows_launch(p, count, (int)M, (hipStream_t)stream, first_row);
-    }
+    if (M > 4 && (count >= rows_min_count || p[0].N >= 16384))
+        return awq_gemv_rows_launch(p, count, (int)M, (hipStream_t)stream);
     // The linears whose K fits the register-resident activations of the streaming kernel at
     // this M go out in one launch; the others (and a lone linear) take one launch of the batch
     // kernel each.
@@ -243,8 +215,6 @@ int grouped_decode(const awq_linear_desc *descs, int count, int64_t M, int group
     }
     return AWQ_OK;
 }
-
-}  // namespace
 
 namespace {
 

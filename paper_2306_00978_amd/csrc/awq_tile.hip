@@ -1,0 +1,387 @@
+// K-split tile kernel for gfx950: one linear at more than 16 tokens, 4-bit (group 128) or 2-bit
+// (group 64) weights.
+//
+// AWQ Sec. 4.2: dequantization fused into the matrix kernel.
+//
+// Mapping.  A workgroup of eight waves computes a tile of 16 MT tokens x 16 NT out-features; its
+// waves divide K (whole runs of 128 columns) and add their tiles through LDS at the end, in a fixed order.
+// Every wave thus needs its own columns of x and its own weight tiles only: nothing is shared
+// during the loop, there is no barrier in it, each weight is fetched and expanded once per
+// 16 MT tokens, and both operands go from memory to registers in the layout of
+// v_mfma_f32_16x16x32_f16 -- the packed weight tile is the B operand, and lane (r, c) of the A operand of step
+// j takes the 16 bytes at row r, column 32 j + 8 c of the run.
+//
+// Arithmetic.  A code becomes the fp16 integer q - z exactly (1024 + q by OR, minus 1024 + z); the
+// products of a group are summed in fp32 by the matrix core and the group's step is applied to the
+// sum, in fp32, with one FMA per output.  No dequantized weight is rounded.
+//
+// Pipeline.  Per run of 128 columns a wave expands NT weight tiles (4 steps x NT fragments in
+// registers), then walks its MT token tiles: 4 NT MFMAs and 4 NT FMAs (8 NT for two groups of 64) per
+// token tile.  Memory -> LDS loads (no staging registers) bring the next three token tiles and the
+// packed words, steps and zero points of the next run into areas that belong to the wave; one load
+// instruction takes four rows of 256 contiguous bytes of x, the 16-byte chunk k of row i landing at place
+// k ^ i, so that the fragment reads of 16 rows hit 16 different bank groups.  (Fragments
+// loaded from memory directly -- 64 pieces of 16 bytes per instruction -- ran at 14 B/clk per CU: 4 us per
+// token tile at K = 4096.)  The loads complete in order and are counted by hand.
+#include "awq_common.h"
+#include "awq_tile.h"
+
+#include <algorithm>
+
+namespace {
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int TILE_WAVES = 8;
+constexpr int RUN = 128;                        // columns per step of the loop
+
+constexpr int TILE_RING = 3;                    // token tiles of x a wave has in LDS
+constexpr int UNIT_BYTES = 16 * RUN * 2;
+// a wave's LDS: the ring, then packed words, steps and zero points (a dword per row and tile) of one run
+constexpr int raw_ofs(int) { return TILE_RING * UNIT_BYTES; }
+constexpr int sc_ofs(int nt) { return raw_ofs(nt) + nt * 1024; }
+constexpr int zp_ofs(int nt) { return sc_ofs(nt) + 256; }
+constexpr int wave_lds(int nt) { return zp_ofs(nt) + 256; }
+// token tiles whose partial sums are in LDS at once in the final exchange
+constexpr int tile_pass(int mt) { return (mt + (mt + 3) / 4 - 1) / ((mt + 3) / 4); }
+constexpr int tile_stride(int nt) { return 16 * nt + 4; }     // floats per row: rows 4 apart fall 16 banks apart
+constexpr int tile_lds(int mt, int nt)
+{
+    const int exchange = TILE_WAVES * tile_pass(mt) * 16 * tile_stride(nt) * 4, loop = TILE_WAVES * wave_lds(nt);
+    return exchange > loop ? exchange : loop;
+}
+
+typedef __attribute__((address_space(3))) void lds_void_t;
+typedef const __attribute__((address_space(1))) void gbl_void_t;
+
+template <int BYTES>
+__device__ __forceinline__ void dma(const unsigned char *g, uint32_t lds_addr)
+{
+    gbl_void_t *src = (gbl_void_t *)(uintptr_t)g;
+    lds_void_t *dst = (lds_void_t *)(uintptr_t)lds_addr;       // + 16 (4 for the small ones) x lane
+    if constexpr (BYTES == 16) __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
+    else if constexpr (BYTES == 4) __builtin_amdgcn_global_load_lds(src, dst, 4, 0, 0);
+    else if constexpr (BYTES == 2) __builtin_amdgcn_global_load_lds(src, dst, 2, 0, 0);
+    else __builtin_amdgcn_global_load_lds(src, dst, 1, 0, 0);
+}
+
+// LDS reads as asm, so that the compiler does not tie them to the loads in flight; each is waited for
+// by an lgkmcnt wait that names its result
+__device__ __forceinline__ u32x4 lds_read16(uint32_t addr)
+{
+    u32x4 v;
+    asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr));
+    return v;
+}
+__device__ __forceinline__ uint32_t lds_read4(uint32_t addr)
+{
+    uint32_t v;
+    asm volatile("ds_read_b32 %0, %1" : "=v"(v) : "v"(addr));
+    return v;
+}
+template <int N>
+__device__ __forceinline__ void wait_loads()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+__device__ __forceinline__ uint32_t sub_pair(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, a) - __builtin_bit_cast(half2_t, b));
+}
+
+template <int BITS, int MT, int NT>
+__global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
+    const unsigned char *__restrict__ x, const unsigned char *__restrict__ qweight,
+    const unsigned char *__restrict__ scales, const unsigned char *__restrict__ zeros,
+    half_t *__restrict__ y, int M, int N, int K, int tiles_n, int tiles_total)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    asm volatile("" ::"s"(x), "s"(qweight), "s"(scales), "s"(zeros), "s"(y), "s"(M), "s"(N), "s"(K),
+                 "s"(tiles_n), "s"(tiles_total));          // arguments in one round
+    // contiguous ranges of tiles, token-tile-major, per XCD (own L2): see gemm_kernel
+    const int per_xcd = (tiles_total + 7) >> 3;
+    const int unit = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
+    if (unit >= tiles_total || ((int)blockIdx.x >> 3) >= per_xcd) return;
+    const int tile_m = unit / tiles_n, tile_n = unit - tile_m * tiles_n;
+    const uint32_t lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t r = lane & 15, c = lane >> 4;
+    const int G = K / RUN;
+    // the wave's runs: wave, wave + 8, ..., walked in cyclic order from a start of the workgroup's own
+    const int cnt = (G - wave + TILE_WAVES - 1) / TILE_WAVES;
+    const int rot = cnt > 0 ? unit % cnt : 0;
+    auto run_at = [&](int i) {                             // i-th run; past the end: a harmless repeat
+        i = min(i, cnt - 1) + rot;
+        return wave + TILE_WAVES * (i < cnt ? i : i - cnt);
+    };
+    const int m0 = tile_m * (16 * MT), nt0 = tile_n * NT;
+
+    // A token tile that would reach past M is moved back to end there (M >= 16); the rows it shares with
+    // its neighbour are computed twice, bit for bit alike, and stored once.
+    auto first_row = [&](int m) { return min(m0 + 16 * m, M - 16); };
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem) + wave * wave_lds(NT);
+    // packed words: tile n of the workgroup, wave-uniform; steps and zero points: one load for all tiles, lane
+    // (r, c) fetching those of row r of tile c.  Ragged N repeats the last tile.  Counted in runs: K % 256 == 0
+    // for the 2-bit layout, so G is even and a tile's first run starts a block.
+    size_t trun[NT];
+#pragma unroll
+    for (int n = 0; n < NT; ++n) trun[n] = (size_t)min(nt0 + n, (N >> 4) - 1) * G;
+    const size_t lrun = (size_t)min(nt0 + min((int)c, NT - 1), (N >> 4) - 1) * G;
+
+    floatx4 tot[MT][NT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) tot[m][n] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    // masks in SGPRs, magic numbers in VGPRs: (w & mask) | magic is then one v_and_or_b32
+    uint32_t mask_lo = 0x000F000Fu, mask_hi = 0x00F000F0u, mask2 = 0x00030003u;
+    uint32_t magA = 0x64006400u, magB = 0x54005400u;
+    asm("" : "+s"(mask_lo), "+s"(mask_hi), "+s"(mask2));
+    asm("" : "+v"(magA), "+v"(magB));
+
+    // x: load i (0..3) of a token tile takes its rows 4 i + c, lane r the chunk that belongs at place r
+    uint32_t xofs[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) xofs[i] = (4 * i + c) * (uint32_t)(K * 2) + 16 * (r ^ (4 * i + c));
+    auto issue_x = [&](int run, int m, uint32_t slot) {
+        const unsigned char *p = x + ((size_t)first_row(m) * K + (size_t)run * RUN) * 2;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dma<16>(p + xofs[i], lds0 + slot + i * 1024);
+    };
+    constexpr int RAW_LOADS = NT + 2;
+    auto issue_raw = [&](int run) {
+        if (BITS == 4) {                                   // a run is a group: 1 KB, 16 steps, 8 bytes of zero points
+#pragma unroll
+            for (int n = 0; n < NT; ++n) dma<16>(qweight + (trun[n] + run) * 1024 + lane * 16, lds0 + raw_ofs(NT) + n * 1024);
+            dma<2>(scales + (lrun + run) * 32 + r * 2, lds0 + sc_ofs(NT));
+            dma<1>(zeros + (lrun + run) * 8 + (r >> 1), lds0 + zp_ofs(NT));
+        } else {                                           // half a block of 256 columns: groups 2 (run % 2), + 1
+#pragma unroll
+            for (int n = 0; n < NT; ++n)
+                dma<16>(qweight + ((trun[n] + run) >> 1) * 1024 + lane * 16, lds0 + raw_ofs(NT) + n * 1024);
+            dma<4>(scales + ((lrun + run) >> 1) * 128 + (run & 1) * 4 + r * 8, lds0 + sc_ofs(NT));
+            dma<1>(zeros + ((lrun + run) >> 1) * 16 + r, lds0 + zp_ofs(NT));
+        }
+    };
+    uint32_t frag[4];                                      // of this lane inside a token tile
+#pragma unroll
+    for (int j = 0; j < 4; ++j) frag[j] = lds0 + r * 256 + (((4 * j + c) ^ r) * 16);
+
+    if (cnt > 0) {
+        issue_raw(run_at(0));
+        issue_x(run_at(0), 0, 0);
+        issue_x(run_at(1 / MT), 1 % MT, UNIT_BYTES);
+        issue_x(run_at(2 / MT), 2 % MT, 2 * UNIT_BYTES);
+        uint32_t slot = 0;                                 // of the token tile being multiplied
+        u32x4 a[4];
+        // Counting: behind a token tile that is waited for, the two after it have been requested (8 loads)
+        // and, if it was itself requested before the run's weights, those as well.  A smaller count only waits longer.
+        for (int i = 0; i < cnt; ++i) {
+            wait_loads<(MT >= 2 ? 8 : 4)>();               // this run's packed words: 4 MT loads behind them
+            u32x4 q[NT];
+            uint32_t sraw[NT], zraw[NT];
+#pragma unroll
+            for (int n = 0; n < NT; ++n) {
+                q[n] = lds_read16(lds0 + raw_ofs(NT) + n * 1024 + lane * 16);
+                sraw[n] = lds_read4(lds0 + sc_ofs(NT) + (16 * n + r) * 4);
+                zraw[n] = lds_read4(lds0 + zp_ofs(NT) + (16 * n + r) * 4);
+            }
+#pragma unroll
+            for (int n = 0; n < NT; ++n) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(q[n]), "+v"(sraw[n]), "+v"(zraw[n]));
+            issue_raw(run_at(i + 1));
+            if (i == 0) {
+                wait_loads<8 + RAW_LOADS>();
+#pragma unroll
+                for (int j = 0; j < 4; ++j) a[j] = lds_read16(frag[j]);
+                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]));
+            }
+            half8_t bf[NT][4];
+            float s0[NT], s1[NT];
+            const int hb = run_at(i) & 1;
+            const float f0 = hb ? 0.0625f : 1.0f, f1 = hb ? 0.015625f : 0.25f;      // 4^-t, BITS = 2
+#pragma unroll
+            for (int n = 0; n < NT; ++n) {
+                if (BITS == 4) {
+                    const uint32_t z = (zraw[n] >> ((r & 1) * 4)) & 0xFu;
+                    const uint32_t zA = magA | (z * 0x00010001u), zB = magB | (z * 0x00100010u);
+                    s0[n] = s1[n] = (float)__builtin_bit_cast(half_t, (uint16_t)sraw[n]);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const uint32_t w = q[n][j], w8 = w >> 8;
+                        bf[n][j] = __builtin_bit_cast(half8_t, u32x4{
+                            sub_pair((w & mask_lo) | magA, zA), sub_pair((w & mask_hi) | magB, zB),
+                            sub_pair((w8 & mask_lo) | magA, zA), sub_pair((w8 & mask_hi) | magB, zB)});
+                    }
+                } else {
+                    // groups t = 2 hb, 2 hb + 1 of the block: codes at bits 2t of a half, scaled by 4^t
+                    const uint32_t zz = zraw[n] * 0x00010001u;
+                    const half2_t ss = __builtin_bit_cast(half2_t, sraw[n]);
+                    s0[n] = (float)ss[0] * f0;
+                    s1[n] = (float)ss[1] * f1;
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        const uint32_t mk = mask2 << (4 * hb + 2 * t);
+                        const uint32_t zt = (zz & mk) | magA;
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            bf[n][2 * t + j] = __builtin_bit_cast(half8_t, u32x4{
+                                sub_pair(((q[n][0] >> (8 * j)) & mk) | magA, zt), sub_pair(((q[n][1] >> (8 * j)) & mk) | magA, zt),
+                                sub_pair(((q[n][2] >> (8 * j)) & mk) | magA, zt), sub_pair(((q[n][3] >> (8 * j)) & mk) | magA, zt)});
+                    }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                // the token tile in registers frees its place in the ring: request the third after it
+                issue_x(run_at(i + (m + 3) / MT), (m + 3) % MT, slot);
+                const uint32_t next = slot == 2 * UNIT_BYTES ? 0 : slot + UNIT_BYTES;
+                if (m < 2) wait_loads<8 + RAW_LOADS>();
+                else wait_loads<8>();
+                u32x4 an[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) an[j] = lds_read16(frag[j] + next);
+                __builtin_amdgcn_sched_barrier(0);
+                floatx4 acc[NT];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const half8_t av = __builtin_bit_cast(half8_t, a[j]);
+#pragma unroll
+                    for (int n = 0; n < NT; ++n) {
+                        if (j == 0 || (BITS == 2 && j == 2)) acc[n] = floatx4{0.f, 0.f, 0.f, 0.f};
+                        acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, bf[n][j], acc[n], 0, 0, 0);
+                    }
+                    if (j == 3 || (BITS == 2 && j == 1)) {
+#pragma unroll
+                        for (int n = 0; n < NT; ++n)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v)
+                                tot[m][n][v] = __builtin_fmaf(acc[n][v], j == 3 ? s1[n] : s0[n], tot[m][n][v]);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);         // the wait stays behind the multiplications
+                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(an[0]), "+v"(an[1]), "+v"(an[2]), "+v"(an[3]));
+#pragma unroll
+                for (int j = 0; j < 4; ++j) a[j] = an[j];
+                slot = next;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        wait_loads<0>();                                   // the harmless repeats
+    }
+    __syncthreads();                                       // the exchange below reuses every wave's LDS
+
+    // Sum over the waves.  Lane (r, c) holds rows 4 c + v, column r of each 16 x 16 tile.
+    constexpr int MC = tile_pass(MT), ST = tile_stride(NT), ROWS = 16 * MC;
+    float *lds = reinterpret_cast<float *>(smem);
+    float *mine = lds + wave * (ROWS * ST);
+#pragma unroll
+    for (int p = 0; p < MT; p += MC) {
+        if (p > 0) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < MC; ++i)
+            if (p + i < MT) {
+#pragma unroll
+                for (int n = 0; n < NT; ++n)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        mine[(16 * i + 4 * c + v) * ST + 16 * n + r] = tot[p + i < MT ? p + i : 0][n][v];
+            }
+        __syncthreads();
+        for (int e = threadIdx.x; e < ROWS * 4 * NT; e += 64 * TILE_WAVES) {
+            const int row = e / (4 * NT), col = (e - row * (4 * NT)) * 4;
+            const int mt = p + (row >> 4), m = first_row(mt) + (row & 15), n = nt0 * 16 + col;
+            if (mt >= MT || m < m0 + 16 * mt || m >= M || n >= N) continue;
+            const float *src = lds + row * ST + col;
+            float4 s = *reinterpret_cast<const float4 *>(src);
+#pragma unroll
+            for (int w = 1; w < TILE_WAVES; ++w) {
+                const float4 b = *reinterpret_cast<const float4 *>(src + w * (ROWS * ST));
+                s.x += b.x; s.y += b.y; s.z += b.z; s.w += b.w;
+            }
+            const half2_t lo = {(half_t)s.x, (half_t)s.y}, hi = {(half_t)s.z, (half_t)s.w};
+            *reinterpret_cast<uint2 *>(y + (size_t)m * N + n) =
+                make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
+        }
+    }
+}
+
+template <int BITS, int MT, int NT>
+int launch_one(const void *x, const void *qweight, const void *scales, const void *zeros, void *y, int M, int N,
+               int K, hipStream_t stream)
+{
+    const int tiles_n = (N / 16 + NT - 1) / NT;
+    const int64_t total = (int64_t)tiles_n * ((M + 16 * MT - 1) / (16 * MT));
+    if (total > (1 << 30)) return AWQ_ERR_BAD_SHAPE;
+    constexpr int lds = tile_lds(MT, NT);
+    static_assert(lds <= 160 * 1024, "LDS of a CU");
+    static AwqOncePerDevice once;
+    std::atomic<bool> &attr_set = once.here();
+    if (lds > 64 * 1024 && !attr_set.load(std::memory_order_relaxed)) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(tile_kernel<BITS, MT, NT>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+            return AWQ_ERR_HIP;
+        attr_set.store(true, std::memory_order_relaxed);
+    }
+    tile_kernel<BITS, MT, NT><<<dim3((unsigned)((total + 7) / 8 * 8)), dim3(64 * TILE_WAVES), lds, stream>>>(
+        (const unsigned char *)x, (const unsigned char *)qweight, (const unsigned char *)scales,
+        (const unsigned char *)zeros, (half_t *)y, M, N, K, tiles_n, (int)total);
+    return awq_launch_status();
+}
+
+typedef int (*TileFn)(const void *, const void *, const void *, const void *, void *, int, int, int, hipStream_t);
+
+constexpr int MTS[] = {1, 2, 3, 4, 5, 6, 8};
+// 128 x 64 does not fit the registers
+constexpr bool tile_built(int mt, int nt) { return !(mt == 8 && nt == 4); }
+
+template <int BITS, int NT>
+TileFn pick_mt(int mt)
+{
+    switch (mt) {
+    case 1: return launch_one<BITS, 1, NT>;
+    case 2: return launch_one<BITS, 2, NT>;
+    case 3: return launch_one<BITS, 3, NT>;
+    case 4: return launch_one<BITS, 4, NT>;
+    case 5: return launch_one<BITS, 5, NT>;
+    case 6: return launch_one<BITS, 6, NT>;
+    default: return launch_one<BITS, 8, NT == 4 ? 3 : NT>;      // (8, 4) is never planned
+    }
+}
+
+template <int BITS>
+TileFn pick(int mt, int nt)
+{
+    return nt == 1 ? pick_mt<BITS, 1>(mt) : nt == 2 ? pick_mt<BITS, 2>(mt) : nt == 3 ? pick_mt<BITS, 3>(mt)
+                                                                                     : pick_mt<BITS, 4>(mt);
+}
+
+}  // namespace
+
+// A launch takes 1.1 us and, per round of 256 workgroups (one per CU: the LDS), 1.5 us plus for every
+// run of a wave 0.235 us per token tile (32 KB of x per CU and tile for the eight waves: 64 B/clk), 0.22 us per
+// weight tile and 0.02 us per pair, plus 0.08 us per pair for the exchange -- fitted to 24 shapes
+// (4096 x 4096, 11008 x 4096, 4096 x 11008 at 17..500 tokens, both bit widths, all MT and NT; rms error 6 %).
+TilePlan awq_tile_plan(int M, int N, int K)
+{
+    TilePlan best = {1, 1, -1.0};
+    const int runs = (K / RUN + TILE_WAVES - 1) / TILE_WAVES;
+    for (const int mt : MTS)
+        for (int nt = 1; nt <= 4; ++nt) {
+            if (!tile_built(mt, nt)) continue;
+            const int64_t wgs = (int64_t)((N / 16 + nt - 1) / nt) * ((M + 16 * mt - 1) / (16 * mt));
+            const double us = 1.1 + (double)((wgs + 255) / 256) *
+                                        (1.5 + runs * (0.235 * mt + 0.22 * nt + 0.02 * mt * nt) + 0.08 * mt * nt);
+            if (best.us < 0.0 || us < best.us) best = {mt, nt, us};
+        }
+    return best;
+}
+
+int awq_tile_launch(int bits, const TilePlan &plan, const void *x, const void *qweight, const void *scales,
+                    const void *zeros, void *y, int M, int N, int K, hipStream_t stream)
+{
+    const TileFn fn = bits == 4 ? pick<4>(plan.mt, plan.nt) : pick<2>(plan.mt, plan.nt);
+    return fn(x, qweight, scales, zeros, y, M, N, K, stream);
+}
