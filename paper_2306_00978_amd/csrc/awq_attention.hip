@@ -18,6 +18,7 @@
 #include "awq_common.h"
 
 #include <cmath>
+#include <cstddef>
 
 namespace {
 
@@ -217,6 +218,375 @@ __global__ __launch_bounds__(256) void attention_partial_kernel(
     }
 }
 
+// ---- grouped query heads ----------------------------------------------------------------------
+// With G = H / Hkv > 2 query heads to a key/value head the kernel above reads every key and value G
+// times (from L2) and spends G times the vector work on it: 26.8 us a call at 64 / 8 heads, 4000
+// positions, for 16 MB of caches.  Here a workgroup serves up to 16 query heads of one kv head at once
+// and both products run on the matrix cores:
+//   scores   v_mfma_f32_16x16x32_f16, A = 16 keys from the cache, B = the rotated queries as the sum of two
+//            halves (high and low part of the fp32 value times a power of two of the head's own,
+//            2^-22 relative: scores as exact as with fp32 queries);
+//   values   v_mfma_f32_16x16x4_f32, fp32 probabilities and fp32 values: nothing is rounded to 16 bits.
+// A score tile has lane (r, c) holding head r, positions 4 c + v: with step v of the value product
+// taken over positions {v, 4 + v, 8 + v, 12 + v} that is its A operand as it stands, and its B operand
+// is a contiguous piece of row 4 c + v if output column r of value tile t is dimension T r + t.
+// Memory -> LDS loads bring blocks of 16 positions into a ring of the wave's own, up to three ahead; no
+// barrier until the waves are merged.  The workspace has room for attention_splits() slices only,
+// which at 64 heads are eight, 64 workgroups: so F workgroups of a slice (on one XCD, sharing its L2) take
+// the same scores and 128 / F dimensions of the values each.  The current token enters as the initial state of
+// one wave, with its key in fp32.  64 / 8 heads, 4000 positions:
+// 26.8 -> 12.8 us a call with the merge; what is left is a chain of latencies (arguments, small inputs 2 us,
+// rotation 1 us, two rounds of cache rows, two merges), not the 16 MB.
+typedef __attribute__((address_space(3))) void lds_void_t;
+typedef const __attribute__((address_space(1))) void gbl_void_t;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ void dma16(const unsigned char *g, uint32_t lds_addr)
+{
+    __builtin_amdgcn_global_load_lds((gbl_void_t *)(uintptr_t)g, (lds_void_t *)(uintptr_t)lds_addr, 16, 0, 0);
+}
+
+constexpr int GQ_BLOCK = 16;                    // positions per step of a wave: one score tile (32: same time)
+constexpr int GQ_WAVES = 8;                     // two to a SIMD: one's chain of dependent steps hides the other's
+template <int F> struct GqShape {
+    static constexpr int T = 8 / F;             // value tiles of 16 dimensions
+    static constexpr int VROW = 256 / F;        // bytes of a value row this workgroup takes
+    static constexpr int STAGE = GQ_BLOCK * (256 + VROW);
+    static constexpr int STAGES = F == 1 ? 2 : 3;
+    static constexpr int LOADS = 4 + 4 / F;     // per stage
+    // 16 query rows (then their high halves), the token's key and value, the rotary table, the low halves, two
+    // numbers per head
+    static constexpr int SHARED = 9 * 1024 + 128;
+    static constexpr int LDS = SHARED + GQ_WAVES * STAGES * STAGE;
+};
+
+// one struct, so that the rotary table can be fetched from the kernel arguments by address
+struct GroupedArgs {
+    const half_t *q, *k, *v;
+    half_t *k_cache, *v_cache;
+    float *partial;
+    int H, Hkv, qgroups, Lmax, pos, chunk, splits, pad;
+    RopeTable tab;
+};
+
+// lane's piece of a value row: T halves
+template <int F> struct GqValue;
+template <> struct GqValue<1> { u32x4 d; };
+template <> struct GqValue<2> { u32x2 d; };
+template <> struct GqValue<4> { uint32_t d; };
+
+template <int F>
+__global__ __launch_bounds__(64 * GQ_WAVES, 1) void attention_grouped_kernel(const GroupedArgs A)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    typedef GqShape<F> Sh;
+    constexpr int T = Sh::T;
+    const int H = A.H, Hkv = A.Hkv, qgroups = A.qgroups, Lmax = A.Lmax, pos = A.pos, chunk = A.chunk, splits = A.splits;
+    const half_t *__restrict__ q = A.q, *__restrict__ k = A.k, *__restrict__ v = A.v;
+    half_t *__restrict__ k_cache = A.k_cache, *__restrict__ v_cache = A.v_cache;
+    float *__restrict__ partial = A.partial;
+    asm volatile("" ::"s"(q), "s"(k), "s"(v), "s"(k_cache), "s"(v_cache), "s"(partial), "s"(H), "s"(Hkv),
+                 "s"(qgroups), "s"(Lmax), "s"(pos), "s"(chunk), "s"(splits));
+    // block -> (XCD, place): the F workgroups of a slice are neighbours on one XCD
+    const int place = (int)blockIdx.x >> 3;
+    const int item = (place / F) * 8 + ((int)blockIdx.x & 7), f = place % F;
+    if (item >= Hkv * qgroups * splits) return;
+    const int split = item % splits, gq = item / splits;
+    const int g_kv = gq / qgroups, G = H / Hkv, h0 = g_kv * G + (gq % qgroups) * 16;
+    const int heads = min(16, G - (gq % qgroups) * 16);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, c = lane >> 4;
+
+    const int p0 = split * chunk, p1 = min(pos, p0 + chunk);             // rows of the caches
+    const int blocks = p1 > p0 ? (p1 - p0 + GQ_BLOCK - 1) / GQ_BLOCK : 0;
+    const int mine = blocks > wave ? (blocks - wave + GQ_WAVES - 1) / GQ_WAVES : 0;
+    const unsigned char *kb = reinterpret_cast<const unsigned char *>(k_cache + (size_t)g_kv * Lmax * AD);
+    const unsigned char *vb = reinterpret_cast<const unsigned char *>(v_cache + (size_t)g_kv * Lmax * AD) + f * Sh::VROW;
+    const uint32_t shared = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
+    const uint32_t lds0 = shared + Sh::SHARED + wave * (Sh::STAGES * Sh::STAGE);
+
+    // Block b of this wave.  Keys: rows of 256 bytes, the 16-byte chunk k of row i at place k ^ (i % 16) (the 16
+    // rows a fragment read touches fall into 16 bank groups); values: rows of VROW bytes as they are.
+    // Rows past the end repeat the last one and are masked; a wave without blocks fetches rows it never uses.
+    const int last_row = max(p1 - 1, 0);
+    auto request = [&](int b, int stage) {
+        b = max(min(b, mine - 1), 0);                                    // past the end: a harmless repeat
+        const int first = p0 + (wave + GQ_WAVES * b) * GQ_BLOCK;
+        const uint32_t dst = lds0 + stage * Sh::STAGE;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int row = 4 * i + c;
+            dma16(kb + (size_t)min(first + row, last_row) * 256 + 16 * (r ^ row), dst + i * 1024);
+        }
+#pragma unroll
+        for (int i = 0; i < 4 / F; ++i) {
+            constexpr int per_row = Sh::VROW / 16;
+            const int row = i * (64 / per_row) + lane / per_row;
+            dma16(vb + (size_t)min(first + row, last_row) * 256 + 16 * (lane % per_row), dst + GQ_BLOCK * 256 + i * 1024);
+        }
+    };
+
+    // The small inputs come the same way, first: a register load between the requests would be waited for
+    // behind all of them.  Each wave fetches four query rows (a missing head repeats the last one; chunks
+    // placed as the keys'), and all of them, alike: the token's key and value and the rotary table.
+    {
+        const int row = 4 * (wave & 3) + c;
+        dma16(reinterpret_cast<const unsigned char *>(q + (size_t)(h0 + min(row, heads - 1)) * AD) + 16 * (r ^ row),
+              shared + (wave & 3) * 1024);
+        const unsigned char *args = (const unsigned char *)__builtin_amdgcn_kernarg_segment_ptr();
+        const unsigned char *src = lane < 16 ? reinterpret_cast<const unsigned char *>(k + (size_t)g_kv * AD) + 16 * lane
+                                 : lane < 32 ? reinterpret_cast<const unsigned char *>(v + (size_t)g_kv * AD) + 16 * (lane - 16)
+                                             : args + offsetof(GroupedArgs, tab) + 16 * (lane - 32);
+        dma16(src, shared + 4096);
+    }
+#pragma unroll
+    for (int st = 0; st < Sh::STAGES; ++st) request(st, st);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(Sh::STAGES * Sh::LOADS) : "memory");
+    __builtin_amdgcn_s_barrier();
+    // Rotation: wave w takes heads 2 w and 2 w + 1, lane i the dimensions i and i + 64 (frequency i, as in
+    // rope_pair), of the key as well.  The queries become high and low halves of q 2^-ex, ex from the head's largest
+    // element (score = accumulator * unscale).
+    const uint32_t qa = shared + 8 * wave * 64 + 2 * (lane & 7), sw = lane >> 3;     // element i of row 2 w: chunk i / 8
+    uint32_t qe[2][2], ke[2], vraw;
+    double rfreq;
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t row = 2 * wave + n;
+            asm volatile("ds_read_u16 %0, %1" : "=v"(qe[n][h]) : "v"(qa + 256 * n + (((sw + 8 * h) ^ row) * 16)));
+        }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) asm volatile("ds_read_u16 %0, %1" : "=v"(ke[h]) : "v"(shared + 4096 + 2 * lane + 128 * h));
+    asm volatile("ds_read_b32 %0, %1" : "=v"(vraw) : "v"(shared + 4352 + 4 * lane));
+    asm volatile("ds_read_b64 %0, %1" : "=v"(rfreq) : "v"(shared + 4608 + 8 * lane));
+    GqValue<F> vnow;                                                     // of the current token, this lane's columns
+    {
+        const uint32_t at = shared + 4352 + f * Sh::VROW + r * (2 * T);
+        if constexpr (F == 1) asm volatile("ds_read_b128 %0, %1" : "=v"(vnow.d) : "v"(at));
+        else if constexpr (F == 2) asm volatile("ds_read_b64 %0, %1" : "=v"(vnow.d) : "v"(at));
+        else asm volatile("ds_read_b32 %0, %1" : "=v"(vnow.d) : "v"(at));
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(qe[0][0]), "+v"(qe[0][1]), "+v"(qe[1][0]), "+v"(qe[1][1]), "+v"(ke[0]), "+v"(ke[1]), "+v"(vraw),
+                   "+v"(rfreq), "+v"(vnow.d));
+    auto half_of = [](const GqValue<F> &g, int t) {
+        uint32_t w;
+        if constexpr (F == 4) w = g.d;
+        else w = g.d[t / 2];
+        return (float)__builtin_bit_cast(half2_t, w)[t & 1];
+    };
+    auto f32 = [](uint32_t h) { return (float)__builtin_bit_cast(half_t, (uint16_t)h); };
+    float sn, cs;
+    {
+        const double ang = (double)pos * rfreq;
+        const double turns = __builtin_rint(ang * 0.15915494309189535);
+        const float red = (float)(ang - turns * 6.283185307179586);
+        sn = sinf(red);
+        cs = cosf(red);
+    }
+    const float ka = f32(ke[0]), kz = f32(ke[1]);
+    const float klo = ka * cs - kz * sn, khi = kz * cs + ka * sn;
+    if (split == 0 && f == 0 && gq % qgroups == 0 && wave == 0) {        // files the token into the caches
+        half_t *kd = k_cache + ((size_t)g_kv * Lmax + pos) * AD;
+        kd[lane] = (half_t)klo;
+        kd[lane + 64] = (half_t)khi;
+        reinterpret_cast<uint32_t *>(v_cache + ((size_t)g_kv * Lmax + pos) * AD)[lane] = vraw;
+    }
+    float qlo_f[2], qhi_f[2], big[2], dot[2];
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        const float a = f32(qe[n][0]), z = f32(qe[n][1]);
+        qlo_f[n] = a * cs - z * sn;
+        qhi_f[n] = z * cs + a * sn;
+        big[n] = fmaxf(__builtin_fabsf(qlo_f[n]), __builtin_fabsf(qhi_f[n]));
+        dot[n] = qlo_f[n] * klo + qhi_f[n] * khi;
+    }
+#pragma unroll
+    for (int d = 1; d <= 32; d <<= 1)
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            big[n] = fmaxf(big[n], __shfl_xor(big[n], d));
+            dot[n] += __shfl_xor(dot[n], d);
+        }
+    // the raw query rows have been read by their wave: rows 2 w, 2 w + 1 of the high halves take their place,
+    // the low halves follow at QLO, then (unscale, score) per head
+    constexpr uint32_t QLO = 5 * 1024, HEAD = 9 * 1024;
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        int ex = 0;
+        if (big[n] > 0.f && big[n] < __builtin_inff()) ex = ilogbf(big[n]) - 10;     // largest element in [2^10, 2^11)
+        const uint32_t row = 2 * wave + n;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float a = ldexpf(h ? qhi_f[n] : qlo_f[n], -ex);
+            const half_t top = (half_t)a, rest = (half_t)(a - (float)top);
+            const uint32_t at = qa + 256 * n + (((sw + 8 * h) ^ row) * 16);
+            asm volatile("ds_write_b16 %0, %1" ::"v"(at), "v"((uint32_t)__builtin_bit_cast(uint16_t, top)) : "memory");
+            asm volatile("ds_write_b16 %0, %1" ::"v"(at + QLO), "v"((uint32_t)__builtin_bit_cast(uint16_t, rest)) : "memory");
+        }
+        if (lane == 0) {
+            const float unscale = ldexpf(0.08838834764831845f, ex), score = dot[n] * 0.08838834764831845f;   // 1 / sqrt(128)
+            asm volatile("ds_write_b64 %0, %1" ::"v"(shared + HEAD + 8 * row),
+                         "v"(u32x2{__builtin_bit_cast(uint32_t, unscale), __builtin_bit_cast(uint32_t, score)}) : "memory");
+        }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    half8_t qhi[4], qlo[4];
+    u32x2 head;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t at = shared + r * 256 + (((4 * j + c) ^ r) * 16);
+        asm volatile("ds_read_b128 %0, %1" : "=v"(qhi[j]) : "v"(at));
+        asm volatile("ds_read_b128 %0, %1" : "=v"(qlo[j]) : "v"(at + QLO));
+    }
+    asm volatile("ds_read_b64 %0, %1" : "=v"(head) : "v"(shared + HEAD + 8 * r));
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(qhi[0]), "+v"(qhi[1]), "+v"(qhi[2]), "+v"(qhi[3]), "+v"(qlo[0]), "+v"(qlo[1]), "+v"(qlo[2]),
+                   "+v"(qlo[3]), "+v"(head));
+    // (values, not elements: a bit_cast of a vector element reads element 0)
+    const uint32_t head_unscale = head[0], head_score = head[1];
+    const float unscale = __builtin_bit_cast(float, head_unscale), now = __builtin_bit_cast(float, head_score);
+
+    // state of head r (m and l; l per lane, added over c at the end) and sums of heads 4 c + v, dimension T r + t
+    float m = -__builtin_inff(), l = 0.f;
+    floatx4 acc[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (wave == 0 && split == pos / chunk) {
+        m = now;
+        l = c == 0 ? 1.f : 0.f;
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const float vt = half_of(vnow, t);
+            acc[t] = floatx4{vt, vt, vt, vt};
+        }
+    }
+
+    uint32_t kofs[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) kofs[j] = r * 256 + (((4 * j + c) ^ r) * 16);
+    int stage = 0;
+    for (int b = 0; b < mine; ++b) {
+        // loads complete in order: this block is there when only the later stages' are outstanding (other loads
+        // of this wave that were issued in between only make the wait longer)
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((Sh::STAGES - 1) * Sh::LOADS) : "memory");
+        const uint32_t base = lds0 + stage * Sh::STAGE;
+        u32x4 kf[4];
+        GqValue<F> vv[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) asm volatile("ds_read_b128 %0, %1" : "=v"(kf[j]) : "v"(base + kofs[j]));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t at = base + GQ_BLOCK * 256 + (4 * c + i) * Sh::VROW + r * (2 * T);
+            if constexpr (F == 1) asm volatile("ds_read_b128 %0, %1" : "=v"(vv[i].d) : "v"(at));
+            else if constexpr (F == 2) asm volatile("ds_read_b64 %0, %1" : "=v"(vv[i].d) : "v"(at));
+            else asm volatile("ds_read_b32 %0, %1" : "=v"(vv[i].d) : "v"(at));
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)"
+                     : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]), "+v"(vv[0].d), "+v"(vv[1].d), "+v"(vv[2].d),
+                       "+v"(vv[3].d));
+        request(b + Sh::STAGES, stage);                                  // the stage has been read
+        stage = stage + 1 == Sh::STAGES ? 0 : stage + 1;
+
+        const int first = p0 + (wave + GQ_WAVES * b) * GQ_BLOCK + 4 * c;
+        floatx4 hi = {0.f, 0.f, 0.f, 0.f}, lo = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const half8_t kv = __builtin_bit_cast(half8_t, kf[j]);
+            lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(kv, qlo[j], lo, 0, 0, 0);
+            hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(kv, qhi[j], hi, 0, 0, 0);
+        }
+        float s[4], top = -__builtin_inff();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            s[i] = first + i < p1 ? (hi[i] + lo[i]) * unscale : -__builtin_inff();
+            top = fmaxf(top, s[i]);
+        }
+        top = fmaxf(top, __shfl_xor(top, 16));
+        top = fmaxf(top, __shfl_xor(top, 32));
+        const float m_new = fmaxf(m, top);                               // finite: a block has a valid position
+        const float keep = __expf(m - m_new);
+        m = m_new;
+        l *= keep;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            s[i] = __expf(s[i] - m_new);
+            l += s[i];
+        }
+        if (__any(keep != 1.0f)) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float ki = __shfl(keep, 4 * c + i);
+#pragma unroll
+                for (int t = 0; t < T; ++t) acc[t][i] *= ki;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(s[i], half_of(vv[i], t), acc[t], 0, 0, 0);
+    }
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+
+    // merge the waves: [wave][head][dimensions, m, l]
+    constexpr int DW = AD / F, ROW = DW + 2;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    float *state = reinterpret_cast<float *>(smem);
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) state[(wave * 16 + 4 * c + i) * ROW + T * r + t] = acc[t][i];
+    if (c == 0) {
+        state[(wave * 16 + r) * ROW + DW] = m;
+        state[(wave * 16 + r) * ROW + DW + 1] = l;
+    }
+    __syncthreads();
+    for (int e = tid; e < heads * DW; e += 64 * GQ_WAVES) {
+        const int h = e / DW, d = e - h * DW;
+        float mm = state[h * ROW + DW];
+#pragma unroll
+        for (int w = 1; w < GQ_WAVES; ++w) mm = fmaxf(mm, state[(w * 16 + h) * ROW + DW]);
+        float ll = 0.f, a = 0.f;
+#pragma unroll
+        for (int w = 0; w < GQ_WAVES; ++w) {
+            const float mw = state[(w * 16 + h) * ROW + DW];
+            const float kf = mw == mm ? 1.0f : __expf(mw - mm);
+            ll += state[(w * 16 + h) * ROW + DW + 1] * kf;
+            a += state[(w * 16 + h) * ROW + d] * kf;
+        }
+        float *dst = partial + ((size_t)(h0 + h) * splits + split) * (AD + 2);
+        dst[f * DW + d] = a;
+        if (f == 0 && d == 0) {
+            dst[AD] = mm;
+            dst[AD + 1] = ll;
+        }
+    }
+}
+
+template <int F>
+int attention_grouped_launch(const GroupedArgs &A, hipStream_t stream)
+{
+    static_assert(GqShape<F>::LDS <= 160 * 1024 && GQ_WAVES * 16 * (AD / F + 2) * 4 <= GqShape<F>::LDS, "LDS");
+    static AwqOncePerDevice once;
+    std::atomic<bool> &attr_set = once.here();
+    if (!attr_set.load(std::memory_order_relaxed)) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(attention_grouped_kernel<F>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, GqShape<F>::LDS) != hipSuccess)
+            return AWQ_ERR_HIP;
+        attr_set.store(true, std::memory_order_relaxed);
+    }
+    const int64_t items = (int64_t)A.Hkv * A.qgroups * A.splits;
+    attention_grouped_kernel<F><<<dim3((unsigned)((items + 7) / 8 * 8 * F)), dim3(64 * GQ_WAVES), GqShape<F>::LDS, stream>>>(A);
+    return awq_launch_status();
+}
+
 // grid H, 256 threads: merge the slices of a head in a fixed order.  The head's partial results
 // (at most 64 x 130 floats) are first copied to LDS with coalesced loads: read one by one from
 // memory they would be a chain of dependent round trips.
@@ -298,10 +668,23 @@ extern "C" int awq_decode_attention(const void *q_f16, const void *k_f16, const 
     chunk = (chunk + 15) / 16 * 16;                  // whole steps of the four waves
     RopeTable tab;
     for (int i = 0; i < AD / 2; ++i) tab.inv_freq[i] = pow((double)rope_theta, -2.0 * i / AD);
-    attention_partial_kernel<<<dim3((unsigned)H, (unsigned)splits), dim3(256), 0, (hipStream_t)stream>>>(
-        (const half_t *)q_f16, (const half_t *)k_f16, (const half_t *)v_f16, (half_t *)k_cache_f16,
-        (half_t *)v_cache_f16, (int)H, (int)Hkv, (int)Lmax, (int)pos, tab, chunk, (float *)workspace);
-    int st = awq_launch_status();
+    const half_t *qp = (const half_t *)q_f16, *kp = (const half_t *)k_f16, *vp = (const half_t *)v_f16;
+    half_t *kc = (half_t *)k_cache_f16, *vc = (half_t *)v_cache_f16;
+    float *partial = (float *)workspace;
+    int st;
+    if (H / Hkv > 2) {
+        GroupedArgs A = {qp, kp, vp, kc, vc, partial, (int)H, (int)Hkv, (int)((H / Hkv + 15) / 16), (int)Lmax, (int)pos,
+                         chunk, splits, 0, tab};
+        // one workgroup per CU (the LDS): the values are divided until there are 256
+        const int64_t items = Hkv * A.qgroups * splits;
+        st = items >= 256 ? attention_grouped_launch<1>(A, (hipStream_t)stream)
+             : items >= 128 ? attention_grouped_launch<2>(A, (hipStream_t)stream)
+                            : attention_grouped_launch<4>(A, (hipStream_t)stream);
+    } else {
+        attention_partial_kernel<<<dim3((unsigned)H, (unsigned)splits), dim3(256), 0, (hipStream_t)stream>>>(
+            qp, kp, vp, kc, vc, (int)H, (int)Hkv, (int)Lmax, (int)pos, tab, chunk, partial);
+        st = awq_launch_status();
+    }
     if (st != AWQ_OK) return st;
     attention_merge_kernel<<<dim3((unsigned)H), dim3(256), 0, (hipStream_t)stream>>>(
         (const float *)workspace, splits, (half_t *)out_f16);
