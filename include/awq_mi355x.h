@@ -95,6 +95,14 @@ int awq_packed_sizes(int64_t N, int64_t K, int group, size_t *qweight_bytes,
 int awq_act_scale(const void *X_f16, int64_t T, int64_t K, float alpha, float *s,
                   void *stream);
 
+/* The same with a workspace for partial sums (device, 16-byte aligned, contents undefined afterwards;
+ * awq_act_scale_workspace_bytes() bytes, 0 where none is of use), which lets a lone matrix of a few thousand
+ * columns occupy the whole chip: the sums are per column, and awq_act_scale has K / 64 workgroups.  Bit for
+ * bit the result of awq_act_scale; workspace may be NULL (then it is that call). */
+size_t awq_act_scale_workspace_bytes(int64_t T, int64_t K);
+int awq_act_scale_ws(const void *X_f16, int64_t T, int64_t K, float alpha, float *s, void *workspace,
+                     size_t workspace_bytes, void *stream);
+
 /* The same computation for up to AWQ_ACT_SCALE_MULTI_MAX matrices in one call (16 per launch),
  * each result bit for bit that of awq_act_scale on its own.  The sums are per column, so a
  * launch has K / 64 workgroups per matrix: one matrix of K = 4096 occupies a quarter of the

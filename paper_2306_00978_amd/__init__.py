@@ -41,7 +41,7 @@ EXPORTS = [
     "awq_w2a16_linear_multi",
     "awq_last_grouped_plan", "awq_static_scratch_bytes", "awq_w4a16_linear_static",
     "awq_quantize_pack_multi", "awq_w4a16_linear_chain", "awq_blob_header_init", "awq_blob_header_check",
-    "awq_act_scale_multi",
+    "awq_act_scale_multi", "awq_act_scale_workspace_bytes", "awq_act_scale_ws",
 ]
 MULTI_MAX = 56
 
@@ -129,6 +129,10 @@ def load() -> ctypes.CDLL:
     lib.awq_packed_sizes.argtypes = [i64, i64, i32, szp, szp, szp]
     lib.awq_act_scale.restype = i32
     lib.awq_act_scale.argtypes = [vp, i64, i64, ctypes.c_float, vp, vp]
+    lib.awq_act_scale_workspace_bytes.restype = sz
+    lib.awq_act_scale_workspace_bytes.argtypes = [i64, i64]
+    lib.awq_act_scale_ws.restype = i32
+    lib.awq_act_scale_ws.argtypes = [vp, i64, i64, ctypes.c_float, vp, vp, sz, vp]
     lib.awq_apply_inv_scale.restype = i32
     lib.awq_apply_inv_scale.argtypes = [vp, vp, i64, i64, vp, vp]
     lib.awq_quantize_pack.restype = i32
@@ -252,7 +256,10 @@ def awq_act_scale(X: torch.Tensor, alpha: float = 0.5, out: torch.Tensor | None 
     T, K = X.shape
     s = out if out is not None else torch.empty(K, dtype=torch.float32, device=X.device)
     _dev(s, torch.float32, "s")
-    _check(load().awq_act_scale(_ptr(X), T, K, float(alpha), _ptr(s), _stream()), "awq_act_scale")
+    lib = load()
+    need = lib.awq_act_scale_workspace_bytes(T, K)        # partial sums of the row classes, where they pay
+    ws = torch.empty(need, dtype=torch.uint8, device=X.device) if need else None
+    _check(lib.awq_act_scale_ws(_ptr(X), T, K, float(alpha), _ptr(s), _ptr(ws), need, _stream()), "awq_act_scale")
     return s
 
 

@@ -35,9 +35,8 @@ struct ActArgs {
 // them: 172 for K = 11008 (5.2 TB/s at 65 536 rows) but 64 for K = 4096, a quarter of the chip --
 // a CU alone takes in about 33 GB/s whatever the number of loads in flight (2.1-2.2 TB/s).
 // Narrower column blocks (16 columns, the workgroups that share a 128-byte line on one XCD) reach
-// 2.5 TB/s for K = 4096 and are slower for wide K; dividing the rows over workgroups would need
-// a place for partial sums, which the call does not have.  What fills the chip is several
-// matrices per launch (awq_act_scale_multi): a decoder layer has four distinct inputs to calibrate.
+// 2.5 TB/s for K = 4096 and are slower for wide K.  What fills the chip is several matrices per launch
+// (awq_act_scale_multi), or a place for partial sums (act_partial_kernel below).
 template <bool RAW>
 __global__ __launch_bounds__(1024) void act_scale_kernel(const ActArgs A)
 {
@@ -112,6 +111,89 @@ int act_scale_launch(const ActProblem *probs, int count, float alpha, hipStream_
     A.alpha = alpha;
     act_scale_kernel<RAW><<<dim3(wg), dim3(1024), 0, stream>>>(A);
     return awq_launch_status();
+}
+
+// The same sums with the rows divided as well, for callers that bring a workspace.  Class j of R takes the
+// row phases p = j (mod R) of act_scale_kernel: the 128 / R phase sums of a class meet in the first levels
+// of that kernel's tree, the R classes in its last levels (act_finish_kernel), so every result is the
+// same bit for bit.  A workgroup has 1024 / R threads; 16 rows are requested ahead, because a CU holds
+// only 1024 / R x K / 64 x R / 256 threads of the one matrix (65 536 x 4096: 256 threads, 64 KB in flight).
+// 65 536 rows: K = 4096 243 -> 106 us = 5.1 TB/s (a large copy moves 4.9), K = 1024 121 -> 31, K = 5120 289 -> 167,
+// K = 8192 270 -> 215.
+__global__ __launch_bounds__(512) void act_partial_kernel(const uint4 *__restrict__ X, int64_t T, int64_t K, int R,
+                                                          float *__restrict__ part)
+{
+    __shared__ float red[ACT_PHASES / 2][ACT_COLS];
+    asm volatile("" ::"s"(X), "s"(T), "s"(K), "s"(R), "s"(part));      // arguments in one round
+    const int j = blockIdx.y, oct = threadIdx.x & 7, i0 = threadIdx.x >> 3;
+    const int64_t col0 = (int64_t)blockIdx.x * ACT_COLS + oct * 8;
+    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (col0 < K) {
+        const int64_t K8 = K / 8;
+        const uint4 *p = X + col0 / 8;
+        constexpr int AHEAD = 16;
+        int64_t t = j + (int64_t)R * i0;
+        for (; t + (AHEAD - 1) * ACT_PHASES < T; t += AHEAD * ACT_PHASES) {
+            uint4 raw[AHEAD];
+#pragma unroll
+            for (int a = 0; a < AHEAD; ++a) raw[a] = p[(t + a * ACT_PHASES) * K8];
+#pragma unroll
+            for (int a = 0; a < AHEAD; ++a) {
+                const half_t *h = reinterpret_cast<const half_t *>(&raw[a]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[e] += __builtin_fabsf((float)h[e]);
+            }
+        }
+        for (; t < T; t += ACT_PHASES) {
+            const uint4 raw = p[t * K8];
+            const half_t *h = reinterpret_cast<const half_t *>(&raw);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] += __builtin_fabsf((float)h[e]);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) red[i0][oct * 8 + e] = acc[e];
+    __syncthreads();
+    for (int half = ACT_PHASES / R / 2; half >= 1; half >>= 1) {
+        for (int i = threadIdx.x; i < half * ACT_COLS; i += blockDim.x)
+            red[i / ACT_COLS][i % ACT_COLS] += red[i / ACT_COLS + half][i % ACT_COLS];
+        __syncthreads();
+    }
+    for (int i = threadIdx.x; i < ACT_COLS; i += blockDim.x) {
+        const int64_t col = (int64_t)blockIdx.x * ACT_COLS + i;
+        if (col < K) part[(int64_t)j * K + col] = red[0][i];
+    }
+}
+
+template <int R>
+__global__ __launch_bounds__(64) void act_finish_kernel(const float *__restrict__ part, int64_t T, int64_t K, float alpha,
+                                                        float *__restrict__ s)
+{
+    asm volatile("" ::"s"(part), "s"(T), "s"(K), "s"(alpha), "s"(s));  // arguments in one round
+    const int64_t col = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    if (col >= K) return;
+    float v[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) v[j] = part[(int64_t)j * K + col];
+#pragma unroll
+    for (int half = R / 2; half >= 1; half >>= 1)
+#pragma unroll
+        for (int j = 0; j < half; ++j) v[j] += v[j + half];
+    s[col] = powf(fmaxf(v[0] / (float)T, 1e-4f), alpha);
+}
+
+// Row classes for a matrix: the most that keep column blocks x classes within 272 workgroups (one per CU; a
+// second one on some CUs costs more than it brings), at most 16.  1, i.e. no workspace, for more than
+// 128 column blocks (65 536 x 11008: 273 us against 350 with two classes) and for few rows, where the
+// second launch costs more than the narrow first one loses (4096 rows: 8.0 -> 7.1 us at K = 4096,
+// 11.9 -> 13.0 at K = 6144; 2048 rows: 5.4 -> 6.9).
+int act_classes(int64_t T, int64_t K)
+{
+    const int64_t blocks = (K + ACT_COLS - 1) / ACT_COLS;
+    if (blocks > 128 || T < (blocks <= 64 ? 4096 : 8192)) return 1;
+    int R = 1;
+    while (R < 16 && blocks * R * 2 <= 272) R *= 2;
+    return R;
 }
 
 int act_scale_check(const void *X_f16, int64_t T, int64_t K, const float *s)
@@ -281,6 +363,39 @@ extern "C" int awq_act_scale(const void *X_f16, int64_t T, int64_t K, float alph
     if (!(alpha >= 0.0f && alpha <= 1.0f)) return AWQ_ERR_BAD_ARGUMENT;
     const ActProblem p = {(const uint4 *)X_f16, s, T, K, 0, 0};
     return act_scale_launch<false>(&p, 1, alpha, (hipStream_t)stream);
+}
+
+extern "C" size_t awq_act_scale_workspace_bytes(int64_t T, int64_t K)
+{
+    if (T <= 0 || K <= 0 || (K % 8) != 0 || K > (int64_t)1 << 30) return 0;
+    const int R = act_classes(T, K);
+    return R > 1 ? (size_t)R * (size_t)K * sizeof(float) : 0;
+}
+
+extern "C" int awq_act_scale_ws(const void *X_f16, int64_t T, int64_t K, float alpha, float *s, void *workspace,
+                                size_t workspace_bytes, void *stream)
+{
+    const size_t need = awq_act_scale_workspace_bytes(T, K);
+    if (need == 0 || !workspace) return awq_act_scale(X_f16, T, K, alpha, s, stream);
+    const int st = act_scale_check(X_f16, T, K, s);
+    if (st != AWQ_OK) return st;
+    if (!(alpha >= 0.0f && alpha <= 1.0f)) return AWQ_ERR_BAD_ARGUMENT;
+    if (workspace_bytes < need) return AWQ_ERR_WORKSPACE_TOO_SMALL;
+    if (!awq_aligned16(workspace)) return AWQ_ERR_MISALIGNED;
+    const int R = act_classes(T, K);
+    float *part = (float *)workspace;
+    act_partial_kernel<<<dim3((unsigned)((K + ACT_COLS - 1) / ACT_COLS), (unsigned)R), dim3(1024 / R), 0,
+                         (hipStream_t)stream>>>((const uint4 *)X_f16, T, K, R, part);
+    const int launched = awq_launch_status();
+    if (launched != AWQ_OK) return launched;
+    const dim3 grid((unsigned)((K + 63) / 64));
+    switch (R) {
+    case 2: act_finish_kernel<2><<<grid, dim3(64), 0, (hipStream_t)stream>>>(part, T, K, alpha, s); break;
+    case 4: act_finish_kernel<4><<<grid, dim3(64), 0, (hipStream_t)stream>>>(part, T, K, alpha, s); break;
+    case 8: act_finish_kernel<8><<<grid, dim3(64), 0, (hipStream_t)stream>>>(part, T, K, alpha, s); break;
+    default: act_finish_kernel<16><<<grid, dim3(64), 0, (hipStream_t)stream>>>(part, T, K, alpha, s); break;
+    }
+    return awq_launch_status();
 }
 
 extern "C" int awq_act_scale_multi(const awq_act_scale_desc *descs, int count, float alpha, void *stream)
