@@ -33,6 +33,7 @@
 //   instructions per MFMA.
 // fp32 accumulation, one rounding to fp16 at the end.
 #include "awq_common.h"
+#include "awq_gemm_epilogue.h"
 
 #include <type_traits>
 
@@ -168,17 +169,23 @@ __device__ __forceinline__ uint32_t word_of(const u32x4 &v, int j)
 // writes its partial tile in fp32 to part[range][M][N] and a second kernel adds the ranges.  For
 // a few hundred tokens there are far fewer tiles than CUs (ceil(M/128) * N/256), and a workgroup
 // per tile would leave most of the chip idle while a handful of CUs walk all of K.
-template <bool SPLIT>
+// GEMM_LOSS (the scale search): nothing is stored; y holds the layer's reference outputs, and the workgroup
+// leaves the sum over its tile of the squared differences to them in loss[tile] -- of the outputs
+// rounded to fp16, eight differences squared and added in fp32, the rest in fp64, in a fixed order, as the
+// separate pass over two stored outputs does it.
+enum { GEMM_PLAIN, GEMM_SPLIT, GEMM_LOSS };
+template <int MODE>
 __global__ __launch_bounds__(512, 1) void gemm_kernel(
     const half_t *__restrict__ x, const unsigned char *__restrict__ qweight,
     const unsigned char *__restrict__ scales, const unsigned char *__restrict__ zeros,
     half_t *__restrict__ y, int M, int N, int K, int G, int tiles_n, int tiles_total,
-    float *__restrict__ part, int ksplit)
+    float *__restrict__ part, int ksplit, double *__restrict__ loss)
 {
+    constexpr bool SPLIT = MODE == GEMM_SPLIT;
     extern __shared__ __align__(16) unsigned char smem[];
     // all arguments fetched in one round (otherwise one scalar-cache miss per first use)
     asm volatile("" ::"s"(x), "s"(qweight), "s"(scales), "s"(zeros), "s"(y), "s"(M), "s"(N), "s"(K), "s"(G),
-                 "s"(tiles_n), "s"(tiles_total), "s"(part), "s"(ksplit));
+                 "s"(tiles_n), "s"(tiles_total), "s"(part), "s"(ksplit), "s"(loss));
     // Workgroups are handed to the eight XCDs round-robin by their linear id, and each XCD has
     // its own L2.  The tile a workgroup computes is therefore chosen so that an XCD gets a
     // contiguous range of tiles in token-block-major order: its workgroups then share a few x
@@ -431,37 +438,8 @@ __global__ __launch_bounds__(512, 1) void gemm_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
 
-    // The two waves of a pair hold partial sums of the same 128 x 64 sub-tile.  Wave kh keeps
-    // token blocks 2 kh, 2 kh + 1 and hands the other two to its partner through the now idle
-    // LDS: 64 accumulators per lane, stored as [wave][accumulator][lane] (consecutive lanes in
-    // consecutive words).
-    {
-        float *xch = reinterpret_cast<float *>(smem);
-        float *mine = xch + (size_t)wave * (64 * 64);
-        const float *theirs = xch + (size_t)(wave ^ 4) * (64 * 64);
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    // the block this wave gives away: kh = 0 gives 2, 3; kh = 1 gives 0, 1
-                    const float give = kh ? acc[ii][b][v] : acc[2 + ii][b][v];
-                    mine[((ii * 2 + b) * 16 + v) * 64 + lane] = give;
-                }
-        __syncthreads();
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float got = theirs[((ii * 2 + b) * 16 + v) * 64 + lane];
-                    if (kh) acc[2 + ii][b][v] += got;
-                    else acc[ii][b][v] += got;
-                }
-        __syncthreads();
-    }
+    floatx16 own[2][2];
+    gemm_pair_sum(acc, own, smem, wave, lane, kh);
 
     if (SPLIT) {
         // partial sums leave in fp32, 32 consecutive columns per half-wave and accumulator
@@ -474,38 +452,47 @@ __global__ __launch_bounds__(512, 1) void gemm_kernel(
                 for (int v = 0; v < 16; ++v) {
                     const int m = m0 + 64 * kh + 32 * ii + 8 * (v >> 2) + 4 * hi + (v & 3);
                     const int n = nt0 * 16 + 32 * b + l32;
-                    const float val = kh ? acc[2 + ii][b][v] : acc[ii][b][v];
-                    if (m < M && n < N) dst[(size_t)m * N + n] = val;
+                    if (m < M && n < N) dst[(size_t)m * N + n] = own[ii][b][v];
                 }
         return;
     }
-    // Epilogue.  Accumulator v of tile (i, b) is y[m0 + 32 i + 8 (v/4) + 4 hi + v%4][16 nt0 + 32 b
-    // + l32]: a lane holds single columns, which would leave as 2-byte stores.  Each wave turns
-    // its 64 x 64 part around through its own 9 KB of LDS (rows of 128 + 16 bytes: the padding
-    // spreads the banks) and stores 16 bytes per lane, 8 rows x 128 contiguous bytes per
-    // instruction.
-    {
-        constexpr int ROWB = 144;
-        unsigned char *mine = smem + (size_t)wave * (64 * ROWB);
+    const unsigned char *mine = gemm_turn(own, smem, wave, l32, hi);
+    if (MODE == GEMM_PLAIN) {
+        gemm_store(mine, y, m0 + 64 * kh, nt0 * 16, M, N, lane);
+        return;
+    }
+    const int n = nt0 * 16 + (lane & 7) * 8;
+    uint4 ref[8];
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+    for (int it = 0; it < 8; ++it) {
+        const int m = m0 + 64 * kh + it * 8 + (lane >> 3);
+        // a place outside the matrix re-reads its end and is not counted
+        ref[it] = *reinterpret_cast<const uint4 *>(y + (size_t)min(m, M - 1) * N + min(n, N - 8));
+    }
+    double sum = 0.0;
 #pragma unroll
-            for (int ii = 0; ii < 2; ++ii)
+    for (int it = 0; it < 8; ++it) {
+        const uint4 v = gemm_row16(mine, it, lane);
+        const half_t *ha = reinterpret_cast<const half_t *>(&v), *hb = reinterpret_cast<const half_t *>(&ref[it]);
+        float c = 0.f;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = 32 * ii + 8 * (v >> 2) + 4 * hi + (v & 3);
-                    const float val = kh ? acc[2 + ii][b][v] : acc[ii][b][v];
-                    *reinterpret_cast<half_t *>(mine + row * ROWB + (32 * b + l32) * 2) = (half_t)val;
-                }
-        // wave-private area: the compiler orders these LDS reads after the writes above
-        const int n = nt0 * 16 + (lane & 7) * 8;
-#pragma unroll
-        for (int it = 0; it < 8; ++it) {
-            const int row = it * 8 + (lane >> 3);
-            const uint4 v = *reinterpret_cast<const uint4 *>(mine + row * ROWB + (lane & 7) * 16);
-            const int m = m0 + 64 * kh + row;
-            if (m < M && n < N) *reinterpret_cast<uint4 *>(y + (size_t)m * N + n) = v;
+        for (int e = 0; e < 8; ++e) {
+            const float d = (float)ha[e] - (float)hb[e];
+            c += d * d;
         }
+        if (m0 + 64 * kh + it * 8 + (lane >> 3) < M && n < N) sum += (double)c;
+    }
+#pragma unroll
+    for (int d = 1; d <= 32; d <<= 1) sum += __shfl_xor(sum, d);
+    __syncthreads();                                         // every wave has read its rows
+    double *sums = reinterpret_cast<double *>(smem);
+    if (lane == 0) sums[wave] = sum;
+    __syncthreads();
+    if (tid == 0) {
+        double total = sums[0];
+#pragma unroll
+        for (int w = 1; w < 8; ++w) total += sums[w];
+        loss[tile] = total;
     }
 }
 
@@ -561,9 +548,9 @@ double awq_gemm_unsplit_us(int M, int N, int K)
 
 namespace {
 
-template <bool SPLIT>
+template <int MODE>
 int gemm_launch_any(const void *x, const void *qweight, const void *scales, const void *zeros,
-                    void *y, int M, int N, int K, float *part, int ksplit, hipStream_t stream)
+                    void *y, int M, int N, int K, float *part, int ksplit, double *loss, hipStream_t stream)
 {
     const int G = K / AWQ_GROUP;
     const int tiles_n = (N + BN - 1) / BN;
@@ -573,14 +560,15 @@ int gemm_launch_any(const void *x, const void *qweight, const void *scales, cons
     static AwqOncePerDevice once;
     std::atomic<bool> &attr_set = once.here();
     if (!attr_set.load(std::memory_order_relaxed)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_kernel<SPLIT>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_kernel<MODE>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess)
             return AWQ_ERR_HIP;
         attr_set.store(true, std::memory_order_relaxed);
     }
-    gemm_kernel<SPLIT><<<grid, block, LDS_BYTES, stream>>>(
+    gemm_kernel<MODE><<<grid, block, LDS_BYTES, stream>>>(
         (const half_t *)x, (const unsigned char *)qweight, (const unsigned char *)scales,
-        (const unsigned char *)zeros, (half_t *)y, M, N, K, G, tiles_n, (int)tiles_total, part, ksplit);
+        (const unsigned char *)zeros, (half_t *)y, M, N, K, G, tiles_n, (int)tiles_total, part, ksplit,
+        loss);
     return awq_launch_status();
 }
 
@@ -590,17 +578,27 @@ int gemm_launch_any(const void *x, const void *qweight, const void *scales, cons
 int awq_gemm_launch(const void *x, const void *qweight, const void *scales, const void *zeros,
                     void *y, int M, int N, int K, hipStream_t stream)
 {
-    return gemm_launch_any<false>(x, qweight, scales, zeros, y, M, N, K, nullptr, 1, stream);
+    return gemm_launch_any<GEMM_PLAIN>(x, qweight, scales, zeros, y, M, N, K, nullptr, 1, nullptr, stream);
 }
 
 // The same with K cut into awq_gemm_ksplit() ranges; part: ksplit * M * N floats, 16-byte aligned.
 int awq_gemm_launch_split(const void *x, const void *qweight, const void *scales, const void *zeros,
                           void *y, int M, int N, int K, void *part, int ksplit, hipStream_t stream)
 {
-    int st = gemm_launch_any<true>(x, qweight, scales, zeros, y, M, N, K, (float *)part, ksplit, stream);
+    int st = gemm_launch_any<GEMM_SPLIT>(x, qweight, scales, zeros, y, M, N, K, (float *)part, ksplit, nullptr, stream);
     if (st != AWQ_OK) return st;
     const int64_t quads = (int64_t)M * N / 4;
     gemm_reduce_kernel<<<dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream>>>(
         (const float4 *)part, (uint2 *)y, quads, ksplit);
     return awq_launch_status();
+}
+
+// The loss form: y_ref [M,N] fp16 is read, loss receives one partial sum for each of awq_gemm_tiles() tiles.
+int64_t awq_gemm_tiles(int M, int N) { return (int64_t)((N + BN - 1) / BN) * ((M + BM - 1) / BM); }
+
+int awq_gemm_launch_loss(const void *x, const void *qweight, const void *scales, const void *zeros, const void *y_ref,
+                         int M, int N, int K, double *loss, hipStream_t stream)
+{
+    return gemm_launch_any<GEMM_LOSS>(x, qweight, scales, zeros, const_cast<void *>(y_ref), M, N, K, nullptr, 1, loss,
+                                      stream);
 }

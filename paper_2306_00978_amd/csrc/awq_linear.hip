@@ -40,6 +40,33 @@ extern "C" size_t awq_linear_workspace_bytes(int64_t M, int64_t N, int64_t K, in
     return ks > 1 ? (size_t)ks * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
 
+namespace {
+
+// The prefill kernel's tiles are 128 x 256: at a few hundred tokens there are few of them, each
+// walking a long K, and cutting K over workgroups costs a second pass over fp32 partial tiles.  The tile
+// kernel cuts K over the waves of a workgroup and pays with more reads of x (a tile is at most 128 x 48
+// or 96 x 64), so it wins until the prefill kernel fills the chip.  Up to 128 tokens always
+// (11008 x 4096 at 77 tokens: 13.8 us against 23.1, 4096 x 11008 at 17: 11.5 against 20.9, 4096 x 4096
+// at 128: 10.9 against 18.5); beyond, by the two estimates, the tile kernel's with 20 % on top (its
+// large launches run at a lower clock than the small ones it was fitted to): 4096 x 4096 at 300 / 500
+// tokens 19.2 / 28.5 us against 26.3 / 31.1; 4096 x 11008 at 300: 41 against 45, at 500: 62 against 55 and
+// left to the prefill kernel.
+bool takes_tile_kernel(const TilePlan &plan, int M, int N, int K, bool split)
+{
+    double gemm_us = 0.0;
+    if (split) (void)awq_gemm_ksplit(M, N, K, &gemm_us);
+    else gemm_us = awq_gemm_unsplit_us(M, N, K);
+    return M <= 128 || 1.2 * plan.us < gemm_us;
+}
+
+}  // namespace
+
+// Whether awq_w4a16_linear without a workspace runs the prefill kernel (whose loss form the scale search uses).
+bool awq_linear_takes_prefill(int M, int N, int K)
+{
+    return M > 16 && !takes_tile_kernel(awq_tile_plan(M, N, K), M, N, K, false);
+}
+
 extern "C" int awq_w4a16_linear(const void *x_f16, const void *qweight, const void *scales,
                                 const void *zeros, void *y_f16, int64_t M, int64_t N,
                                 int64_t K, int group, void *workspace, size_t workspace_bytes,
@@ -77,20 +104,8 @@ extern "C" int awq_w4a16_linear(const void *x_f16, const void *qweight, const vo
         return awq_gemv_launch(x_f16, qweight, scales, zeros, y_f16, (int)M, (int)N, (int)K,
                                (hipStream_t)stream);
     }
-    // The prefill kernel's tiles are 128 x 256: at a few hundred tokens there are few of them, each
-    // walking a long K, and cutting K over workgroups costs a second pass over fp32 partial tiles.  The tile
-    // kernel cuts K over the waves of a workgroup and pays with more reads of x (a tile is at most 128 x 48
-    // or 96 x 64), so it wins until the prefill kernel fills the chip.  Up to 128 tokens always
-    // (11008 x 4096 at 77 tokens: 13.8 us against 23.1, 4096 x 11008 at 17: 11.5 against 20.9, 4096 x 4096
-    // at 128: 10.9 against 18.5); beyond, by the two estimates, the tile kernel's with 20 % on top (its
-    // large launches run at a lower clock than the small ones it was fitted to): 4096 x 4096 at 300 / 500
-    // tokens 19.2 / 28.5 us against 26.3 / 31.1; 4096 x 11008 at 300: 41 against 45, at 500: 62 against 55 and
-    // left to the prefill kernel.
     const TilePlan plan = awq_tile_plan((int)M, (int)N, (int)K);
-    double gemm_us = 0.0;
-    if (split) (void)awq_gemm_ksplit((int)M, (int)N, (int)K, &gemm_us);
-    else gemm_us = awq_gemm_unsplit_us((int)M, (int)N, (int)K);
-    if (M <= 128 || 1.2 * plan.us < gemm_us)
+    if (takes_tile_kernel(plan, (int)M, (int)N, (int)K, split))
         return awq_tile_launch(4, plan, x_f16, qweight, scales, zeros, y_f16, (int)M, (int)N, (int)K,
                                (hipStream_t)stream);
     if (split)

@@ -5,6 +5,7 @@
 // mean |X| over the calibration rows, and Eq. 4 moves diag(s)^-1 onto the
 // activations.  Both are plain streaming passes over X (HBM-bound).
 #include "awq_common.h"
+#include "awq_inv_scale.h"
 
 #include <algorithm>
 
@@ -214,15 +215,8 @@ __global__ __launch_bounds__(256) void apply_inv_scale_kernel(const uint4 *__res
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= runs_total) return;
     const int64_t run = i % K8;
-    uint4 raw = x[i];
-    const half_t *h = reinterpret_cast<const half_t *>(&raw);
-    const float4 a = s[2 * run], b = s[2 * run + 1];
-    const float sv[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-    uint4 out;
-    half_t *o = reinterpret_cast<half_t *>(&out);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = (half_t)((float)h[e] / sv[e]);
-    xs[i] = out;
+    const uint4 raw = x[i];
+    xs[i] = inv_scaled(raw, s[2 * run], s[2 * run + 1]);
 }
 
 // RMS normalisation with the 1/s factor of Eq. 4 folded in (Sec. 4.2: the operators of the

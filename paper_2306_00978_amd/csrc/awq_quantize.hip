@@ -14,6 +14,7 @@
 // (zero point, codes) are taken in IEEE binary32 with one rounding per operation,
 // correctly rounded division and round-half-even, bit for bit.
 #include "awq_common.h"
+#include "awq_inv_scale.h"
 
 #include <algorithm>
 
@@ -121,7 +122,7 @@ struct QuantArgs {
 #endif
 
 template <bool CLIP, bool ACT>
-__global__ __launch_bounds__(256, CLIP ? 1 : AWQ_QUANT_MIN_WAVES) void quantize_pack_kernel(const QuantArgs A, const ClipRatios ratios)
+__device__ __forceinline__ void quantize_wave(const QuantArgs &A, const ClipRatios &ratios)
 {
     const int lane = threadIdx.x & 63;
     const int unit = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
@@ -317,6 +318,45 @@ __global__ __launch_bounds__(256, CLIP ? 1 : AWQ_QUANT_MIN_WAVES) void quantize_
     }
 }
 
+template <bool CLIP, bool ACT>
+__global__ __launch_bounds__(256, CLIP ? 1 : AWQ_QUANT_MIN_WAVES) void quantize_pack_kernel(const QuantArgs A, const ClipRatios ratios)
+{
+    quantize_wave<CLIP, ACT>(A, ratios);
+}
+
+// One grid point of the scale search: W diag(s) quantized by the first workgroups, xs = x / s by the others.  The
+// two do not depend on each other; apart they are two launches too short to reach the memory's rate, the
+// first bound by instruction issue, the second by memory (4096 x 4096, 2048 rows: 12.3 + 7.1 us, together 17.9).
+struct InvArgs {
+    const uint4 *x;
+    const float4 *s;
+    uint4 *xs;
+    int64_t runs;          // M * K / 8
+    int K8, first_block;
+};
+constexpr int INV_RUNS = 4;                        // 16-byte runs per thread, requested together
+__global__ __launch_bounds__(256, AWQ_QUANT_MIN_WAVES) void quantize_inv_kernel(const QuantArgs A, const InvArgs I)
+{
+    if ((int)blockIdx.x < I.first_block) {
+        quantize_wave<false, false>(A, ClipRatios{});
+        return;
+    }
+    const int64_t i0 = (int64_t)((int)blockIdx.x - I.first_block) * (256 * INV_RUNS) + threadIdx.x;
+    uint4 raw[INV_RUNS];
+    float4 a[INV_RUNS], b[INV_RUNS];
+#pragma unroll
+    for (int u = 0; u < INV_RUNS; ++u) {
+        const int64_t i = min(i0 + 256 * u, I.runs - 1);
+        const int run = (int)(i % I.K8);
+        raw[u] = I.x[i];
+        a[u] = I.s[2 * run];
+        b[u] = I.s[2 * run + 1];
+    }
+#pragma unroll
+    for (int u = 0; u < INV_RUNS; ++u)
+        if (i0 + 256 * u < I.runs) I.xs[i0 + 256 * u] = inv_scaled(raw[u], a[u], b[u]);
+}
+
 __global__ __launch_bounds__(256) void unpack_kernel(
     const uint4 *__restrict__ qweight, const uint16_t *__restrict__ scales,
     const uint8_t *__restrict__ zeros, uint8_t *__restrict__ codes,
@@ -382,9 +422,11 @@ int quantize_check(const QuantJob &j, int group)
 // and walks down `rb_per_wave` row blocks; that number is chosen so that the waves of a launch
 // about fill the chip once (three waves per SIMD, the kernel's register budget): more waves
 // would queue behind the resident ones as a second, nearly empty round.
-int quantize_launch(const QuantJob *jobs, int count, const ClipRatios *ratios, hipStream_t stream)
+// inv (one matrix, no clipping): the launch also divides activations; the quantizing waves then take two of the
+// three places of a SIMD, so that the others run beside them.
+int quantize_launch(const QuantJob *jobs, int count, const ClipRatios *ratios, hipStream_t stream, InvArgs *inv = nullptr)
 {
-    const int RESIDENT_WAVES = 256 * 4 * (ratios ? 3 : AWQ_QUANT_MIN_WAVES == 4 ? 4 : 3);
+    const int RESIDENT_WAVES = 256 * 4 * (inv ? 2 : ratios ? 3 : AWQ_QUANT_MIN_WAVES == 4 ? 4 : 3);
     for (int first = 0; first < count; first += QUANT_MAX_PROBLEMS) {
         const int n = std::min(QUANT_MAX_PROBLEMS, count - first);
         int64_t tiles = 0;
@@ -414,7 +456,12 @@ int quantize_launch(const QuantJob *jobs, int count, const ClipRatios *ratios, h
         A.count = n;
         A.num_units = units;
         const dim3 grid((unsigned)((units + 3) / 4)), block(256);
-        if (ratios && act) quantize_pack_kernel<true, true><<<grid, block, 0, stream>>>(A, *ratios);
+        if (inv) {
+            inv->first_block = (int)grid.x;
+            const int64_t blocks = grid.x + (inv->runs + 256 * INV_RUNS - 1) / (256 * INV_RUNS);
+            if (blocks > 0x7fffffff) return AWQ_ERR_BAD_SHAPE;
+            quantize_inv_kernel<<<dim3((unsigned)blocks), block, 0, stream>>>(A, *inv);
+        } else if (ratios && act) quantize_pack_kernel<true, true><<<grid, block, 0, stream>>>(A, *ratios);
         else if (ratios) quantize_pack_kernel<true, false><<<grid, block, 0, stream>>>(A, *ratios);
         else quantize_pack_kernel<false, false><<<grid, block, 0, stream>>>(A, ClipRatios{});
         const int st = awq_launch_status();
@@ -432,6 +479,15 @@ extern "C" int awq_quantize_pack(const void *W_f16, const float *s, int64_t N, i
     const QuantJob j = {W_f16, s, N, K, qweight, scales, zeros, nullptr, nullptr, 0};
     const int st = quantize_check(j, group);
     return st != AWQ_OK ? st : quantize_launch(&j, 1, nullptr, (hipStream_t)stream);
+}
+
+// awq_quantize_pack(W, s) and awq_apply_inv_scale(x, s) in one launch, for the scale search; arguments validated by it.
+int awq_quantize_inv_launch(const void *W, const float *s, int64_t N, int64_t K, void *qweight, void *scales, void *zeros,
+                            const void *x, int64_t M, void *xs, hipStream_t stream)
+{
+    const QuantJob j = {W, s, N, K, qweight, scales, zeros, nullptr, nullptr, 0};
+    InvArgs inv = {(const uint4 *)x, (const float4 *)s, (uint4 *)xs, M * (K / 8), (int)(K / 8), 0};
+    return quantize_launch(&j, 1, nullptr, stream, &inv);
 }
 
 extern "C" int awq_quantize_pack_multi(const awq_quantize_desc *descs, int count, int group, void *stream)

@@ -13,8 +13,15 @@
 // the argmin and s* = s_X^alpha* are taken on the device, so the call neither synchronises nor
 // copies to the host.
 #include "awq_common.h"
+#include "awq_gemm_epilogue.h"
 
 int awq_act_mean_launch(const void *X_f16, int64_t T, int64_t K, float *mean, hipStream_t stream);
+int awq_quantize_inv_launch(const void *W, const float *s, int64_t N, int64_t K, void *qweight, void *scales, void *zeros,
+                            const void *x, int64_t M, void *xs, hipStream_t stream);
+bool awq_linear_takes_prefill(int M, int N, int K);
+int64_t awq_gemm_tiles(int M, int N);
+int awq_gemm_launch_loss(const void *x, const void *qweight, const void *scales, const void *zeros, const void *y_ref,
+                         int M, int N, int K, double *loss, hipStream_t stream);
 
 namespace {
 
@@ -25,96 +32,158 @@ struct AlphaList {
     float a[MAX_ALPHAS];
 };
 
-__global__ __launch_bounds__(256) void pow_kernel(const float *__restrict__ mean, float alpha, int K,
+// s_X^alpha for the grid points [first, first + gridDim.y)
+__global__ __launch_bounds__(256) void pow_kernel(const float *__restrict__ mean, AlphaList alphas, int first, int K,
                                                   float *__restrict__ s)
 {
-    asm volatile("" ::"s"(mean), "s"(alpha), "s"(K), "s"(s));           // arguments in one round
+    asm volatile("" ::"s"(mean), "s"(K), "s"(s));                       // arguments in one round
     const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k < K) s[k] = powf(mean[k], alpha);
+    if (k < K) s[(size_t)blockIdx.y * K + k] = powf(mean[k], alphas.a[first + blockIdx.y]);
 }
 
-// Y[T,N] = X[T,K] W[N,K]^T, fp16 operands, fp32 accumulation, fp16 result: the unquantized layer
-// of Eq. 4.  128 x 128 tile per workgroup, four waves of 64 x 64 (2 x 2 tiles of
-// v_mfma_f32_32x32x16_f16), 64 columns of K per step staged through LDS (rows padded to 144
-// bytes: the 16-byte fragment reads of 16 consecutive rows fall into 16 different bank groups),
-// next step prefetched into registers.  It runs once per search, next to one quantized product
-// per grid point.
-constexpr int DT = 128;
-constexpr int DROW = 144;
+typedef __attribute__((address_space(3))) void lds_void_t;
+typedef const __attribute__((address_space(1))) void gbl_void_t;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void dense_gemm_kernel(const half_t *__restrict__ X,
-                                                         const half_t *__restrict__ W,
-                                                         half_t *__restrict__ Y, int T, int N, int K)
+__device__ __forceinline__ void dma16(const unsigned char *g, uint32_t lds_addr)
 {
-    __shared__ __align__(16) unsigned char lds[2 * DT * DROW];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int l32 = lane & 31, hi = lane >> 5;
-    const int t0 = blockIdx.y * DT, n0 = blockIdx.x * DT;
-    const int lrow = tid >> 3, lchunk = tid & 7;
-    const uint4 *asrc[4], *bsrc[4];
+    __builtin_amdgcn_global_load_lds((gbl_void_t *)(uintptr_t)g, (lds_void_t *)(uintptr_t)lds_addr, 16, 0, 0);
+}
+
+// Y[T,N] = X[T,K] W[N,K]^T, fp16 operands, fp32 accumulation, fp16 result: the unquantized layer of Eq. 4.
+// The geometry of the W4A16 prefill kernel: 128 x 256 tile, eight waves, four side by side along N (128 x 64
+// each, 4 x 2 tiles of v_mfma_f32_32x32x16_f16), the two waves of a SIMD splitting the K steps of a stage
+// between them.  A stage is 64 columns of K: 128 rows of X and 256 of W, 128 bytes each, memory -> LDS in whole
+// cache lines, 16-byte chunk k of row i at place k ^ (i / 2 % 8), so that the fragment reads (32 rows) are free
+// of bank conflicts; a ring of three stages (144 KB), one barrier per stage.  A wave's last step of a
+// stage runs behind the barrier: its MFMAs cover the first fragment reads of the next one.
+// (128 x 128 tiles staged through registers with two barriers per 64 columns: 296 us = 232 TFLOP/s at
+// 2048 x 4096 x 4096; this form 74 us = 930.)
+constexpr int DM = 128, DN = 256, DSTAGES = 3;
+constexpr int D_A = DM * 128, D_STAGE = (DM + DN) * 128;
+constexpr int D_LDS = DSTAGES * D_STAGE;
+
+__global__ __launch_bounds__(512, 1) void dense_gemm_kernel(const half_t *__restrict__ X, const half_t *__restrict__ W,
+                                                            half_t *__restrict__ Y, int T, int N, int K, int tiles_n,
+                                                            int tiles_total)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    asm volatile("" ::"s"(X), "s"(W), "s"(Y), "s"(T), "s"(N), "s"(K), "s"(tiles_n), "s"(tiles_total));
+    const int per_xcd = (tiles_total + 7) >> 3;              // contiguous ranges of tiles per XCD
+    const int tile = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
+    if (tile >= tiles_total || ((int)blockIdx.x >> 3) >= per_xcd) return;
+    const int tile_m = tile / tiles_n, tile_n = tile - tile_m * tiles_n;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nq = wave & 3, kh = wave >> 2, l32 = lane & 31, hi = lane >> 5;
+    const int m0 = tile_m * DM, n0 = tile_n * DN;
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
+
+    // the wave fetches rows 16 w .. + 16 of X and 32 w .. + 32 of W, eight rows per load; rows past the end
+    // repeat the last one
+    const unsigned char *src[6];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        int ra = t0 + lrow + 32 * j;
-        ra = ra < T ? ra : T - 1;                       // ragged edge: repeat the last row
-        int rb = n0 + lrow + 32 * j;
-        rb = rb < N ? rb : N - 1;
-        asrc[j] = reinterpret_cast<const uint4 *>(X + (size_t)ra * K) + lchunk;
-        bsrc[j] = reinterpret_cast<const uint4 *>(W + (size_t)rb * K) + lchunk;
+    for (int i = 0; i < 6; ++i) {
+        const int row = (i < 2 ? 16 * wave + 8 * i : 32 * wave + 8 * (i - 2)) + (lane >> 3);
+        const int chunk = (lane & 7) ^ ((row >> 1) & 7);
+        src[i] = i < 2 ? reinterpret_cast<const unsigned char *>(X + (size_t)min(m0 + row, T - 1) * K) + 16 * chunk
+                       : reinterpret_cast<const unsigned char *>(W + (size_t)min(n0 + row, N - 1) * K) + 16 * chunk;
     }
-    uint4 pa[4], pb[4];
-    floatx16 acc[2][2];
+    const int stages = K / 64;
+    auto request = [&](int st, int slot) {
+        const size_t at = (size_t)min(st, stages - 1) * 128;             // past the end: a harmless repeat
+        const uint32_t dst = lds0 + slot * D_STAGE;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 6; ++i)
+            dma16(src[i] + at, dst + (i < 2 ? wave * 2048 + i * 1024 : D_A + wave * 4096 + (i - 2) * 1024));
+    };
+    // fragments of step t (0, 1) of the wave: columns 16 (2 t + kh) .. + 16 of the stage
+    uint32_t aofs[2], bofs[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const uint32_t place = (uint32_t)(((2 * (2 * t + kh) + hi) ^ ((l32 >> 1) & 7)) * 16);
+        aofs[t] = lds0 + l32 * 128 + place;
+        bofs[t] = lds0 + D_A + (64 * nq + l32) * 128 + place;
+    }
+    u32x4 a[4], b[2], an[4], bn[2];
+#define AWQ_READ(T_, SLOT_)                                                                                   \
+    asm volatile("ds_read_b128 %0, %1" : "=v"(an[0]) : "v"(aofs[T_] + (SLOT_) * D_STAGE));                    \
+    asm volatile("ds_read_b128 %0, %1" : "=v"(bn[0]) : "v"(bofs[T_] + (SLOT_) * D_STAGE));                    \
+    asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(bn[1]) : "v"(bofs[T_] + (SLOT_) * D_STAGE));        \
+    asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(an[1]) : "v"(aofs[T_] + (SLOT_) * D_STAGE));        \
+    asm volatile("ds_read_b128 %0, %1 offset:8192" : "=v"(an[2]) : "v"(aofs[T_] + (SLOT_) * D_STAGE));        \
+    asm volatile("ds_read_b128 %0, %1 offset:12288" : "=v"(an[3]) : "v"(aofs[T_] + (SLOT_) * D_STAGE));
+#define AWQ_ADOPT()                                                                                           \
+    asm volatile("s_waitcnt lgkmcnt(0)"                                                                       \
+                 : "+v"(an[0]), "+v"(an[1]), "+v"(an[2]), "+v"(an[3]), "+v"(bn[0]), "+v"(bn[1]));             \
+    a[0] = an[0]; a[1] = an[1]; a[2] = an[2]; a[3] = an[3]; b[0] = bn[0]; b[1] = bn[1];
+    floatx16 acc[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int steps = K / 64;
+    auto multiply = [&]() {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) { pa[j] = asrc[j][0]; pb[j] = bsrc[j][0]; }
-    for (int ks = 0; ks < steps; ++ks) {
-        __syncthreads();                                 // everyone has read the previous step
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            *reinterpret_cast<uint4 *>(lds + (lrow + 32 * j) * DROW + lchunk * 16) = pa[j];
-            *reinterpret_cast<uint4 *>(lds + (DT + lrow + 32 * j) * DROW + lchunk * 16) = pb[j];
-        }
-        __syncthreads();
-        if (ks + 1 < steps) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                pa[j] = asrc[j][(size_t)(ks + 1) * 8];
-                pb[j] = bsrc[j][(size_t)(ks + 1) * 8];
-            }
-        }
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            half8_t a[2], b[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                a[i] = *reinterpret_cast<const half8_t *>(lds + (64 * wm + 32 * i + l32) * DROW + (2 * s + hi) * 16);
-                b[i] = *reinterpret_cast<const half8_t *>(lds + (DT + 64 * wn + 32 * i + l32) * DROW + (2 * s + hi) * 16);
-            }
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
+            for (int j = 0; j < 2; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, a[i]),
+                                                                   __builtin_bit_cast(half8_t, b[j]), acc[i][j], 0, 0, 0);
+    };
+
+    request(0, 0);
+    request(1, 1);
+    request(2, 2);
+    asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    AWQ_READ(0, 0)
+    AWQ_ADOPT()
+    int slot = 0;
+    for (int st = 0; st < stages; ++st) {
+        AWQ_READ(1, slot)
+        __builtin_amdgcn_sched_barrier(0);
+        multiply();
+        __builtin_amdgcn_sched_barrier(0);
+        AWQ_ADOPT()
+        // this wave has read all it needs of the stage; the next one has landed when only the six loads of
+        // the stage after it are outstanding, and behind the barrier that holds for every wave
+        asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        request(st + 3, slot);
+        slot = slot + 1 == DSTAGES ? 0 : slot + 1;
+        AWQ_READ(0, slot)
+        __builtin_amdgcn_sched_barrier(0);
+        multiply();
+        __builtin_amdgcn_sched_barrier(0);
+        AWQ_ADOPT()
     }
-    // accumulator v of tile (i, j): row 8 (v/4) + 4 hi + v%4, column l32
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int col = n0 + 64 * wn + 32 * j + l32;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = t0 + 64 * wm + 32 * i + 8 * (v >> 2) + 4 * hi + (v & 3);
-                if (row < T && col < N) Y[(size_t)row * N + col] = (half_t)acc[i][j][v];
-            }
-        }
+#undef AWQ_READ
+#undef AWQ_ADOPT
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the harmless repeats
+    __syncthreads();
+    floatx16 own[2][2];
+    gemm_pair_sum(acc, own, smem, wave, lane, kh);
+    gemm_store(gemm_turn(own, smem, wave, l32, hi), Y, m0 + 64 * kh, n0 + 64 * nq, T, N, lane);
+}
+
+int dense_gemm_launch(const half_t *X, const half_t *W, half_t *Y, int T, int N, int K, hipStream_t stream)
+{
+    const int tiles_n = (N + DN - 1) / DN;
+    const int64_t total = (int64_t)tiles_n * ((T + DM - 1) / DM);
+    if (total > (1 << 30)) return AWQ_ERR_BAD_SHAPE;
+    static AwqOncePerDevice once;
+    std::atomic<bool> &attr_set = once.here();
+    if (!attr_set.load(std::memory_order_relaxed)) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(dense_gemm_kernel),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, D_LDS) != hipSuccess)
+            return AWQ_ERR_HIP;
+        attr_set.store(true, std::memory_order_relaxed);
+    }
+    dense_gemm_kernel<<<dim3((unsigned)((total + 7) / 8 * 8)), dim3(512), D_LDS, stream>>>(X, W, Y, T, N, K, tiles_n,
+                                                                                           (int)total);
+    return awq_launch_status();
 }
 
 // partial[b] = sum over the 16-byte chunks of workgroup b of (Yq - Y)^2: eight differences are
@@ -160,27 +229,29 @@ __global__ __launch_bounds__(256) void loss_kernel(const uint4 *__restrict__ Yq,
     if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
-// losses[i] = sum of the partial sums of grid point i (fixed tree); best = first index of the
-// smallest loss (a loss that is not a number never wins); s_best = s_X^alpha[best].
-__global__ __launch_bounds__(1024) void finalize_kernel(const double *__restrict__ partial, int n_alpha,
+// losses[i] = sum of the `count` partial sums of grid point i (a wave per grid point, fixed order); best = first
+// index of the smallest loss (a loss that is not a number never wins); s_best = s_X^alpha[best].
+__global__ __launch_bounds__(1024) void finalize_kernel(const double *__restrict__ partial, int count, int n_alpha,
                                                         AlphaList alphas, const float *__restrict__ mean,
                                                         int K, double *__restrict__ losses,
                                                         int32_t *__restrict__ best, float *__restrict__ s_best)
 {
-    __shared__ double red[LOSS_BLOCKS];
     __shared__ double total[MAX_ALPHAS];
     __shared__ int chosen;
-    const int tid = threadIdx.x;
-    for (int i = 0; i < n_alpha; ++i) {
-        red[tid] = partial[(size_t)i * LOSS_BLOCKS + tid];
-        __syncthreads();
-        for (int half = LOSS_BLOCKS / 2; half >= 1; half >>= 1) {
-            if (tid < half) red[tid] += red[tid + half];
-            __syncthreads();
-        }
-        if (tid == 0) total[i] = red[0];
-        __syncthreads();
+    const int tid = threadIdx.x, lane = tid & 63;
+    for (int i = tid >> 6; i < n_alpha; i += 16) {
+        double v[LOSS_BLOCKS / 64];                 // requested together
+#pragma unroll
+        for (int k = 0; k < LOSS_BLOCKS / 64; ++k)
+            v[k] = lane + 64 * k < count ? partial[(size_t)i * LOSS_BLOCKS + lane + 64 * k] : 0.0;
+        double sum = v[0];
+#pragma unroll
+        for (int k = 1; k < LOSS_BLOCKS / 64; ++k) sum += v[k];
+#pragma unroll
+        for (int d = 1; d <= 32; d <<= 1) sum += __shfl_xor(sum, d);
+        if (lane == 0) total[i] = sum;
     }
+    __syncthreads();
     if (tid == 0) {
         int b = 0;
         double lb = total[0] == total[0] ? total[0] : __builtin_inf();
@@ -270,29 +341,39 @@ extern "C" int awq_search_scale(const void *W_f16, const void *X_f16, int64_t T,
 
     st = awq_act_mean_launch(X_f16, T, K, mean, hs);
     if (st != AWQ_OK) return st;
-    {
-        const dim3 grid((unsigned)((N + DT - 1) / DT), (unsigned)((T + DT - 1) / DT));
-        dense_gemm_kernel<<<grid, dim3(256), 0, hs>>>((const half_t *)X_f16, (const half_t *)W_f16, Y,
-                                                      (int)T, (int)N, (int)K);
-        st = awq_launch_status();
-        if (st != AWQ_OK) return st;
-    }
+    st = dense_gemm_launch((const half_t *)X_f16, (const half_t *)W_f16, Y, (int)T, (int)N, (int)K, hs);
+    if (st != AWQ_OK) return st;
+    // where the layer runs the prefill kernel, its loss form takes the differences in the product's epilogue
+    // (2048 x 4096 x 4096: the product 65 us either way, without the 7 us pass over both outputs); its
+    // tiles have to fit the partial sums of a grid point
+    const int64_t tiles = awq_gemm_tiles((int)T, (int)N);
+    const bool fused = awq_linear_takes_prefill((int)T, (int)N, (int)K) && tiles <= LOSS_BLOCKS;
     const int64_t chunks = T * N / 8;                    // N % 16 == 0
+    // the powers of all grid points in one launch, in the place of the candidate's outputs, where that place is
+    // not used and holds them
+    const bool table = fused && (int64_t)n_alpha * K * 4 <= T * N * 2;
+    float *powers = table ? reinterpret_cast<float *>(Yq) : s;
     for (int i = 0; i < n_alpha; ++i) {
-        pow_kernel<<<dim3((unsigned)((K + 255) / 256)), dim3(256), 0, hs>>>(mean, al.a[i], (int)K, s);
-        st = awq_launch_status();
+        if (!table || i == 0) {
+            pow_kernel<<<dim3((unsigned)((K + 255) / 256), table ? (unsigned)n_alpha : 1u), dim3(256), 0, hs>>>(
+                mean, al, i, (int)K, powers);
+            st = awq_launch_status();
+            if (st != AWQ_OK) return st;
+        }
+        st = awq_quantize_inv_launch(W_f16, table ? powers + (size_t)i * K : s, N, K, q, sc, zp, X_f16, T, xs, hs);
         if (st != AWQ_OK) return st;
-        st = awq_quantize_pack(W_f16, s, N, K, group, q, sc, zp, stream);
-        if (st != AWQ_OK) return st;
-        st = awq_apply_inv_scale(X_f16, s, T, K, xs, stream);
-        if (st != AWQ_OK) return st;
+        double *part = partial + (size_t)i * LOSS_BLOCKS;
+        if (fused) {
+            st = awq_gemm_launch_loss(xs, q, sc, zp, Y, (int)T, (int)N, (int)K, part, hs);
+            if (st != AWQ_OK) return st;
+            continue;
+        }
         st = awq_w4a16_linear(xs, q, sc, zp, Yq, T, N, K, group, nullptr, 0, stream);
         if (st != AWQ_OK) return st;
-        loss_kernel<<<dim3(LOSS_BLOCKS), dim3(256), 0, hs>>>((const uint4 *)Yq, (const uint4 *)Y, chunks,
-                                                             partial + (size_t)i * LOSS_BLOCKS);
+        loss_kernel<<<dim3(LOSS_BLOCKS), dim3(256), 0, hs>>>((const uint4 *)Yq, (const uint4 *)Y, chunks, part);
         st = awq_launch_status();
         if (st != AWQ_OK) return st;
     }
-    finalize_kernel<<<dim3(1), dim3(1024), 0, hs>>>(partial, n_alpha, al, mean, (int)K, losses, best, s_best);
+    finalize_kernel<<<dim3(1), dim3(1024), 0, hs>>>(partial, fused ? (int)tiles : LOSS_BLOCKS, n_alpha, al, mean, (int)K, losses, best, s_best);
     return awq_launch_status();
 }

@@ -1,0 +1,36 @@
+"""awq_search_scale where the layer runs the prefill kernel and the loss is taken in its epilogue: ragged token and
+feature tiles, a single K stage pair of the dense product, many and few grid points, against the same
+arithmetic in plain torch (fp64 products of the fp16 operands)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,N,K,points", [(2125, 1040, 384, 5), (2049, 272, 128, 3), (1000, 4112, 256, 20), (4096, 528, 640, 2)])
+def test_fused_loss_against_plain_torch(T, N, K, points):
+    import torch
+    import paper_2306_00978_amd as awq
+    g = torch.Generator(device="cuda").manual_seed(T + N + K)
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).half()
+    gain = torch.ones(K, device="cuda")
+    gain[torch.randperm(K, generator=g, device="cuda")[:max(1, K // 100)]] = 20.0
+    X = (torch.randn((T, K), generator=g, device="cuda") * gain).half()
+    alphas = [i / points for i in range(points)]
+    best, losses, s_best = awq.awq_search_scale(W, X, alphas)
+    y = X.double() @ W.double().T
+    ref = []
+    for a in alphas:
+        s = awq.awq_act_scale(X, a)
+        codes, scales, zeros = awq.awq_unpack(*awq.awq_quantize_pack(W, s), N, K)
+        q = (codes.double().view(N, K // 128, 128) - zeros.double()[..., None]) * scales.double()[..., None]
+        yq = awq.awq_apply_inv_scale(X, s).double() @ q.view(N, K).T
+        ref.append(float((yq - y).square().sum()))
+    got = losses.cpu().numpy()
+    # fp16 rounding of both outputs and of the dequantized weights: 1e-4 of the loss, and a cross term of
+    # 2e-2 / sqrt(outputs) standard deviation
+    assert np.all(np.abs(got / np.array(ref) - 1) <= 2e-4 + 0.06 / np.sqrt(T * N)), (got, ref)
+    assert int(best) == int(got.argmin())
+    assert torch.equal(s_best, awq.awq_act_scale(X, alphas[int(best)]))
+    again = awq.awq_search_scale(W, X, alphas)[1]
+    assert torch.equal(losses, again)
