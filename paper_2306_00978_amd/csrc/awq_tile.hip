@@ -148,7 +148,11 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
     auto issue_x = [&](int run, int m, uint32_t slot) {
         const unsigned char *p = x + ((size_t)first_row(m) * K + (size_t)run * RUN) * 2;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) dma<16>(p + xofs[i], lds0 + slot + i * 1024);
+        for (int i = 0; i < 4; ++i) {
+            uint32_t at = xofs[i];
+            asm volatile("" : "+v"(at));                   // a 32-bit offset beside a wave-uniform base, not a 64-bit address
+            dma<16>(p + at, lds0 + slot + i * 1024);
+        }
     };
     constexpr int RAW_LOADS = NT + 2;
     auto issue_raw = [&](int run) {
