@@ -81,11 +81,12 @@ template <int BITS> struct Slot {
 
 // HBM -> LDS without a register in between.  Lane l's 16 bytes land at lds + OFF + 16 l (OFF is
 // added to the global address as well); 2- and 1-byte loads land zero-extended at lds + 4 l.
-template <int OFF>
+// NT: the packed words are read once, and the load says so (non-temporal): they do not displace what the L2 holds.
+template <int OFF, bool NT>
 __device__ __forceinline__ void dma16_to_lds(const void *g, uint32_t lds_addr)
 {
     __builtin_amdgcn_global_load_lds((gbl_void_t *)(uintptr_t)g, (lds_void_t *)(uintptr_t)lds_addr,
-                                     16, OFF, 0);
+                                     16, OFF, NT ? 2 : 0);
 }
 __device__ __forceinline__ void dma2_to_lds(const void *g, uint32_t lds_addr)
 {
@@ -301,7 +302,7 @@ struct ChainWait {
 // CHAIN: the table is one stage of a chained launch (see chain_kernel); the first weight jobs are
 // requested before the wait for the stage in front, the activations are read after it.  Returns
 // false if that wait ran out (the workgroup then leaves the launch).
-template <int STAGES, int BITS, bool FUSED, bool CHAIN, int OFF_BEGIN, int OFF_P, int OFF_E, int MAXP, int MAXF>
+template <int STAGES, int BITS, bool FUSED, bool CHAIN, bool NT, int OFF_BEGIN, int OFF_P, int OFF_E, int MAXP, int MAXF>
 __device__ __forceinline__ bool stream_body(const unsigned char *ka, const int M, const int mlog, const int logW,
                                             const int vwg, unsigned char *smem, const ChainWait cw)
 {
@@ -424,10 +425,10 @@ __device__ __forceinline__ bool stream_body(const unsigned char *ka, const int M
         const uint32_t dst = ring + (uint32_t)slot * STAGE_BYTES;
         const unsigned char *tq = qbase + t0 * TILE_BYTES, *ts = scbase + t0 * 32, *tz = zpbase + t0 * 8;
         if (!ragged || b * 4 + 4 <= G) {
-            dma16_to_lds<0>(tq + lane16, dst);
-            dma16_to_lds<1024>(tq + lane16, dst);
-            dma16_to_lds<2048>(tq + lane16, dst);
-            if (BITS == 4) dma16_to_lds<3072>(tq + lane16, dst);
+            dma16_to_lds<0, NT>(tq + lane16, dst);
+            dma16_to_lds<1024, NT>(tq + lane16, dst);
+            dma16_to_lds<2048, NT>(tq + lane16, dst);
+            if (BITS == 4) dma16_to_lds<3072, NT>(tq + lane16, dst);
             dma2_to_lds(ts + sc_lane, dst + STAGE_SC);
             if (lane < 32) dma1_to_lds(tz + zp_lane, dst + STAGE_ZP);
         } else {
@@ -435,14 +436,14 @@ __device__ __forceinline__ bool stream_body(const unsigned char *ka, const int M
             if (BITS == 4) {
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    dma16_to_lds<0>(tq + ((size_t)min(u, last) << 10) + lane16, dst + u * 1024);
+                    dma16_to_lds<0, NT>(tq + ((size_t)min(u, last) << 10) + lane16, dst + u * 1024);
             } else {
                 // the same three loads; a 16-byte chunk that belongs to a tile beyond the last
                 // valid one re-reads that last tile instead (never past the end of the array)
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
                     const int ch = lane + 64 * i, tl = ch / 48, off = 16 * (ch - 48 * tl);
-                    dma16_to_lds<0>(tq + min(tl, last) * 768 + off, dst + i * 1024);
+                    dma16_to_lds<0, NT>(tq + min(tl, last) * 768 + off, dst + i * 1024);
                 }
             }
             const int gl = min(lane & 3, last);
@@ -749,13 +750,13 @@ __device__ __forceinline__ bool stream_body(const unsigned char *ka, const int M
     return true;
 }
 
-template <int STAGES, int BITS, bool FUSED>
+template <int STAGES, int BITS, bool FUSED, bool NT>
 __global__ __launch_bounds__(512, 2) void gemv_stream_kernel(const GemvArgs<FUSED> A)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const unsigned char *ka = (const unsigned char *)__builtin_amdgcn_kernarg_segment_ptr();
     static_assert(!FUSED || offsetof(GemvArgs<true>, e) == sizeof(GemvLaunch), "layout");
-    stream_body<STAGES, BITS, FUSED, false, offsetof(GemvLaunch, wg_begin), offsetof(GemvLaunch, p), sizeof(GemvLaunch),
+    stream_body<STAGES, BITS, FUSED, false, NT, offsetof(GemvLaunch, wg_begin), offsetof(GemvLaunch, p), sizeof(GemvLaunch),
                 GEMV_MAX_PROBLEMS, GEMV_MAX_FUSED>(ka, A.L.M, A.L.mlog, A.L.logW, (int)blockIdx.x, smem,
                                                    ChainWait{});
 }
@@ -807,7 +808,7 @@ __global__ __launch_bounds__(512, 2) void chain_kernel(const ChainArgs A)
         if ((int)blockIdx.x < A.st[s].wgs) {
             const ChainWait cw = {s > 0 ? sync + CHAIN_SHARD_STRIDE * (1 + CHAIN_SHARDS * (s - 1)) : nullptr, workgroups,
                                   sync, A.spin_limit};
-            const bool ok = stream_body<CHAIN_RING, 4, true, true, offsetof(ChainStage, wg_begin), offsetof(ChainStage, p),
+            const bool ok = stream_body<CHAIN_RING, 4, true, true, false, offsetof(ChainStage, wg_begin), offsetof(ChainStage, p),
                                         offsetof(ChainStage, e), CHAIN_MAX_ENTRIES, CHAIN_MAX_ENTRIES>(
                 ka + offsetof(ChainArgs, st) + (size_t)s * sizeof(ChainStage), A.M, A.mlog, A.logW, (int)blockIdx.x,
                 smem, cw);
@@ -881,7 +882,7 @@ struct RowsShape {
     static_assert(LDS <= 160 * 1024, "one workgroup per CU");
 };
 
-template <int MR>
+template <int MR, bool NT>
 __global__ __launch_bounds__(ROWS_THREADS) void gemv_rows_kernel(const GemvArgs<false> A)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1028,17 +1029,17 @@ __global__ __launch_bounds__(ROWS_THREADS) void gemv_rows_kernel(const GemvArgs<
             const uint32_t dst = ring + (uint32_t)slot * STAGE_BYTES;
             const unsigned char *tq = qbase + t0 * 1024, *ts = scbase + t0 * 32, *tz = zpbase + t0 * 8;
             if (!ragged || b * 4 + 4 <= G) {
-                dma16_to_lds<0>(tq + lane16, dst);
-                dma16_to_lds<1024>(tq + lane16, dst);
-                dma16_to_lds<2048>(tq + lane16, dst);
-                dma16_to_lds<3072>(tq + lane16, dst);
+                dma16_to_lds<0, NT>(tq + lane16, dst);
+                dma16_to_lds<1024, NT>(tq + lane16, dst);
+                dma16_to_lds<2048, NT>(tq + lane16, dst);
+                dma16_to_lds<3072, NT>(tq + lane16, dst);
                 dma2_to_lds(ts + sc_lane, dst + STAGE_SC);
                 if (lane < 32) dma1_to_lds(tz + zp_lane, dst + STAGE_ZP);
             } else {
                 const int last = G - 1 - b * 4;                 // last valid group of this batch (0..2)
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    dma16_to_lds<0>(tq + ((size_t)min(u, last) << 10) + lane16, dst + u * 1024);
+                    dma16_to_lds<0, NT>(tq + ((size_t)min(u, last) << 10) + lane16, dst + u * 1024);
                 const int gl = min(lane & 3, last);
                 dma2_to_lds(ts + gl * 32 + (lane >> 2) * 2, dst + STAGE_SC);
                 if (lane < 32) dma1_to_lds(tz + gl * 8 + ((lane >> 2) & 7), dst + STAGE_ZP);
@@ -1318,6 +1319,18 @@ bool plan_paired(const GemvProblem *problems, int count, const int *ksl_of, int 
     return true;
 }
 
+// Whether a launch reads its packed words with non-temporal loads.  A model's weights pass through once per
+// token, and together they are larger than the 256 MB memory-side cache from a launch of this size on (a layer of
+// the 7B shapes is 105 MB): eight layers of the 7B shapes at one token 22.1 -> 20.8 us a layer, in 3 bits 18.9 -> 17.9, a
+// layer of the 70B shapes at eight tokens 86.4 -> 82.5.  Below, a launch is short, and the weights of a small model may well be found in a
+// cache, where the plain loads are the faster ones (all of a 40 MB model repeated: 2 to 4 %).
+bool streams_weights(const GemvProblem *problems, int count, int bits)
+{
+    int64_t bytes = 0;
+    for (int i = 0; i < count; ++i) bytes += (int64_t)problems[i].N * problems[i].K / 8 * bits;
+    return bytes >= (int64_t)16 << 20;
+}
+
 template <int BITS, bool FUSED>
 int stream_launch_bits(const GemvProblem *problems, const GemvFusedExtra *extra, int count, int M,
                        hipStream_t stream)
@@ -1415,18 +1428,20 @@ int stream_launch_bits(const GemvProblem *problems, const GemvFusedExtra *extra,
     std::atomic<bool> &attr_set = once.here();
     if (!attr_set.load(std::memory_order_relaxed)) {
         const int cap = 160 * 1024;
-        const void *kernels[] = {reinterpret_cast<const void *>(gemv_stream_kernel<2, BITS, FUSED>),
-                                 reinterpret_cast<const void *>(gemv_stream_kernel<3, BITS, FUSED>),
-                                 reinterpret_cast<const void *>(gemv_stream_kernel<4, BITS, FUSED>)};
-        for (int k = 0; k < (FUSED ? 1 : 3); ++k)
+        const void *kernels[] = {reinterpret_cast<const void *>(gemv_stream_kernel<2, BITS, FUSED, false>),
+                                 reinterpret_cast<const void *>(gemv_stream_kernel<2, BITS, FUSED, true>),
+                                 reinterpret_cast<const void *>(gemv_stream_kernel<3, BITS, FUSED, false>),
+                                 reinterpret_cast<const void *>(gemv_stream_kernel<4, BITS, FUSED, false>)};
+        for (int k = 0; k < (FUSED ? 2 : 4); ++k)
             if (hipFuncSetAttribute(kernels[k], hipFuncAttributeMaxDynamicSharedMemorySize, cap) != hipSuccess)
                 return AWQ_ERR_HIP;
         attr_set.store(true, std::memory_order_relaxed);
     }
     if (lds > (size_t)160 * 1024) return AWQ_GEMV_STREAM_UNFIT;
-    if (stages == 4 && !FUSED) gemv_stream_kernel<4, BITS, FUSED><<<dim3(wg), dim3(W * 64), lds, stream>>>(A);
-    else if (stages == 3 && !FUSED) gemv_stream_kernel<3, BITS, FUSED><<<dim3(wg), dim3(W * 64), lds, stream>>>(A);
-    else gemv_stream_kernel<2, BITS, FUSED><<<dim3(wg), dim3(W * 64), lds, stream>>>(A);
+    if (stages == 4 && !FUSED) gemv_stream_kernel<4, BITS, FUSED, false><<<dim3(wg), dim3(W * 64), lds, stream>>>(A);
+    else if (stages == 3 && !FUSED) gemv_stream_kernel<3, BITS, FUSED, false><<<dim3(wg), dim3(W * 64), lds, stream>>>(A);
+    else if (streams_weights(problems, count, BITS)) gemv_stream_kernel<2, BITS, FUSED, true><<<dim3(wg), dim3(W * 64), lds, stream>>>(A);
+    else gemv_stream_kernel<2, BITS, FUSED, false><<<dim3(wg), dim3(W * 64), lds, stream>>>(A);
     return awq_launch_status();
 }
 
@@ -1618,15 +1633,21 @@ int awq_gemv_rows_launch(const GemvProblem *problems, int count, int M, hipStrea
     static AwqOncePerDevice once;
     std::atomic<bool> &attr_set = once.here();
     if (!attr_set.load(std::memory_order_relaxed)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(gemv_rows_kernel<8>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, RowsShape<8>::LDS) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(gemv_rows_kernel<16>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, RowsShape<16>::LDS) != hipSuccess)
-            return AWQ_ERR_HIP;
+        const void *kernels[] = {reinterpret_cast<const void *>(gemv_rows_kernel<8, false>),
+                                 reinterpret_cast<const void *>(gemv_rows_kernel<8, true>),
+                                 reinterpret_cast<const void *>(gemv_rows_kernel<16, false>),
+                                 reinterpret_cast<const void *>(gemv_rows_kernel<16, true>)};
+        for (int k = 0; k < 4; ++k)
+            if (hipFuncSetAttribute(kernels[k], hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    k < 2 ? RowsShape<8>::LDS : RowsShape<16>::LDS) != hipSuccess)
+                return AWQ_ERR_HIP;
         attr_set.store(true, std::memory_order_relaxed);
     }
-    if (M <= 8) gemv_rows_kernel<8><<<dim3(wg), dim3(ROWS_THREADS), RowsShape<8>::LDS, stream>>>(A);
-    else gemv_rows_kernel<16><<<dim3(wg), dim3(ROWS_THREADS), RowsShape<16>::LDS, stream>>>(A);
+    const bool nt = streams_weights(problems, count, 4);
+    if (M <= 8 && nt) gemv_rows_kernel<8, true><<<dim3(wg), dim3(ROWS_THREADS), RowsShape<8>::LDS, stream>>>(A);
+    else if (M <= 8) gemv_rows_kernel<8, false><<<dim3(wg), dim3(ROWS_THREADS), RowsShape<8>::LDS, stream>>>(A);
+    else if (nt) gemv_rows_kernel<16, true><<<dim3(wg), dim3(ROWS_THREADS), RowsShape<16>::LDS, stream>>>(A);
+    else gemv_rows_kernel<16, false><<<dim3(wg), dim3(ROWS_THREADS), RowsShape<16>::LDS, stream>>>(A);
     return awq_launch_status();
 }
 
