@@ -365,16 +365,17 @@ int awq_unpack_w3(const void *qweight, const void *scales, const void *zeros, in
 int awq_w3a16_linear(const void *x_f16, const void *qweight, const void *scales,
                      const void *zeros, void *y_f16, int64_t M, int64_t N, int64_t K, int group,
                      void *stream);
-/* Prefill (M > 16) for the 3-bit layout.  There is no 3-bit matrix-matrix kernel: the codes are
+/* Prefill (M > 16) for the 3-bit layout.  Short prompts run on the packed codes as they are (always
+ * up to 128 tokens).  Beyond a size that the two kernels' estimated times decide, the codes are
  * re-packed into the 4-bit layout (the steps and zero points are stored identically in both, and
  * a code 0..7 is a valid 4-bit code), then the prefill kernel of the 4-bit path runs on them --
  * one extra pass over the packed weights, about a tenth of the GEMM's time at M = 2048.
  *   awq_repack_w3_to_w4: qweight_w3 (N*K*3/8 bytes) -> qweight_w4 (N*K/2 bytes, written), both
  *     device, 16-byte aligned; a caller with the memory can keep the result and use the 4-bit
  *     calls with the 3-bit linear's scales and zeros.
- *   awq_w3a16_linear_prefill: the two steps in one call; workspace (device, 16-byte aligned,
- *     awq_w3a16_prefill_workspace_bytes() = N*K/2 bytes) holds the re-packed codes, contents
- *     undefined afterwards.  With N*K/2 rounded up to a multiple of 256, plus
+ *   awq_w3a16_linear_prefill: one call; workspace (device, 16-byte aligned,
+ *     awq_w3a16_prefill_workspace_bytes() = N*K/2 bytes, required at every M) is for the re-packed
+ *     codes, contents undefined afterwards.  With N*K/2 rounded up to a multiple of 256, plus
  *     awq_linear_workspace_bytes(M, N, K, group) bytes, the prefill kernel also cuts K into
  *     ranges for a few hundred tokens, as awq_w4a16_linear does with its workspace.
  *     M <= 16 returns AWQ_ERR_BAD_SHAPE (use awq_w3a16_linear). */

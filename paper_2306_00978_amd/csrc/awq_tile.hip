@@ -1,4 +1,4 @@
-// K-split tile kernel for gfx950: one linear at more than 16 tokens, 4-bit (group 128) or 2-bit
+// K-split tile kernel for gfx950: one linear at more than 16 tokens, 4- or 3-bit (group 128) or 2-bit
 // (group 64) weights.
 //
 // AWQ Sec. 4.2: dequantization fused into the matrix kernel.
@@ -138,8 +138,11 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
     // masks in SGPRs, magic numbers in VGPRs: (w & mask) | magic is then one v_and_or_b32
     uint32_t mask_lo = 0x000F000Fu, mask_hi = 0x00F000F0u, mask2 = 0x00030003u;
     uint32_t magA = 0x64006400u, magB = 0x54005400u;
+    uint32_t mask3[3] = {0x00070007u, 0x00380038u, 0x01C001C0u}, mag3[3] = {0x64006400u, 0x58005800u, 0x4C004C00u};
     asm("" : "+s"(mask_lo), "+s"(mask_hi), "+s"(mask2));
     asm("" : "+v"(magA), "+v"(magB));
+    asm("" : "+s"(mask3[0]), "+s"(mask3[1]), "+s"(mask3[2]));
+    asm("" : "+v"(mag3[0]), "+v"(mag3[1]), "+v"(mag3[2]));
 
     // x: load i (0..3) of a token tile takes its rows 4 i + c, lane r the chunk that belongs at place r
     uint32_t xofs[4];
@@ -156,9 +159,12 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
     };
     constexpr int RAW_LOADS = NT + 2;
     auto issue_raw = [&](int run) {
-        if (BITS == 4) {                                   // a run is a group: 1 KB, 16 steps, 8 bytes of zero points
+        if (BITS != 2) {                                   // a run is a group: 1 KB (768 bytes), 16 steps, 8 bytes of zero points
 #pragma unroll
-            for (int n = 0; n < NT; ++n) dma<16>(qweight + (trun[n] + run) * 1024 + lane * 16, lds0 + raw_ofs(NT) + n * 1024);
+            for (int n = 0; n < NT; ++n) {
+                if (BITS == 4) dma<16>(qweight + (trun[n] + run) * 1024 + lane * 16, lds0 + raw_ofs(NT) + n * 1024);
+                else if (lane < 48) dma<16>(qweight + (trun[n] + run) * 768 + lane * 16, lds0 + raw_ofs(NT) + n * 1024);
+            }
             dma<2>(scales + (lrun + run) * 32 + r * 2, lds0 + sc_ofs(NT));
             dma<1>(zeros + (lrun + run) * 8 + (r >> 1), lds0 + zp_ofs(NT));
         } else {                                           // half a block of 256 columns: groups 2 (run % 2), + 1
@@ -185,15 +191,23 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
         for (int i = 0; i < cnt; ++i) {
             wait_loads<(MT >= 2 ? 8 : 4)>();               // this run's packed words: 4 MT loads behind them
             u32x4 q[NT];
-            uint32_t sraw[NT], zraw[NT];
+            uint32_t sraw[NT], zraw[NT], q3[NT][3];
 #pragma unroll
             for (int n = 0; n < NT; ++n) {
-                q[n] = lds_read16(lds0 + raw_ofs(NT) + n * 1024 + lane * 16);
+                if (BITS != 3) {
+                    q[n] = lds_read16(lds0 + raw_ofs(NT) + n * 1024 + lane * 16);
+                } else {                                   // 12-byte slots
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) q3[n][i] = lds_read4(lds0 + raw_ofs(NT) + n * 1024 + lane * 12 + 4 * i);
+                }
                 sraw[n] = lds_read4(lds0 + sc_ofs(NT) + (16 * n + r) * 4);
                 zraw[n] = lds_read4(lds0 + zp_ofs(NT) + (16 * n + r) * 4);
             }
 #pragma unroll
-            for (int n = 0; n < NT; ++n) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(q[n]), "+v"(sraw[n]), "+v"(zraw[n]));
+            for (int n = 0; n < NT; ++n) {
+                if (BITS != 3) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(q[n]), "+v"(sraw[n]), "+v"(zraw[n]));
+                else asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(q3[n][0]), "+v"(q3[n][1]), "+v"(q3[n][2]), "+v"(sraw[n]), "+v"(zraw[n]));
+            }
             issue_raw(run_at(i + 1));
             if (i == 0) {
                 wait_loads<8 + RAW_LOADS>();
@@ -207,7 +221,27 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
             const float f0 = hb ? 0.0625f : 1.0f, f1 = hb ? 0.015625f : 0.25f;      // 4^-t, BITS = 2
 #pragma unroll
             for (int n = 0; n < NT; ++n) {
-                if (BITS == 4) {
+                if (BITS == 3) {
+                    // pair 5 i + f of word i at bits 3 f: 1024 + q, 128 + q or 16 + q by its place in the mantissa; pair 15
+                    // in the top bits of the three words
+                    const uint32_t z = (zraw[n] >> ((r & 1) * 4)) & 0xFu;
+                    const uint32_t zf[3] = {mag3[0] | (z * 0x00010001u), mag3[1] | (z * 0x00080008u), mag3[2] | (z * 0x00400040u)};
+                    s0[n] = s1[n] = (float)__builtin_bit_cast(half_t, (uint16_t)sraw[n]);
+                    uint32_t pr[16];
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+                        const uint32_t w = q3[n][i], w9 = w >> 9;
+#pragma unroll
+                        for (int f = 0; f < 5; ++f)
+                            pr[5 * i + f] = sub_pair(((f < 3 ? w : w9) & mask3[f % 3]) | mag3[f % 3], zf[f % 3]);
+                    }
+                    const uint32_t top = ((q3[n][0] >> 15) & 0x00010001u) | ((q3[n][1] >> 14) & 0x00020002u) |
+                                         ((q3[n][2] >> 13) & 0x00040004u);
+                    pr[15] = sub_pair(top | mag3[0], zf[0]);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        bf[n][j] = __builtin_bit_cast(half8_t, u32x4{pr[4 * j], pr[4 * j + 1], pr[4 * j + 2], pr[4 * j + 3]});
+                } else if (BITS == 4) {
                     const uint32_t z = (zraw[n] >> ((r & 1) * 4)) & 0xFu;
                     const uint32_t zA = magA | (z * 0x00010001u), zB = magB | (z * 0x00100010u);
                     s0[n] = s1[n] = (float)__builtin_bit_cast(half_t, (uint16_t)sraw[n]);
@@ -386,6 +420,6 @@ TilePlan awq_tile_plan(int M, int N, int K)
 int awq_tile_launch(int bits, const TilePlan &plan, const void *x, const void *qweight, const void *scales,
                     const void *zeros, void *y, int M, int N, int K, hipStream_t stream)
 {
-    const TileFn fn = bits == 4 ? pick<4>(plan.mt, plan.nt) : pick<2>(plan.mt, plan.nt);
+    const TileFn fn = bits == 4 ? pick<4>(plan.mt, plan.nt) : bits == 3 ? pick<3>(plan.mt, plan.nt) : pick<2>(plan.mt, plan.nt);
     return fn(x, qweight, scales, zeros, y, M, N, K, stream);
 }

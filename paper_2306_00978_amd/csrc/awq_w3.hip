@@ -20,6 +20,7 @@
 // This file is compiled with -ffp-contract=off (integer decisions in the quantizer).
 #include "awq_common.h"
 #include "awq_gemv_stream.h"
+#include "awq_tile.h"
 
 int awq_gemv_launch_w3(const void *x, const void *qweight, const void *scales, const void *zeros,
                        void *y, int M, int N, int K, hipStream_t stream);
@@ -192,6 +193,7 @@ int awq_gemm_launch(const void *x, const void *qweight, const void *scales, cons
 int awq_gemm_launch_split(const void *x, const void *qweight, const void *scales, const void *zeros,
                           void *y, int M, int N, int K, void *part, int ksplit, hipStream_t stream);
 int awq_gemm_ksplit(int M, int N, int K, double *estimate_us);
+double awq_gemm_unsplit_us(int M, int N, int K);
 
 extern "C" int awq_repack_w3_to_w4(const void *qweight_w3, int64_t N, int64_t K, int group,
                                    void *qweight_w4, void *stream)
@@ -224,30 +226,28 @@ extern "C" int awq_w3a16_linear_prefill(const void *x_f16, const void *qweight, 
         !awq_aligned16(zeros) || !awq_aligned16(y_f16) || !awq_aligned16(workspace))
         return AWQ_ERR_MISALIGNED;
     if (workspace_bytes < (size_t)(N * K / 2)) return AWQ_ERR_WORKSPACE_TOO_SMALL;
-    if (M <= 128) {
-        // a few dozen tokens: blocks of 16 through the 3-bit decode kernels in one grouped call
-        // (see awq_w4a16_linear); the workspace is not touched
-        const int blocks = (int)((M + 15) / 16);
-        awq_linear_desc d[8];
-        for (int b = 0; b < blocks; ++b) {
-            const int64_t m0 = b + 1 < blocks ? 16 * (int64_t)b : M - 16;
-            d[b].x_f16 = (const half_t *)x_f16 + m0 * K;
-            d[b].qweight = qweight;
-            d[b].scales = scales;
-            d[b].zeros = zeros;
-            d[b].y_f16 = (half_t *)y_f16 + m0 * N;
-            d[b].N = N;
-            d[b].K = K;
-        }
-        return awq_w3a16_linear_multi(d, blocks, 16, group, stream);
-    }
+    // The tile kernel takes the 3-bit words as they are and touches no workspace; the prefill kernel needs
+    // them re-packed first: 2.5 us and N K (3 + 4) / 8 bytes at 4 TB/s, added to its estimate.  Up to 128
+    // tokens always the tile kernel (before: blocks of 16 tokens through the decode kernels, the
+    // weights read again by each: 92 tokens, 5328 x 9216, 87.3 us, now 19.8); beyond, by the two estimates,
+    // as in awq_w4a16_linear (281 tokens, 1152 x 1792: 20.9 us re-packed, 8.8 here; 586, 3104 x 3584:
+    // 31.8 and 23.9; from 821, 5072 x 1792, the prefill kernel).
+    const TilePlan plan = awq_tile_plan((int)M, (int)N, (int)K);
+    const size_t repacked = ((size_t)(N * K / 2) + 255) & ~(size_t)255;
+    const size_t partials = awq_linear_workspace_bytes(M, N, K, group);
+    const bool split = partials > 0 && workspace_bytes >= repacked + partials;
+    double gemm_us = 0.0;
+    if (split) (void)awq_gemm_ksplit((int)M, (int)N, (int)K, &gemm_us);
+    else gemm_us = awq_gemm_unsplit_us((int)M, (int)N, (int)K);
+    gemm_us += 2.5 + (double)N * (double)K * 0.875 / 4.0e6;
+    if (M <= 128 || 1.2 * plan.us < gemm_us)
+        return awq_tile_launch(3, plan, x_f16, qweight, scales, zeros, y_f16, (int)M, (int)N, (int)K,
+                               (hipStream_t)stream);
     st = awq_repack_w3_to_w4(qweight, N, K, group, workspace, stream);
     if (st != AWQ_OK) return st;
     // a few hundred tokens: with room behind the re-packed codes (rounded up to 256 bytes) for the
     // fp32 partial tiles, the prefill kernel cuts K into ranges as in awq_w4a16_linear
-    const size_t repacked = ((size_t)(N * K / 2) + 255) & ~(size_t)255;
-    const size_t partials = awq_linear_workspace_bytes(M, N, K, group);
-    if (partials > 0 && workspace_bytes >= repacked + partials)
+    if (split)
         return awq_gemm_launch_split(x_f16, workspace, scales, zeros, y_f16, (int)M, (int)N, (int)K,
                                      (unsigned char *)workspace + repacked,
                                      awq_gemm_ksplit((int)M, (int)N, (int)K, nullptr), (hipStream_t)stream);

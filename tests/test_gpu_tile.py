@@ -1,4 +1,4 @@
-"""The K-split tile kernel (more than 16 tokens; 4-bit group 128 and 2-bit group 64) against the oracle at the
+"""The K-split tile kernel (more than 16 tokens; 4- and 3-bit group 128, 2-bit group 64) against the oracle at the
 sizes where it can go wrong: token tiles with a remainder (the last one moved back over its
 neighbour), several token tiles and ragged weight tiles per workgroup, fewer runs of K than waves, waves with one
 run more than others, and every pair of tile counts the planner picks on the way."""
@@ -18,20 +18,20 @@ def case(bits, N, K, M, seed):
     W = (g.standard_normal((N, K)) * 0.02).astype(np.float16)
     x = g.standard_normal((M, K)).astype(np.float16)
     s = g.uniform(0.5, 2.0, K).astype(np.float32)
-    quantize = oracle.quantize if bits == 4 else oracle.quantize_w2
-    Wdq = oracle.dequant(*quantize(W, s), group=128 if bits == 4 else 64)
-    pack = awq.awq_quantize_pack if bits == 4 else awq.awq_quantize_pack_w2
+    quantize = {4: oracle.quantize, 3: oracle.quantize_w3, 2: oracle.quantize_w2}[bits]
+    Wdq = oracle.dequant(*quantize(W, s), group=64 if bits == 2 else 128)
+    pack = {4: awq.awq_quantize_pack, 3: awq.awq_quantize_pack_w3, 2: awq.awq_quantize_pack_w2}[bits]
     packed = pack(torch.from_numpy(W).cuda(), torch.from_numpy(s).cuda())
     return x, Wdq, packed
 
 
-@pytest.mark.parametrize("bits", [4, 2])
+@pytest.mark.parametrize("bits", [4, 3, 2])
 @pytest.mark.parametrize("N,K", [(16, 256), (48, 768), (80, 1280), (208, 2304), (1040, 512), (4112, 1024)])
 def test_tile_kernel_against_the_oracle(bits, N, K):
     import oracle
     import torch
     import paper_2306_00978_amd as awq
-    linear = awq.awq_w4a16_linear if bits == 4 else awq.awq_w2a16_linear
+    linear = {4: awq.awq_w4a16_linear, 3: awq.awq_w3a16_linear, 2: awq.awq_w2a16_linear}[bits]
     x, Wdq, packed = case(bits, N, K, 300, N + K + bits)
     for M in (17, 31, 32, 33, 48, 77, 97, 128, 129, 300):
         buf = torch.full((M * N + 16,), float("nan"), dtype=torch.float16, device="cuda")
