@@ -14,6 +14,7 @@
 // copies to the host.
 #include "awq_common.h"
 #include "awq_gemm_epilogue.h"
+#include "awq_tile.h"
 
 int awq_act_mean_launch(const void *X_f16, int64_t T, int64_t K, float *mean, hipStream_t stream);
 int awq_quantize_inv_launch(const void *W, const float *s, int64_t N, int64_t K, void *qweight, void *scales, void *zeros,
@@ -343,11 +344,14 @@ extern "C" int awq_search_scale(const void *W_f16, const void *X_f16, int64_t T,
     if (st != AWQ_OK) return st;
     st = dense_gemm_launch((const half_t *)X_f16, (const half_t *)W_f16, Y, (int)T, (int)N, (int)K, hs);
     if (st != AWQ_OK) return st;
-    // where the layer runs the prefill kernel, its loss form takes the differences in the product's epilogue
-    // (2048 x 4096 x 4096: the product 65 us either way, without the 7 us pass over both outputs); its
-    // tiles have to fit the partial sums of a grid point
-    const int64_t tiles = awq_gemm_tiles((int)T, (int)N);
-    const bool fused = awq_linear_takes_prefill((int)T, (int)N, (int)K) && tiles <= LOSS_BLOCKS;
+    // Above 16 tokens the kernel that the layer runs, prefill or tile, has a loss form that takes the differences
+    // in the product's epilogue (2048 x 4096 x 4096: the product 65 us either way, without the 7 us pass over both
+    // outputs; 159 x 1120 x 2944: 21.2 us a grid point before, 16.5 now, with the powers below); its tiles have to fit the
+    // partial sums of a grid point
+    const bool prefill = T > 16 && awq_linear_takes_prefill((int)T, (int)N, (int)K);
+    const TilePlan plan = awq_tile_plan((int)T, (int)N, (int)K);
+    const int64_t tiles = prefill ? awq_gemm_tiles((int)T, (int)N) : awq_tile_count(plan, (int)T, (int)N);
+    const bool fused = T > 16 && tiles <= LOSS_BLOCKS;
     const int64_t chunks = T * N / 8;                    // N % 16 == 0
     // the powers of all grid points in one launch, in the place of the candidate's outputs, where that place is
     // not used and holds them
@@ -364,7 +368,8 @@ extern "C" int awq_search_scale(const void *W_f16, const void *X_f16, int64_t T,
         if (st != AWQ_OK) return st;
         double *part = partial + (size_t)i * LOSS_BLOCKS;
         if (fused) {
-            st = awq_gemm_launch_loss(xs, q, sc, zp, Y, (int)T, (int)N, (int)K, part, hs);
+            st = prefill ? awq_gemm_launch_loss(xs, q, sc, zp, Y, (int)T, (int)N, (int)K, part, hs)
+                         : awq_tile_launch_loss(plan, xs, q, sc, zp, Y, (int)T, (int)N, (int)K, part, hs);
             if (st != AWQ_OK) return st;
             continue;
         }

@@ -94,11 +94,11 @@ template <int BITS, int MT, int NT>
 __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
     const unsigned char *__restrict__ x, const unsigned char *__restrict__ qweight,
     const unsigned char *__restrict__ scales, const unsigned char *__restrict__ zeros,
-    half_t *__restrict__ y, int M, int N, int K, int tiles_n, int tiles_total)
+    half_t *__restrict__ y, int M, int N, int K, int tiles_n, int tiles_total, double *__restrict__ loss)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     asm volatile("" ::"s"(x), "s"(qweight), "s"(scales), "s"(zeros), "s"(y), "s"(M), "s"(N), "s"(K),
-                 "s"(tiles_n), "s"(tiles_total));          // arguments in one round
+                 "s"(tiles_n), "s"(tiles_total), "s"(loss));          // arguments in one round
     // contiguous ranges of tiles, token-tile-major, per XCD (own L2): see gemm_kernel
     const int per_xcd = (tiles_total + 7) >> 3;
     const int unit = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
@@ -313,7 +313,11 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
 
     // Sum over the waves.  Lane (r, c) holds rows 4 c + v, column r of each 16 x 16 tile.
     constexpr int MC = tile_pass(MT), ST = tile_stride(NT), ROWS = 16 * MC;
+    // With `loss` (the scale search, 4-bit): nothing is stored, y holds the layer's reference outputs, and
+    // loss[workgroup] becomes the sum of the squared differences of the outputs, rounded to fp16, to them: four squared
+    // and added in fp32, the rest in fp64, in a fixed order.
     float *lds = reinterpret_cast<float *>(smem);
+    double diff = 0.0;
     float *mine = lds + wave * (ROWS * ST);
 #pragma unroll
     for (int p = 0; p < MT; p += MC) {
@@ -340,18 +344,39 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
                 s.x += b.x; s.y += b.y; s.z += b.z; s.w += b.w;
             }
             const half2_t lo = {(half_t)s.x, (half_t)s.y}, hi = {(half_t)s.z, (half_t)s.w};
+            if (BITS == 4 && loss) {
+                const uint2 ref = *reinterpret_cast<const uint2 *>(y + (size_t)m * N + n);
+                const half2_t rlo = __builtin_bit_cast(half2_t, ref.x), rhi = __builtin_bit_cast(half2_t, ref.y);
+                const float d0 = (float)lo[0] - (float)rlo[0], d1 = (float)lo[1] - (float)rlo[1];
+                const float d2 = (float)hi[0] - (float)rhi[0], d3 = (float)hi[1] - (float)rhi[1];
+                diff += (double)(d0 * d0 + d1 * d1 + d2 * d2 + d3 * d3);
+                continue;
+            }
             *reinterpret_cast<uint2 *>(y + (size_t)m * N + n) =
                 make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
+        }
+    }
+    if (BITS == 4 && loss) {
+#pragma unroll
+        for (int d = 1; d <= 32; d <<= 1) diff += __shfl_xor(diff, d);
+        __syncthreads();                                   // the last pass has been read
+        double *red = reinterpret_cast<double *>(smem);
+        if (lane == 0) red[wave] = diff;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double sum = red[0];
+            for (int w = 1; w < TILE_WAVES; ++w) sum += red[w];
+            loss[unit] = sum;
         }
     }
 }
 
 template <int BITS, int MT, int NT>
 int launch_one(const void *x, const void *qweight, const void *scales, const void *zeros, void *y, int M, int N,
-               int K, hipStream_t stream)
+               int K, double *loss, hipStream_t stream)
 {
     const int tiles_n = (N / 16 + NT - 1) / NT;
-    const int64_t total = (int64_t)tiles_n * ((M + 16 * MT - 1) / (16 * MT));
+    const int64_t total = awq_tile_count({MT, NT, 0.0}, M, N);
     if (total > (1 << 30)) return AWQ_ERR_BAD_SHAPE;
     constexpr int lds = tile_lds(MT, NT);
     static_assert(lds <= 160 * 1024, "LDS of a CU");
@@ -365,11 +390,11 @@ int launch_one(const void *x, const void *qweight, const void *scales, const voi
     }
     tile_kernel<BITS, MT, NT><<<dim3((unsigned)((total + 7) / 8 * 8)), dim3(64 * TILE_WAVES), lds, stream>>>(
         (const unsigned char *)x, (const unsigned char *)qweight, (const unsigned char *)scales,
-        (const unsigned char *)zeros, (half_t *)y, M, N, K, tiles_n, (int)total);
+        (const unsigned char *)zeros, (half_t *)y, M, N, K, tiles_n, (int)total, loss);
     return awq_launch_status();
 }
 
-typedef int (*TileFn)(const void *, const void *, const void *, const void *, void *, int, int, int, hipStream_t);
+typedef int (*TileFn)(const void *, const void *, const void *, const void *, void *, int, int, int, double *, hipStream_t);
 
 constexpr int MTS[] = {1, 2, 3, 4, 5, 6, 8};
 // 128 x 64 does not fit the registers
@@ -409,7 +434,7 @@ TilePlan awq_tile_plan(int M, int N, int K)
     for (const int mt : MTS)
         for (int nt = 1; nt <= 4; ++nt) {
             if (!tile_built(mt, nt)) continue;
-            const int64_t wgs = (int64_t)((N / 16 + nt - 1) / nt) * ((M + 16 * mt - 1) / (16 * mt));
+            const int64_t wgs = awq_tile_count({mt, nt, 0.0}, M, N);
             const double us = 1.1 + (double)((wgs + 255) / 256) *
                                         (1.5 + runs * (0.235 * mt + 0.22 * nt + 0.02 * mt * nt) + 0.08 * mt * nt);
             if (best.us < 0.0 || us < best.us) best = {mt, nt, us};
@@ -417,9 +442,20 @@ TilePlan awq_tile_plan(int M, int N, int K)
     return best;
 }
 
+int64_t awq_tile_count(const TilePlan &plan, int M, int N)
+{
+    return (int64_t)((N / 16 + plan.nt - 1) / plan.nt) * ((M + 16 * plan.mt - 1) / (16 * plan.mt));
+}
+
 int awq_tile_launch(int bits, const TilePlan &plan, const void *x, const void *qweight, const void *scales,
                     const void *zeros, void *y, int M, int N, int K, hipStream_t stream)
 {
     const TileFn fn = bits == 4 ? pick<4>(plan.mt, plan.nt) : bits == 3 ? pick<3>(plan.mt, plan.nt) : pick<2>(plan.mt, plan.nt);
-    return fn(x, qweight, scales, zeros, y, M, N, K, stream);
+    return fn(x, qweight, scales, zeros, y, M, N, K, nullptr, stream);
+}
+
+int awq_tile_launch_loss(const TilePlan &plan, const void *x, const void *qweight, const void *scales, const void *zeros,
+                         const void *y_ref, int M, int N, int K, double *loss, hipStream_t stream)
+{
+    return pick<4>(plan.mt, plan.nt)(x, qweight, scales, zeros, const_cast<void *>(y_ref), M, N, K, loss, stream);
 }

@@ -1,13 +1,15 @@
-"""awq_search_scale where the layer runs the prefill kernel and the loss is taken in its epilogue: ragged token and
-feature tiles, a single K stage pair of the dense product, many and few grid points, against the same
-arithmetic in plain torch (fp64 products of the fp16 operands)."""
+"""awq_search_scale where the loss is taken in the epilogue of the layer's kernel, prefill or tile (17 tokens up): ragged
+token and feature tiles, token tiles moved back over their neighbour, a single K stage pair of the dense product,
+many and few grid points, against the same arithmetic in plain torch (fp64 products of the fp16 operands)."""
 import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T,N,K,points", [(2125, 1040, 384, 5), (2049, 272, 128, 3), (1000, 4112, 256, 20), (4096, 528, 640, 2)])
+@pytest.mark.parametrize("T,N,K,points", [(2125, 1040, 384, 5), (2049, 272, 128, 3), (1000, 4112, 256, 20), (4096, 528, 640, 2),
+                                          (16, 64, 256, 3), (17, 272, 1280, 20), (159, 1120, 2944, 20), (300, 1040, 128, 4),
+                                          (513, 4112, 1024, 2)])
 def test_fused_loss_against_plain_torch(T, N, K, points):
     import torch
     import paper_2306_00978_amd as awq
