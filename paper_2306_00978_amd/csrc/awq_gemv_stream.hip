@@ -1360,23 +1360,49 @@ int stream_launch_bits(const GemvProblem *problems, const GemvFusedExtra *extra,
 
     int ksl_of[GEMV_MAX_PROBLEMS], iters_of[GEMV_MAX_PROBLEMS];
     int logW = 2;
-    for (int i = 0; i < count; ++i) {
-        const int NBT = (problems[i].K / 128 + 3) / 4;
-        const int ksl_min = ceil_log2((NBT + bpr - 1) / bpr);
-        if (ksl_min > 3) return AWQ_GEMV_STREAM_UNFIT;
-        // K is split over as few waves as the register slots allow (splitting costs a pass
-        // through LDS and a barrier per row block)
-        int best_ksl = ksl_min;
-        // ... unless the launch is so small that a wave would then have far more jobs than its
-        // share T (a single projection): more waves along K put the whole matrix in flight
-        while (best_ksl < 3 && (2 << best_ksl) <= NBT && ((NBT + (1 << best_ksl) - 1) >> best_ksl) > 1.5 * T)
-            ++best_ksl;
-        if (f_ksl > ksl_min) best_ksl = std::min(3, f_ksl);
-        while ((1 << best_ksl) > NBT && best_ksl > ksl_min) --best_ksl;
-        if ((1 << best_ksl) > NBT) return AWQ_GEMV_STREAM_UNFIT;
-        ksl_of[i] = best_ksl;
-        logW = std::max(logW, best_ksl);
-    }
+    // workgroups at T jobs per wave, and the row-block steps of each
+    auto count_workgroups = [&](double jobs) {
+        int wgs = 0;
+        for (int i = 0; i < count; ++i) {
+            const int NBT = (problems[i].K / 128 + 3) / 4;
+            const int nbw = (NBT + (1 << ksl_of[i]) - 1) >> ksl_of[i];
+            const int RW = (1 << logW) >> ksl_of[i];
+            const int steps = (problems[i].N / 16 + RW - 1) / RW;            // row-block steps of the whole linear
+            iters_of[i] = std::min(f_iters > 0 ? f_iters : std::max(1, (int)(jobs / nbw + 0.5)), steps);
+            wgs += (steps + iters_of[i] - 1) / iters_of[i];
+        }
+        return wgs;
+    };
+    // Waves that split K, per linear (at most 2^most), and with them the workgroup size
+    int ksl_least = 0;
+    auto split_k = [&](int most) {
+        logW = 2;
+        for (int i = 0; i < count; ++i) {
+            const int NBT = (problems[i].K / 128 + 3) / 4;
+            const int ksl_min = ceil_log2((NBT + bpr - 1) / bpr);
+            if (ksl_min > 3) return false;
+            ksl_least = std::max(ksl_least, ksl_min);
+            // K is split over as few waves as the register slots allow (splitting costs a pass
+            // through LDS and a barrier per row block)
+            int best_ksl = ksl_min;
+            // ... unless the launch is so small that a wave would then have far more jobs than its
+            // share T (a single projection): more waves along K put the whole matrix in flight
+            while (best_ksl < most && (2 << best_ksl) <= NBT && ((NBT + (1 << best_ksl) - 1) >> best_ksl) > 1.5 * T)
+                ++best_ksl;
+            if (f_ksl > ksl_min) best_ksl = std::min(3, f_ksl);
+            while ((1 << best_ksl) > NBT && best_ksl > ksl_min) --best_ksl;
+            if ((1 << best_ksl) > NBT) return false;
+            ksl_of[i] = best_ksl;
+            logW = std::max(logW, best_ksl);
+        }
+        return true;
+    };
+    if (!split_k(3)) return AWQ_GEMV_STREAM_UNFIT;
+    // A CU holds one workgroup of eight waves (156 registers: three waves to a SIMD); more of them than
+    // CUs would be a second round.  Then four waves, three workgroups to a CU, where the register slots
+    // allow it (a layer of hidden size 1280 / 4352 at one token, 266 workgroups: 10.1 us, now 7.2; where they do not, T grows until it is one round (4352 / 15104
+    // at four tokens: 42.4 us, now 28.4)
+    if (logW == 3 && ksl_least < 3 && count_workgroups(T) > 256) (void)split_k(2);
     if (f_logw >= 0) logW = std::min(3, std::max(f_logw, logW));
     L.logW = logW;
     const int W = 1 << logW;
@@ -1385,10 +1411,10 @@ int stream_launch_bits(const GemvProblem *problems, const GemvFusedExtra *extra,
                        (FUSED ? (size_t)W * 16 * 4 : 0);
 
     // The row-block steps per workgroup bring the jobs of a wave as close to T as they get.
-    // Workgroups of eight waves take more than half of a CU's LDS, so only one is resident per
-    // CU: their number must not exceed the CUs (a second round would run nearly alone), and T
+    // One workgroup of eight waves is resident per CU (registers, and with more than half of a CU's LDS
+    // that as well): their number must not exceed the CUs (a second round would run nearly alone), and T
     // is raised until it does not.
-    const int wg_cap = lds * 2 > 160 * 1024 ? 256 : (1 << 30);
+    const int wg_cap = W == 8 || lds * 2 > 160 * 1024 ? 256 : (1 << 30);
     int wg = 0;
     static const int f_paired = awq_knob("AWQ_GEMV_PAIRED", 1);
     bool paired = false;
@@ -1402,27 +1428,22 @@ int stream_launch_bits(const GemvProblem *problems, const GemvFusedExtra *extra,
         }
     }
     g_last_plan.store(paired ? 2 : 1, std::memory_order_relaxed);
-    for (int attempt = 0; attempt < 64 && !paired; ++attempt) {
+    if (!paired) {
+        for (int attempt = 0; attempt < 64; ++attempt) {
+            wg = count_workgroups(T);
+            if (wg <= wg_cap || f_iters > 0 || f_jobs > 0) break;
+            T *= 1.04;
+        }
         wg = 0;
         for (int i = 0; i < count; ++i) {
             GemvProblem p = problems[i];
-            const int NBT = (p.K / 128 + 3) / 4;
-            const int nbw = (NBT + (1 << ksl_of[i]) - 1) >> ksl_of[i];
-            int it = std::max(1, (int)(T / nbw + 0.5));
-            if (f_iters > 0) it = f_iters;
-            const int NRB = p.N / 16;
-            const int RW = W >> ksl_of[i];
-            const int steps = (NRB + RW - 1) / RW;            // row-block steps of the whole linear
-            const int iters = std::min(it, steps);
-            iters_of[i] = iters;
-            p.plan = ksl_of[i] | (iters << 4);
-            p.nrb = NRB;
+            p.plan = ksl_of[i] | (iters_of[i] << 4);
+            p.nrb = p.N / 16;
             L.wg_begin[i] = wg;
-            wg += (steps + iters - 1) / iters;
+            const int RW = W >> ksl_of[i], steps = (p.nrb + RW - 1) / RW;
+            wg += (steps + iters_of[i] - 1) / iters_of[i];
             L.p[i] = p;
         }
-        if (wg <= wg_cap || f_iters > 0 || f_jobs > 0) break;
-        T *= 1.04;
     }
     static AwqOncePerDevice once;
     std::atomic<bool> &attr_set = once.here();
