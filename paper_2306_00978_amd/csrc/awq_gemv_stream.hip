@@ -261,6 +261,45 @@ __device__ __forceinline__ floatx4 consume_batch_w3(const Landed &b, const uint4
     return bacc;
 }
 
+// INT3 without factors on the activations: every pair is shifted to the bottom of its halves and reads as the fp16
+// subnormals q * 2^-24, so the activations stay as they came.  (q - z by its place in the mantissa, without sums of
+// x, was the same or slower: 41.1 us against 37.8 for a layer of hidden size 5120 at 12 tokens.)
+__device__ __forceinline__ floatx4 consume_batch_w3_shifted(const Landed &b, const uint4 (&xa)[16],
+                                                            const floatx4 (&xsum)[4], uint32_t mask, int zshift)
+{
+    floatx4 bacc = {0.f, 0.f, 0.f, 0.f};
+    const uint32_t sraw[4] = {b.s.x, b.s.y, b.s.z, b.s.w};
+    const uint32_t zraw[4] = {b.z.x, b.z.y, b.z.z, b.z.w};
+#pragma unroll
+    for (int u = 0; u < 4; u += 2) {
+        floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint32_t w[3] = {b.q[u + h].x, b.q[u + h].y, b.q[u + h].z};
+                uint32_t t[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int p = 4 * j + i;
+                    t[i] = p < 15 ? (w[p / 5] >> (3 * (p % 5))) & mask
+                                  : ((w[0] >> 15) & 0x00010001u) | ((w[1] >> 14) & 0x00020002u) | ((w[2] >> 13) & 0x00040004u);
+                }
+                acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, xa[4 * (u + h) + j]),
+                                                                __builtin_bit_cast(half8_t, make_uint4(t[0], t[1], t[2], t[3])),
+                                                                acc[h], 0, 0, 0);
+            }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float z = (float)((zraw[u + h] >> zshift) & 0xFu);
+            const float sc = (float)__builtin_bit_cast(half_t, (uint16_t)sraw[u + h]) * 16777216.f;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) bacc[v] += sc * (acc[h][v] - z * xsum[u + h][v]);
+        }
+    }
+    return bacc;
+}
+
 // Mixed-precision helpers of the fused normalisation (fp16 operands taken from a packed pair,
 // fp32 arithmetic, no separate conversions): acc + lo(h2)^2 + hi(h2)^2, and the pair
 // fp16(lo(x2) * f * lo(w2)), fp16(hi(x2) * f * hi(w2)).
@@ -872,30 +911,32 @@ constexpr int ROWS_UNITS = 2;
 constexpr int ROWS_THREADS = 64 * ROWS_UNITS * (ROWS_CW + 1);
 // MR = token rows kept in LDS (8 or 16; tokens beyond M repeat token M - 1, and with MR = 8 the
 // MFMA rows 8..15 read the LDS rows 0..7 again).  Half the rows leave room for a fourth ring slot.
-template <int MR>
+template <int MR, int BITS>
 struct RowsShape {
     static constexpr int X_BUF = MR * ROWS_X_ROW;
-    static constexpr int RING = MR == 8 ? 4 : 3;       // ring slots per compute wave
-    static constexpr int UNIT_LDS = ROWS_CW * RING * Slot<4>::BYTES + 2 * X_BUF + 64;   // + the progress words
+    static constexpr int RING = MR == 8 || BITS == 3 ? 4 : 3;       // ring slots per compute wave
+    static constexpr int UNIT_LDS = ROWS_CW * RING * Slot<BITS>::BYTES + 2 * X_BUF + 64;   // + the progress words
     static constexpr int LDS = ROWS_UNITS * UNIT_LDS;
-    static_assert(ROWS_MAX_ITERS * 1024 <= RING * Slot<4>::BYTES, "the hand-over of the sums uses a wave's ring");
+    static_assert(ROWS_MAX_ITERS * 1024 <= RING * Slot<BITS>::BYTES, "the hand-over of the sums uses a wave's ring");
     static_assert(LDS <= 160 * 1024, "one workgroup per CU");
 };
 
-template <int MR, bool NT>
+template <int BITS, int MR, bool NT>
 __global__ __launch_bounds__(ROWS_THREADS) void gemv_rows_kernel(const GemvArgs<false> A)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int ROWS_X_BUF = RowsShape<MR>::X_BUF, ROWS_RING = RowsShape<MR>::RING;
-    constexpr int ROWS_UNIT_LDS = RowsShape<MR>::UNIT_LDS;
-    constexpr int STAGE_BYTES = Slot<4>::BYTES, STAGE_SC = Slot<4>::SC, STAGE_ZP = Slot<4>::ZP;
-    constexpr int LOADS_PER_JOB = Slot<4>::LOADS;
+    constexpr int ROWS_X_BUF = RowsShape<MR, BITS>::X_BUF, ROWS_RING = RowsShape<MR, BITS>::RING;
+    constexpr int ROWS_UNIT_LDS = RowsShape<MR, BITS>::UNIT_LDS;
+    constexpr int TILE = Slot<BITS>::TILE, STAGE_BYTES = Slot<BITS>::BYTES, STAGE_SC = Slot<BITS>::SC, STAGE_ZP = Slot<BITS>::ZP;
+    constexpr int LOADS_PER_JOB = Slot<BITS>::LOADS;       // a last batch of fewer groups may take one more: a longer wait
     typedef const __attribute__((address_space(1))) half_t gbl_half_t;
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
     typedef const __attribute__((address_space(1))) u32x4_t gbl_u32x4_t;
     uint32_t mask_lo = 0x000F000Fu, mask_hi = 0x00F000F0u;
     asm("" : "+s"(mask_lo));
     asm("" : "+s"(mask_hi));
+    uint32_t mask3 = 0x00070007u;
+    asm("" : "+s"(mask3));
     const GemvLaunch &L = A.L;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -994,8 +1035,10 @@ __global__ __launch_bounds__(ROWS_THREADS) void gemv_rows_kernel(const GemvArgs<
 #pragma unroll
             for (int m = 0; m < MR; ++m) {
                 uint4 v = reg[m];
-                v.y = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, v.y) * sixteenth);
-                v.w = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, v.w) * sixteenth);
+                if (BITS == 4) {
+                    v.y = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, v.y) * sixteenth);
+                    v.w = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, v.w) * sixteenth);
+                }
                 if (!valid) v = make_uint4(0, 0, 0, 0);
                 *reinterpret_cast<uint4 *>(dst + m * ROWS_X_ROW) = v;
             }
@@ -1027,19 +1070,19 @@ __global__ __launch_bounds__(ROWS_THREADS) void gemv_rows_kernel(const GemvArgs<
             rb = rb < NRB ? rb : NRB - 1;                       // surplus waves redo the last block
             const size_t t0 = (size_t)rb * G + (size_t)b * 4;
             const uint32_t dst = ring + (uint32_t)slot * STAGE_BYTES;
-            const unsigned char *tq = qbase + t0 * 1024, *ts = scbase + t0 * 32, *tz = zpbase + t0 * 8;
+            const unsigned char *tq = qbase + t0 * TILE, *ts = scbase + t0 * 32, *tz = zpbase + t0 * 8;
             if (!ragged || b * 4 + 4 <= G) {
                 dma16_to_lds<0, NT>(tq + lane16, dst);
                 dma16_to_lds<1024, NT>(tq + lane16, dst);
                 dma16_to_lds<2048, NT>(tq + lane16, dst);
-                dma16_to_lds<3072, NT>(tq + lane16, dst);
+                if (BITS == 4) dma16_to_lds<3072, NT>(tq + lane16, dst);
                 dma2_to_lds(ts + sc_lane, dst + STAGE_SC);
                 if (lane < 32) dma1_to_lds(tz + zp_lane, dst + STAGE_ZP);
             } else {
                 const int last = G - 1 - b * 4;                 // last valid group of this batch (0..2)
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    dma16_to_lds<0, NT>(tq + ((size_t)min(u, last) << 10) + lane16, dst + u * 1024);
+                    if (BITS == 4 || lane < 48) dma16_to_lds<0, NT>(tq + min(u, last) * TILE + lane16, dst + u * TILE);
                 const int gl = min(lane & 3, last);
                 dma2_to_lds(ts + gl * 32 + (lane >> 2) * 2, dst + STAGE_SC);
                 if (lane < 32) dma1_to_lds(tz + gl * 8 + ((lane >> 2) & 7), dst + STAGE_ZP);
@@ -1058,8 +1101,9 @@ __global__ __launch_bounds__(ROWS_THREADS) void gemv_rows_kernel(const GemvArgs<
         for (int t = 0; t < ROWS_RING - 1; ++t)
             if (nj < J) issue_next();
 
-        const half8_t ones = __builtin_bit_cast(half8_t, make_uint4(0x00010001u, 0x00100010u, 0x00010001u, 0x00100010u));
-        const uint32_t rd_tile = ring + lane16, rd_sc = ring + 16 * r, rd_zp = ring + 16 * (r >> 1);
+        const uint32_t hi1 = BITS == 4 ? 0x00100010u : 0x00010001u;
+        const half8_t ones = __builtin_bit_cast(half8_t, make_uint4(0x00010001u, hi1, 0x00010001u, hi1));
+        const uint32_t rd_tile = ring + (BITS == 4 ? lane16 : 12u * (uint32_t)lane), rd_sc = ring + 16 * r, rd_zp = ring + 16 * (r >> 1);
         const uint32_t rd_x = xbuf + (uint32_t)(r & (MR - 1)) * ROWS_X_ROW + (uint32_t)c4 * 16;
         int cslot = 0, j = 0;
         for (int c = 0; c < NC; ++c) {
@@ -1102,9 +1146,12 @@ __global__ __launch_bounds__(ROWS_THREADS) void gemv_rows_kernel(const GemvArgs<
                     else wait_loads<0>();
                     Landed cur;
                     const uint32_t off = (uint32_t)cslot * STAGE_BYTES;
-                    read_slot(cur, rd_tile + off, rd_sc + off, rd_zp + off);
+                    if (BITS == 4) read_slot(cur, rd_tile + off, rd_sc + off, rd_zp + off);
+                    else read_slot_w3(cur, rd_tile + off, rd_sc + off, rd_zp + off);
                     if (++cslot == ROWS_RING) cslot = 0;
-                    const floatx4 b = consume_batch(cur, xa, xsum, mask_lo, mask_hi, zshift);
+                    floatx4 b;
+                    if constexpr (BITS == 4) b = consume_batch(cur, xa, xsum, mask_lo, mask_hi, zshift);
+                    else b = consume_batch_w3_shifted(cur, xa, xsum, mask3, zshift);
 #pragma unroll
                     for (int v = 0; v < 4; ++v) acc[it][v] += b[v];
                     ++j;
@@ -1580,7 +1627,10 @@ int awq_gemv_chain_launch(const GemvProblem *const *problems, const GemvFusedExt
 // the cost of taking a chunk of x out of LDS is shared by that many jobs (measured: 1.5 us per job
 // with one step, 0.9 us with three).  The plan is the one with the smallest largest such estimate
 // among those with at most 256 workgroups.
-int awq_gemv_rows_launch(const GemvProblem *problems, int count, int M, hipStream_t stream)
+namespace {
+
+template <int BITS>
+int rows_launch_bits(const GemvProblem *problems, int count, int M, hipStream_t stream)
 {
     if (count < 1 || count > GEMV_MAX_PROBLEMS || M < 1 || M > 16) return AWQ_ERR_BAD_ARGUMENT;
     struct Option {
@@ -1654,22 +1704,38 @@ int awq_gemv_rows_launch(const GemvProblem *problems, int count, int M, hipStrea
     static AwqOncePerDevice once;
     std::atomic<bool> &attr_set = once.here();
     if (!attr_set.load(std::memory_order_relaxed)) {
-        const void *kernels[] = {reinterpret_cast<const void *>(gemv_rows_kernel<8, false>),
-                                 reinterpret_cast<const void *>(gemv_rows_kernel<8, true>),
-                                 reinterpret_cast<const void *>(gemv_rows_kernel<16, false>),
-                                 reinterpret_cast<const void *>(gemv_rows_kernel<16, true>)};
-        for (int k = 0; k < 4; ++k)
+        const void *kernels[] = {reinterpret_cast<const void *>(gemv_rows_kernel<BITS, 16, false>),
+                                 reinterpret_cast<const void *>(gemv_rows_kernel<BITS, 16, true>),
+                                 reinterpret_cast<const void *>(gemv_rows_kernel<4, 8, false>),
+                                 reinterpret_cast<const void *>(gemv_rows_kernel<4, 8, true>)};
+        for (int k = 0; k < (BITS == 4 ? 4 : 2); ++k)
             if (hipFuncSetAttribute(kernels[k], hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    k < 2 ? RowsShape<8>::LDS : RowsShape<16>::LDS) != hipSuccess)
+                                    k < 2 ? RowsShape<16, BITS>::LDS : RowsShape<8, 4>::LDS) != hipSuccess)
                 return AWQ_ERR_HIP;
         attr_set.store(true, std::memory_order_relaxed);
     }
-    const bool nt = streams_weights(problems, count, 4);
-    if (M <= 8 && nt) gemv_rows_kernel<8, true><<<dim3(wg), dim3(ROWS_THREADS), RowsShape<8>::LDS, stream>>>(A);
-    else if (M <= 8) gemv_rows_kernel<8, false><<<dim3(wg), dim3(ROWS_THREADS), RowsShape<8>::LDS, stream>>>(A);
-    else if (nt) gemv_rows_kernel<16, true><<<dim3(wg), dim3(ROWS_THREADS), RowsShape<16>::LDS, stream>>>(A);
-    else gemv_rows_kernel<16, false><<<dim3(wg), dim3(ROWS_THREADS), RowsShape<16>::LDS, stream>>>(A);
+    const bool nt = streams_weights(problems, count, BITS);
+    if (BITS == 4 && M <= 8) {
+        if (nt) gemv_rows_kernel<4, 8, true><<<dim3(wg), dim3(ROWS_THREADS), RowsShape<8, 4>::LDS, stream>>>(A);
+        else gemv_rows_kernel<4, 8, false><<<dim3(wg), dim3(ROWS_THREADS), RowsShape<8, 4>::LDS, stream>>>(A);
+    } else if (nt) {
+        gemv_rows_kernel<BITS, 16, true><<<dim3(wg), dim3(ROWS_THREADS), RowsShape<16, BITS>::LDS, stream>>>(A);
+    } else {
+        gemv_rows_kernel<BITS, 16, false><<<dim3(wg), dim3(ROWS_THREADS), RowsShape<16, BITS>::LDS, stream>>>(A);
+    }
     return awq_launch_status();
+}
+
+}  // namespace
+
+int awq_gemv_rows_launch(const GemvProblem *problems, int count, int M, hipStream_t stream)
+{
+    return rows_launch_bits<4>(problems, count, M, stream);
+}
+
+int awq_gemv_rows_launch_w3(const GemvProblem *problems, int count, int M, hipStream_t stream)
+{
+    return rows_launch_bits<3>(problems, count, M, stream);
 }
 
 int awq_gemv_stream_launch(const GemvProblem *problems, int count, int M, hipStream_t stream)

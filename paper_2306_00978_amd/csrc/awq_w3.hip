@@ -342,6 +342,18 @@ extern "C" int awq_w3a16_linear_multi(const awq_linear_desc *descs, int count, i
         p[i].N = (int)d.N;
         p[i].K = (int)d.K;
     }
+    // From nine tokens the streaming kernel holds one batch of K per wave and takes K up to 4096 only, and not
+    // every such K; the linears it does not take would be a launch each.  With two or more of those,
+    // and row blocks enough for every CU, the kernel that takes the activations through LDS (any K) runs all in one
+    // launch: a layer of hidden size 1280 at 12 tokens 26.1 us before, 10.8 now, 3072 48.4 / 19.4, 7168 120.9 /
+    // 63.7.  (One such linear: 0.97 to 1.2, left as it was; 2 x (512 x 8192), 64 row blocks: 12.8 and 16.2.)
+    int unfit = 0, row_blocks = 0;
+    for (int i = 0; i < count; ++i) {
+        unfit += !awq_gemv_stream_fits(p[i].N, p[i].K, (int)M);
+        row_blocks += p[i].N / 16;
+    }
+    if (M > 8 && unfit >= 2 && row_blocks >= 256)
+        return awq_gemv_rows_launch_w3(p, count, (int)M, (hipStream_t)stream);
     GemvProblem fit[GEMV_MAX_PROBLEMS];
     int nfit = 0;
     bool grouped[GEMV_MAX_PROBLEMS] = {};
