@@ -194,7 +194,17 @@ extern "C" int awq_w4a16_linear_multi(const awq_linear_desc *descs, int count, i
     // smaller one stays with the batch kernel, where everything requested at once is the faster way
     // through a small matrix (N = 4096, K = 11008: 10 us against 20 us).
     static const int rows_min_count = awq_knob("AWQ_ROWS_MIN_COUNT", 2);
-    if (M > 4 && (count >= rows_min_count || p[0].N >= 16384))
+    // At five and six tokens a small launch is the streaming kernel's still, whose waves request all of it at
+    // once (a layer of hidden size 1280 / 3840 at five tokens, 9.4 MB: 7.6 us and 9.7 through LDS; 2048 / 6144, 24 MB: 10.1
+    // and 12.8; 2560 / 7680, 38 MB: 14.2 and 15.2; 3072 / 9216, 54 MB: 19.3 and 17.0; at eight tokens even).
+    bool small = M <= 6 && count > 1;
+    int64_t packed = 0;
+    for (int i = 0; i < count; ++i) {
+        packed += (int64_t)p[i].N * p[i].K / 2;
+        small = small && awq_gemv_stream_fits(p[i].N, p[i].K, (int)M);
+    }
+    small = small && packed <= (int64_t)32 << 20;
+    if (M > 4 && !small && (count >= rows_min_count || p[0].N >= 16384))
         return awq_gemv_rows_launch(p, count, (int)M, (hipStream_t)stream);
     // The linears whose K fits the register-resident activations of the streaming kernel at
     // this M go out in one launch; the others (and a lone linear) take one launch of the batch
