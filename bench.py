@@ -828,7 +828,7 @@ def main():
         del lay70
 
         M = workloads.PREFILL_M
-        # a short prefill: 64 tokens, 4096 x 4096 (decode kernels on blocks of 16 tokens, one grouped launch)
+        # a short prefill: 64 tokens, 4096 x 4096 (the tile kernel)
         x64 = x_by_k[4096][:64].contiguous()
         y64 = torch.empty((64, 4096), dtype=torch.float16, device=dev)
         for i in range(4):
@@ -843,7 +843,7 @@ def main():
         ms64 = e0.elapsed_time(e1) / 40
         extras["prefill_m64_4096x4096"] = {"us": round(ms64 * 1e3, 2),
                                            "TFLOP/s": round(workloads.flops(64, 4096, 4096) / (ms64 * 1e-3) / 1e12, 1),
-                                           "note": "17..128 tokens: blocks of 16 through the decode kernels"}
+                                           "note": "17..128 tokens: the tile kernel"}
         # a prompt of 512 tokens, the three distinct shapes: the prefill kernel with K cut into ranges
         # (the workspace of awq_w4a16_linear), next to the same call without the workspace
         pre512 = {}
