@@ -422,7 +422,10 @@ __global__ __launch_bounds__(64 * GQ_WAVES, 1) void attention_grouped_kernel(con
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const float a = ldexpf(h ? qhi_f[n] : qlo_f[n], -ex);
-            const half_t top = (half_t)a, rest = (half_t)(a - (float)top);
+            half_t top = (half_t)a;
+            // an element too small for the high half keeps its sign there, for keys that hold an infinity
+            if (a != 0.f && top == (half_t)0.f) top = (half_t)__builtin_copysignf(0x1p-24f, a);
+            const half_t rest = (half_t)(a - (float)top);
             const uint32_t at = qa + 256 * n + (((sw + 8 * h) ^ row) * 16);
             asm volatile("ds_write_b16 %0, %1" ::"v"(at), "v"((uint32_t)__builtin_bit_cast(uint16_t, top)) : "memory");
             asm volatile("ds_write_b16 %0, %1" ::"v"(at + QLO), "v"((uint32_t)__builtin_bit_cast(uint16_t, rest)) : "memory");
@@ -456,9 +459,10 @@ __global__ __launch_bounds__(64 * GQ_WAVES, 1) void attention_grouped_kernel(con
     floatx4 acc[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-    if (wave == 0 && split == pos / chunk) {
+    // (a score of -inf has the weight 0: the state stays empty; +inf gives NaN, as inf - inf does)
+    if (wave == 0 && split == pos / chunk && now != -__builtin_inff()) {
         m = now;
-        l = c == 0 ? 1.f : 0.f;
+        l = c == 0 ? 1.f + (now - now) : 0.f;
 #pragma unroll
         for (int t = 0; t < T; ++t) {
             const float vt = half_of(vnow, t);
@@ -493,6 +497,10 @@ __global__ __launch_bounds__(64 * GQ_WAVES, 1) void attention_grouped_kernel(con
         stage = stage + 1 == Sh::STAGES ? 0 : stage + 1;
 
         const int first = p0 + (wave + GQ_WAVES * b) * GQ_BLOCK + 4 * c;
+        // rows past the end have the weight 0, and an infinity times 0 is NaN: their values become 0
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (first + i >= p1) vv[i].d = decltype(vv[i].d){};
         floatx4 hi = {0.f, 0.f, 0.f, 0.f}, lo = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -503,18 +511,22 @@ __global__ __launch_bounds__(64 * GQ_WAVES, 1) void attention_grouped_kernel(con
         float s[4], top = -__builtin_inff();
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            s[i] = first + i < p1 ? (hi[i] + lo[i]) * unscale : -__builtin_inff();
+            // a key with an infinity: the high halves alone have the sign; Inf times a low half of 0 or of the other
+            // sign would make it NaN
+            const float both = __builtin_fabsf(hi[i]) < __builtin_inff() ? hi[i] + lo[i] : hi[i];
+            s[i] = first + i < p1 ? both * unscale : -__builtin_inff();
             top = fmaxf(top, s[i]);
         }
         top = fmaxf(top, __shfl_xor(top, 16));
         top = fmaxf(top, __shfl_xor(top, 32));
-        const float m_new = fmaxf(m, top);                               // finite: a block has a valid position
-        const float keep = __expf(m - m_new);
+        const float m_new = fmaxf(m, top);
+        const float zero = m_new == -__builtin_inff() ? 0.f : m_new;     // all scores so far -inf: all weights 0
+        const float keep = __expf(m - zero);
         m = m_new;
         l *= keep;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            s[i] = __expf(s[i] - m_new);
+            s[i] = __expf(s[i] - zero);
             l += s[i];
         }
         if (__any(keep != 1.0f)) {

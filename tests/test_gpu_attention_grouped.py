@@ -44,3 +44,60 @@ def test_grouped_attention_against_the_oracle(H, Hkv, positions):
         assert np.array_equal(np.delete(kn, pos, 1).view(np.uint16), np.delete(kc, pos, 1).view(np.uint16))
         a, b = kn[:, pos].astype(np.float64), kc_ref[:, pos].astype(np.float64)
         assert np.all(np.abs(a - b) <= np.abs(b) * 2.0 ** -10 + 1e-7)
+
+
+# F = 4, 2 and 1 workgroups to a slice of the positions (64, 144 and 256 items)
+SPLITS = [(64, 8, 1000), (96, 24, 330), (384, 128, 700)]
+
+
+@pytest.mark.parametrize("H,Hkv,pos", SPLITS)
+@pytest.mark.parametrize("where", ["value of the last row", "keys", "key of the token", "key, positive", "key of the token, positive"])
+def test_infinities_in_the_caches_have_the_weight_of_their_score(H, Hkv, pos, where):
+    """An infinite value reaches its own output column only; a key whose score is -Inf has the weight 0, wherever it lies
+    (alone, a whole block of 16 rows, the first row of a slice, the token itself); a score of +Inf gives NaN."""
+    import torch
+    import paper_2306_00978_amd as awq
+    from oracle import rope_rotate
+    g = np.random.default_rng(H + pos)
+    lmax = pos + 3
+    q, k, v = (g.standard_normal((n, 128)).astype(np.float16) for n in (H, Hkv, Hkv))
+    q[:, 63] = 0.5 + np.abs(q[:, 63])                                    # the slowest pair: positive after the rotation
+    q[:, 127] = 0.5 + np.abs(q[:, 127])
+    q[1, 5], q[1, 63], q[1, 127] = 30000, 2.0 ** -22, 2.0 ** -24         # elements below the high halves of the head's largest
+    kc, vc = np.full((2, Hkv, lmax, 128), np.nan, np.float16)
+    kc[:, :pos], vc[:, :pos] = g.standard_normal((2, Hkv, pos, 128))
+    kc[:, :, 5] = 0
+    kc[:, :, 69] = 0
+    k[:, 5] = k[:, 69] = 0
+    if where == "value of the last row":
+        vc[:, pos - 1, 7] = np.inf
+        vc[:, pos - 1, 100] = -np.inf
+    elif where == "keys":
+        kc[:, 16:32, 63] = kc[:, 0, 63] = kc[:, 77, 63] = kc[:, pos - 1, 63] = -np.inf
+    elif where == "key of the token":
+        k[:, 63] = -np.inf
+    elif where == "key, positive":
+        kc[:, 3, 63] = np.inf
+    else:
+        k[:, 63] = np.inf
+    qr, kr = rope_rotate(q.astype(np.float64), pos), rope_rotate(k.astype(np.float64), pos)
+    assert (qr[:, 63] > 0).all() and (qr[:, 127] > 0).all()
+    keys = np.concatenate([kc[:, :pos].astype(np.float64), kr[:, None]], 1)
+    vals = np.concatenate([vc[:, :pos].astype(np.float64), v[:, None].astype(np.float64)], 1)
+    G = H // Hkv
+    with np.errstate(invalid="ignore"):
+        score = np.einsum("gld,ghd->ghl", keys, qr.reshape(Hkv, G, 128)) / np.sqrt(128)
+        weight = np.exp(score - score.max(-1, keepdims=True))
+        weight /= weight.sum(-1, keepdims=True)
+        want = np.einsum("ghl,gld->ghd", weight, np.where(np.isinf(vals), 0, vals))
+        for g_, l, d in zip(*np.nonzero(np.isinf(vals))):
+            want[g_, :, d] += weight[g_, :, l] * vals[g_, l, d]
+    want = want.reshape(H, 128)
+    out = torch.full((H, 128), 7.0, dtype=torch.float16, device="cuda")
+    awq.awq_decode_attention(*(torch.from_numpy(t).cuda() for t in (q, k, v)), torch.from_numpy(kc).cuda(),
+                             torch.from_numpy(vc).cuda(), pos, out=out)
+    got = out.cpu().numpy().astype(np.float64)
+    fine = np.isfinite(want)
+    assert fine.all() == (where in ("keys", "key of the token"))
+    assert np.array_equal(got[~fine], want[~fine], equal_nan=True)
+    assert np.abs(got[fine] - want[fine]).max(initial=0) <= TOL * np.abs(vals[np.isfinite(vals)]).max()
