@@ -223,9 +223,9 @@ __global__ __launch_bounds__(256) void attention_partial_kernel(
 // times (from L2) and spends G times the vector work on it: 26.8 us a call at 64 / 8 heads, 4000
 // positions, for 16 MB of caches.  Here a workgroup serves up to 16 query heads of one kv head at once
 // and both products run on the matrix cores:
-//   scores   v_mfma_f32_16x16x32_f16, A = 16 keys from the cache, B = the rotated queries as the sum of two
-//            halves (high and low part of the fp32 value times a power of two of the head's own,
-//            2^-22 relative: scores as exact as with fp32 queries);
+//   scores   v_mfma_f32_16x16x32_f16, A = 16 keys from the cache, B = the rotated queries as the sum of three
+//            halves (of the fp32 value times a power of two of the head's own; the third is what is left of it times
+//            2^20): all 24 bits of every element down to 2^-31 of the head's largest, 2^-55 of that beyond;
 //   values   v_mfma_f32_16x16x4_f32, fp32 probabilities and fp32 values: nothing is rounded to 16 bits.
 // A score tile has lane (r, c) holding head r, positions 4 c + v: with step v of the value product
 // taken over positions {v, 4 + v, 8 + v, 12 + v} that is its A operand as it stands, and its B operand
@@ -235,7 +235,8 @@ __global__ __launch_bounds__(256) void attention_partial_kernel(
 // which at 64 heads are eight, 64 workgroups: so F workgroups of a slice (on one XCD, sharing its L2) take
 // the same scores and 128 / F dimensions of the values each.  The current token enters as the initial state of
 // one wave, with its key in fp32.  64 / 8 heads, 4000 positions:
-// 26.8 -> 12.8 us a call with the merge; what is left is a chain of latencies (arguments, small inputs 2 us,
+// 26.8 -> 13.3 us a call with the merge (12.8 with two halves to a query, which left small elements beside a large
+// one with fewer bits than fp32 has); what is left is a chain of latencies (arguments, small inputs 2 us,
 // rotation 1 us, two rounds of cache rows, two merges), not the 16 MB.
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef const __attribute__((address_space(1))) void gbl_void_t;
@@ -255,9 +256,9 @@ template <int F> struct GqShape {
     static constexpr int STAGE = GQ_BLOCK * (256 + VROW);
     static constexpr int STAGES = F == 1 ? 2 : 3;
     static constexpr int LOADS = 4 + 4 / F;     // per stage
-    // 16 query rows (then their high halves), the token's key and value, the rotary table, the low halves, two
-    // numbers per head
-    static constexpr int SHARED = 9 * 1024 + 128;
+    // 16 query rows (then their high halves), the token's key and value, the rotary table, the low halves, the
+    // third ones, two numbers per head
+    static constexpr int SHARED = 13 * 1024 + 128;
     static constexpr int LDS = SHARED + GQ_WAVES * STAGES * STAGE;
 };
 
@@ -346,8 +347,8 @@ __global__ __launch_bounds__(64 * GQ_WAVES, 1) void attention_grouped_kernel(con
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(Sh::STAGES * Sh::LOADS) : "memory");
     __builtin_amdgcn_s_barrier();
     // Rotation: wave w takes heads 2 w and 2 w + 1, lane i the dimensions i and i + 64 (frequency i, as in
-    // rope_pair), of the key as well.  The queries become high and low halves of q 2^-ex, ex from the head's largest
-    // element (score = accumulator * unscale).
+    // rope_pair), of the key as well.  The queries become three halves of q 2^-ex, ex from the head's largest
+    // element (score = accumulators * unscale).
     const uint32_t qa = shared + 8 * wave * 64 + 2 * (lane & 7), sw = lane >> 3;     // element i of row 2 w: chunk i / 8
     uint32_t qe[2][2], ke[2], vraw;
     double rfreq;
@@ -412,8 +413,8 @@ __global__ __launch_bounds__(64 * GQ_WAVES, 1) void attention_grouped_kernel(con
             dot[n] += __shfl_xor(dot[n], d);
         }
     // the raw query rows have been read by their wave: rows 2 w, 2 w + 1 of the high halves take their place,
-    // the low halves follow at QLO, then (unscale, score) per head
-    constexpr uint32_t QLO = 5 * 1024, HEAD = 9 * 1024;
+    // the low and third halves follow at QLO and QREST, then (unscale, score) per head
+    constexpr uint32_t QLO = 5 * 1024, QREST = 9 * 1024, HEAD = 13 * 1024;
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
         int ex = 0;
@@ -422,13 +423,17 @@ __global__ __launch_bounds__(64 * GQ_WAVES, 1) void attention_grouped_kernel(con
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const float a = ldexpf(h ? qhi_f[n] : qlo_f[n], -ex);
-            half_t top = (half_t)a;
+            half_t top = (half_t)a, low = (half_t)(a - (float)top);
+            const half_t rest = (half_t)((a - (float)top - (float)low) * 0x1p20f);
             // an element too small for the high half keeps its sign there, for keys that hold an infinity
-            if (a != 0.f && top == (half_t)0.f) top = (half_t)__builtin_copysignf(0x1p-24f, a);
-            const half_t rest = (half_t)(a - (float)top);
+            if (a != 0.f && top == (half_t)0.f) {
+                top = (half_t)__builtin_copysignf(0x1p-24f, a);
+                low = -top;
+            }
             const uint32_t at = qa + 256 * n + (((sw + 8 * h) ^ row) * 16);
             asm volatile("ds_write_b16 %0, %1" ::"v"(at), "v"((uint32_t)__builtin_bit_cast(uint16_t, top)) : "memory");
-            asm volatile("ds_write_b16 %0, %1" ::"v"(at + QLO), "v"((uint32_t)__builtin_bit_cast(uint16_t, rest)) : "memory");
+            asm volatile("ds_write_b16 %0, %1" ::"v"(at + QLO), "v"((uint32_t)__builtin_bit_cast(uint16_t, low)) : "memory");
+            asm volatile("ds_write_b16 %0, %1" ::"v"(at + QREST), "v"((uint32_t)__builtin_bit_cast(uint16_t, rest)) : "memory");
         }
         if (lane == 0) {
             const float unscale = ldexpf(0.08838834764831845f, ex), score = dot[n] * 0.08838834764831845f;   // 1 / sqrt(128)
@@ -438,18 +443,19 @@ __global__ __launch_bounds__(64 * GQ_WAVES, 1) void attention_grouped_kernel(con
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
-    half8_t qhi[4], qlo[4];
+    half8_t qhi[4], qlo[4], qrest[4];
     u32x2 head;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const uint32_t at = shared + r * 256 + (((4 * j + c) ^ r) * 16);
         asm volatile("ds_read_b128 %0, %1" : "=v"(qhi[j]) : "v"(at));
         asm volatile("ds_read_b128 %0, %1" : "=v"(qlo[j]) : "v"(at + QLO));
+        asm volatile("ds_read_b128 %0, %1" : "=v"(qrest[j]) : "v"(at + QREST));
     }
     asm volatile("ds_read_b64 %0, %1" : "=v"(head) : "v"(shared + HEAD + 8 * r));
     asm volatile("s_waitcnt lgkmcnt(0)"
                  : "+v"(qhi[0]), "+v"(qhi[1]), "+v"(qhi[2]), "+v"(qhi[3]), "+v"(qlo[0]), "+v"(qlo[1]), "+v"(qlo[2]),
-                   "+v"(qlo[3]), "+v"(head));
+                   "+v"(qlo[3]), "+v"(qrest[0]), "+v"(qrest[1]), "+v"(qrest[2]), "+v"(qrest[3]), "+v"(head));
     // (values, not elements: a bit_cast of a vector element reads element 0)
     const uint32_t head_unscale = head[0], head_score = head[1];
     const float unscale = __builtin_bit_cast(float, head_unscale), now = __builtin_bit_cast(float, head_score);
@@ -501,10 +507,11 @@ __global__ __launch_bounds__(64 * GQ_WAVES, 1) void attention_grouped_kernel(con
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             if (first + i >= p1) vv[i].d = decltype(vv[i].d){};
-        floatx4 hi = {0.f, 0.f, 0.f, 0.f}, lo = {0.f, 0.f, 0.f, 0.f};
+        floatx4 hi = {0.f, 0.f, 0.f, 0.f}, lo = {0.f, 0.f, 0.f, 0.f}, rest = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const half8_t kv = __builtin_bit_cast(half8_t, kf[j]);
+            rest = __builtin_amdgcn_mfma_f32_16x16x32_f16(kv, qrest[j], rest, 0, 0, 0);
             lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(kv, qlo[j], lo, 0, 0, 0);
             hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(kv, qhi[j], hi, 0, 0, 0);
         }
@@ -513,8 +520,8 @@ __global__ __launch_bounds__(64 * GQ_WAVES, 1) void attention_grouped_kernel(con
         for (int i = 0; i < 4; ++i) {
             // a key with an infinity: the high halves alone have the sign; Inf times a low half of 0 or of the other
             // sign would make it NaN
-            const float both = __builtin_fabsf(hi[i]) < __builtin_inff() ? hi[i] + lo[i] : hi[i];
-            s[i] = first + i < p1 ? both * unscale : -__builtin_inff();
+            const float all = __builtin_fabsf(hi[i]) < __builtin_inff() ? hi[i] + (lo[i] + rest[i] * 0x1p-20f) : hi[i];
+            s[i] = first + i < p1 ? all * unscale : -__builtin_inff();
             top = fmaxf(top, s[i]);
         }
         top = fmaxf(top, __shfl_xor(top, 16));

@@ -101,3 +101,27 @@ def test_infinities_in_the_caches_have_the_weight_of_their_score(H, Hkv, pos, wh
     assert fine.all() == (where in ("keys", "key of the token"))
     assert np.array_equal(got[~fine], want[~fine], equal_nan=True)
     assert np.abs(got[fine] - want[fine]).max(initial=0) <= TOL * np.abs(vals[np.isfinite(vals)]).max()
+
+
+@pytest.mark.parametrize("H,Hkv,pos", [(32, 4, 20), (96, 24, 20), (384, 64, 40), (768, 256, 20)])
+def test_small_elements_beside_a_large_one_keep_their_bits(H, Hkv, pos):
+    """A head whose largest elements meet zeros in every key: the scores are those of the small ones, 2^-30 of the
+    largest and multiplied by keys of 2^15, and need their fp32 bits."""
+    import oracle
+    import torch
+    import paper_2306_00978_amd as awq
+    g = np.random.default_rng(H)
+    q = (g.standard_normal((H, 128)) * 6e-5).astype(np.float16)
+    q[:, 63], q[:, 127] = 60000, -20000
+    k, *rows = (np.where(g.random((Hkv, 128)) < 0.5, -32768, 32768).astype(np.float16) for _ in range(pos + 1))
+    kc, vc = np.zeros((2, Hkv, pos + 5, 128), np.float16)
+    kc[:, :pos] = np.stack(rows, 1)
+    kc[:, :, [63, 127]] = k[:, [63, 127]] = 0
+    vc[:, :pos] = g.standard_normal((Hkv, pos, 128))
+    v = g.standard_normal((Hkv, 128)).astype(np.float16)
+    ref, _, _ = oracle.decode_attention(q, k, v, kc, vc, pos)
+    out = awq.awq_decode_attention(*(torch.from_numpy(t).cuda() for t in (q, k, v, kc, vc)), pos)
+    # the rounding of the output and of the reference, half a unit of 2^-10 each, and fp32 sums of 128 products of about 0.2
+    # (scores off by 1e-5); with two halves to a query the scores were off by 2e-2 and the outputs by 6e-3
+    scale = np.abs(vc.astype(np.float64)).max()
+    assert np.abs(out.cpu().numpy().astype(np.float64) - ref.astype(np.float64)).max() <= 1.1e-3 * scale
