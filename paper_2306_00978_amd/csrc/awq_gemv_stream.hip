@@ -1366,16 +1366,18 @@ bool plan_paired(const GemvProblem *problems, int count, const int *ksl_of, int 
     return true;
 }
 
-// Whether a launch reads its packed words with non-temporal loads.  A model's weights pass through once per
-// token, and together they are larger than the 256 MB memory-side cache from a launch of this size on (a layer of
-// the 7B shapes is 105 MB): eight layers of the 7B shapes at one token 22.1 -> 20.8 us a layer, in 3 bits 18.9 -> 17.9, a
-// layer of the 70B shapes at eight tokens 86.4 -> 82.5.  Below, a launch is short, and the weights of a small model may well be found in a
-// cache, where the plain loads are the faster ones (all of a 40 MB model repeated: 2 to 4 %).
+// Whether a launch reads its packed words with non-temporal loads.  They are the faster ones for weights that come
+// from memory and the slower ones for weights that the 256 MB memory-side cache holds, whatever the size of the
+// launch (layers of one size used in turn, us a layer, non-temporal / plain, four bits at one token:
+// 24 MB x 8 layers 8.4 / 7.9, x 16 8.7 / 9.0; 38 MB x 4 11.0 / 10.4, x 8 11.2 / 11.5; 96 MB x 2 20.4 / 20.1, x 8 21.2 / 22.5).  A
+// launch does not know what else the program reads between two uses of its weights.  From an eighth of the cache on it
+// takes them to be gone by then: eight launches of that size, a small part of a model's layers, are more than it holds.
+// (7B layers, eight in turn, one token 22.1 -> 20.8 us, in 3 bits 18.9 -> 17.9; 70B layers at eight tokens 86.4 -> 82.5.)
 bool streams_weights(const GemvProblem *problems, int count, int bits)
 {
     int64_t bytes = 0;
     for (int i = 0; i < count; ++i) bytes += (int64_t)problems[i].N * problems[i].K / 8 * bits;
-    return bytes >= (int64_t)16 << 20;
+    return bytes >= (int64_t)32 << 20;
 }
 
 template <int BITS, bool FUSED>
