@@ -250,16 +250,40 @@ def awq_packed_sizes(N: int, K: int, group: int = GROUP):
     return q.value, s.value, z.value
 
 
-def awq_act_scale(X: torch.Tensor, alpha: float = 0.5, out: torch.Tensor | None = None):
-    """s[k] = max(mean_t |X[t,k]|, 1e-4)^alpha; X [T,K] fp16 -> s [K] fp32."""
+def awq_act_scale_workspace_bytes(T: int, K: int) -> int:
+    return int(load().awq_act_scale_workspace_bytes(T, K))
+
+
+# Rows from which awq_act_scale brings a workspace by itself.  The library's rule says where the device gains; on the
+# host the second launch and the allocation take 2.6 us, which fewer rows do not earn (us a call, without and with: 4096 x
+# 1024 7.4 and 9.9, 5000 x 1024 8.9 and 9.9, 4096 x 2240 9.1 and 9.9; 6000 x 2240 13.5 and 13.4, 6000 x 1024 16.5 and 10.8).
+ACT_SCALE_WORKSPACE_ROWS = 6000
+
+
+def awq_act_scale(X: torch.Tensor, alpha: float = 0.5, out: torch.Tensor | None = None,
+                  workspace: torch.Tensor | None = None):
+    """s[k] = max(mean_t |X[t,k]|, 1e-4)^alpha; X [T,K] fp16 -> s [K] fp32.  `workspace`: a uint8 tensor of
+    awq_act_scale_workspace_bytes() bytes (70 KB at most), None (allocated here where it pays and there is room) or
+    False (run without it: bit for bit the same result, and with `out` nothing is allocated)."""
     _dev(X, torch.float16, "X")
     T, K = X.shape
     s = out if out is not None else torch.empty(K, dtype=torch.float32, device=X.device)
     _dev(s, torch.float32, "s")
     lib = load()
     need = lib.awq_act_scale_workspace_bytes(T, K)        # partial sums of the row classes, where they pay
-    ws = torch.empty(need, dtype=torch.uint8, device=X.device) if need else None
-    _check(lib.awq_act_scale_ws(_ptr(X), T, K, float(alpha), _ptr(s), _ptr(ws), need, _stream()), "awq_act_scale")
+    ws_bytes = 0
+    if workspace is False or not need:
+        workspace = None
+    else:
+        if workspace is None and T >= ACT_SCALE_WORKSPACE_ROWS:
+            try:
+                workspace = torch.empty(need, dtype=torch.uint8, device=X.device)
+            except torch.OutOfMemoryError:                # the call needs none
+                pass
+        if workspace is not None:
+            ws_bytes = workspace.numel() * workspace.element_size()
+    _check(lib.awq_act_scale_ws(_ptr(X), T, K, float(alpha), _ptr(s), _ptr(workspace), ws_bytes, _stream()),
+           "awq_act_scale")
     return s
 
 

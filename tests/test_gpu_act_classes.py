@@ -31,3 +31,34 @@ def test_row_classes_equal_the_undivided_sums_bit_for_bit(T, K):
     assert bool((ws[need:] == 0xAB).all())
     assert lib.awq_act_scale_ws(X.data_ptr(), T, K, 0.5, out.data_ptr(), ws.data_ptr(), need - 4, st) == -5
     assert lib.awq_act_scale_ws(X.data_ptr(), T, K, 0.5, out.data_ptr(), ctypes.c_void_p(ws.data_ptr() + 4), need, st) == -4
+
+
+@pytest.mark.parametrize("T,K,own", [(4249, 2240, False), (8200, 1024, True)])
+def test_python_call_allocates_a_workspace_where_it_pays_and_only_if_it_may(T, K, own, monkeypatch):
+    import torch
+    import paper_2306_00978_amd as awq
+    need = awq.awq_act_scale_workspace_bytes(T, K)
+    assert need > 0
+    X = (torch.randn((T, K), device="cuda") * 3).half()
+    want = torch.empty(K, device="cuda")
+    assert awq.load().awq_act_scale(X.data_ptr(), T, K, 0.5, want.data_ptr(), awq._stream()) == 0
+    out, ws = torch.empty(K, device="cuda"), torch.zeros(need, dtype=torch.uint8, device="cuda")
+
+    def allocations(**kw):
+        out.fill_(-1.0)
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        awq.awq_act_scale(X, 0.5, out=out, **kw)
+        after = torch.cuda.memory_stats()["allocation.all.allocated"]
+        assert torch.equal(out, want)
+        return after - before
+
+    assert allocations(workspace=False) == 0
+    assert allocations() == int(own)
+    assert allocations(workspace=ws) == 0 and bool(ws.any())             # the caller's one was used
+    with pytest.raises(awq.AwqError):
+        awq.awq_act_scale(X, 0.5, out=out, workspace=ws[:need - 16])
+
+    def full(*a, **kw):
+        raise torch.OutOfMemoryError("no room")
+    monkeypatch.setattr(torch, "empty", full)
+    assert allocations() == 0
