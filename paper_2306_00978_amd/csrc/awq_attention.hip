@@ -656,6 +656,18 @@ int attention_splits(int64_t H, int64_t L)
     return (int)s;
 }
 
+// Which kernel takes G = H / Hkv > 2 query heads to a kv head.  The grouped one starts slower (1.3 to 2 us: twice the
+// threads, its inputs through LDS, two barriers) and then reads every cache row for up to 16 heads at once; the
+// other one's time grows with the rows that all heads read.  The line is where the two met over 17 pairs of
+// H and Hkv, 3 <= G <= 48, at 0 to 16000 positions (graph replays): H * L of 17 to 20 thousand for G of 5 to 9, 30 to 42 for 4
+// and for 16 and more, 67 to 110 for 3, whose tiles are mostly empty.  us, vector and grouped: 64 / 8 heads at 100 positions 7.2 / 8.4, 300
+// 9.1 / 8.7, 1000 11.7 / 9.3; 128 / 32 at 300 10.0 / 10.1, 500 11.8 / 10.4; 24 / 8 at 1500 10.9 / 12.8, 6000 18.5 / 16.9.
+bool attention_grouped(int64_t H, int64_t Hkv, int64_t L)
+{
+    const int64_t G = H / Hkv;
+    return H * L >= (G < 4 ? 110000 : G > 4 && G < 10 ? 20000 : 42000);
+}
+
 }  // namespace
 
 extern "C" size_t awq_decode_attention_workspace_bytes(int64_t H, int64_t D, int64_t L)
@@ -691,14 +703,18 @@ extern "C" int awq_decode_attention(const void *q_f16, const void *k_f16, const 
     half_t *kc = (half_t *)k_cache_f16, *vc = (half_t *)v_cache_f16;
     float *partial = (float *)workspace;
     int st;
-    if (H / Hkv > 2) {
+    // (the tuning build can force the kernel: 0, or the number of workgroups to a slice)
+    const int forced = awq_knob("AWQ_ATTENTION_F", -1);
+    if (H / Hkv > 2 && (forced < 0 ? attention_grouped(H, Hkv, L) : forced > 0)) {
         GroupedArgs A = {qp, kp, vp, kc, vc, partial, (int)H, (int)Hkv, (int)((H / Hkv + 15) / 16), (int)Lmax, (int)pos,
                          chunk, splits, 0, tab};
-        // one workgroup per CU (the LDS): the values are divided until there are 256
+        // One workgroup per CU (the LDS): the values are divided as long as all workgroups run at once.  24 / 8 heads, 1500
+        // positions, 176 items: 12.8 us undivided, 16.5 in two, 19.9 in four; 128 / 32, 700, 128 items: 12.8, 11.6, 15.9
         const int64_t items = Hkv * A.qgroups * splits;
-        st = items >= 256 ? attention_grouped_launch<1>(A, (hipStream_t)stream)
-             : items >= 128 ? attention_grouped_launch<2>(A, (hipStream_t)stream)
-                            : attention_grouped_launch<4>(A, (hipStream_t)stream);
+        const int F = forced > 0 ? forced : items <= 64 ? 4 : items <= 128 ? 2 : 1;
+        st = F == 1 ? attention_grouped_launch<1>(A, (hipStream_t)stream)
+             : F == 2 ? attention_grouped_launch<2>(A, (hipStream_t)stream)
+                      : attention_grouped_launch<4>(A, (hipStream_t)stream);
     } else {
         attention_partial_kernel<<<dim3((unsigned)H, (unsigned)splits), dim3(256), 0, (hipStream_t)stream>>>(
             qp, kp, vp, kc, vc, (int)H, (int)Hkv, (int)Lmax, (int)pos, tab, chunk, partial);

@@ -1,15 +1,19 @@
 """Decode attention with several query heads to a key/value head (the kernel that runs both products on
 the matrix cores) against the oracle: positions around its blocks of 16, waves and slices without
 positions, 3 to 20 query heads to a kv head (partly filled and several head tiles), each of its three splits of the
-value dimensions."""
+value dimensions.  The library as it is takes few positions to the other kernel and picks the split; the tuning build runs
+this one, with each split, at every size."""
 import numpy as np
 import pytest
+
+from tuning_build import tuning_build
 
 pytestmark = pytest.mark.gpu
 
 TOL = 2e-3          # of max|v|: fp16 rounding of the output (2^-11) and fp32 sums / exponentials
 
 
+@pytest.mark.parametrize("F", [None, 4, 2, 1])
 @pytest.mark.parametrize("H,Hkv,positions", [
     (12, 4, (0, 1, 31, 32, 33, 63, 130)),
     (64, 8, (0, 15, 127, 128, 300, 4000)),
@@ -18,7 +22,7 @@ TOL = 2e-3          # of max|v|: fp16 rounding of the output (2^-11) and fp32 su
     (256, 32, (40, 1030)),
     (96, 32, (2, 513)),
 ])
-def test_grouped_attention_against_the_oracle(H, Hkv, positions):
+def test_grouped_attention_against_the_oracle(H, Hkv, positions, F):
     import oracle
     import torch
     import paper_2306_00978_amd as awq
@@ -34,7 +38,8 @@ def test_grouped_attention_against_the_oracle(H, Hkv, positions):
         ref, kc_ref, vc_ref = oracle.decode_attention(q, k, v, kc, vc, pos)
         kg, vg = torch.from_numpy(kc).cuda(), torch.from_numpy(vc).cuda()
         out = torch.full((H, 128), float("nan"), dtype=torch.float16, device="cuda")
-        awq.awq_decode_attention(*(torch.from_numpy(t).cuda() for t in (q, k, v)), kg, vg, pos, out=out)
+        with tuning_build(AWQ_ATTENTION_F=F):
+            awq.awq_decode_attention(*(torch.from_numpy(t).cuda() for t in (q, k, v)), kg, vg, pos, out=out)
         got = out.cpu().numpy().astype(np.float64)
         assert np.all(np.isfinite(got)), pos
         scale = np.abs(vc_ref[:, :pos + 1].astype(np.float64)).max()
@@ -46,8 +51,8 @@ def test_grouped_attention_against_the_oracle(H, Hkv, positions):
         assert np.all(np.abs(a - b) <= np.abs(b) * 2.0 ** -10 + 1e-7)
 
 
-# F = 4, 2 and 1 workgroups to a slice of the positions (64, 144 and 256 items)
-SPLITS = [(64, 8, 1000), (96, 24, 330), (384, 128, 700)]
+# the library's choice is F = 4, 2 and 1 workgroups to a slice of the positions (64, 128 and 256 items)
+SPLITS = [(64, 8, 1000), (128, 32, 700), (384, 128, 700)]
 
 
 @pytest.mark.parametrize("H,Hkv,pos", SPLITS)
@@ -103,8 +108,9 @@ def test_infinities_in_the_caches_have_the_weight_of_their_score(H, Hkv, pos, wh
     assert np.abs(got[fine] - want[fine]).max(initial=0) <= TOL * np.abs(vals[np.isfinite(vals)]).max()
 
 
-@pytest.mark.parametrize("H,Hkv,pos", [(32, 4, 20), (96, 24, 20), (384, 64, 40), (768, 256, 20)])
-def test_small_elements_beside_a_large_one_keep_their_bits(H, Hkv, pos):
+@pytest.mark.parametrize("F", [None, 4, 2, 1])
+@pytest.mark.parametrize("H,Hkv,pos", [(32, 4, 20), (96, 24, 20), (384, 64, 40)])
+def test_small_elements_beside_a_large_one_keep_their_bits(H, Hkv, pos, F):
     """A head whose largest elements meet zeros in every key: the scores are those of the small ones, 2^-30 of the
     largest and multiplied by keys of 2^15, and need their fp32 bits."""
     import oracle
@@ -120,7 +126,8 @@ def test_small_elements_beside_a_large_one_keep_their_bits(H, Hkv, pos):
     vc[:, :pos] = g.standard_normal((Hkv, pos, 128))
     v = g.standard_normal((Hkv, 128)).astype(np.float16)
     ref, _, _ = oracle.decode_attention(q, k, v, kc, vc, pos)
-    out = awq.awq_decode_attention(*(torch.from_numpy(t).cuda() for t in (q, k, v, kc, vc)), pos)
+    with tuning_build(AWQ_ATTENTION_F=F):
+        out = awq.awq_decode_attention(*(torch.from_numpy(t).cuda() for t in (q, k, v, kc, vc)), pos)
     # the rounding of the output and of the reference, half a unit of 2^-10 each, and fp32 sums of 128 products of about 0.2
     # (scores off by 1e-5); with two halves to a query the scores were off by 2e-2 and the outputs by 6e-3
     scale = np.abs(vc.astype(np.float64)).max()
