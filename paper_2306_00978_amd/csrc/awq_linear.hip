@@ -44,18 +44,26 @@ namespace {
 // The prefill kernel's tiles are 128 x 256: at a few hundred tokens there are few of them, each
 // walking a long K, and cutting K over workgroups costs a second pass over fp32 partial tiles.  The tile
 // kernel cuts K over the waves of a workgroup and pays with more reads of x (a tile is at most 128 x 48
-// or 96 x 64), so it wins until the prefill kernel fills the chip.  Up to 128 tokens always
-// (11008 x 4096 at 77 tokens: 13.8 us against 23.1, 4096 x 11008 at 17: 11.5 against 20.9, 4096 x 4096
-// at 128: 10.9 against 18.5); beyond, by the two estimates, the tile kernel's with 20 % on top (its
-// large launches run at a lower clock than the small ones it was fitted to): 4096 x 4096 at 300 / 500
-// tokens 19.2 / 28.5 us against 26.3 / 31.1; 4096 x 11008 at 300: 41 against 45, at 500: 62 against 55 and
-// left to the prefill kernel.
+// or 96 x 64), so it wins until the prefill kernel fills the chip.
+//
+// Without a workspace: up to 128 tokens always (blocks of 16 through the decode kernels, which ran before, took
+// 1.25 to 7.5 times as long over 25 shapes; the prefill kernel 43 us where 4096 x 4096 at 128 tokens takes 10.7), beyond by the two estimates, the tile
+// kernel's with its margin: 4096 x 4096 at 300 / 512 / 700 tokens 17.4 / 28.1 / 36.8 us against 43 / 45 / 48;
+// 8192 x 28672 at 300 / 512 tokens 199 / 354 against 287 / 297.
+// With a workspace K is cut into ranges and the estimate is that form's, which is itself 0.92 to 1.36 of what it
+// really takes.  Up to 128 tokens the estimates stand side by side (us, tile kernel and ranges: 11008 x 4096 at 128 17.3 /
+// 25.6; 32000 x 4096 at 96 / 128 36.8 / 44.1 and 53.5 / 46.0; 28672 x 8192 at 96 / 128 58.8 / 66.2 and 90.4 / 69.1); beyond, the tile kernel
+// has to win by a fifth.  That is cautious: 4096 x 4096 at 400 / 512 tokens runs over ranges, 30.1 / 34.3, where the
+// call without a workspace takes 25.6 / 28.1.
 bool takes_tile_kernel(const TilePlan &plan, int M, int N, int K, bool split)
 {
-    double gemm_us = 0.0;
-    if (split) (void)awq_gemm_ksplit(M, N, K, &gemm_us);
-    else gemm_us = awq_gemm_unsplit_us(M, N, K);
-    return M <= 128 || 1.2 * plan.us < gemm_us;
+    if (awq_tile_override() >= 0) return awq_tile_forced();
+    if (split) {
+        double ranges_us = 0.0;
+        (void)awq_gemm_ksplit(M, N, K, &ranges_us);
+        return (M <= 128 ? 1.0 : 1.2) * plan.us < ranges_us;
+    }
+    return M <= 128 || awq_tile_margin(K) * plan.us < awq_gemm_unsplit_us(M, N, K);
 }
 
 }  // namespace

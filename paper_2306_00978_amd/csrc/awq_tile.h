@@ -1,9 +1,7 @@
 // Host interface of the K-split tile kernel (awq_tile.hip): one linear, 4-, 3- or 2-bit weights.
 #pragma once
 
-#include <hip/hip_runtime.h>
-
-#include <cstdint>
+#include "awq_common.h"
 
 struct TilePlan {
     int mt, nt;          // 16-row token tiles and 16-row weight tiles per workgroup
@@ -12,6 +10,16 @@ struct TilePlan {
 
 // The workgroup shape with the smallest estimated time.
 TilePlan awq_tile_plan(int M, int N, int K);
+
+// What a launch of more than 128 tokens takes at most, in units of its estimate: it runs at a lower clock than the small
+// ones that the estimate was fitted to (1.04 to 1.19 over 129 to 700 tokens at K up to 13824), and its waves wait for
+// more than they compute where K is very long (K = 28672: 1.24 to 1.45 with 8192 features, up to 1.6 with 512).
+inline double awq_tile_margin(int K) { return K <= 8192 ? 1.2 : 1.2 + 0.35 * (K - 8192) / 20480.0; }
+
+// The tuning build can force the shape (AWQ_TILE_PLAN = 10 * mt + nt, at every token count above 16) or, with 0, the
+// kernels that run where this one does not.
+inline int awq_tile_override() { return awq_knob("AWQ_TILE_PLAN", -1); }
+inline bool awq_tile_forced() { return awq_tile_override() > 0; }
 int64_t awq_tile_count(const TilePlan &plan, int M, int N);          // workgroups
 
 // bits is 4, 3 (group 128) or 2 (group 64); M >= 16; other arguments were validated by the caller.

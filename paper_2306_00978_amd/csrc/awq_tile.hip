@@ -429,6 +429,8 @@ TileFn pick(int mt, int nt)
 // (4096 x 4096, 11008 x 4096, 4096 x 11008 at 17..500 tokens, both bit widths, all MT and NT; rms error 6 %).
 TilePlan awq_tile_plan(int M, int N, int K)
 {
+    const int forced = awq_tile_override();
+    if (forced > 0) return {forced / 10, forced % 10, 0.0};
     TilePlan best = {1, 1, -1.0};
     const int runs = (K / RUN + TILE_WAVES - 1) / TILE_WAVES;
     for (const int mt : MTS)

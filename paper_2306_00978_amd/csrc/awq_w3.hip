@@ -227,7 +227,8 @@ extern "C" int awq_w3a16_linear_prefill(const void *x_f16, const void *qweight, 
         return AWQ_ERR_MISALIGNED;
     if (workspace_bytes < (size_t)(N * K / 2)) return AWQ_ERR_WORKSPACE_TOO_SMALL;
     // The tile kernel takes the 3-bit words as they are and touches no workspace; the prefill kernel needs
-    // them re-packed first: 2.5 us and N K (3 + 4) / 8 bytes at 4 TB/s, added to its estimate.  Up to 128
+    // them re-packed first: 2.5 us and N K (3 + 4) / 8 bytes at 8 TB/s (it is read back from a cache; 4096 x 11008 4 to
+    // 6 us, 28672 x 8192 6 to 28), added to its estimate.  Up to 128
     // tokens always the tile kernel (before: blocks of 16 tokens through the decode kernels, the
     // weights read again by each: 92 tokens, 5328 x 9216, 87.3 us, now 19.8); beyond, by the two estimates,
     // as in awq_w4a16_linear (281 tokens, 1152 x 1792: 20.9 us re-packed, 8.8 here; 586, 3104 x 3584:
@@ -239,8 +240,9 @@ extern "C" int awq_w3a16_linear_prefill(const void *x_f16, const void *qweight, 
     double gemm_us = 0.0;
     if (split) (void)awq_gemm_ksplit((int)M, (int)N, (int)K, &gemm_us);
     else gemm_us = awq_gemm_unsplit_us((int)M, (int)N, (int)K);
-    gemm_us += 2.5 + (double)N * (double)K * 0.875 / 4.0e6;
-    if (M <= 128 || 1.2 * plan.us < gemm_us)
+    gemm_us += 2.5 + (double)N * (double)K * 0.875 / 8.0e6;
+    const int forced = awq_tile_override();
+    if (forced < 0 ? M <= 128 || (split ? 1.2 : awq_tile_margin((int)K)) * plan.us < gemm_us : forced > 0)
         return awq_tile_launch(3, plan, x_f16, qweight, scales, zeros, y_f16, (int)M, (int)N, (int)K,
                                (hipStream_t)stream);
     st = awq_repack_w3_to_w4(qweight, N, K, group, workspace, stream);

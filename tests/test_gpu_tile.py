@@ -1,9 +1,12 @@
 """The K-split tile kernel (more than 16 tokens; 4- and 3-bit group 128, 2-bit group 64) against the oracle at the
 sizes where it can go wrong: token tiles with a remainder (the last one moved back over its
 neighbour), several token tiles and ragged weight tiles per workgroup, fewer runs of K than waves, waves with one
-run more than others, and every pair of tile counts the planner picks on the way."""
+run more than others; then every pair of tile counts that is built, through the tuning build, which can force it; the
+prefill kernel at the ragged shapes that this one has taken over; and where the line between the kernels lies."""
 import numpy as np
 import pytest
+
+from tuning_build import tuning_build
 
 pytestmark = pytest.mark.gpu
 
@@ -60,3 +63,129 @@ def test_tile_kernel_keeps_infinities_and_nan_in_their_rows():
     others = [m for m in range(M) if m not in (20, 30)]
     assert np.array_equal(y[others].view(np.uint16), clean[others].view(np.uint16))
     assert not np.any(np.isfinite(y[20].astype(np.float32))) and np.all(np.isnan(y[30]))
+
+
+PLANS = [(mt, nt) for mt in (1, 2, 3, 4, 5, 6, 8) for nt in (1, 2, 3, 4) if (mt, nt) != (8, 4)]
+
+
+@pytest.mark.parametrize("bits", [4, 3, 2])
+@pytest.mark.parametrize("N,K", [(208, 2304), (16, 256), (48, 768)])
+def test_every_built_shape_of_a_workgroup(bits, N, K):
+    """Feature tiles that the count does not divide, waves with one run of K more than others and without any; a token
+    tile that is full, one that is moved back, and more than one workgroup of them."""
+    import oracle
+    import torch
+    import paper_2306_00978_amd as awq
+    linear = {4: awq.awq_w4a16_linear, 3: awq.awq_w3a16_linear, 2: awq.awq_w2a16_linear}[bits]
+    x, Wdq, packed = case(bits, N, K, 16 * 8 * 2 + 5, N + K + bits)
+    ref = oracle.matmul(x, Wdq)
+    for mt, nt in PLANS:
+        for M in sorted({17, 16 * max(mt, 2), 16 * max(mt, 2) - 3, 32 * mt + 5}):
+            buf = torch.full((M * N + 16,), float("nan"), dtype=torch.float16, device="cuda")
+            y, xg = buf[:M * N].view(M, N), torch.from_numpy(x[:M]).cuda()
+            with tuning_build(AWQ_TILE_PLAN=10 * mt + nt):
+                linear(xg, *packed, N, out=y)
+            got = y.cpu().numpy().copy()
+            assert bool(torch.isnan(buf[M * N:]).all())                 # nothing written past the end
+            assert np.all(np.isfinite(got.astype(np.float32))), (mt, nt, M, "unwritten output")
+            err = oracle.norm_error(got, ref[:M], x[:M], Wdq)
+            assert err.max() <= TOL, (mt, nt, M, err.max())
+            with tuning_build(AWQ_TILE_PLAN=10 * mt + nt):
+                linear(xg, *packed, N, out=y)
+            assert np.array_equal(got.view(np.uint16), y.cpu().numpy().view(np.uint16)), (mt, nt, M)
+
+
+@pytest.mark.parametrize("plan", [0] + [10 * mt + nt for mt, nt in PLANS])
+def test_loss_form_of_every_built_shape_and_of_the_prefill_kernel(plan):
+    """The scale search against the same arithmetic in plain torch (fp64 products of the fp16 operands); 0: the prefill
+    kernel's loss form, at a ragged shape that it does not get otherwise."""
+    import torch
+    import paper_2306_00978_amd as awq
+    T, N, K, alphas = 165, 272, 1280, [0.0, 0.4, 0.7]
+    g = torch.Generator(device="cuda").manual_seed(9)
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).half()
+    gain = torch.ones(K, device="cuda")
+    gain[torch.randperm(K, generator=g, device="cuda")[:K // 100]] = 20.0
+    X = (torch.randn((T, K), generator=g, device="cuda") * gain).half()
+    with tuning_build(AWQ_TILE_PLAN=plan):
+        best, losses, _ = awq.awq_search_scale(W, X, alphas)
+    y = X.double() @ W.double().T
+    for a, got in zip(alphas, losses.cpu().numpy()):
+        s = awq.awq_act_scale(X, a)
+        codes, scales, zeros = awq.awq_unpack(*awq.awq_quantize_pack(W, s), N, K)
+        q = (codes.double().view(N, K // 128, 128) - zeros.double()[..., None]) * scales.double()[..., None]
+        ref = float((awq.awq_apply_inv_scale(X, s).double() @ q.view(N, K).T - y).square().sum())
+        # fp16 rounding of both outputs and of the dequantized weights: 1e-4 of the loss, and a cross term of
+        # 2e-2 / sqrt(outputs) standard deviation
+        assert abs(got / ref - 1) <= 2e-4 + 0.06 / np.sqrt(T * N), (a, got, ref)
+    assert int(best) == int(losses.argmin())
+
+
+@pytest.mark.parametrize("N,K,M", [(176, 1408, 17), (176, 1408, 300), (272, 256, 129), (1040, 512, 100), (2064, 1152, 257)])
+def test_prefill_kernel_at_shapes_the_tile_kernel_took_over(N, K, M):
+    """Token and feature tiles with a remainder, plain and with K in ranges (where the workspace call cuts it), 4 bits, and
+    3 bits through the re-packed codes, whose workspace is then seen to be used."""
+    import oracle
+    import torch
+    import paper_2306_00978_amd as awq
+    for bits in (4, 3):
+        x, Wdq, packed = case(bits, N, K, M, N + K + M)
+        ref, xg = oracle.matmul(x, Wdq), torch.from_numpy(x).cuda()
+        need = awq.awq_linear_workspace_bytes(M, N, K)
+        codes = (N * K // 2 + 255) // 256 * 256 if bits == 3 else 0
+        for ranges in (False, True) if need else (False,):
+            size = codes + (need if ranges else 0)
+            ws = torch.full((max(size, 16),), 0xA5, dtype=torch.uint8, device="cuda")
+            buf = torch.full((M * N + 16,), float("nan"), dtype=torch.float16, device="cuda")
+            y = buf[:M * N].view(M, N)
+            with tuning_build(AWQ_TILE_PLAN=0):
+                if bits == 4:
+                    awq.awq_w4a16_linear(xg, *packed, N, out=y, workspace=ws if ranges else False)
+                else:
+                    st = awq.load().awq_w3a16_linear_prefill(
+                        xg.data_ptr(), *(t.data_ptr() for t in packed), y.data_ptr(), M, N, K, 128, ws.data_ptr(),
+                        size if ranges else N * K // 2, awq._stream())
+                    assert st == 0
+            got = y.cpu().numpy()
+            assert bool(torch.isnan(buf[M * N:]).all()) and np.all(np.isfinite(got.astype(np.float32)))
+            if bits == 3 or ranges:
+                assert not bool((ws[:16] == 0xA5).all())
+            if ranges:
+                assert not bool((ws[size - 16:] == 0xA5).all())
+            err = oracle.norm_error(got, ref, x, Wdq)
+            assert err.max() <= TOL, (bits, ranges, err.max())
+
+
+@pytest.mark.parametrize("bits,N,K,M,used", [
+    (4, 11008, 4096, 128, False),                    # few tokens: the tile kernel, whatever the workspace
+    (4, 28672, 8192, 128, True),                     # two rounds of its workgroups: K over ranges (69 us against 90)
+    (4, 4096, 11008, 200, True),
+    (3, 4096, 4096, 300, False),
+    (3, 4096, 4096, 2048, True),                     # the prefill kernel, on re-packed codes
+    (3, 8192, 28672, 512, True),                     # very long K (309 us against 334)
+])
+def test_line_between_the_tile_and_the_prefill_kernel(bits, N, K, M, used):
+    """What the kernel that does not run would have left in the workspace tells the two apart."""
+    import oracle
+    import torch
+    import paper_2306_00978_amd as awq
+    g = torch.Generator(device="cuda").manual_seed(N + K + M)
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).half()
+    x = torch.randn((M, K), generator=g, device="cuda").half()
+    packed = {4: awq.awq_quantize_pack, 3: awq.awq_quantize_pack_w3}[bits](W, torch.ones(K, device="cuda"))
+    size = awq.awq_linear_workspace_bytes(M, N, K) if bits == 4 else N * K // 2
+    ws = torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda")
+    if bits == 4:
+        y = awq.awq_w4a16_linear(x, *packed, N, workspace=ws)
+    else:
+        y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+        assert awq.load().awq_w3a16_linear_prefill(x.data_ptr(), *(t.data_ptr() for t in packed), y.data_ptr(), M, N, K,
+                                                   128, ws.data_ptr(), size, awq._stream()) == 0
+    assert bool((ws == 0xA5).all()) != used
+    codes, scales, zeros = (awq.awq_unpack if bits == 4 else awq.awq_unpack_w3)(*packed, N, K)
+    rows = np.linspace(0, M - 1, 3).astype(int)
+    cols = slice(0, N, max(1, N // 256))
+    Wdq = oracle.dequant(*(t[cols].cpu().numpy() for t in (codes, scales, zeros)))
+    xr = x[rows].cpu().numpy()
+    err = oracle.norm_error(np.ascontiguousarray(y[rows][:, cols].cpu().numpy()), oracle.matmul(xr, Wdq), xr, Wdq)
+    assert err.max() <= TOL, err.max()
