@@ -406,7 +406,7 @@ int awq_w3a16_linear_multi(const awq_linear_desc *descs, int count, int64_t M, i
  * codes u8[N,K], scales f16[N,K/64], zeros u8[N,K/64] (each optional).
  * awq_w2a16_linear: y = x' * dequant(q)^T with fp32 accumulation, any M >= 1: up to 16 rows
  * through the decode kernel, more through the tile kernel of awq_w4a16_linear, which reads the packed
- * weights once per 128 rows at most.  awq_w2a16_linear_multi: as awq_w4a16_linear_multi
+ * weights once per 128 rows at most, or, on small matrices, through the decode kernel in blocks of 16.  awq_w2a16_linear_multi: as awq_w4a16_linear_multi
  * (1 <= M <= 16, up to AWQ_MULTI_MAX linears, eight per launch). */
 #define AWQ_GROUP_W2 64
 int awq_packed_sizes_w2(int64_t N, int64_t K, int group, size_t *qweight_bytes,

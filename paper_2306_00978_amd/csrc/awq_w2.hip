@@ -416,6 +416,16 @@ int launch_w2(const W2Problem *probs, int count, int M, hipStream_t stream)
     }
 }
 
+// Whether 17 and more rows run as blocks of 16 through the decode kernel: small matrices at up to 96 rows, where a
+// wave of the tile kernel has one or two runs of K and its eight waves' exchange weighs most.  us, blocks and tile
+// kernel, graph replays: 1024 x 1024 at 17 / 64 / 96 rows 3.1 / 3.3 / 3.7 and 3.5 / 3.6 / 3.8; 4096 x 1024 at 32 / 48 / 64 3.6 /
+// 4.1 / 5.3 and 3.8 / 4.2 / 4.3; 2048 x 2048 at 32 / 64 3.8 / 4.7 and 4.0 / 4.5.  K of 512 and less: alike up to 33 rows, then the
+// tile kernel; 4096: alike at 17.
+bool decode_blocks(int64_t blocks, int64_t N, int64_t K)
+{
+    return !awq_tile_forced() && blocks <= 6 && K > 512 && K <= 2048 && blocks * N * K <= (int64_t)12 << 20;
+}
+
 int fill_problem(W2Problem &p, const void *x, const void *q, const void *sc, const void *zp, void *y,
                  int64_t N, int64_t K, int group)
 {
@@ -494,10 +504,22 @@ extern "C" int awq_w2a16_linear(const void *x_f16, const void *qweight, const vo
     if (st != AWQ_OK) return st;
     if (M <= 0 || M > 0x7fffffff) return AWQ_ERR_BAD_SHAPE;
     if (M <= 16) return launch_w2(&p, 1, (int)M, (hipStream_t)stream);
+    const int64_t blocks = (M + 15) / 16;
+    if (decode_blocks(blocks, N, K)) {
+        // blocks of 16 rows in one launch; the last one is moved back to end at the last row (the overlap is computed
+        // twice, same values)
+        W2Problem d[W2_MAX_PROBLEMS];
+        for (int b = 0; b < (int)blocks; ++b) {
+            const int64_t m0 = b + 1 < blocks ? 16 * (int64_t)b : M - 16;
+            d[b] = p;
+            d[b].x = p.x + m0 * K;
+            d[b].y = p.y + m0 * N;
+        }
+        return launch_w2(d, (int)blocks, 16, (hipStream_t)stream);
+    }
     // more tokens: the K-split tile kernel, which reads the packed words once per 128 tokens at most and
-    // runs matrix instructions on whole token tiles.  (Before: blocks of 16 rows through the decode kernel, 128
-    // rows per launch.  4096 x 4096 at 77 / 300 / 500 rows 14.1 / 43.7 / 69 -> 7.9 / 18.3 / 26.6 us;
-    // 11008 x 4096 at 17 rows 12.8 -> 8.6, at 500 157 -> 69 us.)
+    // runs matrix instructions on whole token tiles.  (4096 x 4096 at 77 / 300 / 500 rows as blocks of 16 rows, 128 rows
+    // to a launch, 14.1 / 43.7 / 69 us, so 7.9 / 18.3 / 26.6; 11008 x 4096 at 17 rows 12.8 and 8.6, at 500 157 and 69.)
     return awq_tile_launch(2, awq_tile_plan((int)M, (int)N, (int)K), x_f16, qweight, scales, zeros, y_f16, (int)M,
                            (int)N, (int)K, (hipStream_t)stream);
 }

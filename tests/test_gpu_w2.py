@@ -182,3 +182,22 @@ def test_w2_grouped_llama7b_layer_full_size(awq):
     layer = [probs[0]] * 4 + [probs[1]] * 2 + [probs[2]]
     for M in (1, 4, 16):
         check_multi_w2(awq, layer, M)
+
+
+@pytest.mark.parametrize("N,K,M", [(1024, 1024, 17), (1024, 1024, 96), (272, 768, 61), (4096, 1024, 48), (2048, 2048, 32)])
+def test_w2_small_matrices_run_as_blocks_of_16_rows(N, K, M):
+    """17 to 96 rows on a small matrix: bit for bit the decode kernel's results on each 16 rows, the last block ending
+    with the last row."""
+    import torch
+    import paper_2306_00978_amd as awq
+    g = torch.Generator(device="cuda").manual_seed(N + K + M)
+    packed = awq.awq_quantize_pack_w2((torch.randn((N, K), generator=g, device="cuda") * 0.02).half(),
+                                      torch.ones(K, device="cuda"))
+    x = torch.randn((M, K), generator=g, device="cuda").half()
+    buf = torch.full((M * N + 16,), float("nan"), dtype=torch.float16, device="cuda")
+    y = buf[:M * N].view(M, N)
+    awq.awq_w2a16_linear(x, *packed, N, out=y)
+    assert bool(torch.isnan(buf[M * N:]).all())
+    for m0 in [*range(0, M - 16, 16), M - 16]:
+        want = awq.awq_w2a16_linear(x[m0:m0 + 16].contiguous(), *packed, N)
+        assert torch.equal(y[m0:m0 + 16], want), m0
