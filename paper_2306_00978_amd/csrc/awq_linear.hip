@@ -203,15 +203,19 @@ extern "C" int awq_w4a16_linear_multi(const awq_linear_desc *descs, int count, i
     // through a small matrix (N = 4096, K = 11008: 10 us against 20 us).
     static const int rows_min_count = awq_knob("AWQ_ROWS_MIN_COUNT", 2);
     // At five and six tokens a small launch is the streaming kernel's still, whose waves request all of it at
-    // once (a layer of hidden size 1280 / 3840 at five tokens, 9.4 MB: 7.6 us and 9.7 through LDS; 2048 / 6144, 24 MB: 10.1
-    // and 12.8; 2560 / 7680, 38 MB: 14.2 and 15.2; 3072 / 9216, 54 MB: 19.3 and 17.0; at eight tokens even).
-    bool small = M <= 6 && count > 1;
+    // once (a layer of hidden size 1280 / 3840 at five tokens, 9.4 MB: 7.5 us and 10.1 through LDS; 2048 / 5632, 22 MB: 9.8
+    // and 13.3; at eight tokens even).  How small: a wave holds two batches of 512 columns of K at these M, and where K is no
+    // multiple of the waves' share some have two and some one.  Groups of two and three linears over 4 to 31 MiB, streaming over rows kernel:
+    // K of 2048, 4096 and more 1.03 to 1.9 throughout; other K 1.07 to 1.6 at 4 MiB and 0.80 to 1.3 from 8 on.  Layers of
+    // seven linears, hidden sizes 1024 to 2304: 1.05 to 1.4 up to 25 MiB, 0.92 to 1.2 from there.
+    bool small = M <= 6 && count > 1, even = true;
     int64_t packed = 0;
     for (int i = 0; i < count; ++i) {
         packed += (int64_t)p[i].N * p[i].K / 2;
+        even = even && (p[i].K == 2048 || p[i].K >= 4096);
         small = small && awq_gemv_stream_fits(p[i].N, p[i].K, (int)M);
     }
-    small = small && packed <= (int64_t)32 << 20;
+    small = small && packed <= (int64_t)(even ? 32 : count >= 4 ? 24 : 4) << 20;
     if (M > 4 && !small && (count >= rows_min_count || p[0].N >= 16384))
         return awq_gemv_rows_launch(p, count, (int)M, (hipStream_t)stream);
     // The linears whose K fits the register-resident activations of the streaming kernel at
