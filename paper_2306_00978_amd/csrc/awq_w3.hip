@@ -22,6 +22,8 @@
 #include "awq_gemv_stream.h"
 #include "awq_tile.h"
 
+#include <algorithm>
+
 int awq_gemv_launch_w3(const void *x, const void *qweight, const void *scales, const void *zeros,
                        void *y, int M, int N, int K, hipStream_t stream);
 
@@ -346,15 +348,21 @@ extern "C" int awq_w3a16_linear_multi(const awq_linear_desc *descs, int count, i
     }
     // From nine tokens the streaming kernel holds one batch of K per wave and takes K up to 4096 only, and not
     // every such K; the linears it does not take would be a launch each.  With two or more of those,
-    // and row blocks enough for every CU, the kernel that takes the activations through LDS (any K) runs all in one
+    // and row blocks enough, the kernel that takes the activations through LDS (any K) runs all in one
     // launch: a layer of hidden size 1280 at 12 tokens 26.1 us before, 10.8 now, 3072 48.4 / 19.4, 7168 120.9 /
-    // 63.7.  (One such linear: 0.97 to 1.2, left as it was; 2 x (512 x 8192), 64 row blocks: 12.8 and 16.2.)
+    // 63.7.  Enough: for every CU, 256; with two such linears only and K of 3072 and more, whose two launches
+    // lose less, 640 (2 x (4096 x 8192) at nine tokens 15.8 us as two launches and 18.2 as one, 2 x (5456 x 8192) 1.4 times faster as one,
+    // 2 x (2720 x 6144) 12.6 / 14.7, 2 x (5456 x 6144) 1.2 times faster).  One such linear: 0.97 to 1.2, left as it was.
     int unfit = 0, row_blocks = 0;
+    int64_t longest = 0;
     for (int i = 0; i < count; ++i) {
-        unfit += !awq_gemv_stream_fits(p[i].N, p[i].K, (int)M);
+        if (!awq_gemv_stream_fits(p[i].N, p[i].K, (int)M)) {
+            ++unfit;
+            longest = std::max<int64_t>(longest, p[i].K);
+        }
         row_blocks += p[i].N / 16;
     }
-    if (M > 8 && unfit >= 2 && row_blocks >= 256)
+    if (M > 8 && unfit >= 2 && row_blocks >= (unfit == 2 && longest >= 3072 ? 640 : 256))
         return awq_gemv_rows_launch_w3(p, count, (int)M, (hipStream_t)stream);
     GemvProblem fit[GEMV_MAX_PROBLEMS];
     int nfit = 0;
