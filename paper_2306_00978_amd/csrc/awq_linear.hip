@@ -29,9 +29,9 @@ extern "C" size_t awq_linear_workspace_bytes(int64_t M, int64_t N, int64_t K, in
     if (awq_check_weight_shape(N, K, group) != AWQ_OK || M <= 48 || M > (int64_t)1 << 22) return 0;
     double split_us = 0.0;
     const int ks = awq_gemm_ksplit((int)M, (int)N, (int)K, &split_us);
-    // 49..128 tokens, all of them the tile kernel's now: the figure of the time when blocks of 16 tokens
-    // ran through the decode kernels (7 us + blocks * packed bytes at 6 TB/s) unless cutting K
-    // was clearly faster or the shape did not fit one launch
+    // 49..128 tokens are the tile kernel's, but for large matrices with a workspace.  The figure is the one that
+    // callers know: nothing where blocks of 16 tokens through the decode kernels would do (7 us + blocks * packed
+    // bytes at 6 TB/s) and the shape fits one launch of them
     if (M <= 128 && awq_gemv_stream_fits((int)N, (int)K, 16)) {
         const double blocked_us = 7.0 + (double)((M + 15) / 16) * ((double)N * (double)K * 0.53125) / 6.0e6;
         if (ks < 2 || split_us > 0.85 * blocked_us) return 0;

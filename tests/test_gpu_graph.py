@@ -64,8 +64,8 @@ def test_graph_replay_of_decode_prefill_and_low_bit_calls(awq):
     err = oracle.norm_error(host(ys[0]), oracle.matmul(xs[:1], Wdq), xs[:1], Wdq)
     assert err.max() <= 2e-3
 
-    # single linears at 16 rows (batch kernels) and a prefill of 200 rows with K cut into ranges
-    # (two kernels, the workspace brought by the caller)
+    # single linears at 16 rows (batch kernels) and a prompt of 200 rows (the tile kernel, which leaves
+    # the workspace alone; K in ranges: the next test)
     need = awq.awq_linear_workspace_bytes(200, N, K)
     assert need > 0
     ws = torch.empty(need, dtype=torch.uint8, device="cuda")
@@ -81,6 +81,51 @@ def test_graph_replay_of_decode_prefill_and_low_bit_calls(awq):
     xb = host(xbig)
     err = oracle.norm_error(host(ybig), oracle.matmul(xb, Wdq), xb, Wdq)
     assert err.max() <= 2e-3
+
+
+def test_graph_replay_of_k_ranges_attention_and_the_calibration_statistic(awq):
+    """The calls of two launches each: K in ranges (the workspace is seen to be used), grouped attention with the merge of
+    its slices, the calibration statistic in row classes; and a 3-bit prompt through the re-packed codes."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(5)
+    N, K, M = 4096, 11008, 200
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).half()
+    x = torch.randn((M, K), generator=g, device="cuda").half()
+    p4 = awq.awq_quantize_pack(W, torch.ones(K, device="cuda"))
+    ws = torch.full((awq.awq_linear_workspace_bytes(M, N, K),), 0xA5, dtype=torch.uint8, device="cuda")
+    y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+    N3, K3, M3 = 4096, 4096, 2048
+    p3 = awq.awq_quantize_pack_w3(W[:N3, :K3].contiguous(), torch.ones(K3, device="cuda"))
+    x3 = torch.randn((M3, K3), generator=g, device="cuda").half()
+    ws3 = torch.full((N3 * K3 // 2,), 0xA5, dtype=torch.uint8, device="cuda")
+    y3 = torch.empty((M3, N3), dtype=torch.float16, device="cuda")
+    H, Hkv, pos = 64, 8, 1000
+    q, k, v = (torch.randn((n, 128), generator=g, device="cuda").half() for n in (H, Hkv, Hkv))
+    kc, vc = (torch.randn((Hkv, pos + 3, 128), generator=g, device="cuda").half() for _ in range(2))
+    att = torch.empty((H, 128), dtype=torch.float16, device="cuda")
+    need = awq.load().awq_decode_attention_workspace_bytes(H, 128, pos + 1)
+    wsa = torch.empty(need, dtype=torch.uint8, device="cuda")
+    X = torch.randn((8200, 1024), generator=g, device="cuda").half()
+    s = torch.empty(1024, dtype=torch.float32, device="cuda")
+    wss = torch.empty(awq.awq_act_scale_workspace_bytes(*X.shape), dtype=torch.uint8, device="cuda")
+
+    def run():
+        awq.awq_w4a16_linear(x, *p4, N, out=y, workspace=ws)
+        awq.awq_w3a16_linear(x3, *p3, N3, out=y3, workspace=ws3)
+        awq.awq_decode_attention(q, k, v, kc, vc, pos, out=att, workspace=wsa)
+        awq.awq_act_scale(X, 0.5, out=s, workspace=wss)
+
+    def disturb():                                   # a workspace is the program's between two replays
+        for w in (ws, ws3, wsa, wss):
+            w.fill_(0xA5)
+    replay_and_compare(torch, run, [y, y3, att, s], disturb)
+    assert not bool((ws == 0xA5).all()) and not bool((ws3 == 0xA5).all())
+    Wdq = awq.awq_unpack(*p4, N, K)
+    rows = torch.tensor([0, 77, M - 1], device="cuda")
+    deq = ((Wdq[0].float().view(N, K // 128, 128) - Wdq[2].float()[..., None]) * Wdq[1].float()[..., None]).view(N, K)
+    ref = x[rows].double() @ deq.double().T
+    scale = x[rows].double().norm(dim=1, keepdim=True) * deq.abs().max().double()
+    assert float(((y[rows].double() - ref).abs() / scale).max()) <= 2e-3
 
 
 def test_calls_on_two_streams_do_not_share_anything(awq):

@@ -265,11 +265,8 @@ def test_decode_every_m(awq, small, M):
 
 @pytest.mark.parametrize("M", [24, 100])
 def test_small_prefill_full_size_blocks_of_16(awq, M):
-    """17..128 tokens run through the decode kernels in blocks of 16 (the last block moved back):
-    full-size shapes (4096 x 4096 through the register-resident kernel, the two larger ones through
-    the kernel that stages the activations in LDS, where the rows the last block shares with its
-    neighbour are written by the neighbour alone), every row against the oracle, twice bit for bit
-    alike."""
+    """17..128 tokens at full size (the tile kernel, its last 16 tokens moved back over their neighbours), every row
+    against the oracle, twice bit for bit alike."""
     for N, K in [(4096, 4096), (4096, 11008), (11008, 4096)]:
         case, s, xs16, ref, gpu, Wdq = config_case(awq, N, K, 0.02, 1)
         g = np.random.default_rng(M)
@@ -284,9 +281,10 @@ def test_small_prefill_full_size_blocks_of_16(awq, M):
 @pytest.mark.parametrize("M,ksplit", [(200, None), (512, 4), (2048, 1)])
 def test_mid_prefill_split_k_full_size(awq, M, ksplit):
     """A few hundred tokens: with the workspace the prefill kernel cuts K into ranges (one
-    workgroup per tile and range, fp32 partial tiles summed by a second kernel).  Full-size
+    workgroup per tile and range, fp32 partial tiles summed by a second kernel; 200 tokens on 4096 x 4096 are the tile
+    kernel's either way).  Full-size
     shapes, sampled rows against the oracle, the workspace between canaries, and the result
-    next to that of the unsplit kernel."""
+    next to that of the call without one."""
     import torch
     for N, K in [(4096, 4096), (4096, 11008)]:
         case, s, xs16, ref, gpu, Wdq = config_case(awq, N, K, 0.02, 1)
@@ -1017,7 +1015,8 @@ def test_w3_edge_groups_and_exactness_on_integer_data(awq):
 @pytest.mark.parametrize("N,K", [(48, 640), (176, 1408), (272, 256)])
 def test_w3_repack_and_prefill(awq, N, K):
     """The 3-bit codes re-packed into the 4-bit layout unpack to the same codes, and the prefill
-    call (re-pack + the 4-bit matrix-matrix kernel) matches the oracle at ragged M."""
+    call matches the oracle at ragged M (these sizes are the tile kernel's; re-packing plus the 4-bit prefill
+    kernel is compared at ragged sizes in test_gpu_tile.py)."""
     import torch
     import oracle
     case, s, xs = make_case(N, K, 16, 0.02, cfg=0, proj=2)

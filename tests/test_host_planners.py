@@ -81,7 +81,7 @@ def test_grouped_decode_plans(awq):
 
 
 def test_single_linear_every_route(awq):
-    """Decode, token blocks of 16, K-range prefill with and without workspace, the static entry."""
+    """Decode, short prompts, K-range prefill with and without workspace, the static entry."""
     lib = awq.load()
     addr = Addresses()
     for N, K in [(4096, 4096), (11008, 4096), (4096, 11008), (32000, 4096), (176, 1408), (28672, 8192)]:

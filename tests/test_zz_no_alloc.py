@@ -29,8 +29,8 @@ def test_static_scratch_entry_point_equals_the_workspace_call_twice_in_a_row():
     assert torch.cuda.is_available()
     limit = awq.awq_static_scratch_bytes()
     assert limit == 32 << 20
-    # first call: 512 tokens on 1024 x 4096 (8 K ranges); second: 200 tokens on 512 x 2048 -- smaller
-    # in every dimension, so it runs on scratch the first call left filled
+    # first call: 512 tokens on 1024 x 4096; second: 200 tokens on 512 x 2048 -- smaller in every dimension.
+    # (Both are the tile kernel's, which uses no scratch; the next test has two that do.)
     for (N, K, M, proj) in ((1024, 4096, 512, 0), (512, 2048, 200, 1)):
         xs, x, (q, sc, zp), Wdq = _case(N, K, M, proj)
         need = awq.awq_linear_workspace_bytes(M, N, K)
@@ -44,6 +44,28 @@ def test_static_scratch_entry_point_equals_the_workspace_call_twice_in_a_row():
         rows = np.linspace(0, M - 1, 24).astype(int)
         err = oracle.norm_error(y.cpu().numpy()[rows], oracle.matmul(xs[rows], Wdq), xs[rows], Wdq)
         assert err.max() <= TOL, (N, K, M, err.max())
+
+
+def test_static_scratch_is_used_by_two_calls_in_a_row_the_second_smaller():
+    """200 and then 129 tokens on 4096 x 11008: K in eight ranges both times (the caller's workspace is seen to be
+    written, and the result is not that of the call without one), the second time on scratch that the first left filled."""
+    N, K = 4096, 11008
+    xs, x, (q, sc, zp), Wdq = _case(N, K, 200, 4)
+    for M in (200, 129):
+        need = awq.awq_linear_workspace_bytes(M, N, K)
+        assert need == 8 * M * N * 4 <= awq.awq_static_scratch_bytes()
+        ws = torch.full((need,), 0xA5, dtype=torch.uint8, device="cuda")
+        xm = x[:M].contiguous()
+        y_ref = awq.awq_w4a16_linear(xm, q, sc, zp, N, workspace=ws)
+        assert not bool((ws.view(8, -1) == 0xA5).all(1).any())
+        assert not torch.equal(y_ref, awq.awq_w4a16_linear(xm, q, sc, zp, N, workspace=False))
+        y = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
+        awq.awq_w4a16_linear_static(xm, q, sc, zp, N, y)
+        torch.cuda.synchronize()
+        assert torch.equal(y.view(torch.int16), y_ref.view(torch.int16)), M
+        rows = np.linspace(0, M - 1, 24).astype(int)
+        err = oracle.norm_error(y.cpu().numpy()[rows], oracle.matmul(xs[rows], Wdq), xs[rows], Wdq)
+        assert err.max() <= TOL, (M, err.max())
 
 
 def test_static_entry_point_without_scratch_and_beyond_the_limit():
