@@ -844,8 +844,8 @@ def main():
         extras["prefill_m64_4096x4096"] = {"us": round(ms64 * 1e3, 2),
                                            "TFLOP/s": round(workloads.flops(64, 4096, 4096) / (ms64 * 1e-3) / 1e12, 1),
                                            "note": "17..128 tokens: the tile kernel"}
-        # a prompt of 512 tokens, the three distinct shapes: the prefill kernel with K cut into ranges
-        # (the workspace of awq_w4a16_linear), next to the same call without the workspace
+        # a prompt of 512 tokens, the three distinct shapes: with the workspace of awq_w4a16_linear the prefill kernel cuts
+        # K into ranges (k_ranges > 1), without one the tile kernel or the prefill kernel runs, whichever is estimated faster
         pre512 = {}
         for p in (0, 4, 6):
             name, N, K = shapes[p]

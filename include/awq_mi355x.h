@@ -201,19 +201,21 @@ int awq_unpack(const void *qweight, const void *scales, const void *zeros, int64
  * matrix-matrix kernel has far fewer output tiles (ceil(M/128) * N/256) than the chip has CUs, and
  * with the workspace it cuts K into 2..8 ranges, one workgroup per tile and range, whose fp32
  * partial tiles (ranges * M * N * 4 bytes) a second kernel adds.  The workspace is optional: with
- * NULL the call runs without it (1.2 to 2.9 times slower at 50..1000 tokens). */
+ * NULL the call runs without it (0.8 to 1.4 times as long; most where K or N is long).  Some of the
+ * shapes that have a figure run a kernel that leaves the workspace alone. */
 size_t awq_linear_workspace_bytes(int64_t M, int64_t N, int64_t K, int group);
 
 /* Sec. 4.2 (on-the-fly dequantization fused into the MV / MM kernel):
  *   y[m,n] = fp16( sum_k fp32(x[m,k]) * (q[n,k] - zero[n,k/128]) * scale[n,k/128] )
  * with fp32 accumulation.  x_f16 [M,K] fp16 row-major, already divided by s;
  * qweight/scales/zeros as written by awq_quantize_pack; y_f16 [M,N] fp16 row-major
- * (written).  M <= 16 takes the decode path (streams the packed weights once), 17..128 tokens, and
- * more where that is estimated to be faster, a tile kernel that cuts K over the waves of a workgroup and
- * uses no workspace, larger M the prefill kernel (with the workspace also over K ranges).  `workspace` may be NULL; if it is given where
+ * (written).  M <= 16 takes the decode path (streams the packed weights once); 17..128 tokens (but large matrices with a
+ * workspace), and more where that is estimated to be faster, a tile kernel that cuts K over the waves of a workgroup and
+ * uses no workspace; the others the prefill kernel (with the workspace also over K ranges).  `workspace` may be NULL; if it is given where
  * awq_linear_workspace_bytes() is not 0 it must hold that many bytes (AWQ_ERR_WORKSPACE_TOO_SMALL)
  * and be 16-byte aligned (AWQ_ERR_MISALIGNED); its contents are undefined afterwards.  Results with and without the workspace
- * differ by the order of the fp32 sums only. */
+ * differ by the order of the fp32 sums and, where one of them is the tile kernel's, by the rounding of (q - zero) * scale
+ * to fp16, which the prefill kernel does and that one does not. */
 int awq_w4a16_linear(const void *x_f16, const void *qweight, const void *scales,
                      const void *zeros, void *y_f16, int64_t M, int64_t N, int64_t K,
                      int group, void *workspace, size_t workspace_bytes, void *stream);
