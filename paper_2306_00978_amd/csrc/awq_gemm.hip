@@ -5,37 +5,44 @@
 // epilogue as with W8A8), and dequantized weights are never written to memory.
 //
 // Mapping.  A workgroup computes a 128 (tokens) x 256 (out-features) tile of y with
-// eight waves: four side by side along N (128 x 64 = 4 x 2 tiles of
-// v_mfma_f32_32x32x16_f16, 128 fp32 accumulators per lane), each of them twice, the two
-// copies sharing a SIMD and splitting K between them: of the eight MFMA steps of a
-// quantization group (128 columns) one wave takes the even ones, the other the odd ones, and
+// eight waves: four side by side along N (128 x 64 = 8 x 4 tiles of
+// v_mfma_f32_16x16x32_f16, 128 fp32 accumulators per lane), each of them twice, the two
+// copies sharing a SIMD and splitting K between them: of a quantization group (128 columns) each takes half of the
+// slots of every packed tile, two MFMA steps of 32 columns, and
 // the two partial tiles are added through LDS at the end.  A single wave per SIMD cannot keep
 // the matrix pipe busy (loop overhead, waits, the change of group all stall it); with two,
-// one computes while the other does that work, and no weight is dequantized twice.  The
-// 32x32x16 shape is chosen for its issue budget: one MFMA occupies the matrix pipe for 32
-// cycles, and in that shadow the wave issues everything else (operand reads, dequantization).
+// one computes while the other does that work, and no weight is dequantized twice.
+//
+// What bounds it is power, then issue: on activations and 4-bit weights a loop of nothing but MFMAs runs at 2000
+// TFLOP/s with the 16x16x32 shape and at 1740 with 32x32x16 (the clock falls; on zeros both reach 2400), and every
+// vector instruction beside them costs about as much energy as a thirtieth of an MFMA.  Hence the small shape, 126 vector
+// instructions to 64 MFMAs (offsets that stay in their registers, constants by one multiply-add each), fragment reads
+// without bank conflicts, and consecutive MFMAs that share their weight fragment and then their token fragment.  Against
+// the 32x32x16 form of the same tile: 2048 x 11008 x 4096 176 -> 160 us (1150 TFLOP/s), 2048 x 4096 x 4096 62 -> 56.5, 2048 x 4096 x 11008
+// 156 -> 138, on zeros 138 -> 127, 48 -> 44, 118 -> 104.
 //
 // Operands.  Nothing is staged through registers on the way in: both operands are
 // fetched with global_load_lds (memory -> LDS, 16 bytes per lane landing in lane order),
 // two groups ahead of the one being computed, into a ring of three stages.
 //   * x: one load instruction fetches 8 rows x 128 contiguous bytes (whole cache lines) and
 //     lands as 8 LDS rows of 128 bytes.  Which 16-byte chunk of the row a lane fetches is
-//     XOR-swizzled with the row index, so that the A fragment of any MFMA step (lane l: row
-//     l%32, 16 bytes at columns 16 s + 8 (l/32)) is read back with one conflict-free
+//     XOR-swizzled with the row index, so that a fragment (16 rows, a chunk each) is read back with one conflict-free
 //     ds_read_b128.  All waves share the x tile (wave (n-quarter q, k-half h) loads row block
 //     q, column half h of every group); one barrier per group.
-//   * weights: the packed layout is already the B-operand layout.  For a block of 32
-//     out-features (two 16-row tiles), lane l takes slot (l%16) + 16 (2h + l/32) of tile
-//     (l%32)/16: its word j is the fragment of MFMA step 2 j + h, i.e. half h of a tile holds
-//     exactly the steps of k-half h.  A wave loads and reads only its own half.
-//   Each fragment word is expanded in registers to fp16 (q - z) * scale and feeds four
-//   MFMAs (the four token blocks), so dequantization costs about three vector
-//   instructions per MFMA.
+//   * weights: the packed layout is already the B-operand layout.  A wave loads and reads only its own half of a tile,
+//     the slots 2 h and 2 h + 1 of every row (512 contiguous bytes), and its own steps and zero points.  Lane (r, c) takes
+//     words 2 (c/2) and 2 (c/2) + 1 of slot 2 h + c%2, one in each of the wave's steps; the columns that they hold are
+//     chunk 4 step + 2 h + c%2 of column half c/2 of the group, which is what the token fragment reads.  (A pair of
+//     adjacent words: with words c/2 and 2 + c/2, which would make the columns of a step contiguous, the reads had two-way
+//     bank conflicts, 4 % on 2048 x 11008 x 4096.)
+//   Each fragment word is expanded in registers to fp16 (q - z) * scale and feeds eight
+//   MFMAs (the token tiles).
 // fp32 accumulation, one rounding to fp16 at the end.
 #include "awq_common.h"
 #include "awq_gemm_epilogue.h"
 
 #include <type_traits>
+#include <utility>
 
 namespace {
 
@@ -43,14 +50,17 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 typedef const __attribute__((address_space(1))) void gbl_void_t;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int BM = 128, BN = 256;
 constexpr int NSTAGE = 3;
 constexpr int A_STAGE = 32 * 1024;               // 4 row blocks x 2 column halves x (32 rows x 128 B)
-constexpr int B_STAGE = 4096 + 256 + 128;        // 2 blocks x 2 halves x 1 KB, 64 steps, 32 zero bytes
-constexpr int B_SC = 4096, B_ZP = 4352;
-constexpr int LDS_BYTES = NSTAGE * A_STAGE + 4 * NSTAGE * B_STAGE;
-constexpr int LOADS_PER_GROUP = 4 + 2 + 1;       // per wave
+constexpr int B_STAGE = 2048 + 256 + 256;        // of a wave: half of four tiles, 64 steps, 64 zero bytes (a dword each)
+constexpr int B_SC = 2048, B_ZP = 2304;
+constexpr int LDS_BYTES = NSTAGE * A_STAGE + 8 * NSTAGE * B_STAGE;
+constexpr int LOADS_PER_GROUP = 4 + 2 + 2;       // per wave
+constexpr int PART_ROW = 68;                     // floats per row of a partial tile on its way out
+static_assert(8 * 64 * PART_ROW * 4 <= LDS_BYTES && LDS_BYTES <= 160 * 1024, "LDS");
 
 __device__ __forceinline__ void dma16(const void *g, uint32_t lds_addr)
 {
@@ -70,12 +80,6 @@ __device__ __forceinline__ void dma1(const void *g, uint32_t lds_addr)
 
 // LDS reads are written as asm so that the compiler does not tie them to the outstanding
 // memory->LDS loads of later groups; the waits are placed by hand.
-__device__ __forceinline__ u32x4 lds_read16(uint32_t addr)
-{
-    u32x4 v;
-    asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr));
-    return v;
-}
 template <int OFF>
 __device__ __forceinline__ u32x4 lds_read16_off(uint32_t addr)
 {
@@ -83,15 +87,31 @@ __device__ __forceinline__ u32x4 lds_read16_off(uint32_t addr)
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
     return v;
 }
-__device__ __forceinline__ uint32_t lds_read4(uint32_t addr)
+template <int OFF>
+__device__ __forceinline__ u32x2 lds_read8(uint32_t addr)
 {
-    uint32_t v;
-    asm volatile("ds_read_b32 %0, %1" : "=v"(v) : "v"(addr));
+    u32x2 v;
+    asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
+    return v;
+}
+// the dwords at addr + 4 O0 and addr + 4 O1
+template <int O0, int O1>
+__device__ __forceinline__ u32x2 lds_read2(uint32_t addr)
+{
+    u32x2 v;
+    asm volatile("ds_read2_b32 %0, %1 offset0:%2 offset1:%3" : "=v"(v) : "v"(addr), "n"(O0), "n"(O1));
     return v;
 }
 __device__ __forceinline__ void lds_wait(u32x4 &a, u32x4 &b, u32x4 &c, u32x4 &d)
 {
     asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+}
+
+// f(integral_constant 0), f(1), ... in order
+template <int... I, class F>
+__device__ __forceinline__ void in_order(std::integer_sequence<int, I...>, F f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
 }
 
 struct DqConsts {
@@ -137,32 +157,20 @@ __device__ __forceinline__ void dq_step(DqWord &d, const DqConsts &k, half2_t zA
     }
 }
 
-// steps [26 SLOT / 8, 26 (SLOT + 1) / 8) of the 26 that dequantize the two words of an MFMA step
-template <int SLOT>
-__device__ __forceinline__ void dq_slice(DqWord (&d)[2], const DqConsts &k, const half2_t (&zA)[2],
-                                         const half2_t (&zB)[2], const half2_t (&s2)[2])
+// part SLOT of SLOTS of the 52 steps that dequantize the four words of an MFMA step
+template <int SLOT, int SLOTS>
+__device__ __forceinline__ void dq_slice(DqWord (&d)[4], const DqConsts &k, const half2_t (&zA)[4],
+                                         const half2_t (&zB)[4], const half2_t (&s2)[4])
 {
-#define AWQ_DQ_ONE(I)                                                                           \
-    if ((I) >= 26 * SLOT / 8 && (I) < 26 * (SLOT + 1) / 8) {                                    \
-        constexpr int b_ = (I) / 13, op_ = (I) % 13;                                            \
-        dq_step<op_>(d[b_], k, zA[b_], zB[b_], s2[b_]);                                         \
-    }
-    AWQ_DQ_ONE(0) AWQ_DQ_ONE(1) AWQ_DQ_ONE(2) AWQ_DQ_ONE(3) AWQ_DQ_ONE(4) AWQ_DQ_ONE(5) AWQ_DQ_ONE(6)
-    AWQ_DQ_ONE(7) AWQ_DQ_ONE(8) AWQ_DQ_ONE(9) AWQ_DQ_ONE(10) AWQ_DQ_ONE(11) AWQ_DQ_ONE(12)
-    AWQ_DQ_ONE(13) AWQ_DQ_ONE(14) AWQ_DQ_ONE(15) AWQ_DQ_ONE(16) AWQ_DQ_ONE(17) AWQ_DQ_ONE(18)
-    AWQ_DQ_ONE(19) AWQ_DQ_ONE(20) AWQ_DQ_ONE(21) AWQ_DQ_ONE(22) AWQ_DQ_ONE(23) AWQ_DQ_ONE(24)
-    AWQ_DQ_ONE(25)
-#undef AWQ_DQ_ONE
+    in_order(std::make_integer_sequence<int, 52>{}, [&](auto step) {
+        constexpr int I = decltype(step)::value, n = I / 13, op = I % 13;
+        if constexpr (I >= 52 * SLOT / SLOTS && I < 52 * (SLOT + 1) / SLOTS) dq_step<op>(d[n], k, zA[n], zB[n], s2[n]);
+    });
 }
 
 __device__ __forceinline__ half8_t dq_result(const DqWord &d)
 {
     return __builtin_bit_cast(half8_t, make_uint4(d.t[0], d.t[1], d.t[2], d.t[3]));
-}
-
-__device__ __forceinline__ uint32_t word_of(const u32x4 &v, int j)
-{
-    return v[j];
 }
 
 // SPLIT: K is cut into `ksplit` ranges of whole groups, one workgroup per (tile, range); each
@@ -209,254 +217,217 @@ __global__ __launch_bounds__(512, 1) void gemm_kernel(
     // waves w and w+4 run on the same SIMD: they form a pair on the same 128 x 64 sub-tile
     const int nq = wave & 3;                                 // which 64 out-features
     const int kh = wave >> 2;                                // which MFMA steps: 2 t + kh
-    const int l32 = lane & 31, hi = lane >> 5;
+    const int r = lane & 15, c = lane >> 4;
     const int m0 = tile_m * BM;
     const int NT = N >> 4;                                   // 16-row weight tiles in the matrix
     const int nt0 = tile_n * (BN / 16) + nq * 4;            // first of the pair's four tiles
 
-    // ---- sources of this lane's memory->LDS loads (group 0), advanced by constant strides
+    // ---- sources of this lane's memory->LDS loads: 32-bit offsets beside wave-uniform bases (group 0)
     // x: the wave fetches rows 32 nq .. +32, columns 64 kh .. +64 of the group; load q (0..3)
     // covers rows 8 q .. +8 of them; lane l takes row 8 q + l/8 (rows >= M repeat row M-1) and
     // chunk (l%8) ^ f, f = ((row in block)/2)%8, and lands at chunk l%8: sixteen consecutive
     // rows then hold any given chunk in sixteen different bank groups
-    const unsigned char *xsrc[4];
+    const unsigned char *xbase = reinterpret_cast<const unsigned char *>(x) + (size_t)m0 * K * 2 + kh * 128 + (size_t)gofs * 256;
+    uint32_t xofs[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        int xr = m0 + 32 * nq + 8 * q + (lane >> 3);
-        xr = xr < M ? xr : M - 1;
+        const int row = min(32 * nq + 8 * q + (lane >> 3), M - 1 - m0);
         const int chunk = (lane & 7) ^ (((8 * q + (lane >> 3)) >> 1) & 7);
-        xsrc[q] = reinterpret_cast<const unsigned char *>(x) + ((size_t)xr * K + 8 * chunk) * 2 + kh * 128 +
-                  (size_t)gofs * 256;
+        xofs[q] = (uint32_t)row * (uint32_t)(K * 2) + 16 * chunk;
     }
-    // weights: block b (32 out-features = tiles nt0+2b, nt0+2b+1), half kh
-    const unsigned char *qsrc[2];
+    // weights: half kh of the tiles, two tiles (2 b, 2 b + 1) per load: lane l takes slot (l%16) + 16 (2 kh + l/32)
+    // of tile 2 b + l/16 % 2.  Ragged N: repeats the last tile.
+    const unsigned char *qbase[2];
+    uint32_t qofs[2];
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-        int t = nt0 + 2 * b + (l32 >> 4);
-        t = t < NT ? t : NT - 1;                             // ragged N: repeat the last tile
-        qsrc[b] = qweight + ((size_t)t * G * 64 + (l32 & 15) + 16 * hi) * 16 + kh * 512 + (size_t)gofs * 1024;
+        const int t0 = min(nt0 + 2 * b, NT - 1), t1 = min(nt0 + 2 * b + 1, NT - 1);
+        qbase[b] = qweight + (size_t)t0 * G * 1024 + kh * 512 + (size_t)gofs * 1024;
+        qofs[b] = (c & 1) * (uint32_t)((t1 - t0) * G * 1024) + (r + 16 * (c >> 1)) * 16;
     }
-    // steps (fetched by the kh = 0 wave): lane -> block lane/32, row l32;
-    // zero points (kh = 1 wave): lane < 32 -> block lane/16, byte lane%16
-    const unsigned char *msrc;
-    if (kh == 0) {
-        int t = nt0 + 2 * hi + (l32 >> 4);
-        t = t < NT ? t : NT - 1;
-        msrc = scales + ((size_t)t * G * 16 + (l32 & 15)) * 2 + (size_t)gofs * 32;
-    } else {
-        int tz = nt0 + 2 * ((lane >> 4) & 1) + ((lane >> 3) & 1);
-        tz = tz < NT ? tz : NT - 1;
-        msrc = zeros + (size_t)tz * G * 8 + (lane & 7) + (size_t)gofs * 8;
-    }
+    // steps and zero points: lane (r, c) those of row r of tile c
+    const int mt0 = min(nt0, NT - 1);
+    const uint32_t mrun = (uint32_t)((min(nt0 + c, NT - 1) - mt0) * G);
+    const unsigned char *sbase = scales + ((size_t)mt0 * G + gofs) * 32, *zbase = zeros + ((size_t)mt0 * G + gofs) * 8;
+    uint32_t sofs = mrun * 32 + r * 2, zofs = mrun * 8 + (r >> 1);
 
     const uint32_t a_ring = lds0;
-    const uint32_t b_ring = lds0 + NSTAGE * A_STAGE + (uint32_t)nq * (NSTAGE * B_STAGE);
+    const uint32_t b_ring = lds0 + NSTAGE * A_STAGE + (uint32_t)wave * (NSTAGE * B_STAGE);
 
-    // One of the 7 loads of a group (PIECE 0..3: x, 4..5: weights, 6: steps or zero points).
+    // One of the 8 loads of a group (PIECE 0..3: x, 4..5: weights, 6: steps, 7: zero points).
     // They are issued one at a time from the issue shadow of the MFMAs.
     auto issue_piece = [&](auto piece_tag, int g, int stage) {
         constexpr int PIECE = decltype(piece_tag)::value;
         g = g < GL ? g : GL - 1;                             // past the end: a harmless repeat
+        uint32_t &at = PIECE < 4 ? xofs[PIECE & 3] : PIECE < 6 ? qofs[PIECE & 1] : PIECE == 6 ? sofs : zofs;
+        asm volatile("" : "+v"(at));                         // an offset, not part of a 64-bit address
         if constexpr (PIECE < 4) {
             // LDS: [row block 4][column half 2][32 rows x 128 B]
             const uint32_t adst = a_ring + (uint32_t)stage * A_STAGE + (uint32_t)nq * 8192 + (uint32_t)kh * 4096;
-            dma16(xsrc[PIECE] + (size_t)g * 256, adst + PIECE * 1024);
+            dma16(xbase + (size_t)g * 256 + at, adst + PIECE * 1024);
         } else {
             const uint32_t bdst = b_ring + (uint32_t)stage * B_STAGE;
-            if constexpr (PIECE < 6) {
-                constexpr int b = PIECE - 4;
-                dma16(qsrc[b] + (size_t)g * 1024, bdst + (2 * b) * 1024 + (uint32_t)kh * 1024);
-            } else if (kh == 0) {
-                dma2(msrc + (size_t)g * 32, bdst + B_SC);
-            } else {
-                if (lane < 32) dma1(msrc + (size_t)g * 8, bdst + B_ZP);
-            }
+            if constexpr (PIECE < 6) dma16(qbase[PIECE & 1] + (size_t)g * 1024 + at, bdst + (PIECE & 1) * 1024);
+            else if constexpr (PIECE == 6) dma2(sbase + (size_t)g * 32 + at, bdst + B_SC);
+            else dma1(zbase + (size_t)g * 8 + at, bdst + B_ZP);
         }
     };
-#define AWQ_PIECE(P, G_, ST_) issue_piece(std::integral_constant<int, (P)>{}, (G_), (ST_))
     auto issue_group = [&](int g, int stage) {
-        AWQ_PIECE(0, g, stage); AWQ_PIECE(1, g, stage); AWQ_PIECE(2, g, stage); AWQ_PIECE(3, g, stage);
-        AWQ_PIECE(4, g, stage); AWQ_PIECE(5, g, stage); AWQ_PIECE(6, g, stage);
+        in_order(std::make_integer_sequence<int, LOADS_PER_GROUP>{}, [&](auto piece) { issue_piece(piece, g, stage); });
     };
 
-    floatx16 acc[4][2];
+    floatx4 acc[8][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][b][v] = 0.f;
+        for (int n = 0; n < 4; ++n) acc[i][n] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     issue_group(0, 0);
     issue_group(1, 1);
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS_PER_GROUP) : "memory");
     __builtin_amdgcn_s_barrier();
 
-    const uint32_t lane16 = (uint32_t)lane << 4;
-    // byte offset of this lane's A fragment inside a row block for the wave's four steps
-    // S = 2 t + kh of a group: column half S/4, row l32, chunk (2 (S%4) + hi) ^ ((l32/2)%8)
-    uint32_t aoff[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-        aoff[t] = (uint32_t)(t >> 1) * 4096 + (uint32_t)l32 * 128 +
-                  (uint32_t)(((4 * (t & 1) + 2 * kh + hi) ^ ((l32 >> 1) & 7)) * 16);
+    // This lane's words of a tile: those of slot 2 kh + c%2 at 2 (c/2) + step, a pair of dwords.  So its A fragment of a
+    // step is, of row r of a token tile, chunk 4 step + 2 kh + c%2 of column half c/2.
+    const uint32_t boff = (uint32_t)(c & 1) * 512 + (uint32_t)r * 16 + (uint32_t)(c >> 1) * 8;
+    const uint32_t aoff[2] = {(uint32_t)(c >> 1) * 4096 + (uint32_t)r * 128 + (uint32_t)(((2 * kh + (c & 1)) ^ ((r >> 1) & 7)) * 16),
+                              (uint32_t)(c >> 1) * 4096 + (uint32_t)r * 128 + (uint32_t)(((4 + 2 * kh + (c & 1)) ^ ((r >> 1) & 7)) * 16)};
+    const uint32_t moff = (uint32_t)r * 4;
+    const int zshift = (r & 1) * 4;
 
     // ---- what a wave holds in registers for the group it is computing
-    u32x4 braw[2];               // packed words of its k-half: [block], word t = its step t
-    half2_t s2[2], zA[2], zB[2]; // per block: step, 1024 + z, 64 + z (as half pairs)
-    u32x4 a[4];                  // A fragments of the current step
-    DqWord dq[2];                // dequantization in flight (current or next step)
+    u32x2 braw[4];                        // packed words: [tile][step]
+    u32x2 sraw[2], zraw[2];               // steps and zero points as read: [tile / 2][tile % 2]
+    half2_t s2[4], zA[4], zB[4];          // per tile: step, 1024 + z, 64 + z (as half pairs)
+    u32x4 a[4];                           // A fragments: half of the token tiles
+    DqWord dq[4];                         // dequantization in flight (next step)
+    half8_t bf[4];                        // B fragments of the current step
 
-    // request the packed words, steps, zero points and the first A fragments of a stage
-    u32x4 nbraw[2], na[4];
-    uint32_t nsraw[2], nzraw[2];
-    auto read_group = [&](int st) {
+    auto read_weights = [&](int st) {
         const uint32_t bb = b_ring + (uint32_t)st * B_STAGE;
-        const uint32_t bk = bb + (uint32_t)kh * 1024 + lane16;
-        const uint32_t ab = a_ring + (uint32_t)st * A_STAGE + aoff[0];
-        nbraw[0] = lds_read16_off<0>(bk);
-        nbraw[1] = lds_read16_off<2048>(bk);
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            nsraw[b] = lds_read4(bb + B_SC + 4 * (32 * b + l32));
-            nzraw[b] = lds_read4(bb + B_ZP + 4 * (16 * b + (l32 >> 1)));
-        }
-        na[0] = lds_read16_off<0>(ab);
-        na[1] = lds_read16_off<8192>(ab);
-        na[2] = lds_read16_off<16384>(ab);
-        na[3] = lds_read16_off<24576>(ab);
+        braw[0] = lds_read8<0>(bb + boff);
+        braw[1] = lds_read8<256>(bb + boff);
+        braw[2] = lds_read8<1024>(bb + boff);
+        braw[3] = lds_read8<1280>(bb + boff);
+        sraw[0] = lds_read2<0, 16>(bb + B_SC + moff);
+        sraw[1] = lds_read2<32, 48>(bb + B_SC + moff);
+        zraw[0] = lds_read2<0, 16>(bb + B_ZP + moff);
+        zraw[1] = lds_read2<32, 48>(bb + B_ZP + moff);
     };
-    auto wait_group = [&]() {
+    auto wait_weights = [&]() {
         asm volatile("s_waitcnt lgkmcnt(0)"
-                     : "+v"(nbraw[0]), "+v"(nbraw[1]), "+v"(nsraw[0]), "+v"(nsraw[1]), "+v"(nzraw[0]),
-                       "+v"(nzraw[1]), "+v"(na[0]), "+v"(na[1]), "+v"(na[2]), "+v"(na[3]));
+                     : "+v"(braw[0]), "+v"(braw[1]), "+v"(braw[2]), "+v"(braw[3]), "+v"(sraw[0]), "+v"(sraw[1]),
+                       "+v"(zraw[0]), "+v"(zraw[1]));
     };
-    // the group's constants from what was read, and step 0 of its dequantization set up
-    half2_t ns2[2], nzA[2], nzB[2];
-    DqWord ndq[2];
-    auto group_consts = [&]() {
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const half_t sh = __builtin_bit_cast(half_t, (uint16_t)nsraw[b]);
-            ns2[b] = half2_t{sh, sh};
-            const uint32_t z = (nzraw[b] >> ((l32 & 1) * 4)) & 0xFu;
-            nzA[b] = __builtin_bit_cast(half2_t, 0x64006400u | (z * 0x00010001u));
-            nzB[b] = __builtin_bit_cast(half2_t, 0x54005400u | (z * 0x00100010u));
-            ndq[b].w = nbraw[b][0];
-        }
+    // a tile's constants from what was read, and its first step's word set up
+    auto tile_consts = [&](int n) {
+        const uint32_t sw = sraw[n >> 1][n & 1], zw = zraw[n >> 1][n & 1];
+        const half_t sh = __builtin_bit_cast(half_t, (uint16_t)sw);
+        s2[n] = half2_t{sh, sh};
+        const uint32_t z = (zw >> zshift) & 0xFu;
+        zA[n] = __builtin_bit_cast(half2_t, kc.magA + z * 0x00010001u);
+        zB[n] = __builtin_bit_cast(half2_t, kc.magB + z * 0x00100010u);
+        dq[n].w = braw[n][0];
     };
-    auto adopt_group = [&]() {
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            braw[b] = nbraw[b];
-            s2[b] = ns2[b]; zA[b] = nzA[b]; zB[b] = nzB[b];
-            dq[b] = ndq[b];
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = na[i];
+    // fragments of token tiles 4 HALF .. + 3 for step S (0, 1) of the wave: one at a time
+    auto read_a = [&](auto which, uint32_t stage_base, auto step, auto half) {
+        constexpr int I = 4 * decltype(half)::value + decltype(which)::value;
+        return lds_read16_off<(I >> 1) * 8192 + (I & 1) * 2048>(stage_base + aoff[decltype(step)::value]);
     };
+    typedef std::integral_constant<int, 0> C0;
+    typedef std::integral_constant<int, 1> C1;
 
     // group 0: nothing to overlap with yet
-    read_group(0);
-    wait_group();
-    group_consts();
-    dq_slice<0>(ndq, kc, nzA, nzB, ns2); dq_slice<1>(ndq, kc, nzA, nzB, ns2);
-    dq_slice<2>(ndq, kc, nzA, nzB, ns2); dq_slice<3>(ndq, kc, nzA, nzB, ns2);
-    dq_slice<4>(ndq, kc, nzA, nzB, ns2); dq_slice<5>(ndq, kc, nzA, nzB, ns2);
-    dq_slice<6>(ndq, kc, nzA, nzB, ns2); dq_slice<7>(ndq, kc, nzA, nzB, ns2);
-    adopt_group();
-
-    // One MFMA and, in its issue shadow, EXTRA.  The scheduling barrier pins the interleaving.
-#define AWQ_MFMA_SLOT(I, B, EXTRA)                                                                 \
-    acc[I][B] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, a[I]),          \
-                                                       (B) ? bf1 : bf0, acc[I][B], 0, 0, 0);       \
-    EXTRA;                                                                                         \
-    __builtin_amdgcn_sched_barrier(0);
+    read_weights(0);
+    wait_weights();
+#pragma unroll
+    for (int n = 0; n < 4; ++n) tile_consts(n);
+    in_order(std::make_integer_sequence<int, 4>{}, [&](auto i) { a[i] = read_a(i, a_ring, C0{}, C0{}); });
+    dq_slice<0, 1>(dq, kc, zA, zB, s2);
+    lds_wait(a[0], a[1], a[2], a[3]);
 
     int stage = 0;
     for (int g = 0; g < GL; ++g) {
-        int nstage = stage + 1 == NSTAGE ? 0 : stage + 1;    // stage of group g+1
-        int fstage = nstage + 1 == NSTAGE ? 0 : nstage + 1;  // stage to fill with group g+2; it was
-                                                             // last read in group g-1, which every
-                                                             // wave left before the previous barrier
-        const uint32_t abase = a_ring + (uint32_t)stage * A_STAGE;
-        // the wave's steps 0..2: every MFMA is followed by a slice of the dequantization of its
-        // next step; the first four also by a fragment read of that step, later ones by a load
-        // of group g+2
+        const int nstage = stage + 1 == NSTAGE ? 0 : stage + 1;    // stage of group g+1
+        const int fstage = nstage + 1 == NSTAGE ? 0 : nstage + 1;  // stage to fill with group g+2; it was
+                                                                   // last read in group g-1, which every
+                                                                   // wave left before the previous barrier
+        const uint32_t abase = a_ring + (uint32_t)stage * A_STAGE, nbase = a_ring + (uint32_t)nstage * A_STAGE;
+        // Four quarters: step 0 on token tiles 0..3 and 4..7, then step 1.  A quarter is 16 MFMAs, each with
+        // something in its issue shadow (the scheduling barriers pin the interleaving): the fragment reads of the
+        // next quarter, the loads of group g+2 (quarters 0 and 1), the dequantization of step 1 (0 and 1) or of
+        // step 0 of group g+1 (2 and 3).
+        in_order(std::make_integer_sequence<int, 4>{}, [&](auto quarter) {
+            constexpr int t = decltype(quarter)::value;
+            if constexpr ((t & 1) == 0) {
 #pragma unroll
-        for (int t = 0; t < 3; ++t) {
-            const half8_t bf0 = dq_result(dq[0]), bf1 = dq_result(dq[1]);
+                for (int n = 0; n < 4; ++n) bf[n] = dq_result(dq[n]);
+            }
+            if constexpr (t == 0) {
+#pragma unroll
+                for (int n = 0; n < 4; ++n) dq[n].w = braw[n][1];
+            }
+            // this wave's loads of group g+1 have landed once only those of group g+2 are outstanding; behind the
+            // barrier that holds for every wave, and nobody reads this group's stage any more
+            if constexpr (t == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS_PER_GROUP) : "memory");
+            if constexpr (t == 3) __builtin_amdgcn_s_barrier();
             u32x4 an[4];
-            const uint32_t ad = abase + aoff[t + 1];
-#pragma unroll
-            for (int b = 0; b < 2; ++b) dq[b].w = word_of(braw[b], t + 1);
             __builtin_amdgcn_sched_barrier(0);
-            AWQ_MFMA_SLOT(0, 0, an[0] = lds_read16_off<0>(ad); dq_slice<0>(dq, kc, zA, zB, s2))
-            AWQ_MFMA_SLOT(0, 1, an[1] = lds_read16_off<8192>(ad); dq_slice<1>(dq, kc, zA, zB, s2))
-            AWQ_MFMA_SLOT(1, 0, an[2] = lds_read16_off<16384>(ad); dq_slice<2>(dq, kc, zA, zB, s2))
-            AWQ_MFMA_SLOT(1, 1, an[3] = lds_read16_off<24576>(ad); dq_slice<3>(dq, kc, zA, zB, s2))
-            AWQ_MFMA_SLOT(2, 0, if (t == 0) AWQ_PIECE(0, g + 2, fstage); if (t == 1) AWQ_PIECE(2, g + 2, fstage);
-                                if (t == 2) AWQ_PIECE(4, g + 2, fstage);
-                                dq_slice<4>(dq, kc, zA, zB, s2))
-            AWQ_MFMA_SLOT(2, 1, if (t == 0) AWQ_PIECE(1, g + 2, fstage); if (t == 1) AWQ_PIECE(3, g + 2, fstage);
-                                if (t == 2) AWQ_PIECE(5, g + 2, fstage);
-                                dq_slice<5>(dq, kc, zA, zB, s2))
-            AWQ_MFMA_SLOT(3, 0, if (t == 2) AWQ_PIECE(6, g + 2, fstage); dq_slice<6>(dq, kc, zA, zB, s2))
-            AWQ_MFMA_SLOT(3, 1, dq_slice<7>(dq, kc, zA, zB, s2))
+            in_order(std::make_integer_sequence<int, 16>{}, [&](auto slot) {
+                constexpr int s = decltype(slot)::value, n = s >> 2, i = (n & 1) ? 3 - (s & 3) : s & 3;
+                acc[4 * (t & 1) + i][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a[i]), bf[n],
+                                                                                 acc[4 * (t & 1) + i][n], 0, 0, 0);
+                if constexpr (s < 4) {
+                    if constexpr (t == 0) an[s] = read_a(slot, abase, C0{}, C1{});
+                    if constexpr (t == 1) an[s] = read_a(slot, abase, C1{}, C0{});
+                    if constexpr (t == 2) an[s] = read_a(slot, abase, C1{}, C1{});
+                    if constexpr (t == 3) an[s] = read_a(slot, nbase, C0{}, C0{});
+                }
+                if constexpr (t < 2) {
+                    if constexpr (s >= 4 && s < 12 && (s & 1) == 0)
+                        issue_piece(std::integral_constant<int, 4 * t + (s - 4) / 2>{}, g + 2, fstage);
+                    dq_slice<16 * t + s, 32>(dq, kc, zA, zB, s2);
+                }
+                if constexpr (t == 2 && s == 4) read_weights(nstage);
+                if constexpr (t == 2 && s == 9) wait_weights();
+                if constexpr (t == 2 && s >= 9 && s < 13) tile_consts(s - 9);
+                if constexpr (t == 2 && s >= 13) dq_slice<s - 13, 19>(dq, kc, zA, zB, s2);
+                if constexpr (t == 3) dq_slice<3 + s, 19>(dq, kc, zA, zB, s2);
+                __builtin_amdgcn_sched_barrier(0);
+            });
             lds_wait(an[0], an[1], an[2], an[3]);
 #pragma unroll
             for (int i = 0; i < 4; ++i) a[i] = an[i];
-        }
-
-        // group g+1 has landed once only the loads of group g+2 are outstanding; after the barrier
-        // every wave's part of it is visible.  The wave's last step of this group has all its
-        // operands in registers already: its MFMAs cover the reads and the set-up of group g+1.
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS_PER_GROUP) : "memory");
-        __builtin_amdgcn_s_barrier();
-        {
-            const half8_t bf0 = dq_result(dq[0]), bf1 = dq_result(dq[1]);
-            read_group(nstage);
-            __builtin_amdgcn_sched_barrier(0);
-            AWQ_MFMA_SLOT(0, 0, (void)0)
-            AWQ_MFMA_SLOT(0, 1, (void)0)
-            AWQ_MFMA_SLOT(1, 0, (void)0)
-            AWQ_MFMA_SLOT(1, 1, (void)0)
-            wait_group();
-            group_consts();
-            __builtin_amdgcn_sched_barrier(0);
-            AWQ_MFMA_SLOT(2, 0, dq_slice<0>(ndq, kc, nzA, nzB, ns2); dq_slice<1>(ndq, kc, nzA, nzB, ns2))
-            AWQ_MFMA_SLOT(2, 1, dq_slice<2>(ndq, kc, nzA, nzB, ns2); dq_slice<3>(ndq, kc, nzA, nzB, ns2))
-            AWQ_MFMA_SLOT(3, 0, dq_slice<4>(ndq, kc, nzA, nzB, ns2); dq_slice<5>(ndq, kc, nzA, nzB, ns2))
-            AWQ_MFMA_SLOT(3, 1, dq_slice<6>(ndq, kc, nzA, nzB, ns2); dq_slice<7>(ndq, kc, nzA, nzB, ns2))
-            adopt_group();
-        }
+        });
         stage = nstage;
     }
-#undef AWQ_MFMA_SLOT
-#undef AWQ_PIECE
     // drain the two harmless repeats; after the barrier nobody reads the rings any more
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
 
-    floatx16 own[2][2];
+    floatx4 own[4][4];
     gemm_pair_sum(acc, own, smem, wave, lane, kh);
 
     if (SPLIT) {
-        // partial sums leave in fp32, 32 consecutive columns per half-wave and accumulator
+        // partial sums leave in fp32, turned around through the wave's own LDS: 16 bytes per lane, four rows of
+        // 256 contiguous bytes per instruction
+        float *turn = reinterpret_cast<float *>(smem) + wave * (64 * PART_ROW);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int n = 0; n < 4; ++n)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) turn[(16 * i + 4 * c + v) * PART_ROW + 16 * n + r] = own[i][n][v];
         float *dst = part + (size_t)ks * M * N;
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int m = m0 + 64 * kh + 32 * ii + 8 * (v >> 2) + 4 * hi + (v & 3);
-                    const int n = nt0 * 16 + 32 * b + l32;
-                    if (m < M && n < N) dst[(size_t)m * N + n] = own[ii][b][v];
-                }
+        for (int it = 0; it < 16; ++it) {
+            const int m = m0 + 64 * kh + 4 * it + c, n = nt0 * 16 + 4 * r;
+            const float4 v = *reinterpret_cast<const float4 *>(turn + (4 * it + c) * PART_ROW + 4 * r);
+            if (m < M && n < N) *reinterpret_cast<float4 *>(dst + (size_t)m * N + n) = v;
+        }
         return;
     }
-    const unsigned char *mine = gemm_turn(own, smem, wave, l32, hi);
+    const unsigned char *mine = gemm_turn(own, smem, wave, lane);
     if (MODE == GEMM_PLAIN) {
         gemm_store(mine, y, m0 + 64 * kh, nt0 * 16, M, N, lane);
         return;

@@ -1,62 +1,58 @@
 // The end of a 128 x 256 output tile computed by eight waves in pairs (wave w and w + 4 hold partial sums of
-// the same 128 x 64 sub-tile, 4 x 2 tiles of 32x32 accumulators): shared by the W4A16 prefill kernel and the dense
+// the same 128 x 64 sub-tile, 8 x 4 tiles of 16x16 accumulators): shared by the W4A16 prefill kernel and the dense
 // fp16 product of the scale search.
 #pragma once
 
 #include "awq_common.h"
 
-// Wave kh (0, 1) of a pair keeps token blocks 2 kh, 2 kh + 1 and hands the other two to its partner
+// Wave kh (0, 1) of a pair keeps the token tiles 4 kh .. 4 kh + 3 and hands the other four to its partner
 // through LDS: 64 accumulators per lane, stored as [wave][accumulator][lane] (consecutive lanes in consecutive
-// words; 128 KB).  own receives the sums of the two it keeps.  (Values are selected, not references: a selected
+// words; 128 KB).  own receives the sums of the four it keeps.  (Values are selected, not references: a selected
 // reference puts the accumulators into scratch memory.)  Nobody may use the LDS for anything else: every wave has passed a barrier.
-__device__ __forceinline__ void gemm_pair_sum(const floatx16 (&acc)[4][2], floatx16 (&own)[2][2], unsigned char *smem,
+__device__ __forceinline__ void gemm_pair_sum(const floatx4 (&acc)[8][4], floatx4 (&own)[4][4], unsigned char *smem,
                                               int wave, int lane, int kh)
 {
     float *xch = reinterpret_cast<float *>(smem);
     float *mine = xch + (size_t)wave * (64 * 64);
     const float *theirs = xch + (size_t)(wave ^ 4) * (64 * 64);
 #pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int n = 0; n < 4; ++n)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                // the block this wave gives away: kh = 0 gives 2, 3; kh = 1 gives 0, 1
-                const float first = acc[ii][b][v], second = acc[2 + ii][b][v];
+            for (int v = 0; v < 4; ++v) {
+                // the tile this wave gives away: kh = 0 gives 4 .. 7; kh = 1 gives 0 .. 3
+                const float first = acc[i][n][v], second = acc[4 + i][n][v];
                 const float give = kh ? first : second;
-                own[ii][b][v] = kh ? second : first;
-                mine[((ii * 2 + b) * 16 + v) * 64 + lane] = give;
+                own[i][n][v] = kh ? second : first;
+                mine[((i * 4 + n) * 4 + v) * 64 + lane] = give;
             }
     __syncthreads();
 #pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int n = 0; n < 4; ++n)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                own[ii][b][v] += theirs[((ii * 2 + b) * 16 + v) * 64 + lane];
-            }
+            for (int v = 0; v < 4; ++v) own[i][n][v] += theirs[((i * 4 + n) * 4 + v) * 64 + lane];
     __syncthreads();
 }
 
-// Accumulator v of tile (i, b) is y[m0 + 32 i + 8 (v/4) + 4 hi + v%4][16 nt0 + 32 b + l32]: a lane holds
-// single columns, which would leave as 2-byte stores.  Each wave turns its 64 x 64 part around, rounded to fp16,
+// Lane (r, c) = (l % 16, l / 16): accumulator v of tile (i, n) is y[m0 + 16 i + 4 c + v][16 nt0 + 16 n + r]: a lane
+// holds single columns, which would leave as 2-byte stores.  Each wave turns its 64 x 64 part around, rounded to fp16,
 // through its own 9 KB of LDS (rows of 128 + 16 bytes: the padding spreads the banks); afterwards lane l reads
 // row 8 it + l / 8, columns 8 (l % 8) .. + 8 with gemm_row16.
 constexpr int GEMM_ROWB = 144;
-__device__ __forceinline__ unsigned char *gemm_turn(const floatx16 (&own)[2][2], unsigned char *smem, int wave, int l32,
-                                                    int hi)
+__device__ __forceinline__ unsigned char *gemm_turn(const floatx4 (&own)[4][4], unsigned char *smem, int wave, int lane)
 {
     unsigned char *mine = smem + (size_t)wave * (64 * GEMM_ROWB);
+    const int r = lane & 15, c = lane >> 4;
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
+        for (int n = 0; n < 4; ++n)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = 32 * ii + 8 * (v >> 2) + 4 * hi + (v & 3);
-                *reinterpret_cast<half_t *>(mine + row * GEMM_ROWB + (32 * b + l32) * 2) = (half_t)own[ii][b][v];
-            }
+            for (int v = 0; v < 4; ++v)
+                *reinterpret_cast<half_t *>(mine + (16 * i + 4 * c + v) * GEMM_ROWB + (16 * n + r) * 2) = (half_t)own[i][n][v];
     // wave-private area: the compiler orders the LDS reads after the writes above
     return mine;
 }

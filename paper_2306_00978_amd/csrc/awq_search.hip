@@ -16,6 +16,8 @@
 #include "awq_gemm_epilogue.h"
 #include "awq_tile.h"
 
+#include <type_traits>
+
 int awq_act_mean_launch(const void *X_f16, int64_t T, int64_t K, float *mean, hipStream_t stream);
 int awq_quantize_inv_launch(const void *W, const float *s, int64_t N, int64_t K, void *qweight, void *scales, void *zeros,
                             const void *x, int64_t M, void *xs, hipStream_t stream);
@@ -53,13 +55,13 @@ __device__ __forceinline__ void dma16(const unsigned char *g, uint32_t lds_addr)
 
 // Y[T,N] = X[T,K] W[N,K]^T, fp16 operands, fp32 accumulation, fp16 result: the unquantized layer of Eq. 4.
 // The geometry of the W4A16 prefill kernel: 128 x 256 tile, eight waves, four side by side along N (128 x 64
-// each, 4 x 2 tiles of v_mfma_f32_32x32x16_f16), the two waves of a SIMD splitting the K steps of a stage
-// between them.  A stage is 64 columns of K: 128 rows of X and 256 of W, 128 bytes each, memory -> LDS in whole
-// cache lines, 16-byte chunk k of row i at place k ^ (i / 2 % 8), so that the fragment reads (32 rows) are free
-// of bank conflicts; a ring of three stages (144 KB), one barrier per stage.  A wave's last step of a
-// stage runs behind the barrier: its MFMAs cover the first fragment reads of the next one.
+// each, 8 x 4 tiles of v_mfma_f32_16x16x32_f16), the two waves of a SIMD taking a half of a stage's columns
+// each.  A stage is 64 columns of K: 128 rows of X and 256 of W, 128 bytes each, memory -> LDS in whole
+// cache lines, 16-byte chunk k of row i at place k ^ (i / 2 % 8), so that the fragment reads (16 rows) are free
+// of bank conflicts; a ring of three stages (144 KB), one barrier per stage.  The second half of a wave's token tiles
+// runs behind the barrier: its MFMAs cover the first fragment reads of the next stage.
 // (128 x 128 tiles staged through registers with two barriers per 64 columns: 296 us = 232 TFLOP/s at
-// 2048 x 4096 x 4096; this form 74 us = 930.)
+// 2048 x 4096 x 4096; this form 71 us = 970; with 32x32x16 MFMAs 75.)
 constexpr int DM = 128, DN = 256, DSTAGES = 3;
 constexpr int D_A = DM * 128, D_STAGE = (DM + DN) * 128;
 constexpr int D_LDS = DSTAGES * D_STAGE;
@@ -76,7 +78,7 @@ __global__ __launch_bounds__(512, 1) void dense_gemm_kernel(const half_t *__rest
     const int tile_m = tile / tiles_n, tile_n = tile - tile_m * tiles_n;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int nq = wave & 3, kh = wave >> 2, l32 = lane & 31, hi = lane >> 5;
+    const int nq = wave & 3, kh = wave >> 2, r = lane & 15, c = lane >> 4;
     const int m0 = tile_m * DM, n0 = tile_n * DN;
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
 
@@ -98,40 +100,41 @@ __global__ __launch_bounds__(512, 1) void dense_gemm_kernel(const half_t *__rest
         for (int i = 0; i < 6; ++i)
             dma16(src[i] + at, dst + (i < 2 ? wave * 2048 + i * 1024 : D_A + wave * 4096 + (i - 2) * 1024));
     };
-    // fragments of step t (0, 1) of the wave: columns 16 (2 t + kh) .. + 16 of the stage
-    uint32_t aofs[2], bofs[2];
+    // fragments of the wave's step, columns 32 kh .. + 32 of the stage: rows 16 i + r, chunk 4 kh + c
+    const uint32_t place = (uint32_t)(((4 * kh + c) ^ ((r >> 1) & 7)) * 16);
+    const uint32_t aofs = lds0 + r * 128 + place, bofs = lds0 + D_A + (64 * nq + r) * 128 + place;
+    u32x4 a[4], b[4], an[4], bn[4];
+#define AWQ_READ_A(HALF_, SLOT_)                                                                              \
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(an[0]) : "v"(aofs + (SLOT_) * D_STAGE), "n"((HALF_) * 8192));        \
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(an[1]) : "v"(aofs + (SLOT_) * D_STAGE), "n"((HALF_) * 8192 + 2048)); \
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(an[2]) : "v"(aofs + (SLOT_) * D_STAGE), "n"((HALF_) * 8192 + 4096)); \
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(an[3]) : "v"(aofs + (SLOT_) * D_STAGE), "n"((HALF_) * 8192 + 6144));
+#define AWQ_READ_B(SLOT_)                                                                                     \
+    asm volatile("ds_read_b128 %0, %1" : "=v"(bn[0]) : "v"(bofs + (SLOT_) * D_STAGE));                        \
+    asm volatile("ds_read_b128 %0, %1 offset:2048" : "=v"(bn[1]) : "v"(bofs + (SLOT_) * D_STAGE));            \
+    asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(bn[2]) : "v"(bofs + (SLOT_) * D_STAGE));            \
+    asm volatile("ds_read_b128 %0, %1 offset:6144" : "=v"(bn[3]) : "v"(bofs + (SLOT_) * D_STAGE));
+#define AWQ_ADOPT_A()                                                                                         \
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(an[0]), "+v"(an[1]), "+v"(an[2]), "+v"(an[3]));                \
+    a[0] = an[0]; a[1] = an[1]; a[2] = an[2]; a[3] = an[3];
+#define AWQ_ADOPT_B()                                                                                         \
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(bn[0]), "+v"(bn[1]), "+v"(bn[2]), "+v"(bn[3]));                \
+    b[0] = bn[0]; b[1] = bn[1]; b[2] = bn[2]; b[3] = bn[3];
+    floatx4 acc[8][4];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const uint32_t place = (uint32_t)(((2 * (2 * t + kh) + hi) ^ ((l32 >> 1) & 7)) * 16);
-        aofs[t] = lds0 + l32 * 128 + place;
-        bofs[t] = lds0 + D_A + (64 * nq + l32) * 128 + place;
-    }
-    u32x4 a[4], b[2], an[4], bn[2];
-#define AWQ_READ(T_, SLOT_)                                                                                   \
-    asm volatile("ds_read_b128 %0, %1" : "=v"(an[0]) : "v"(aofs[T_] + (SLOT_) * D_STAGE));                    \
-    asm volatile("ds_read_b128 %0, %1" : "=v"(bn[0]) : "v"(bofs[T_] + (SLOT_) * D_STAGE));                    \
-    asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(bn[1]) : "v"(bofs[T_] + (SLOT_) * D_STAGE));        \
-    asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(an[1]) : "v"(aofs[T_] + (SLOT_) * D_STAGE));        \
-    asm volatile("ds_read_b128 %0, %1 offset:8192" : "=v"(an[2]) : "v"(aofs[T_] + (SLOT_) * D_STAGE));        \
-    asm volatile("ds_read_b128 %0, %1 offset:12288" : "=v"(an[3]) : "v"(aofs[T_] + (SLOT_) * D_STAGE));
-#define AWQ_ADOPT()                                                                                           \
-    asm volatile("s_waitcnt lgkmcnt(0)"                                                                       \
-                 : "+v"(an[0]), "+v"(an[1]), "+v"(an[2]), "+v"(an[3]), "+v"(bn[0]), "+v"(bn[1]));             \
-    a[0] = an[0]; a[1] = an[1]; a[2] = an[2]; a[3] = an[3]; b[0] = bn[0]; b[1] = bn[1];
-    floatx16 acc[4][2];
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](auto half) {
+        constexpr int H = decltype(half)::value;
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-    auto multiply = [&]() {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, a[i]),
-                                                                   __builtin_bit_cast(half8_t, b[j]), acc[i][j], 0, 0, 0);
+        for (int s = 0; s < 16; ++s) {
+            // back and forth along the tokens: see the W4A16 prefill kernel
+            const int j = s >> 2, i = (j & 1) ? 3 - (s & 3) : s & 3;
+            acc[4 * H + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a[i]),
+                                                                       __builtin_bit_cast(half8_t, b[j]),
+                                                                       acc[4 * H + i][j], 0, 0, 0);
+        }
     };
 
     request(0, 0);
@@ -139,34 +142,40 @@ __global__ __launch_bounds__(512, 1) void dense_gemm_kernel(const half_t *__rest
     request(2, 2);
     asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
     __builtin_amdgcn_s_barrier();
-    AWQ_READ(0, 0)
-    AWQ_ADOPT()
+    AWQ_READ_A(0, 0)
+    AWQ_READ_B(0)
+    AWQ_ADOPT_A()
+    AWQ_ADOPT_B()
     int slot = 0;
     for (int st = 0; st < stages; ++st) {
-        AWQ_READ(1, slot)
+        AWQ_READ_A(1, slot)
         __builtin_amdgcn_sched_barrier(0);
-        multiply();
+        multiply(std::integral_constant<int, 0>{});
         __builtin_amdgcn_sched_barrier(0);
-        AWQ_ADOPT()
+        AWQ_ADOPT_A()
         // this wave has read all it needs of the stage; the next one has landed when only the six loads of
         // the stage after it are outstanding, and behind the barrier that holds for every wave
         asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         request(st + 3, slot);
         slot = slot + 1 == DSTAGES ? 0 : slot + 1;
-        AWQ_READ(0, slot)
+        AWQ_READ_A(0, slot)
+        AWQ_READ_B(slot)
         __builtin_amdgcn_sched_barrier(0);
-        multiply();
+        multiply(std::integral_constant<int, 1>{});
         __builtin_amdgcn_sched_barrier(0);
-        AWQ_ADOPT()
+        AWQ_ADOPT_A()
+        AWQ_ADOPT_B()
     }
-#undef AWQ_READ
-#undef AWQ_ADOPT
+#undef AWQ_READ_A
+#undef AWQ_READ_B
+#undef AWQ_ADOPT_A
+#undef AWQ_ADOPT_B
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the harmless repeats
     __syncthreads();
-    floatx16 own[2][2];
+    floatx4 own[4][4];
     gemm_pair_sum(acc, own, smem, wave, lane, kh);
-    gemm_store(gemm_turn(own, smem, wave, l32, hi), Y, m0 + 64 * kh, n0 + 64 * nq, T, N, lane);
+    gemm_store(gemm_turn(own, smem, wave, lane), Y, m0 + 64 * kh, n0 + 64 * nq, T, N, lane);
 }
 
 int dense_gemm_launch(const half_t *X, const half_t *W, half_t *Y, int T, int N, int K, hipStream_t stream)

@@ -189,3 +189,23 @@ def test_line_between_the_tile_and_the_prefill_kernel(bits, N, K, M, used):
     xr = x[rows].cpu().numpy()
     err = oracle.norm_error(np.ascontiguousarray(y[rows][:, cols].cpu().numpy()), oracle.matmul(xr, Wdq), xr, Wdq)
     assert err.max() <= TOL, err.max()
+
+
+@pytest.mark.parametrize("K", [128, 256, 384, 640])
+@pytest.mark.parametrize("N", [16, 48, 80, 272])
+def test_prefill_kernel_at_its_shortest_k(N, K):
+    """One group of 128 columns (less than the loads ahead of the first product), two, three (the ring goes round once) and five;
+    feature tiles of a wave with one, three and, in the second wave, one of four."""
+    import oracle
+    import torch
+    import paper_2306_00978_amd as awq
+    M = 145
+    x, Wdq, packed = case(4, N, K, M, N + K)
+    buf = torch.full((M * N + 16,), float("nan"), dtype=torch.float16, device="cuda")
+    y = buf[:M * N].view(M, N)
+    with tuning_build(AWQ_TILE_PLAN=0):
+        awq.awq_w4a16_linear(torch.from_numpy(x).cuda(), *packed, N, out=y, workspace=False)
+    got = y.cpu().numpy()
+    assert bool(torch.isnan(buf[M * N:]).all()) and np.all(np.isfinite(got.astype(np.float32)))
+    err = oracle.norm_error(got, oracle.matmul(x, Wdq), x, Wdq)
+    assert err.max() <= TOL, err.max()
