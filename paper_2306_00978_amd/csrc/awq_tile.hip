@@ -11,9 +11,12 @@
 // v_mfma_f32_16x16x32_f16 -- the packed weight tile is the B operand, and lane (r, c) of the A operand of step
 // j takes the 16 bytes at row r, column 32 j + 8 c of the run.
 //
-// Arithmetic.  A code becomes the fp16 integer q - z exactly (1024 + q by OR, minus 1024 + z); the
-// products of a group are summed in fp32 by the matrix core and the group's step is applied to the
-// sum, in fp32, with one FMA per output.  No dequantized weight is rounded.
+// Arithmetic.  A code becomes (q - z) 2^-9 in fp16, exactly (the masked codes are fp16 subnormals; one fused multiply-add
+// scales them and subtracts the zero point); the products of a group are summed in fp32 by the matrix core and the group's
+// step, times 2^9, is applied to the sum, in fp32, with one FMA per output.  No dequantized weight is rounded.
+// The vector instructions are chosen by what they cost with two waves to a SIMD (measured): 2.3 cycles for and, or, shift,
+// add and fp32 multiply-adds, 4.4 for v_and_or, packed fp16 and mixed-precision ones.  So a pair of codes costs 6.7 cycles where
+// v_and_or and a packed subtraction cost 9.1, and the steps are converted to fp32 once instead of 20 times.
 //
 // Pipeline.  Per run of 128 columns a wave expands NT weight tiles (4 steps x NT fragments in
 // registers), then walks its MT token tiles: 4 NT MFMAs and 4 NT FMAs (8 NT for two groups of 64) per
@@ -23,6 +26,13 @@
 // k ^ i, so that the fragment reads of 16 rows hit 16 different bank groups.  (Fragments
 // loaded from memory directly -- 64 pieces of 16 bytes per instruction -- ran at 14 B/clk per CU: 4 us per
 // token tile at K = 4096.)  The loads complete in order and are counted by hand.
+//
+// What bounds it (11008 x 4096 at 77 tokens, time stamps, 25 thousand cycles): the token tiles, 11 thousand, where the two waves
+// of a SIMD share its matrix pipe; the expansions, 4.7 thousand, which both do at the same time; 4.6 thousand until the first
+// words are there; waiting for the last wave and the exchange, 4.9 thousand.  Loading alone (62 B/clk per CU) would take
+// 12 thousand.  Started later, or with a raised priority throughout, one wave of a SIMD does not leave the other's
+// step; expanding the next run beside the MFMAs of this one takes 32 more registers per weight tile and was slower at every
+// shape (13.0 -> 14.8 us for 8192 x 4096 at 77 tokens).
 #include "awq_common.h"
 #include "awq_tile.h"
 
@@ -42,12 +52,17 @@ constexpr int raw_ofs(int) { return TILE_RING * UNIT_BYTES; }
 constexpr int sc_ofs(int nt) { return raw_ofs(nt) + nt * 1024; }
 constexpr int zp_ofs(int nt) { return sc_ofs(nt) + 256; }
 constexpr int wave_lds(int nt) { return zp_ofs(nt) + 256; }
-// token tiles whose partial sums are in LDS at once in the final exchange
-constexpr int tile_pass(int mt) { return (mt + (mt + 3) / 4 - 1) / ((mt + 3) / 4); }
-constexpr int tile_stride(int nt) { return 16 * nt + 4; }     // floats per row: rows 4 apart fall 16 banks apart
+// The final exchange: a 16 x 16 tile takes 320 floats, row 4 c + v at 80 c + 16 v (the rows of a write fall 16 banks
+// apart); token tiles whose partial sums are in LDS at once
+constexpr int EXCHANGE_TILE = 320;
+constexpr int tile_pass(int mt, int nt)
+{
+    const int fit = 16 / nt, passes = (mt + fit - 1) / fit;
+    return (mt + passes - 1) / passes;
+}
 constexpr int tile_lds(int mt, int nt)
 {
-    const int exchange = TILE_WAVES * tile_pass(mt) * 16 * tile_stride(nt) * 4, loop = TILE_WAVES * wave_lds(nt);
+    const int exchange = TILE_WAVES * tile_pass(mt, nt) * nt * EXCHANGE_TILE * 4, loop = TILE_WAVES * wave_lds(nt);
     return exchange > loop ? exchange : loop;
 }
 
@@ -85,32 +100,47 @@ __device__ __forceinline__ void wait_loads()
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-__device__ __forceinline__ uint32_t sub_pair(uint32_t a, uint32_t b)
+// Codes of up to four bits in bits 0 .. 9 of the halves of a dword are fp16 subnormals, multiples of 2^-24.  With f a power of
+// two that brings them to multiples of 2^-9 and nz = -z 2^-9 in both halves, (q - z) 2^-9, exactly.
+__device__ __forceinline__ uint32_t centred(uint32_t codes, uint32_t f, uint32_t nz)
 {
-    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, a) - __builtin_bit_cast(half2_t, b));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(half2_t, codes), __builtin_bit_cast(half2_t, f),
+                                                                  __builtin_bit_cast(half2_t, nz)));
+}
+__device__ __forceinline__ constexpr uint32_t half_pair(int exponent) { return (uint32_t)(exponent + 15) * 0x04000400u; }   // 2^exponent twice
+// -z 2^-9 in both halves, z in the low bits (up to four) of a dword
+__device__ __forceinline__ uint32_t negated_zero(uint32_t z)
+{
+    const half2_t minus = __builtin_bit_cast(half2_t, half_pair(15) | 0x80008000u);
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, z * 0x00010001u) * minus);
 }
 
 template <int BITS, int MT, int NT>
 __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
     const unsigned char *__restrict__ x, const unsigned char *__restrict__ qweight,
     const unsigned char *__restrict__ scales, const unsigned char *__restrict__ zeros,
-    half_t *__restrict__ y, int M, int N, int K, int tiles_n, int tiles_total, double *__restrict__ loss)
+    half_t *__restrict__ y, int M, int N, int K, int tiles_n, uint32_t tiles_n_inverse, int tiles_total,
+    double *__restrict__ loss)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     asm volatile("" ::"s"(x), "s"(qweight), "s"(scales), "s"(zeros), "s"(y), "s"(M), "s"(N), "s"(K),
-                 "s"(tiles_n), "s"(tiles_total), "s"(loss));          // arguments in one round
+                 "s"(tiles_n), "s"(tiles_n_inverse), "s"(tiles_total), "s"(loss));          // arguments in one round
     // contiguous ranges of tiles, token-tile-major, per XCD (own L2): see gemm_kernel
     const int per_xcd = (tiles_total + 7) >> 3;
     const int unit = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
     if (unit >= tiles_total || ((int)blockIdx.x >> 3) >= per_xcd) return;
-    const int tile_m = unit / tiles_n, tile_n = unit - tile_m * tiles_n;
+    // unit / tiles_n by the inverse floor((2^32 - 1) / tiles_n), which is one too small at most: a division by an argument is
+    // 150 cycles in front of the first load
+    int tile_m = (int)(((uint64_t)(uint32_t)unit * tiles_n_inverse) >> 32);
+    if (unit - tile_m * tiles_n >= tiles_n) ++tile_m;
+    const int tile_n = unit - tile_m * tiles_n;
     const uint32_t lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t r = lane & 15, c = lane >> 4;
     const int G = K / RUN;
     // the wave's runs: wave, wave + 8, ..., walked in cyclic order from a start of the workgroup's own
     const int cnt = (G - wave + TILE_WAVES - 1) / TILE_WAVES;
-    const int rot = cnt > 0 ? unit % cnt : 0;
+    const int rot = (int)(((uint64_t)((uint32_t)unit * 0x9E3779B9u) * (uint32_t)max(cnt, 0)) >> 32);
     auto run_at = [&](int i) {                             // i-th run; past the end: a harmless repeat
         i = min(i, cnt - 1) + rot;
         return wave + TILE_WAVES * (i < cnt ? i : i - cnt);
@@ -135,15 +165,6 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
 #pragma unroll
         for (int n = 0; n < NT; ++n) tot[m][n] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    // masks in SGPRs, magic numbers in VGPRs: (w & mask) | magic is then one v_and_or_b32
-    uint32_t mask_lo = 0x000F000Fu, mask_hi = 0x00F000F0u, mask2 = 0x00030003u;
-    uint32_t magA = 0x64006400u, magB = 0x54005400u;
-    uint32_t mask3[3] = {0x00070007u, 0x00380038u, 0x01C001C0u}, mag3[3] = {0x64006400u, 0x58005800u, 0x4C004C00u};
-    asm("" : "+s"(mask_lo), "+s"(mask_hi), "+s"(mask2));
-    asm("" : "+v"(magA), "+v"(magB));
-    asm("" : "+s"(mask3[0]), "+s"(mask3[1]), "+s"(mask3[2]));
-    asm("" : "+v"(mag3[0]), "+v"(mag3[1]), "+v"(mag3[2]));
-
     // x: load i (0..3) of a token tile takes its rows 4 i + c, lane r the chunk that belongs at place r
     uint32_t xofs[4];
 #pragma unroll
@@ -152,9 +173,8 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
         const unsigned char *p = x + ((size_t)first_row(m) * K + (size_t)run * RUN) * 2;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            uint32_t at = xofs[i];
-            asm volatile("" : "+v"(at));                   // a 32-bit offset beside a wave-uniform base, not a 64-bit address
-            dma<16>(p + at, lds0 + slot + i * 1024);
+            asm volatile("" : "+v"(xofs[i]));              // a 32-bit offset beside a wave-uniform base, not a 64-bit address
+            dma<16>(p + xofs[i], lds0 + slot + i * 1024);
         }
     };
     constexpr int RAW_LOADS = NT + 2;
@@ -217,59 +237,58 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
             }
             half8_t bf[NT][4];
             float s0[NT], s1[NT];
+            __builtin_amdgcn_s_setprio(1);                 // (1 to 4 %: a wave that expands lets the other's MFMAs wait, not itself)
             const int hb = run_at(i) & 1;
-            const float f0 = hb ? 0.0625f : 1.0f, f1 = hb ? 0.015625f : 0.25f;      // 4^-t, BITS = 2
 #pragma unroll
             for (int n = 0; n < NT; ++n) {
                 if (BITS == 3) {
-                    // pair 5 i + f of word i at bits 3 f: 1024 + q, 128 + q or 16 + q by its place in the mantissa; pair 15
-                    // in the top bits of the three words
-                    const uint32_t z = (zraw[n] >> ((r & 1) * 4)) & 0xFu;
-                    const uint32_t zf[3] = {mag3[0] | (z * 0x00010001u), mag3[1] | (z * 0x00080008u), mag3[2] | (z * 0x00400040u)};
-                    s0[n] = s1[n] = (float)__builtin_bit_cast(half_t, (uint16_t)sraw[n]);
+                    // pair 5 i + f of word i at bits 3 f; pair 15 in the top bits of the three words
+                    const uint32_t nz = negated_zero((zraw[n] >> ((r & 1) * 4)) & 0xFu);
+                    s0[n] = s1[n] = (float)__builtin_bit_cast(half_t, (uint16_t)sraw[n]) * 512.0f;
                     uint32_t pr[16];
 #pragma unroll
                     for (int i = 0; i < 3; ++i) {
                         const uint32_t w = q3[n][i], w9 = w >> 9;
 #pragma unroll
                         for (int f = 0; f < 5; ++f)
-                            pr[5 * i + f] = sub_pair(((f < 3 ? w : w9) & mask3[f % 3]) | mag3[f % 3], zf[f % 3]);
+                            pr[5 * i + f] = centred((f < 3 ? w : w9) & (0x00070007u << (3 * (f % 3))), half_pair(15 - 3 * (f % 3)), nz);
                     }
                     const uint32_t top = ((q3[n][0] >> 15) & 0x00010001u) | ((q3[n][1] >> 14) & 0x00020002u) |
                                          ((q3[n][2] >> 13) & 0x00040004u);
-                    pr[15] = sub_pair(top | mag3[0], zf[0]);
+                    pr[15] = centred(top, half_pair(15), nz);
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
                         bf[n][j] = __builtin_bit_cast(half8_t, u32x4{pr[4 * j], pr[4 * j + 1], pr[4 * j + 2], pr[4 * j + 3]});
                 } else if (BITS == 4) {
-                    const uint32_t z = (zraw[n] >> ((r & 1) * 4)) & 0xFu;
-                    const uint32_t zA = magA | (z * 0x00010001u), zB = magB | (z * 0x00100010u);
-                    s0[n] = s1[n] = (float)__builtin_bit_cast(half_t, (uint16_t)sraw[n]);
+                    const uint32_t nz = negated_zero((zraw[n] >> ((r & 1) * 4)) & 0xFu);
+                    s0[n] = s1[n] = (float)__builtin_bit_cast(half_t, (uint16_t)sraw[n]) * 512.0f;
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const uint32_t w = q[n][j], w8 = w >> 8;
                         bf[n][j] = __builtin_bit_cast(half8_t, u32x4{
-                            sub_pair((w & mask_lo) | magA, zA), sub_pair((w & mask_hi) | magB, zB),
-                            sub_pair((w8 & mask_lo) | magA, zA), sub_pair((w8 & mask_hi) | magB, zB)});
+                            centred(w & 0x000F000Fu, half_pair(15), nz), centred(w & 0x00F000F0u, half_pair(11), nz),
+                            centred(w8 & 0x000F000Fu, half_pair(15), nz), centred(w8 & 0x00F000F0u, half_pair(11), nz)});
                     }
                 } else {
-                    // groups t = 2 hb, 2 hb + 1 of the block: codes at bits 2t of a half, scaled by 4^t
-                    const uint32_t zz = zraw[n] * 0x00010001u;
+                    // groups t = 2 hb, 2 hb + 1 of the block: codes at bits 2t of a half
                     const half2_t ss = __builtin_bit_cast(half2_t, sraw[n]);
-                    s0[n] = (float)ss[0] * f0;
-                    s1[n] = (float)ss[1] * f1;
+                    s0[n] = (float)ss[0] * 512.0f;
+                    s1[n] = (float)ss[1] * 512.0f;
 #pragma unroll
                     for (int t = 0; t < 2; ++t) {
-                        const uint32_t mk = mask2 << (4 * hb + 2 * t);
-                        const uint32_t zt = (zz & mk) | magA;
+                        const uint32_t mk = 0x00030003u << (4 * hb + 2 * t), f = half_pair(15 - 4 * hb - 2 * t);
+                        const uint32_t nz = negated_zero((zraw[n] >> (4 * hb + 2 * t)) & 3u);
 #pragma unroll
                         for (int j = 0; j < 2; ++j)
                             bf[n][2 * t + j] = __builtin_bit_cast(half8_t, u32x4{
-                                sub_pair(((q[n][0] >> (8 * j)) & mk) | magA, zt), sub_pair(((q[n][1] >> (8 * j)) & mk) | magA, zt),
-                                sub_pair(((q[n][2] >> (8 * j)) & mk) | magA, zt), sub_pair(((q[n][3] >> (8 * j)) & mk) | magA, zt)});
+                                centred((q[n][0] >> (8 * j)) & mk, f, nz), centred((q[n][1] >> (8 * j)) & mk, f, nz),
+                                centred((q[n][2] >> (8 * j)) & mk, f, nz), centred((q[n][3] >> (8 * j)) & mk, f, nz)});
                     }
                 }
+                // (steps in fp32 registers: left to itself the compiler multiplies with the fp16 step, at half the rate)
+                asm("" : "+v"(s0[n]), "+v"(s1[n]));
             }
+            __builtin_amdgcn_s_setprio(0);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int m = 0; m < MT; ++m) {
@@ -311,14 +330,15 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
     }
     __syncthreads();                                       // the exchange below reuses every wave's LDS
 
-    // Sum over the waves.  Lane (r, c) holds rows 4 c + v, column r of each 16 x 16 tile.
-    constexpr int MC = tile_pass(MT), ST = tile_stride(NT), ROWS = 16 * MC;
+    // Sum over the waves.  Lane (r, c) holds rows 4 c + v, column r of each 16 x 16 tile.  All tiles that fit at once: in passes
+    // of three token tiles, each with a nearly empty second round of lanes, this took 3.8 thousand cycles at (5, 3), now 2.8.
+    constexpr int MC = tile_pass(MT, NT), TILES = MC * NT;
     // With `loss` (the scale search, 4-bit): nothing is stored, y holds the layer's reference outputs, and
     // loss[workgroup] becomes the sum of the squared differences of the outputs, rounded to fp16, to them: four squared
     // and added in fp32, the rest in fp64, in a fixed order.
     float *lds = reinterpret_cast<float *>(smem);
     double diff = 0.0;
-    float *mine = lds + wave * (ROWS * ST);
+    float *mine = lds + wave * (TILES * EXCHANGE_TILE) + 80 * c + r;
 #pragma unroll
     for (int p = 0; p < MT; p += MC) {
         if (p > 0) __syncthreads();
@@ -329,18 +349,21 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
                 for (int n = 0; n < NT; ++n)
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        mine[(16 * i + 4 * c + v) * ST + 16 * n + r] = tot[p + i < MT ? p + i : 0][n][v];
+                        mine[(i * NT + n) * EXCHANGE_TILE + 16 * v] = tot[p + i < MT ? p + i : 0][n][v];
             }
         __syncthreads();
-        for (int e = threadIdx.x; e < ROWS * 4 * NT; e += 64 * TILE_WAVES) {
-            const int row = e / (4 * NT), col = (e - row * (4 * NT)) * 4;
-            const int mt = p + (row >> 4), m = first_row(mt) + (row & 15), n = nt0 * 16 + col;
-            if (mt >= MT || m < m0 + 16 * mt || m >= M || n >= N) continue;
-            const float *src = lds + row * ST + col;
+        // a wave adds whole tiles, a lane four columns of a row
+#pragma unroll
+        for (int t0 = 0; t0 < TILES; t0 += TILE_WAVES) {
+            const int t = t0 + wave, i = t / NT;
+            const int row = lane >> 2, col = ((t - i * NT) * 4 + (lane & 3)) * 4;
+            const int mt = p + i, m = first_row(mt) + row, n = nt0 * 16 + col;
+            if (t >= TILES || mt >= MT || m < m0 + 16 * mt || m >= M || n >= N) continue;
+            const float *src = lds + t * EXCHANGE_TILE + 80 * (row >> 2) + 16 * (row & 3) + 4 * (lane & 3);
             float4 s = *reinterpret_cast<const float4 *>(src);
 #pragma unroll
             for (int w = 1; w < TILE_WAVES; ++w) {
-                const float4 b = *reinterpret_cast<const float4 *>(src + w * (ROWS * ST));
+                const float4 b = *reinterpret_cast<const float4 *>(src + w * (TILES * EXCHANGE_TILE));
                 s.x += b.x; s.y += b.y; s.z += b.z; s.w += b.w;
             }
             const half2_t lo = {(half_t)s.x, (half_t)s.y}, hi = {(half_t)s.z, (half_t)s.w};
@@ -390,7 +413,7 @@ int launch_one(const void *x, const void *qweight, const void *scales, const voi
     }
     tile_kernel<BITS, MT, NT><<<dim3((unsigned)((total + 7) / 8 * 8)), dim3(64 * TILE_WAVES), lds, stream>>>(
         (const unsigned char *)x, (const unsigned char *)qweight, (const unsigned char *)scales,
-        (const unsigned char *)zeros, (half_t *)y, M, N, K, tiles_n, (int)total, loss);
+        (const unsigned char *)zeros, (half_t *)y, M, N, K, tiles_n, 0xFFFFFFFFu / (uint32_t)tiles_n, (int)total, loss);
     return awq_launch_status();
 }
 
