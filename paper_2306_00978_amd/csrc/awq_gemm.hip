@@ -181,34 +181,46 @@ __device__ __forceinline__ half8_t dq_result(const DqWord &d)
 // leaves the sum over its tile of the squared differences to them in loss[tile] -- of the outputs
 // rounded to fp16, eight differences squared and added in fp32, the rest in fp64, in a fixed order, as the
 // separate pass over two stored outputs does it.
+// How the units of a launch are numbered, without a division in the kernel (two by arguments and one in 64 bits are 0.4 us
+// in front of the first load): a / b is the high half of a times floor((2^32 - 1) / b), one too small at most.
+struct GemmUnits {
+    int tiles_n, ksplit, units_total, group_base, group_rem;      // G = ksplit * group_base + group_rem
+    uint32_t tiles_n_inverse, ksplit_inverse;
+};
+__device__ __forceinline__ int quotient(int a, int b, uint32_t inverse)
+{
+    const int q = (int)(((uint64_t)(uint32_t)a * inverse) >> 32);
+    return a - q * b >= b ? q + 1 : q;
+}
+
 enum { GEMM_PLAIN, GEMM_SPLIT, GEMM_LOSS };
 template <int MODE>
 __global__ __launch_bounds__(512, 1) void gemm_kernel(
     const half_t *__restrict__ x, const unsigned char *__restrict__ qweight,
     const unsigned char *__restrict__ scales, const unsigned char *__restrict__ zeros,
-    half_t *__restrict__ y, int M, int N, int K, int G, int tiles_n, int tiles_total,
-    float *__restrict__ part, int ksplit, double *__restrict__ loss)
+    half_t *__restrict__ y, int M, int N, int K, int G, const GemmUnits U, float *__restrict__ part,
+    double *__restrict__ loss)
 {
     constexpr bool SPLIT = MODE == GEMM_SPLIT;
     extern __shared__ __align__(16) unsigned char smem[];
     // all arguments fetched in one round (otherwise one scalar-cache miss per first use)
     asm volatile("" ::"s"(x), "s"(qweight), "s"(scales), "s"(zeros), "s"(y), "s"(M), "s"(N), "s"(K), "s"(G),
-                 "s"(tiles_n), "s"(tiles_total), "s"(part), "s"(ksplit), "s"(loss));
+                 "s"(U.tiles_n), "s"(U.ksplit), "s"(U.units_total), "s"(U.group_base), "s"(U.group_rem), "s"(U.tiles_n_inverse),
+                 "s"(U.ksplit_inverse), "s"(part), "s"(loss));
     // Workgroups are handed to the eight XCDs round-robin by their linear id, and each XCD has
     // its own L2.  The tile a workgroup computes is therefore chosen so that an XCD gets a
     // contiguous range of tiles in token-block-major order: its workgroups then share a few x
     // row blocks and sweep the same weight groups at about the same time, which keeps the
     // operand traffic inside that L2.
-    const int units_total = SPLIT ? tiles_total * ksplit : tiles_total;      // (tile, K range) pairs
-    const int per_xcd = (units_total + 7) >> 3;
+    const int per_xcd = (U.units_total + 7) >> 3;            // units: (tile, K range) pairs
     const int unit = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
-    if (unit >= units_total) return;
-    const int tile = SPLIT ? unit / ksplit : unit;
-    const int ks = SPLIT ? unit - tile * ksplit : 0;
-    // groups [gofs, gofs + GL) of the G of a row
-    const int gofs = SPLIT ? (int)(((int64_t)G * ks) / ksplit) : 0;
-    const int GL = SPLIT ? (int)(((int64_t)G * (ks + 1)) / ksplit) - gofs : G;
-    const int tile_m = tile / tiles_n, tile_n = tile - tile_m * tiles_n;
+    if (unit >= U.units_total) return;
+    const int tile = SPLIT ? quotient(unit, U.ksplit, U.ksplit_inverse) : unit;
+    const int ks = SPLIT ? unit - tile * U.ksplit : 0;
+    // groups [gofs, gofs + GL) of the G of a row: the first ranges are one longer where the count does not divide G
+    const int gofs = SPLIT ? ks * U.group_base + min(ks, U.group_rem) : 0;
+    const int GL = SPLIT ? U.group_base + (ks < U.group_rem ? 1 : 0) : G;
+    const int tile_m = quotient(tile, U.tiles_n, U.tiles_n_inverse), tile_n = tile - tile_m * U.tiles_n;
     const DqConsts kc = dq_consts();
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
     const int tid = threadIdx.x;
@@ -467,16 +479,21 @@ __global__ __launch_bounds__(512, 1) void gemm_kernel(
     }
 }
 
-// y = fp16(sum over the K ranges of the fp32 partial tiles), four outputs per thread
-__global__ __launch_bounds__(256) void gemm_reduce_kernel(const float4 *__restrict__ part, uint2 *__restrict__ y,
-                                                          int64_t quads, int ksplit)
+// y = fp16(sum over the KS ranges of the fp32 partial tiles), four outputs per thread, all ranges requested at once (one by
+// one they are a chain of KS round trips)
+template <int KS>
+__global__ __launch_bounds__(256) void gemm_reduce_kernel(const float4 *__restrict__ part, uint2 *__restrict__ y, int64_t quads)
 {
+    asm volatile("" ::"s"(part), "s"(y), "s"(quads));        // arguments in one round
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= quads) return;
-    float4 a = part[i];
-    for (int k = 1; k < ksplit; ++k) {
-        const float4 b = part[(int64_t)k * quads + i];
-        a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+    float4 v[KS];
+#pragma unroll
+    for (int k = 0; k < KS; ++k) v[k] = part[(int64_t)k * quads + i];
+    float4 a = v[0];
+#pragma unroll
+    for (int k = 1; k < KS; ++k) {
+        a.x += v[k].x; a.y += v[k].y; a.z += v[k].z; a.w += v[k].w;
     }
     const half2_t lo = {(half_t)a.x, (half_t)a.y}, hi = {(half_t)a.z, (half_t)a.w};
     y[i] = make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
@@ -532,6 +549,8 @@ int gemm_launch_any(const void *x, const void *qweight, const void *scales, cons
     const int64_t tiles_total = (int64_t)tiles_n * ((M + BM - 1) / BM);
     if (tiles_total * ksplit > (1 << 30)) return AWQ_ERR_BAD_SHAPE;
     const dim3 grid((unsigned)((tiles_total * ksplit + 7) / 8 * 8)), block(512);
+    const GemmUnits units = {tiles_n, ksplit, (int)(tiles_total * ksplit), G / ksplit, G % ksplit, 0xFFFFFFFFu / (uint32_t)tiles_n,
+                             0xFFFFFFFFu / (uint32_t)ksplit};
     static AwqOncePerDevice once;
     std::atomic<bool> &attr_set = once.here();
     if (!attr_set.load(std::memory_order_relaxed)) {
@@ -542,8 +561,7 @@ int gemm_launch_any(const void *x, const void *qweight, const void *scales, cons
     }
     gemm_kernel<MODE><<<grid, block, LDS_BYTES, stream>>>(
         (const half_t *)x, (const unsigned char *)qweight, (const unsigned char *)scales,
-        (const unsigned char *)zeros, (half_t *)y, M, N, K, G, tiles_n, (int)tiles_total, part, ksplit,
-        loss);
+        (const unsigned char *)zeros, (half_t *)y, M, N, K, G, units, part, loss);
     return awq_launch_status();
 }
 
@@ -563,8 +581,19 @@ int awq_gemm_launch_split(const void *x, const void *qweight, const void *scales
     int st = gemm_launch_any<GEMM_SPLIT>(x, qweight, scales, zeros, y, M, N, K, (float *)part, ksplit, nullptr, stream);
     if (st != AWQ_OK) return st;
     const int64_t quads = (int64_t)M * N / 4;
-    gemm_reduce_kernel<<<dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream>>>(
-        (const float4 *)part, (uint2 *)y, quads, ksplit);
+    const dim3 grid((unsigned)((quads + 255) / 256)), block(256);
+    const float4 *p = (const float4 *)part;
+    uint2 *out = (uint2 *)y;
+    switch (ksplit) {
+    case 2: gemm_reduce_kernel<2><<<grid, block, 0, stream>>>(p, out, quads); break;
+    case 3: gemm_reduce_kernel<3><<<grid, block, 0, stream>>>(p, out, quads); break;
+    case 4: gemm_reduce_kernel<4><<<grid, block, 0, stream>>>(p, out, quads); break;
+    case 5: gemm_reduce_kernel<5><<<grid, block, 0, stream>>>(p, out, quads); break;
+    case 6: gemm_reduce_kernel<6><<<grid, block, 0, stream>>>(p, out, quads); break;
+    case 7: gemm_reduce_kernel<7><<<grid, block, 0, stream>>>(p, out, quads); break;
+    case 8: gemm_reduce_kernel<8><<<grid, block, 0, stream>>>(p, out, quads); break;
+    default: return AWQ_ERR_BAD_SHAPE;                       // awq_gemm_ksplit gives 2 to 8 where there is a workspace
+    }
     return awq_launch_status();
 }
 
