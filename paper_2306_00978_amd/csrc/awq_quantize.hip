@@ -325,36 +325,52 @@ __global__ __launch_bounds__(256, CLIP ? 1 : AWQ_QUANT_MIN_WAVES) void quantize_
 }
 
 // One grid point of the scale search: W diag(s) quantized by the first workgroups, xs = x / s by the others.  The
-// two do not depend on each other; apart they are two launches too short to reach the memory's rate, the
-// first bound by instruction issue, the second by memory (4096 x 4096, 2048 rows: 12.3 + 7.1 us, together 17.9).
+// two do not depend on each other; apart they are two launches too short to reach the memory's rate.  Both are bound by
+// instruction issue, at the low clock that the products in between leave: a dividing wave therefore keeps the
+// scales of its 64 runs of eight columns, and their reciprocals, for all its rows.  (4096 x 4096, 2048 rows: 17.1 us with a
+// division per element and the run of a thread by a 64-bit modulo, 16.1 now; 1722 x 3472 x 2304 10.3 and 9.7.)
 struct InvArgs {
     const uint4 *x;
     const float4 *s;
     uint4 *xs;
-    int64_t runs;          // M * K / 8
-    int K8, first_block;
+    int M, K8;             // K8: runs of a row
+    int strips, rows;      // strips of 64 runs, rows of a wave (a multiple of INV_ROWS)
+    int first_block, units;
 };
-constexpr int INV_RUNS = 4;                        // 16-byte runs per thread, requested together
+constexpr int INV_ROWS = 4;                        // requested together
+__device__ __forceinline__ void inverse_wave(const InvArgs &I)
+{
+    const int lane = threadIdx.x & 63;
+    const int unit = __builtin_amdgcn_readfirstlane(((int)blockIdx.x - I.first_block) * 4 + (threadIdx.x >> 6));
+    if (unit >= I.units) return;
+    const int part = unit / I.strips, strip = unit - part * I.strips;
+    const int run = 64 * strip + lane, at = min(run, I.K8 - 1);
+    const int m0 = part * I.rows, m1 = min(I.M, m0 + I.rows);
+    const float4 a = I.s[2 * at], b = I.s[2 * at + 1];
+    uint4 cur[INV_ROWS], nxt[INV_ROWS];
+    auto request = [&](uint4 (&raw)[INV_ROWS], int m) {          // rows past the end repeat the last one
+#pragma unroll
+        for (int u = 0; u < INV_ROWS; ++u) raw[u] = I.x[(int64_t)min(m + u, m1 - 1) * I.K8 + at];
+    };
+    request(cur, m0);
+    const float s[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    float y[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[e] = 1.0f / s[e];
+    for (int m = m0; m < m1; m += INV_ROWS) {
+        request(nxt, m + INV_ROWS);
+#pragma unroll
+        for (int u = 0; u < INV_ROWS; ++u) {
+            const uint4 out = inv_scaled_by(cur[u], s, y);
+            if (run < I.K8 && m + u < m1) I.xs[(int64_t)(m + u) * I.K8 + run] = out;
+            cur[u] = nxt[u];
+        }
+    }
+}
 __global__ __launch_bounds__(256, AWQ_QUANT_MIN_WAVES) void quantize_inv_kernel(const QuantArgs A, const InvArgs I)
 {
-    if ((int)blockIdx.x < I.first_block) {
-        quantize_wave<false, false>(A, ClipRatios{});
-        return;
-    }
-    const int64_t i0 = (int64_t)((int)blockIdx.x - I.first_block) * (256 * INV_RUNS) + threadIdx.x;
-    uint4 raw[INV_RUNS];
-    float4 a[INV_RUNS], b[INV_RUNS];
-#pragma unroll
-    for (int u = 0; u < INV_RUNS; ++u) {
-        const int64_t i = min(i0 + 256 * u, I.runs - 1);
-        const int run = (int)(i % I.K8);
-        raw[u] = I.x[i];
-        a[u] = I.s[2 * run];
-        b[u] = I.s[2 * run + 1];
-    }
-#pragma unroll
-    for (int u = 0; u < INV_RUNS; ++u)
-        if (i0 + 256 * u < I.runs) I.xs[i0 + 256 * u] = inv_scaled(raw[u], a[u], b[u]);
+    if ((int)blockIdx.x < I.first_block) quantize_wave<false, false>(A, ClipRatios{});
+    else inverse_wave(I);
 }
 
 __global__ __launch_bounds__(256) void unpack_kernel(
@@ -458,8 +474,14 @@ int quantize_launch(const QuantJob *jobs, int count, const ClipRatios *ratios, h
         const dim3 grid((unsigned)((units + 3) / 4)), block(256);
         if (inv) {
             inv->first_block = (int)grid.x;
-            const int64_t blocks = grid.x + (inv->runs + 256 * INV_RUNS - 1) / (256 * INV_RUNS);
-            if (blocks > 0x7fffffff) return AWQ_ERR_BAD_SHAPE;
+            // one wave to a SIMD, beside two that quantize
+            inv->strips = (inv->K8 + 63) / 64;
+            const int64_t rows = ((int64_t)inv->M * inv->strips + 1023) / 1024;
+            inv->rows = (int)((rows + INV_ROWS - 1) / INV_ROWS * INV_ROWS);
+            const int64_t waves = (int64_t)((inv->M + inv->rows - 1) / inv->rows) * inv->strips;
+            const int64_t blocks = grid.x + (waves + 3) / 4;
+            if (waves > 0x3fffffff || blocks > 0x7fffffff) return AWQ_ERR_BAD_SHAPE;
+            inv->units = (int)waves;
             quantize_inv_kernel<<<dim3((unsigned)blocks), block, 0, stream>>>(A, *inv);
         } else if (ratios && act) quantize_pack_kernel<true, true><<<grid, block, 0, stream>>>(A, *ratios);
         else if (ratios) quantize_pack_kernel<true, false><<<grid, block, 0, stream>>>(A, *ratios);
@@ -486,7 +508,7 @@ int awq_quantize_inv_launch(const void *W, const float *s, int64_t N, int64_t K,
                             const void *x, int64_t M, void *xs, hipStream_t stream)
 {
     const QuantJob j = {W, s, N, K, qweight, scales, zeros, nullptr, nullptr, 0};
-    InvArgs inv = {(const uint4 *)x, (const float4 *)s, (uint4 *)xs, M * (K / 8), (int)(K / 8), 0};
+    InvArgs inv = {(const uint4 *)x, (const float4 *)s, (uint4 *)xs, (int)M, (int)(K / 8), 0, 0, 0, 0};
     return quantize_launch(&j, 1, nullptr, stream, &inv);
 }
 

@@ -33,3 +33,15 @@ def test_a_band_that_is_too_narrow_is_caught(tmp_path):
     p = subprocess.run([_build(tmp_path, "narrow", "-DBAND_VALUE=1e-7f")], capture_output=True, text=True,
                        timeout=600)
     assert p.returncode == 1 and "MISS" in p.stdout
+
+
+def test_quotient_from_the_reciprocal_is_the_ieee_quotient_for_every_half(tmp_path):
+    """What the scale search divides activations by (csrc/awq_inv_scale.h, quotient_by): exact for every pair of significands, and
+    not without its correction."""
+    src = os.path.join(HERE, "reciprocal_quotient_check.c")
+    for name, defs, code in (("exact", (), 0), ("uncorrected", ("-DNO_CORRECTION",), 1)):
+        exe = str(tmp_path / name)
+        subprocess.run(["gcc", "-O3", "-march=native", "-ffp-contract=off", *defs, "-o", exe, src, "-lm", "-lpthread"], check=True)
+        p = subprocess.run([exe, str(min(8, os.cpu_count() or 1)), "1"], capture_output=True, text=True, timeout=600)
+        assert p.returncode == code, p.stdout
+        assert (", 0 mismatches" in p.stdout) == (code == 0)
