@@ -527,15 +527,26 @@ int awq_gemm_ksplit(int M, int N, int K, double *estimate_us)
     return best;
 }
 
-// The time of the launch that does not cut K: rounds of 256 workgroups, 6 us + 1.18 us a group each, and up to half as
-// much again as the chip fills, where the power limit lowers the clock.  Over 328 measured launches (25 shapes from
-// 16 x 512 to 128256 x 4096 and 28672 x 8192, 129 to 2048 tokens) 1.02 of the measured time, 2.5 % standard deviation, at most
-// 10 % off.  (The estimate above for one range, without the clock, is 12 % off by the same measure.)
+// The time of the launch that does not cut K: rounds of 256 workgroups, 5 us + 1.08 us a group each, and up to half as
+// much again as the chip fills, where the power limit lowers the clock.  186 measured launches (16 x 256 to 128256 x 4096 and
+// 28672 x 8192, 40 to 1500 tokens): 2.7 % rms, at most 9 % off.
 double awq_gemm_unsplit_us(int M, int N, int K)
 {
     const int64_t tiles = (int64_t)((N + BN - 1) / BN) * ((M + BM - 1) / BM);
     const double rounds = (double)((tiles + 255) / 256), full = (double)tiles / (256.0 * rounds);
-    return rounds * (6.0 + 1.18 * (K / AWQ_GROUP)) * (1.0 + 0.5 * full * full);
+    return 1.56 + rounds * (5.0 + 1.083 * (K / AWQ_GROUP)) * (1.0 + 0.46 * full * full);
+}
+
+// The time with K cut into awq_gemm_ksplit() ranges: the same with the groups of a range, and the second kernel, which moves
+// (ranges + 1/2) * M * N * 4 bytes at 4 TB/s after 7 us of launch, run-out and the first kernel's own stores.  122 launches: 4 % rms.
+// (The estimate above is 0.92 to 1.36 of the time; it stays what decides the number of ranges and the size of the workspace.)
+double awq_gemm_ranges_us(int M, int N, int K)
+{
+    const int G = K / AWQ_GROUP, ks = awq_gemm_ksplit(M, N, K, nullptr);
+    const int64_t units = (int64_t)((N + BN - 1) / BN) * ((M + BM - 1) / BM) * ks;
+    const double rounds = (double)((units + 255) / 256), full = (double)units / (256.0 * rounds);
+    return 7.19 + rounds * (2.185 + 1.088 * ((G + ks - 1) / ks)) * (1.0 + 0.342 * full * full) +
+           0.25 * (ks + 0.5) * (double)M * (double)N * 4.0e-6;
 }
 
 namespace {

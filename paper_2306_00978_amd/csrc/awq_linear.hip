@@ -20,6 +20,7 @@ int awq_gemm_launch_split(const void *x, const void *qweight, const void *scales
                           void *y, int M, int N, int K, void *part, int ksplit, hipStream_t stream);
 int awq_gemm_ksplit(int M, int N, int K, double *estimate_us);
 double awq_gemm_unsplit_us(int M, int N, int K);
+double awq_gemm_ranges_us(int M, int N, int K);
 
 // Only the prefill kernel at a few hundred tokens uses scratch: fp32 partial tiles of its K ranges.  (The
 // tile kernel has taken over part of these shapes and needs none; the figure stays what callers size
@@ -46,24 +47,18 @@ namespace {
 // kernel cuts K over the waves of a workgroup and pays with more reads of x (a tile is at most 128 x 48
 // or 96 x 64), so it wins until the prefill kernel fills the chip.
 //
-// Without a workspace: up to 128 tokens always (blocks of 16 through the decode kernels, which ran before, took
-// 1.25 to 7.5 times as long over 25 shapes; the prefill kernel 43 us where 4096 x 4096 at 128 tokens takes 10.7), beyond by the two estimates, the tile
-// kernel's with its margin: 4096 x 4096 at 300 / 512 / 700 tokens 17.4 / 28.1 / 36.8 us against 43 / 45 / 48;
-// 8192 x 28672 at 300 / 512 tokens 199 / 354 against 287 / 297.
-// With a workspace K is cut into ranges and the estimate is that form's, which is itself 0.92 to 1.36 of what it
-// really takes.  Up to 128 tokens the estimates stand side by side (us, tile kernel and ranges: 11008 x 4096 at 128 17.3 /
-// 25.6; 32000 x 4096 at 96 / 128 36.8 / 44.1 and 53.5 / 46.0; 28672 x 8192 at 96 / 128 58.8 / 66.2 and 90.4 / 69.1); beyond, the tile kernel
-// has to win by a fifth.  That is cautious: 4096 x 4096 at 400 / 512 tokens runs over ranges, 30.1 / 34.3, where the
-// call without a workspace takes 25.6 / 28.1.
+// By the estimates, the tile kernel's with its margin.  Without a workspace (us, tile kernel and K whole): 4096 x 4096 at 300 /
+// 512 / 1000 tokens 18.1 / 28.5 / 51.2 and 42.7 / 44.1 / 48.3; up to 160 tokens always the tile kernel, which rounds no weight and
+// is the slower one from 32000 features on only (160 tokens 9 %, 128256 features at 128 tokens 197 and 117).
+// With one (tile kernel and ranges): 4096 x 4096 at 400 / 700 / 1000 24.7 / 36.2 / 51.2 and 29.2 / 37.8 / 42.7; 4096 x 11008 at 256 / 500
+// 32.2 / 64.7 and 36.0 / 52.4; 28672 x 8192 at 96 / 128 58.2 / 86.9 and 59.6 / 62.7.  Over 90 shapes from 1024 x 1024 to 11008 x 11008 at 60
+// to 1500 tokens the chosen form took 0.8 % longer than the fastest one on average, 11 % at most (with a margin of a fifth 1.8 %
+// and 25 %).
 bool takes_tile_kernel(const TilePlan &plan, int M, int N, int K, bool split)
 {
     if (awq_tile_override() >= 0) return awq_tile_forced();
-    if (split) {
-        double ranges_us = 0.0;
-        (void)awq_gemm_ksplit(M, N, K, &ranges_us);
-        return (M <= 128 ? 1.0 : 1.2) * plan.us < ranges_us;
-    }
-    return M <= 128 || awq_tile_margin(K) * plan.us < awq_gemm_unsplit_us(M, N, K);
+    if (split) return (M <= 128 ? 1.0 : awq_tile_margin(K)) * plan.us < awq_gemm_ranges_us(M, N, K);
+    return M <= 160 || awq_tile_margin(K) * plan.us < awq_gemm_unsplit_us(M, N, K);
 }
 
 }  // namespace

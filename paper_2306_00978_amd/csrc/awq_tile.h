@@ -11,10 +11,9 @@ struct TilePlan {
 // The workgroup shape with the smallest estimated time.
 TilePlan awq_tile_plan(int M, int N, int K);
 
-// What a launch of more than 128 tokens takes at most, in units of its estimate: it runs at a lower clock than the small
-// ones that the estimate was fitted to (1.04 to 1.19 over 129 to 700 tokens at K up to 13824), and its waves wait for
-// more than they compute where K is very long (K = 28672: 1.24 to 1.45 with 8192 features, up to 1.6 with 512).
-inline double awq_tile_margin(int K) { return K <= 8192 ? 1.2 : 1.2 + 0.35 * (K - 8192) / 20480.0; }
+// By how much its estimate has to be below the other kernel's: where K is long its waves wait for more than they
+// compute (K = 28672: 1.05 to 1.6 of the estimate).
+inline double awq_tile_margin(int K) { return K <= 8192 ? 1.0 : 1.0 + 0.6 * (K - 8192) / 20480.0; }
 
 // The tuning build can force the shape (AWQ_TILE_PLAN = 10 * mt + nt, at every token count above 16) or, with 0, the
 // kernels that run where this one does not.

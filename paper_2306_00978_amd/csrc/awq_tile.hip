@@ -446,10 +446,11 @@ TileFn pick(int mt, int nt)
 
 }  // namespace
 
-// A launch takes 1.1 us and, per round of 256 workgroups (one per CU: the LDS), 1.5 us plus for every
-// run of a wave 0.235 us per token tile (32 KB of x per CU and tile for the eight waves: 64 B/clk), 0.22 us per
-// weight tile and 0.02 us per pair, plus 0.08 us per pair for the exchange -- fitted to 24 shapes
-// (4096 x 4096, 11008 x 4096, 4096 x 11008 at 17..500 tokens, both bit widths, all MT and NT; rms error 6 %).
+// A launch takes 1.28 us and, per round of 256 workgroups (one per CU: the LDS), 1.41 us plus for every
+// run of a wave 0.226 us per token tile (32 KB of x per CU and tile for the eight waves: 62 B/clk), 0.165 us per
+// weight tile and 0.015 us per pair (a twelfth more where four weight tiles leave a shorter ring), plus 0.067 us per pair
+// for the exchange; up to a quarter more as the round fills the chip.  Fitted to 680 launches of 168 shapes (256 x 4096 to
+// 128256 x 4096 and 4096 x 14336, 40 to 1500 tokens, the four likeliest shapes of a workgroup each): rms error 6 %.
 TilePlan awq_tile_plan(int M, int N, int K)
 {
     const int forced = awq_tile_override();
@@ -460,8 +461,9 @@ TilePlan awq_tile_plan(int M, int N, int K)
         for (int nt = 1; nt <= 4; ++nt) {
             if (!tile_built(mt, nt)) continue;
             const int64_t wgs = awq_tile_count({mt, nt, 0.0}, M, N);
-            const double us = 1.1 + (double)((wgs + 255) / 256) *
-                                        (1.5 + runs * (0.235 * mt + 0.22 * nt + 0.02 * mt * nt) + 0.08 * mt * nt);
+            const double rounds = (double)((wgs + 255) / 256), full = (double)wgs / (256.0 * rounds);
+            const double loop = runs * (0.226 * mt + 0.165 * nt + 0.015 * mt * nt) * (nt == 4 ? 1.089 : 1.0);
+            const double us = 1.275 + rounds * (1.408 + loop + 0.067 * mt * nt) * (1.0 + 0.237 * full * full);
             if (best.us < 0.0 || us < best.us) best = {mt, nt, us};
         }
     return best;

@@ -209,3 +209,14 @@ def test_prefill_kernel_at_its_shortest_k(N, K):
     assert bool(torch.isnan(buf[M * N:]).all()) and np.all(np.isfinite(got.astype(np.float32)))
     err = oracle.norm_error(got, oracle.matmul(x, Wdq), x, Wdq)
     assert err.max() <= TOL, err.max()
+
+
+@pytest.mark.parametrize("bits,N,K,M,used", [
+    (4, 4096, 4096, 400, False),                     # the estimates side by side (us, tile kernel and ranges: 24.7, 29.2)
+    (4, 4096, 4096, 1000, True),                     # 51.2, 42.7
+    (4, 4096, 11008, 256, False),                    # long K, the tile kernel's estimate with its margin: 32.2, 36.0
+    (4, 4096, 11008, 500, True),                     # 64.7, 52.4
+    (3, 4096, 4096, 160, False),                     # the last token count that takes the tile kernel without a look
+])
+def test_line_where_both_kernels_have_estimates(bits, N, K, M, used):
+    test_line_between_the_tile_and_the_prefill_kernel(bits, N, K, M, used)
