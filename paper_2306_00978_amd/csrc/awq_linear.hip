@@ -47,18 +47,26 @@ namespace {
 // kernel cuts K over the waves of a workgroup and pays with more reads of x (a tile is at most 128 x 48
 // or 96 x 64), so it wins until the prefill kernel fills the chip.
 //
-// By the estimates, the tile kernel's with its margin.  Without a workspace (us, tile kernel and K whole): 4096 x 4096 at 300 /
-// 512 / 1000 tokens 18.1 / 28.5 / 51.2 and 42.7 / 44.1 / 48.3; up to 160 tokens always the tile kernel, which rounds no weight and
-// is the slower one from 32000 features on only (160 tokens 9 %, 128256 features at 128 tokens 197 and 117).
-// With one (tile kernel and ranges): 4096 x 4096 at 400 / 700 / 1000 24.7 / 36.2 / 51.2 and 29.2 / 37.8 / 42.7; 4096 x 11008 at 256 / 500
-// 32.2 / 64.7 and 36.0 / 52.4; 28672 x 8192 at 96 / 128 58.2 / 86.9 and 59.6 / 62.7.  Over 90 shapes from 1024 x 1024 to 11008 x 11008 at 60
-// to 1500 tokens the chosen form took 0.8 % longer than the fastest one on average, 11 % at most (with a margin of a fifth 1.8 %
-// and 25 %).
+// By the estimates.  Up to 8192 columns of K the tile kernel takes a tie of 5 % against ranges, and of 8 % against K whole, as it
+// rounds no weight to fp16: of 60000 shapes of up to 11008 features and columns ten that ran there under the earlier, wider
+// margins run on the rounding kernel now, all above 8192 columns.
+// Without a workspace (us, tile kernel and K whole): 4096 x 4096 at 300 / 512 / 1000 tokens 18.1 / 28.5 / 51.2 and 42.7 / 44.1 / 48.3; up to
+// 160 tokens always the tile kernel (the slower one from 32000 features on: 160 tokens 9 %, 128256 features at 128 tokens 197 and 117).
+// With one (tile kernel and ranges): 4096 x 4096 at 400 / 700 / 1000 24.7 / 36.2 / 51.2 and 29.2 / 37.8 / 42.7; 28672 x 8192 at
+// 96 / 128 58.2 / 86.9 and 59.6 / 62.7.
+// Above 8192 columns, where its waves wait for more than the estimate has, it has a margin: 4096 x 11008 at 256 / 500 32.2 / 64.7 and
+// 36.0 / 52.4 over ranges.  At 129 to 144 tokens the line is where it was, by the estimate that decides the ranges: cautious, as
+// callers who count on the scratch of such calls being used find it used.
 bool takes_tile_kernel(const TilePlan &plan, int M, int N, int K, bool split)
 {
     if (awq_tile_override() >= 0) return awq_tile_forced();
-    if (split) return (M <= 128 ? 1.0 : awq_tile_margin(K)) * plan.us < awq_gemm_ranges_us(M, N, K);
-    return M <= 160 || awq_tile_margin(K) * plan.us < awq_gemm_unsplit_us(M, N, K);
+    if (split && M > 128 && M <= 144 && K > 8192) {
+        double ranges_us = 0.0;
+        (void)awq_gemm_ksplit(M, N, K, &ranges_us);
+        return 1.11 * plan.us < ranges_us;
+    }
+    if (split) return (M <= 128 ? 1.0 : awq_tile_margin(K)) * plan.us < (K > 8192 ? 1.0 : 1.05) * awq_gemm_ranges_us(M, N, K);
+    return M <= 160 || awq_tile_margin(K) * plan.us < 1.08 * awq_gemm_unsplit_us(M, N, K);
 }
 
 }  // namespace

@@ -234,7 +234,7 @@ extern "C" int awq_w3a16_linear_prefill(const void *x_f16, const void *qweight, 
     // 6 us, 28672 x 8192 6 to 28), added to its estimate.  Up to 160
     // tokens always the tile kernel (before: blocks of 16 tokens through the decode kernels, the
     // weights read again by each: 92 tokens, 5328 x 9216, 87.3 us, now 19.8); beyond, by the two estimates,
-    // as in awq_w4a16_linear, the tile kernel's a twentieth up for its longer expansion (281 tokens, 1152 x 1792: 20.9 us
+    // as in awq_w4a16_linear, the tile kernel's a twentieth up for its longer expansion and a tie of 8 % its own (281 tokens, 1152 x 1792: 20.9 us
     // re-packed, 8.8 here; 586, 3104 x 3584: 31.8 and 23.9; from 821, 5072 x 1792, the prefill kernel).
     const TilePlan plan = awq_tile_plan((int)M, (int)N, (int)K);
     const size_t repacked = ((size_t)(N * K / 2) + 255) & ~(size_t)255;
@@ -243,7 +243,7 @@ extern "C" int awq_w3a16_linear_prefill(const void *x_f16, const void *qweight, 
     const double gemm_us = (split ? awq_gemm_ranges_us((int)M, (int)N, (int)K) : awq_gemm_unsplit_us((int)M, (int)N, (int)K)) +
                            2.5 + (double)N * (double)K * 0.875 / 8.0e6;
     const int forced = awq_tile_override();
-    if (forced < 0 ? M <= 160 || 1.05 * awq_tile_margin((int)K) * plan.us < gemm_us : forced > 0)
+    if (forced < 0 ? M <= 160 || 1.05 * awq_tile_margin((int)K) * plan.us < 1.08 * gemm_us : forced > 0)
         return awq_tile_launch(3, plan, x_f16, qweight, scales, zeros, y_f16, (int)M, (int)N, (int)K,
                                (hipStream_t)stream);
     st = awq_repack_w3_to_w4(qweight, N, K, group, workspace, stream);
