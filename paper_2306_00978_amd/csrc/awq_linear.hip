@@ -47,9 +47,9 @@ namespace {
 // kernel cuts K over the waves of a workgroup and pays with more reads of x (a tile is at most 128 x 48
 // or 96 x 64), so it wins until the prefill kernel fills the chip.
 //
-// By the estimates.  Up to 8192 columns of K the tile kernel takes a tie of 5 % against ranges, and of 8 % against K whole, as it
-// rounds no weight to fp16: of 60000 shapes of up to 11008 features and columns ten that ran there under the earlier, wider
-// margins run on the rounding kernel now, all above 8192 columns.
+// By the estimates.  The tile kernel takes a tie of 5 % (over ranges up to 8192 columns of K), as it rounds no weight to fp16: of
+// 60000 shapes of up to 11008 features and columns ten that ran there under the earlier, wider margins run on the rounding
+// kernel now (133 without the tie).  8 % would leave none, but at 4096 x 4096 and 1000 tokens 51.2 us where K whole takes 48.3.
 // Without a workspace (us, tile kernel and K whole): 4096 x 4096 at 300 / 512 / 1000 tokens 18.1 / 28.5 / 51.2 and 42.7 / 44.1 / 48.3; up to
 // 160 tokens always the tile kernel (the slower one from 32000 features on: 160 tokens 9 %, 128256 features at 128 tokens 197 and 117).
 // With one (tile kernel and ranges): 4096 x 4096 at 400 / 700 / 1000 24.7 / 36.2 / 51.2 and 29.2 / 37.8 / 42.7; 28672 x 8192 at
@@ -66,7 +66,7 @@ bool takes_tile_kernel(const TilePlan &plan, int M, int N, int K, bool split)
         return 1.11 * plan.us < ranges_us;
     }
     if (split) return (M <= 128 ? 1.0 : awq_tile_margin(K)) * plan.us < (K > 8192 ? 1.0 : 1.05) * awq_gemm_ranges_us(M, N, K);
-    return M <= 160 || awq_tile_margin(K) * plan.us < 1.08 * awq_gemm_unsplit_us(M, N, K);
+    return M <= 160 || awq_tile_margin(K) * plan.us < 1.05 * awq_gemm_unsplit_us(M, N, K);
 }
 
 }  // namespace
