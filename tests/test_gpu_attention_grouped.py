@@ -51,6 +51,25 @@ def test_grouped_attention_against_the_oracle(H, Hkv, positions, F):
         assert np.all(np.abs(a - b) <= np.abs(b) * 2.0 ** -10 + 1e-7)
 
 
+# eight heads have a slice per 64 positions up to 64 of them: both sides of 16 slices, above which another kernel merges them, and
+# the rows of its four waves
+@pytest.mark.parametrize("slices", [1, 3, 4, 5, 8, 9, 16, 17, 61, 64])
+@pytest.mark.parametrize("short", [0, 63])
+def test_merge_of_every_number_of_slices(slices, short):
+    import oracle
+    import torch
+    import paper_2306_00978_amd as awq
+    H, pos = 8, 64 * slices - 1 - short
+    assert awq.load().awq_decode_attention_workspace_bytes(H, 128, pos + 1) == H * slices * 130 * 4
+    g = np.random.default_rng(100 * slices + short)
+    q, k, v = (g.standard_normal((H, 128)).astype(np.float16) for _ in range(3))
+    q[1] *= 30                                                           # one slice has nearly all the weight
+    kc, vc = (g.standard_normal((H, pos + 1, 128)).astype(np.float16) for _ in range(2))
+    ref = oracle.decode_attention(q, k, v, kc, vc, pos)[0].astype(np.float64)
+    out = awq.awq_decode_attention(*(torch.from_numpy(t).cuda() for t in (q, k, v, kc, vc)), pos)
+    assert np.abs(out.cpu().numpy().astype(np.float64) - ref).max() <= TOL * np.abs(vc.astype(np.float64)).max()
+
+
 # the library's choice is F = 4, 2 and 1 workgroups to a slice of the positions (64, 128 and 256 items)
 SPLITS = [(64, 8, 1000), (128, 32, 700), (384, 128, 700)]
 
