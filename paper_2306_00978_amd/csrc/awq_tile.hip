@@ -115,32 +115,39 @@ __device__ __forceinline__ uint32_t negated_zero(uint32_t z)
     return __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, z * 0x00010001u) * minus);
 }
 
+// a / b by the inverse floor((2^32 - 1) / b), which gives one too little at most: a division by an argument is 150 cycles in
+// front of the first load
+__device__ __forceinline__ int quotient(int a, int b, uint32_t inverse)
+{
+    const int q = (int)(((uint64_t)(uint32_t)a * inverse) >> 32);
+    return a - q * b >= b ? q + 1 : q;
+}
+
 template <int BITS, int MT, int NT>
 __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
     const unsigned char *__restrict__ x, const unsigned char *__restrict__ qweight,
     const unsigned char *__restrict__ scales, const unsigned char *__restrict__ zeros,
-    half_t *__restrict__ y, int M, int N, int K, int tiles_n, uint32_t tiles_n_inverse, int tiles_total,
-    double *__restrict__ loss)
+    half_t *__restrict__ y, int M, int N, int K, int tiles_n, uint32_t tiles_n_inverse, uint32_t runs_inverse,
+    uint32_t runs_inverse_long, int tiles_total, double *__restrict__ loss)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    asm volatile("" ::"s"(x), "s"(qweight), "s"(scales), "s"(zeros), "s"(y), "s"(M), "s"(N), "s"(K),
-                 "s"(tiles_n), "s"(tiles_n_inverse), "s"(tiles_total), "s"(loss));          // arguments in one round
+    asm volatile("" ::"s"(x), "s"(qweight), "s"(scales), "s"(zeros), "s"(y), "s"(M), "s"(N), "s"(K), "s"(tiles_n),
+                 "s"(tiles_n_inverse), "s"(runs_inverse), "s"(runs_inverse_long), "s"(tiles_total), "s"(loss));   // arguments in one round
     // contiguous ranges of tiles, token-tile-major, per XCD (own L2): see gemm_kernel
     const int per_xcd = (tiles_total + 7) >> 3;
     const int unit = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
     if (unit >= tiles_total || ((int)blockIdx.x >> 3) >= per_xcd) return;
-    // unit / tiles_n by the inverse floor((2^32 - 1) / tiles_n), which is one too small at most: a division by an argument is
-    // 150 cycles in front of the first load
-    int tile_m = (int)(((uint64_t)(uint32_t)unit * tiles_n_inverse) >> 32);
-    if (unit - tile_m * tiles_n >= tiles_n) ++tile_m;
-    const int tile_n = unit - tile_m * tiles_n;
+    const int tile_m = quotient(unit, tiles_n, tiles_n_inverse), tile_n = unit - tile_m * tiles_n;
     const uint32_t lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t r = lane & 15, c = lane >> 4;
     const int G = K / RUN;
-    // the wave's runs: wave, wave + 8, ..., walked in cyclic order from a start of the workgroup's own
+    // The wave's runs: wave, wave + 8, ..., walked in cyclic order from a start of the workgroup's own, one run after its
+    // neighbour's (unit % cnt): the workgroups of a token tile then read a run of x one step after the other, while the L2
+    // has it.  Spread over all of K they read it at any time, and where the token tiles of an XCD are more than its 4 MB
+    // each brings it in again (1024 x 28672 at 700 tokens 95 us, so 69; 256 x 28672 at 960 58 and 37).
     const int cnt = (G - wave + TILE_WAVES - 1) / TILE_WAVES;
-    const int rot = (int)(((uint64_t)((uint32_t)unit * 0x9E3779B9u) * (uint32_t)max(cnt, 0)) >> 32);
+    const int rot = cnt > 0 ? unit - cnt * quotient(unit, cnt, wave < G % TILE_WAVES ? runs_inverse_long : runs_inverse) : 0;
     auto run_at = [&](int i) {                             // i-th run; past the end: a harmless repeat
         i = min(i, cnt - 1) + rot;
         return wave + TILE_WAVES * (i < cnt ? i : i - cnt);
@@ -411,9 +418,12 @@ int launch_one(const void *x, const void *qweight, const void *scales, const voi
             return AWQ_ERR_HIP;
         attr_set.store(true, std::memory_order_relaxed);
     }
+    // a wave has G / 8 runs, or one more
+    const uint32_t runs = (uint32_t)(K / RUN / TILE_WAVES);
     tile_kernel<BITS, MT, NT><<<dim3((unsigned)((total + 7) / 8 * 8)), dim3(64 * TILE_WAVES), lds, stream>>>(
         (const unsigned char *)x, (const unsigned char *)qweight, (const unsigned char *)scales,
-        (const unsigned char *)zeros, (half_t *)y, M, N, K, tiles_n, 0xFFFFFFFFu / (uint32_t)tiles_n, (int)total, loss);
+        (const unsigned char *)zeros, (half_t *)y, M, N, K, tiles_n, 0xFFFFFFFFu / (uint32_t)tiles_n,
+        0xFFFFFFFFu / (runs > 0 ? runs : 1u), 0xFFFFFFFFu / (runs + 1), (int)total, loss);
     return awq_launch_status();
 }
 

@@ -95,6 +95,28 @@ def test_every_built_shape_of_a_workgroup(bits, N, K):
             assert np.array_equal(got.view(np.uint16), y.cpu().numpy().view(np.uint16)), (mt, nt, M)
 
 
+def test_neighbouring_workgroups_start_a_run_apart():
+    """The order in which a wave adds its runs, from where it starts: that of the workgroup before, and one run further on.
+    Three runs of the first wave add 2^25, 1 and -2^25 to every output: 1 where it starts at the third, else 0."""
+    import oracle
+    import torch
+    import paper_2306_00978_amd as awq
+    tiles, K, M = 13, 24 * 128, 17                                       # 16 x 16 tiles of y: 26 workgroups
+    N = 16 * tiles
+    codes, zeros = np.zeros((N, K), np.uint8), np.zeros((N, K // 128), np.uint8)
+    scales, x = np.ones((N, K // 128), np.float16), np.zeros((M, K), np.float16)
+    for run, value in ((0, 32768), (8, 1), (16, -32768)):
+        x[:, run * 128] = value
+        codes[:, run * 128] = 1 if value == 1 else 8
+        scales[:, run] = 1 if value == 1 else 128
+    packed = [torch.from_numpy(a).cuda() for a in oracle.pack(codes, scales, zeros)]
+    packed[1] = packed[1].view(torch.float16)
+    with tuning_build(AWQ_TILE_PLAN=11):
+        y = awq.awq_w4a16_linear(torch.from_numpy(x).cuda(), *packed, N, workspace=False).cpu().numpy()
+    unit = np.arange(N)[None, :] // 16 + tiles * (np.arange(M)[:, None] // 16)
+    assert np.array_equal(y, (unit % 3 == 2).astype(np.float16))
+
+
 @pytest.mark.parametrize("plan", [0] + [10 * mt + nt for mt, nt in PLANS])
 def test_loss_form_of_every_built_shape_and_of_the_prefill_kernel(plan):
     """The scale search against the same arithmetic in plain torch (fp64 products of the fp16 operands); 0: the prefill
