@@ -231,7 +231,7 @@ extern "C" int awq_w3a16_linear_prefill(const void *x_f16, const void *qweight, 
     if (workspace_bytes < (size_t)(N * K / 2)) return AWQ_ERR_WORKSPACE_TOO_SMALL;
     // The tile kernel takes the 3-bit words as they are and touches no workspace; the prefill kernel needs
     // them re-packed first: 2.5 us and N K (3 + 4) / 8 bytes at 8 TB/s (it is read back from a cache; 4096 x 11008 4 to
-    // 6 us, 28672 x 8192 6 to 28), added to its estimate.  Up to 160
+    // 6 us, 28672 x 8192 6 to 28), added to its estimate.  Up to 128
     // tokens always the tile kernel (before: blocks of 16 tokens through the decode kernels, the
     // weights read again by each: 92 tokens, 5328 x 9216, 87.3 us, now 19.8); beyond, by the two estimates,
     // as in awq_w4a16_linear, the tile kernel's a twentieth up for its longer expansion and a tie of 8 % its own (281 tokens, 1152 x 1792: 20.9 us
@@ -243,7 +243,7 @@ extern "C" int awq_w3a16_linear_prefill(const void *x_f16, const void *qweight, 
     const double gemm_us = (split ? awq_gemm_ranges_us((int)M, (int)N, (int)K) : awq_gemm_unsplit_us((int)M, (int)N, (int)K)) +
                            2.5 + (double)N * (double)K * 0.875 / 8.0e6;
     const int forced = awq_tile_override();
-    if (forced < 0 ? M <= 160 || 1.05 * awq_tile_margin((int)K) * plan.us < 1.08 * gemm_us : forced > 0)
+    if (forced < 0 ? M <= 128 || 1.05 * awq_tile_margin((int)K) * plan.us < 1.08 * gemm_us : forced > 0)
         return awq_tile_launch(3, plan, x_f16, qweight, scales, zeros, y_f16, (int)M, (int)N, (int)K,
                                (hipStream_t)stream);
     st = awq_repack_w3_to_w4(qweight, N, K, group, workspace, stream);

@@ -238,7 +238,29 @@ def test_prefill_kernel_at_its_shortest_k(N, K):
     (4, 4096, 4096, 1000, True),                     # 51.2, 42.7
     (4, 4096, 11008, 256, False),                    # long K, the tile kernel's estimate with its margin: 32.2, 36.0
     (4, 4096, 11008, 500, True),                     # 64.7, 52.4
-    (3, 4096, 4096, 160, False),                     # the last token count that takes the tile kernel without a look
+    (3, 4096, 4096, 160, False),                     # 12.9, re-packed 50.6
+    (3, 28672, 256, 145, True),                      # many features, short K, just above the token counts without a look: 20.8, 16.5
 ])
 def test_line_where_both_kernels_have_estimates(bits, N, K, M, used):
     test_line_between_the_tile_and_the_prefill_kernel(bits, N, K, M, used)
+
+
+@pytest.mark.parametrize("N,K,M,tile", [
+    (28672, 512, 128, True),                         # up to here without a look
+    (28672, 512, 129, False),                        # us, tile kernel and K whole: 21.1, 13.9
+    (57344, 512, 160, False),                        # 36.1, 24.9
+    (4096, 4096, 160, True),                         # 13.9, 44
+    (11008, 4096, 161, True),
+])
+def test_line_without_a_workspace(N, K, M, tile):
+    """Nothing but the bits of the result tells which kernel ran: the same call with the prefill kernel forced."""
+    import torch
+    import paper_2306_00978_amd as awq
+    g = torch.Generator(device="cuda").manual_seed(N + K + M)
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).half()
+    x = torch.randn((M, K), generator=g, device="cuda").half()
+    packed = awq.awq_quantize_pack(W, torch.ones(K, device="cuda"))
+    y = awq.awq_w4a16_linear(x, *packed, N, workspace=False)
+    with tuning_build(AWQ_TILE_PLAN=0):
+        prefill = awq.awq_w4a16_linear(x, *packed, N, workspace=False)
+    assert torch.equal(y, prefill) != tile
