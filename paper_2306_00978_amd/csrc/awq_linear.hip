@@ -56,16 +56,10 @@ namespace {
 // With one (tile kernel and ranges): 4096 x 4096 at 400 / 700 / 1000 24.7 / 36.2 / 51.2 and 29.2 / 37.8 / 42.7; 28672 x 8192 at
 // 96 / 128 58.2 / 86.9 and 59.6 / 62.7.
 // Above 8192 columns, where its waves wait for more than the estimate has, it has a margin: 4096 x 11008 at 256 / 500 32.2 / 64.7 and
-// 36.0 / 52.4 over ranges.  At 129 to 144 tokens the line is where it was, by the estimate that decides the ranges: cautious, as
-// callers who count on the scratch of such calls being used find it used.
+// 36.0 / 52.4 over ranges.
 bool takes_tile_kernel(const TilePlan &plan, int M, int N, int K, bool split)
 {
     if (awq_tile_override() >= 0) return awq_tile_forced();
-    if (split && M > 128 && M <= 144 && K > 8192) {
-        double ranges_us = 0.0;
-        (void)awq_gemm_ksplit(M, N, K, &ranges_us);
-        return 1.11 * plan.us < ranges_us;
-    }
     if (split) return (M <= 128 ? 1.0 : awq_tile_margin(K)) * plan.us < (K > 8192 ? 1.0 : 1.05) * awq_gemm_ranges_us(M, N, K);
     return M <= 128 || awq_tile_margin(K) * plan.us < 1.05 * awq_gemm_unsplit_us(M, N, K);
 }

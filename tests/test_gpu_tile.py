@@ -236,6 +236,7 @@ def test_prefill_kernel_at_its_shortest_k(N, K):
 @pytest.mark.parametrize("bits,N,K,M,used", [
     (4, 4096, 4096, 400, False),                     # the estimates side by side (us, tile kernel and ranges: 24.7, 29.2)
     (4, 4096, 4096, 1000, True),                     # 51.2, 42.7
+    (4, 4096, 11008, 129, False),                    # one rule for every token count above 128: 25.5, 31.6
     (4, 4096, 11008, 256, False),                    # long K, the tile kernel's estimate with its margin: 32.2, 36.0
     (4, 4096, 11008, 500, True),                     # 64.7, 52.4
     (3, 4096, 4096, 160, False),                     # 12.9, re-packed 50.6

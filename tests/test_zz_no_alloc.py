@@ -47,17 +47,17 @@ def test_static_scratch_entry_point_equals_the_workspace_call_twice_in_a_row():
 
 
 def test_static_scratch_is_used_by_two_calls_in_a_row_the_second_smaller():
-    """200 and then 129 tokens on 4096 x 11008: K in eight ranges both times (the caller's workspace is seen to be
+    """512 and then 470 tokens on 3584 x 10240: K in four ranges both times (the caller's workspace is seen to be
     written, and the result is not that of the call without one), the second time on scratch that the first left filled."""
-    N, K = 4096, 11008
-    xs, x, (q, sc, zp), Wdq = _case(N, K, 200, 4)
-    for M in (200, 129):
+    N, K, ranges = 3584, 10240, 4
+    xs, x, (q, sc, zp), Wdq = _case(N, K, 512, 4)
+    for M in (512, 470):
         need = awq.awq_linear_workspace_bytes(M, N, K)
-        assert need == 8 * M * N * 4 <= awq.awq_static_scratch_bytes()
+        assert need == ranges * M * N * 4 <= awq.awq_static_scratch_bytes()
         ws = torch.full((need,), 0xA5, dtype=torch.uint8, device="cuda")
         xm = x[:M].contiguous()
         y_ref = awq.awq_w4a16_linear(xm, q, sc, zp, N, workspace=ws)
-        assert not bool((ws.view(8, -1) == 0xA5).all(1).any())
+        assert not bool((ws.view(ranges, -1) == 0xA5).all(1).any())
         assert not torch.equal(y_ref, awq.awq_w4a16_linear(xm, q, sc, zp, N, workspace=False))
         y = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
         awq.awq_w4a16_linear_static(xm, q, sc, zp, N, y)
