@@ -47,21 +47,17 @@ namespace {
 // kernel cuts K over the waves of a workgroup and pays with more reads of x (a tile is at most 128 x 48
 // or 96 x 64), so it wins until the prefill kernel fills the chip.
 //
-// By the estimates.  The tile kernel takes a tie of 5 % (over ranges up to 8192 columns of K), as it rounds no weight to fp16: of
-// 60000 shapes of up to 11008 features and columns ten that ran there under the earlier, wider margins run on the rounding
-// kernel now (133 without the tie).  8 % would leave none, but at 4096 x 4096 and 1000 tokens 51.2 us where K whole takes 48.3.
-// Without a workspace (us, tile kernel and K whole): 4096 x 4096 at 300 / 512 / 1000 tokens 18.1 / 28.5 / 51.2 and 42.7 / 44.1 / 48.3; up to
-// 128 tokens always the tile kernel, which is the slower one where features are many and K is short (128 tokens: 28672 x 512 18.3
-// and 12.2, 128256 x 4096 201 and 115), beyond by the estimates (160 tokens: 28672 x 512 21.5 and 14.1, 57344 x 512 36.1 and 24.9).
-// With one (tile kernel and ranges): 4096 x 4096 at 400 / 700 / 1000 24.7 / 36.2 / 51.2 and 29.2 / 37.8 / 42.7; 28672 x 8192 at
-// 96 / 128 58.2 / 86.9 and 59.6 / 62.7.
-// Above 8192 columns, where its waves wait for more than the estimate has, it has a margin: 4096 x 11008 at 256 / 500 32.2 / 64.7 and
-// 36.0 / 52.4 over ranges.
+// By the estimates; a tie is the tile kernel's (awq_tile.h).  us, tile kernel and K whole: 4096 x 4096 at 300 / 512 / 1000 tokens
+// 18 / 29 / 50 and 43 / 44 / 48, 4096 x 14336 at 960 127 and 140; tile kernel and ranges: 4096 x 4096 at 400 / 700 / 1000 25 / 36 /
+// 51 and 29 / 38 / 43, 4096 x 11008 at 129 / 200 / 256 / 448 25 / 32 / 32 / 57 and 32 / 34 / 36 / 50, 1024 x 28672 at 256 33 and 43,
+// 28672 x 8192 at 96 / 128 58 / 87 and 60 / 63.
+// Without a workspace up to 128 tokens always the tile kernel: the faster one but where features are many (128 tokens: 28672 x 512
+// 18.3 and 12.2, 128256 x 4096 201 and 115; 160 tokens 28672 x 512 21.5 and 14.1, 57344 x 512 36.1 and 24.9).
 bool takes_tile_kernel(const TilePlan &plan, int M, int N, int K, bool split)
 {
     if (awq_tile_override() >= 0) return awq_tile_forced();
-    if (split) return (M <= 128 ? 1.0 : awq_tile_margin(K)) * plan.us < (K > 8192 ? 1.0 : 1.05) * awq_gemm_ranges_us(M, N, K);
-    return M <= 128 || awq_tile_margin(K) * plan.us < 1.05 * awq_gemm_unsplit_us(M, N, K);
+    if (split) return plan.us < AWQ_TILE_TIE * awq_gemm_ranges_us(M, N, K);
+    return M <= 128 || plan.us < AWQ_TILE_TIE * awq_gemm_unsplit_us(M, N, K);
 }
 
 }  // namespace

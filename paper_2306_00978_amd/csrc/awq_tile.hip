@@ -456,24 +456,35 @@ TileFn pick(int mt, int nt)
 
 }  // namespace
 
-// A launch takes 1.28 us and, per round of 256 workgroups (one per CU: the LDS), 1.41 us plus for every
-// run of a wave 0.226 us per token tile (32 KB of x per CU and tile for the eight waves: 62 B/clk), 0.165 us per
-// weight tile and 0.015 us per pair (a twelfth more where four weight tiles leave a shorter ring), plus 0.067 us per pair
-// for the exchange; up to a quarter more as the round fills the chip.  Fitted to 680 launches of 168 shapes (256 x 4096 to
-// 128256 x 4096 and 4096 x 14336, 40 to 1500 tokens, the four likeliest shapes of a workgroup each): rms error 6 %.
+// The estimate, in us, of a launch from a graph, the weights of which no cache holds: 2.9 and, per round of 256 workgroups (one per
+// CU: the LDS), 0.75, for every 1024 columns of K (a run of each wave) 0.24 per token tile (32 KB of x per CU: 62 B/clk) and 0.185
+// per weight tile (7 % more with four of them: measured, not explained), and 0.113 per pair for the exchange; up to a quarter more
+// as the round fills the chip.
+// Long K: x comes from the L2 as long as it fits.  Where the rows of one token tile are more than 0.4 of its 4 MB, or those of all
+// token tiles that an XCD works on more than 0.75, its part takes longer.
+// Fitted to 12300 launches of 2036 shapes (256 to 128256 features, 128 to 32768 columns, 17 to 1600 tokens; of each the shapes of a
+// workgroup within a quarter of the fastest): 6 % rms, 9 % above 24576 columns (where it is 32 % off in one of twenty without the
+// last two terms).  The shape it picks takes 0.8 % longer than the fastest one on average.
 TilePlan awq_tile_plan(int M, int N, int K)
 {
     const int forced = awq_tile_override();
     if (forced > 0) return {forced / 10, forced % 10, 0.0};
     TilePlan best = {1, 1, -1.0};
-    const int runs = (K / RUN + TILE_WAVES - 1) / TILE_WAVES;
     for (const int mt : MTS)
         for (int nt = 1; nt <= 4; ++nt) {
             if (!tile_built(mt, nt)) continue;
-            const int64_t wgs = awq_tile_count({mt, nt, 0.0}, M, N);
+            const int tiles_n = (N / 16 + nt - 1) / nt, tiles_m = (int)(((unsigned)M + 16 * mt - 1) / (16u * mt));
+            const int64_t wgs = (int64_t)tiles_n * tiles_m;
             const double rounds = (double)((wgs + 255) / 256), full = (double)wgs / (256.0 * rounds);
-            const double loop = runs * (0.226 * mt + 0.165 * nt + 0.015 * mt * nt) * (nt == 4 ? 1.089 : 1.0);
-            const double us = 1.275 + rounds * (1.408 + loop + 0.067 * mt * nt) * (1.0 + 0.237 * full * full);
+            const double l2 = mt * (double)K / 131072.0;                            // a token tile's rows, of 4 MB
+            double longer = 1.0;
+            if (l2 * tiles_m > 0.4) {
+                const int xcd = ((int)std::min<int64_t>(wgs, 256) + 7) / 8;         // workgroups of an XCD at a time
+                const double l2_all = l2 * std::min((double)tiles_m, 1.0 + (xcd - 1) / (double)tiles_n);
+                longer += 0.4 * std::max(l2 - 0.4, 0.0) + 0.25 * std::min(std::max(l2_all - 0.75, 0.0), 1.0);
+            }
+            const double loop = K / 1024.0 * (0.24 * mt * longer + 0.185 * nt) * (nt == 4 ? 1.07 : 1.0);
+            const double us = 2.9 + rounds * (0.75 + loop + 0.113 * mt * nt) * (1.0 + 0.24 * full * full);
             if (best.us < 0.0 || us < best.us) best = {mt, nt, us};
         }
     return best;

@@ -230,20 +230,19 @@ extern "C" int awq_w3a16_linear_prefill(const void *x_f16, const void *qweight, 
         return AWQ_ERR_MISALIGNED;
     if (workspace_bytes < (size_t)(N * K / 2)) return AWQ_ERR_WORKSPACE_TOO_SMALL;
     // The tile kernel takes the 3-bit words as they are and touches no workspace; the prefill kernel needs
-    // them re-packed first: 2.5 us and N K (3 + 4) / 8 bytes at 8 TB/s (it is read back from a cache; 4096 x 11008 4 to
-    // 6 us, 28672 x 8192 6 to 28), added to its estimate.  Up to 128
+    // them re-packed first: 3.1 us and N K (3 + 4) / 8 bytes at 5.7 TB/s (500 shapes, 5 % rms), added to its estimate.  Up to 128
     // tokens always the tile kernel (before: blocks of 16 tokens through the decode kernels, the
     // weights read again by each: 92 tokens, 5328 x 9216, 87.3 us, now 19.8); beyond, by the two estimates,
-    // as in awq_w4a16_linear, the tile kernel's a twentieth up for its longer expansion and a tie of 8 % its own (281 tokens, 1152 x 1792: 20.9 us
-    // re-packed, 8.8 here; 586, 3104 x 3584: 31.8 and 23.9; from 821, 5072 x 1792, the prefill kernel).
+    // as in awq_w4a16_linear (281 tokens, 1152 x 1792: 20.9 us re-packed, 8.8 here; 586, 3104 x 3584: 31.8 and 23.9; 8192 x 28672
+    // at 512: 320 and 297, over ranges 224).  Over 500 shapes the tile kernel takes 1.02 of its estimate in 3 bits.
     const TilePlan plan = awq_tile_plan((int)M, (int)N, (int)K);
     const size_t repacked = ((size_t)(N * K / 2) + 255) & ~(size_t)255;
     const size_t partials = awq_linear_workspace_bytes(M, N, K, group);
     const bool split = partials > 0 && workspace_bytes >= repacked + partials;
     const double gemm_us = (split ? awq_gemm_ranges_us((int)M, (int)N, (int)K) : awq_gemm_unsplit_us((int)M, (int)N, (int)K)) +
-                           2.5 + (double)N * (double)K * 0.875 / 8.0e6;
+                           3.1 + (double)N * (double)K * 0.875 / 5.7e6;
     const int forced = awq_tile_override();
-    if (forced < 0 ? M <= 128 || 1.05 * awq_tile_margin((int)K) * plan.us < 1.08 * gemm_us : forced > 0)
+    if (forced < 0 ? M <= 128 || plan.us < AWQ_TILE_TIE * gemm_us : forced > 0)
         return awq_tile_launch(3, plan, x_f16, qweight, scales, zeros, y_f16, (int)M, (int)N, (int)K,
                                (hipStream_t)stream);
     st = awq_repack_w3_to_w4(qweight, N, K, group, workspace, stream);

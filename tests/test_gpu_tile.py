@@ -181,10 +181,10 @@ def test_prefill_kernel_at_shapes_the_tile_kernel_took_over(N, K, M):
 @pytest.mark.parametrize("bits,N,K,M,used", [
     (4, 11008, 4096, 128, False),                    # few tokens: the tile kernel, whatever the workspace
     (4, 28672, 8192, 128, True),                     # two rounds of its workgroups: K over ranges (69 us against 90)
-    (4, 4096, 11008, 200, True),
+    (4, 4096, 11008, 448, True),                     # us, tile kernel and ranges: 57.3, 50.5
     (3, 4096, 4096, 300, False),
     (3, 4096, 4096, 2048, True),                     # the prefill kernel, on re-packed codes
-    (3, 8192, 28672, 512, True),                     # very long K (309 us against 334)
+    (3, 8192, 28672, 512, False),                    # very long K: 297, re-packed 320
 ])
 def test_line_between_the_tile_and_the_prefill_kernel(bits, N, K, M, used):
     """What the kernel that does not run would have left in the workspace tells the two apart."""
@@ -237,8 +237,12 @@ def test_prefill_kernel_at_its_shortest_k(N, K):
     (4, 4096, 4096, 400, False),                     # the estimates side by side (us, tile kernel and ranges: 24.7, 29.2)
     (4, 4096, 4096, 1000, True),                     # 51.2, 42.7
     (4, 4096, 11008, 129, False),                    # one rule for every token count above 128: 25.5, 31.6
-    (4, 4096, 11008, 256, False),                    # long K, the tile kernel's estimate with its margin: 32.2, 36.0
-    (4, 4096, 11008, 500, True),                     # 64.7, 52.4
+    (4, 4096, 11008, 200, False),                    # long K: 31.4, 34.2
+    (4, 4096, 11008, 256, False),                    # 31.6, 36.5
+    (4, 4096, 11008, 500, True),                     # 57.3, 50.5 at 448 tokens
+    (4, 4096, 14336, 300, False),                    # 46.6, 49.4
+    (4, 1024, 28672, 256, False),                    # 33.2, 44.0
+    (4, 1024, 14336, 500, False),                    # 28.2, 30.5
     (3, 4096, 4096, 160, False),                     # 12.9, re-packed 50.6
     (3, 28672, 256, 145, True),                      # many features, short K, just above the token counts without a look: 20.8, 16.5
 ])
@@ -252,6 +256,8 @@ def test_line_where_both_kernels_have_estimates(bits, N, K, M, used):
     (57344, 512, 160, False),                        # 36.1, 24.9
     (4096, 4096, 160, True),                         # 13.9, 44
     (11008, 4096, 161, True),
+    (4096, 14336, 960, True),                        # long K: 128, 144
+    (5120, 13824, 700, True),                        # 121, 135
 ])
 def test_line_without_a_workspace(N, K, M, tile):
     """Nothing but the bits of the result tells which kernel ran: the same call with the prefill kernel forced."""
@@ -265,3 +271,19 @@ def test_line_without_a_workspace(N, K, M, tile):
     with tuning_build(AWQ_TILE_PLAN=0):
         prefill = awq.awq_w4a16_linear(x, *packed, N, workspace=False)
     assert torch.equal(y, prefill) != tile
+
+
+@pytest.mark.parametrize("N,K,M,shape,slower", [(1024, 28672, 700, 34, 43), (1536, 24576, 448, 34, 43), (512, 14336, 1300, 34, 43)])
+def test_shape_of_a_workgroup_where_rows_are_long(N, K, M, shape, slower):
+    """Where the token tiles of an XCD are more than its L2, workgroups of few tokens (10 * mt + nt): 67, 50 and 35 us; the slower
+    shape takes 81, 58 and 43.  They show in the bits of the result, as a workgroup's waves start elsewhere."""
+    import torch
+    import paper_2306_00978_amd as awq
+    g = torch.Generator(device="cuda").manual_seed(N + K + M)
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).half()
+    x = torch.randn((M, K), generator=g, device="cuda").half()
+    packed = awq.awq_quantize_pack(W, torch.ones(K, device="cuda"))
+    y = awq.awq_w4a16_linear(x, *packed, N, workspace=False)
+    for plan in (shape, slower):
+        with tuning_build(AWQ_TILE_PLAN=plan):
+            assert torch.equal(y, awq.awq_w4a16_linear(x, *packed, N, workspace=False)) == (plan == shape)
