@@ -646,9 +646,12 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float *__res
 
 // The same for more than 16 slices, where the loops above are what takes the time.  Wave w takes slices w, w + 4, ..., a pair of
 // dimensions per lane, and every wave the maxima and sums of all slices, one per lane, everything requested in one round.
-// Maximum and sum are shuffles, the weight of a slice is one lane's exponential, and the four waves meet in LDS once.  us a call at
-// 18, 24, 32 and 61 slices 11.2 -> 10.9, 11.4 -> 10.9, 11.5 -> 11.1, 12.4 -> 10.9 (of which the host needs ten).  At 8 and 16 slices the twelve dependent shuffles cost more than the
-// loops (13.3 -> 13.8 and 12.0 -> 12.8 us; by DPP instead 13.5 and 12.6), so those stay with the kernel above.
+// Maximum and sum are shuffles, the weight of a slice is one lane's exponential, and the four waves meet in LDS once.  us a call from
+// a graph, above and here: 8 heads at 17, 21, 32, 47 and 63 slices 7.3 / 7.2, 8.6 / 7.6, 8.7 / 7.8, 11.0 / 8.8, 12.2 / 9.2; 30 heads
+// at 17 and 18 9.3 / 9.1, 10.3 / 9.5.  (Only rows that are there are requested: with the last one again in the place of the others
+// it was slower than above by up to 11 % where heads are no multiple of 8, whose slices lie in other L2s.)  At 8 and 16
+// slices the twelve dependent shuffles cost more than the loops (measured with those repeats: 13.3 -> 13.8 and 12.0 -> 12.8 us; by
+// DPP instead 13.5 and 12.6), so those stay with the kernel above.
 constexpr int MERGE_WAVES = 4, MERGE_ROWS = 16;
 __global__ __launch_bounds__(64 * MERGE_WAVES) void attention_merge_many_kernel(const float *__restrict__ partial,
                                                                                 int splits, half_t *__restrict__ out)
@@ -661,8 +664,9 @@ __global__ __launch_bounds__(64 * MERGE_WAVES) void attention_merge_many_kernel(
     const float2 state = *reinterpret_cast<const float2 *>(p + min(lane, splits - 1) * (AD + 2) + AD);
     float2 row[MERGE_ROWS];
 #pragma unroll
-    for (int i = 0; i < MERGE_ROWS; ++i)                          // past the end: the last one again, not added
-        row[i] = *reinterpret_cast<const float2 *>(p + min(wave + MERGE_WAVES * i, splits - 1) * (AD + 2) + 2 * lane);
+    for (int i = 0; i < MERGE_ROWS; ++i)
+        if (wave + MERGE_WAVES * i < splits)
+            row[i] = *reinterpret_cast<const float2 *>(p + (wave + MERGE_WAVES * i) * (AD + 2) + 2 * lane);
     float m = state.x;
 #pragma unroll
     for (int d = 1; d <= 32; d <<= 1) m = fmaxf(m, __shfl_xor(m, d));

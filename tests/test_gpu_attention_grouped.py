@@ -70,11 +70,30 @@ def test_merge_of_every_number_of_slices(slices, short):
     assert np.abs(out.cpu().numpy().astype(np.float64) - ref).max() <= TOL * np.abs(vc.astype(np.float64)).max()
 
 
+# a slice has whole blocks of 16 positions: the last ones have none, in both kernels, and their maximum is -Inf and their sum 0
+@pytest.mark.parametrize("H,Hkv,pos,slices,filled", [(8, 8, 4096, 64, 52), (24, 24, 3999, 22, 21), (8, 1, 4096, 64, 52), (28, 4, 2000, 19, 18)])
+def test_merge_of_slices_without_positions(H, Hkv, pos, slices, filled):
+    import oracle
+    import torch
+    import paper_2306_00978_amd as awq
+    need = awq.load().awq_decode_attention_workspace_bytes(H, 128, pos + 1)
+    assert need == H * slices * 130 * 4
+    chunk = (-(-(pos + 1) // slices) + 15) // 16 * 16
+    assert -(-(pos + 1) // chunk) == filled < slices
+    g = np.random.default_rng(H + pos)
+    q, k, v = (g.standard_normal((n, 128)).astype(np.float16) for n in (H, Hkv, Hkv))
+    kc, vc = (g.standard_normal((Hkv, pos + 1, 128)).astype(np.float16) for _ in range(2))
+    ref = oracle.decode_attention(q, k, v, kc, vc, pos)[0].astype(np.float64)
+    out = awq.awq_decode_attention(*(torch.from_numpy(t).cuda() for t in (q, k, v, kc, vc)), pos)
+    assert np.abs(out.cpu().numpy().astype(np.float64) - ref).max() <= TOL * np.abs(vc.astype(np.float64)).max()
+
+
 # the library's choice is F = 4, 2 and 1 workgroups to a slice of the positions (64, 128 and 256 items)
 SPLITS = [(64, 8, 1000), (128, 32, 700), (384, 128, 700)]
+MANY_SLICES = [(28, 4, 1100), (24, 3, 1200), (16, 2, 1400)]             # 18, 19 and 22 slices: the other merge
 
 
-@pytest.mark.parametrize("H,Hkv,pos", SPLITS)
+@pytest.mark.parametrize("H,Hkv,pos", SPLITS + MANY_SLICES)
 @pytest.mark.parametrize("where", ["value of the last row", "keys", "key of the token", "key, positive", "key of the token, positive"])
 def test_infinities_in_the_caches_have_the_weight_of_their_score(H, Hkv, pos, where):
     """An infinite value reaches its own output column only; a key whose score is -Inf has the weight 0, wherever it lies
