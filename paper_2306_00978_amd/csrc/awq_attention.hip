@@ -606,29 +606,29 @@ int attention_grouped_launch(const GroupedArgs &A, hipStream_t stream)
     return awq_launch_status();
 }
 
-// grid H, 256 threads: merge the slices of a head in a fixed order.  The head's partial results
-// (at most 64 x 130 floats) are first copied to LDS with coalesced loads: read one by one from
+// grid H, 256 threads: merge up to 16 slices of a head in a fixed order.  The head's partial results
+// (at most 16 x 130 floats) are first copied to LDS with coalesced loads: read one by one from
 // memory they would be a chain of dependent round trips.
+constexpr int MERGE_LOOP_SLICES = 16, MERGE_LOOP_LOADS = 9;
+static_assert(MERGE_LOOP_SLICES * (AD + 2) <= 256 * MERGE_LOOP_LOADS, "one round of loads");
 __global__ __launch_bounds__(256) void attention_merge_kernel(const float *__restrict__ partial,
                                                               int splits, half_t *__restrict__ out)
 {
-    __shared__ float ps[64 * (AD + 2)];
+    __shared__ float ps[MERGE_LOOP_SLICES * (AD + 2)];
     const int h = blockIdx.x, t = threadIdx.x;
     const float *p = partial + (size_t)h * splits * (AD + 2);
     asm volatile("" ::"s"(partial), "s"(splits), "s"(out));       // arguments in one round
     const int n = splits * (AD + 2);
-    for (int base = 0; base < n; base += 256 * 9) {               // nine loads in flight: 16 slices in one round
-        float tmp[9];
+    float tmp[MERGE_LOOP_LOADS];                                  // in flight together
 #pragma unroll
-        for (int e = 0; e < 9; ++e) {
-            const int i = base + 256 * e + t;
-            tmp[e] = p[i < n ? i : n - 1];
-        }
+    for (int e = 0; e < MERGE_LOOP_LOADS; ++e) {
+        const int i = 256 * e + t;
+        tmp[e] = p[i < n ? i : n - 1];
+    }
 #pragma unroll
-        for (int e = 0; e < 9; ++e) {
-            const int i = base + 256 * e + t;
-            if (i < n) ps[i] = tmp[e];
-        }
+    for (int e = 0; e < MERGE_LOOP_LOADS; ++e) {
+        const int i = 256 * e + t;
+        if (i < n) ps[i] = tmp[e];
     }
     __syncthreads();
     if (t >= AD) return;
@@ -773,7 +773,7 @@ extern "C" int awq_decode_attention(const void *q_f16, const void *k_f16, const 
         st = awq_launch_status();
     }
     if (st != AWQ_OK) return st;
-    if (splits > 16)                                 // (at most 64: attention_splits)
+    if (splits > MERGE_LOOP_SLICES)                  // (at most 64: attention_splits)
         attention_merge_many_kernel<<<dim3((unsigned)H), dim3(64 * MERGE_WAVES), 0, (hipStream_t)stream>>>(
             (const float *)workspace, splits, (half_t *)out_f16);
     else

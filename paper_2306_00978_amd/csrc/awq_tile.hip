@@ -48,8 +48,8 @@ constexpr int RUN = 128;                        // columns per step of the loop
 constexpr int TILE_RING = 3;                    // token tiles of x a wave has in LDS
 constexpr int UNIT_BYTES = 16 * RUN * 2;
 // a wave's LDS: the ring, then packed words, steps and zero points (a dword per row and tile) of one run
-constexpr int raw_ofs(int) { return TILE_RING * UNIT_BYTES; }
-constexpr int sc_ofs(int nt) { return raw_ofs(nt) + nt * 1024; }
+constexpr int RAW_OFS = TILE_RING * UNIT_BYTES;
+constexpr int sc_ofs(int nt) { return RAW_OFS + nt * 1024; }
 constexpr int zp_ofs(int nt) { return sc_ofs(nt) + 256; }
 constexpr int wave_lds(int nt) { return zp_ofs(nt) + 256; }
 // The final exchange: a 16 x 16 tile takes 320 floats, row 4 c + v at 80 c + 16 v (the rows of a write fall 16 banks
@@ -189,15 +189,15 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
         if (BITS != 2) {                                   // a run is a group: 1 KB (768 bytes), 16 steps, 8 bytes of zero points
 #pragma unroll
             for (int n = 0; n < NT; ++n) {
-                if (BITS == 4) dma<16>(qweight + (trun[n] + run) * 1024 + lane * 16, lds0 + raw_ofs(NT) + n * 1024);
-                else if (lane < 48) dma<16>(qweight + (trun[n] + run) * 768 + lane * 16, lds0 + raw_ofs(NT) + n * 1024);
+                if (BITS == 4) dma<16>(qweight + (trun[n] + run) * 1024 + lane * 16, lds0 + RAW_OFS + n * 1024);
+                else if (lane < 48) dma<16>(qweight + (trun[n] + run) * 768 + lane * 16, lds0 + RAW_OFS + n * 1024);
             }
             dma<2>(scales + (lrun + run) * 32 + r * 2, lds0 + sc_ofs(NT));
             dma<1>(zeros + (lrun + run) * 8 + (r >> 1), lds0 + zp_ofs(NT));
         } else {                                           // half a block of 256 columns: groups 2 (run % 2), + 1
 #pragma unroll
             for (int n = 0; n < NT; ++n)
-                dma<16>(qweight + ((trun[n] + run) >> 1) * 1024 + lane * 16, lds0 + raw_ofs(NT) + n * 1024);
+                dma<16>(qweight + ((trun[n] + run) >> 1) * 1024 + lane * 16, lds0 + RAW_OFS + n * 1024);
             dma<4>(scales + ((lrun + run) >> 1) * 128 + (run & 1) * 4 + r * 8, lds0 + sc_ofs(NT));
             dma<1>(zeros + ((lrun + run) >> 1) * 16 + r, lds0 + zp_ofs(NT));
         }
@@ -222,10 +222,10 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
 #pragma unroll
             for (int n = 0; n < NT; ++n) {
                 if (BITS != 3) {
-                    q[n] = lds_read16(lds0 + raw_ofs(NT) + n * 1024 + lane * 16);
+                    q[n] = lds_read16(lds0 + RAW_OFS + n * 1024 + lane * 16);
                 } else {                                   // 12-byte slots
 #pragma unroll
-                    for (int i = 0; i < 3; ++i) q3[n][i] = lds_read4(lds0 + raw_ofs(NT) + n * 1024 + lane * 12 + 4 * i);
+                    for (int i = 0; i < 3; ++i) q3[n][i] = lds_read4(lds0 + RAW_OFS + n * 1024 + lane * 12 + 4 * i);
                 }
                 sraw[n] = lds_read4(lds0 + sc_ofs(NT) + (16 * n + r) * 4);
                 zraw[n] = lds_read4(lds0 + zp_ofs(NT) + (16 * n + r) * 4);
