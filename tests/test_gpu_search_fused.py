@@ -36,3 +36,28 @@ def test_fused_loss_against_plain_torch(T, N, K, points):
     assert torch.equal(s_best, awq.awq_act_scale(X, alphas[int(best)]))
     again = awq.awq_search_scale(W, X, alphas)[1]
     assert torch.equal(losses, again)
+
+
+@pytest.mark.parametrize("T,K", [(1, 128), (3, 640), (16, 4224), (17, 1152), (1025, 384), (2125, 1408)])
+def test_activations_of_a_grid_point_are_divided_as_by_awq_apply_inv_scale(T, K):
+    """The quotient from a kept reciprocal against the division, bit for bit, on columns that are no multiple of a wave's 512 and rows
+    that are none of its four: zeros of both signs, subnormals, the largest halves, infinities and NaN among them.  What the search
+    leaves in its workspace behind the means and the scales of K columns is x / s of the last grid point."""
+    import torch
+    import paper_2306_00978_amd as awq
+    g = torch.Generator(device="cuda").manual_seed(T + K)
+    N = 32
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).half()
+    X = (torch.randn((T, K), generator=g, device="cuda") * 10 ** (8 * torch.rand(K, generator=g, device="cuda") - 4)).clamp(-65504, 65504).half()
+    X[:, 0], X[0, 1], X[-1, 2], X[T // 2, 3] = 0, -0.0, 65504, -2.0 ** -24
+    X[-1, 5], X[0, 6], X[T // 2, 7] = float("inf"), -float("inf"), float("nan")
+    workspace = torch.empty(awq.load().awq_search_scale_workspace_bytes(T, N, K, 1, 128), dtype=torch.uint8, device="cuda")
+    for alpha in (0.0, 0.3, 1.0):
+        workspace.fill_(0xA5)
+        s = awq.awq_search_scale(W, X, [alpha], workspace=workspace)[2]
+        at = 2 * ((4 * K + 255) // 256 * 256)
+        got = workspace[at:at + 2 * T * K].view(torch.int16).view(T, K)
+        ref = awq.awq_apply_inv_scale(X, s)
+        nan = ref.isnan()
+        assert torch.equal(got.view(torch.float16).isnan(), nan)
+        assert torch.equal(got[~nan], ref.view(torch.int16)[~nan]), alpha
