@@ -18,8 +18,9 @@
 // vector instruction beside them costs about as much energy as a thirtieth of an MFMA.  Hence the small shape, 126 vector
 // instructions to 64 MFMAs (offsets that stay in their registers, constants by one multiply-add each), fragment reads
 // without bank conflicts, and consecutive MFMAs that share their weight fragment and then their token fragment.  Against
-// the 32x32x16 form of the same tile: 2048 x 11008 x 4096 176 -> 160 us (1150 TFLOP/s), 2048 x 4096 x 4096 62 -> 56.5, 2048 x 4096 x 11008
-// 156 -> 138, on zeros 138 -> 127, 48 -> 44, 118 -> 104.
+// the 32x32x16 form of the same tile, at first: 2048 x 11008 x 4096 176 -> 160 us, 2048 x 4096 x 4096 62 -> 56.5, 2048 x 4096 x 11008
+// 156 -> 138, on zeros 138 -> 127, 48 -> 44, 118 -> 104; with the shorter start and exchange (GemmUnits, gemm_pair_sum) the first
+// takes 152 to 161 from box to box (1150 to 1215 TFLOP/s).
 //
 // Operands.  Nothing is staged through registers on the way in: both operands are
 // fetched with global_load_lds (memory -> LDS, 16 bytes per lane landing in lane order),
@@ -503,9 +504,11 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float4 *__restri
 
 // How many K ranges the prefill launch of this shape is cut into when a workspace is given: the
 // count (1..8, at least four groups per range) with the smallest estimated time.  A workgroup
-// takes about 4 us + 1.4 us per group, workgroups run in rounds of 256 (one per CU), and the
-// second kernel moves (ranges + 1/2) * M * N * 4 bytes at about 3.5 TB/s after a launch of
-// 2.5 us -- figures measured on the three Llama-2-7B shapes at 160..2048 tokens.  Cutting K pays
+// taken at 4 us + 1.4 us per group, workgroups in rounds of 256 (one per CU), and the
+// second kernel at (ranges + 1/2) * M * N * 4 bytes at 3.5 TB/s after a launch of
+// 2.5 us -- figures of an earlier form of the kernel on the three Llama-2-7B shapes at 160..2048 tokens.  They stay because the
+// size of the workspace, which callers know, follows from the count: by the estimates below two shapes of 2000 would gain more
+// than 5 % from another one, 6 % at most.  Cutting K pays
 // while the tiles (ceil(M/128) * N/256) are fewer than the CUs, or just over a multiple of them.
 int awq_gemm_ksplit(int M, int N, int K, double *estimate_us)
 {
@@ -529,7 +532,7 @@ int awq_gemm_ksplit(int M, int N, int K, double *estimate_us)
 
 // The time of the launch that does not cut K: rounds of 256 workgroups, 5 us + 1.08 us a group each, and up to half as
 // much again as the chip fills, where the power limit lowers the clock.  186 measured launches (16 x 256 to 128256 x 4096 and
-// 28672 x 8192, 40 to 1500 tokens): 2.7 % rms, at most 9 % off.
+// 28672 x 8192, 40 to 1500 tokens): 2.7 % rms, at most 9 % off; 736 others of up to 28672 columns 3.4 %.
 double awq_gemm_unsplit_us(int M, int N, int K)
 {
     const int64_t tiles = (int64_t)((N + BN - 1) / BN) * ((M + BM - 1) / BM);
@@ -538,8 +541,8 @@ double awq_gemm_unsplit_us(int M, int N, int K)
 }
 
 // The time with K cut into awq_gemm_ksplit() ranges: the same with the groups of a range, and the second kernel, which moves
-// (ranges + 1/2) * M * N * 4 bytes at 4 TB/s after 7 us of launch, run-out and the first kernel's own stores.  122 launches: 4 % rms.
-// (The estimate above is 0.92 to 1.36 of the time; it stays what decides the number of ranges and the size of the workspace.)
+// (ranges + 1/2) * M * N * 4 bytes at 4 TB/s after 7 us of launch, run-out and the first kernel's own stores.  122 launches: 4 % rms, 482 others too.
+// (The estimate above is 0.92 to 1.36 of the time.)
 double awq_gemm_ranges_us(int M, int N, int K)
 {
     const int G = K / AWQ_GROUP, ks = awq_gemm_ksplit(M, N, K, nullptr);

@@ -354,7 +354,7 @@ extern "C" int awq_search_scale(const void *W_f16, const void *X_f16, int64_t T,
     st = dense_gemm_launch((const half_t *)X_f16, (const half_t *)W_f16, Y, (int)T, (int)N, (int)K, hs);
     if (st != AWQ_OK) return st;
     // Above 16 tokens the kernel that the layer runs, prefill or tile, has a loss form that takes the differences
-    // in the product's epilogue (2048 x 4096 x 4096: the product 65 us either way, without the 7 us pass over both
+    // in the product's epilogue (2048 x 4096 x 4096: the product 59 us either way, without the 7 us pass over both
     // outputs; 159 x 1120 x 2944: 21.2 us a grid point before, 16.5 now, with the powers below); its tiles have to fit the
     // partial sums of a grid point
     const bool prefill = T > 16 && awq_linear_takes_prefill((int)T, (int)N, (int)K);
