@@ -449,6 +449,11 @@ int awq_decode_attention(const void *q_f16, const void *k_f16, const void *v_f16
  * sums. */
 size_t awq_search_scale_workspace_bytes(int64_t T, int64_t N, int64_t K, int n_alpha, int group);
 
+/* The same with room for several candidates (about 128 MB of them): given that much,
+ * or what lies between the two figures, awq_search_scale evaluates several grid points per launch.
+ * The losses then differ in the order of their sums only. */
+size_t awq_search_scale_batch_workspace_bytes(int64_t T, int64_t N, int64_t K, int n_alpha, int group);
+
 /* Sec. 3.2 (the search for the scale), Eq. 4-5: for every alpha of the grid, s = s_X^alpha with
  * s_X[k] = max(mean_t |X[t,k]|, 1e-4), and
  *   loss(alpha) = sum_{t,n} ( y_q[t,n] - y[t,n] )^2,
@@ -458,7 +463,7 @@ size_t awq_search_scale_workspace_bytes(int64_t T, int64_t N, int64_t K, int n_a
  * s_best = s_X^alphas[best], bit-identical to awq_act_scale(X, alphas[best]).
  *   W_f16 [N,K], X_f16 [T,K] fp16 row-major (device, read); alphas: HOST array of n_alpha
  *   values in [0,1], 1 <= n_alpha <= AWQ_SEARCH_MAX_ALPHAS, read before the call returns;
- *   workspace: device, 256-byte aligned, awq_search_scale_workspace_bytes() bytes, contents
+ *   workspace: device, 256-byte aligned, awq_search_scale_workspace_bytes() bytes or more, contents
  *   undefined afterwards; losses [n_alpha] fp64, best [1] int32, s_best [K] fp32: device,
  *   written.  Like every other call it only enqueues work on `stream`. */
 int awq_search_scale(const void *W_f16, const void *X_f16, int64_t T, int64_t N, int64_t K,

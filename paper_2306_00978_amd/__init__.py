@@ -31,7 +31,7 @@ EXPORTS = [
     "awq_version", "awq_status_string", "awq_packed_sizes", "awq_act_scale",
     "awq_apply_inv_scale", "awq_quantize_pack", "awq_unpack", "awq_linear_workspace_bytes",
     "awq_w4a16_linear", "awq_w4a16_linear_multi",
-    "awq_search_scale_workspace_bytes", "awq_search_scale", "awq_quantize_pack_clip",
+    "awq_search_scale_workspace_bytes", "awq_search_scale_batch_workspace_bytes", "awq_search_scale", "awq_quantize_pack_clip",
     "awq_packed_sizes_w3", "awq_quantize_pack_w3", "awq_unpack_w3", "awq_w3a16_linear",
     "awq_w3a16_linear_multi", "awq_rmsnorm_inv_scale", "awq_read_probe",
     "awq_decode_attention_workspace_bytes", "awq_decode_attention", "awq_silu_mul",
@@ -207,6 +207,8 @@ def load() -> ctypes.CDLL:
     lib.awq_w3a16_linear_multi.argtypes = [ctypes.POINTER(LinearDesc), i32, i64, i32, vp]
     lib.awq_search_scale_workspace_bytes.restype = sz
     lib.awq_search_scale_workspace_bytes.argtypes = [i64, i64, i64, i32, i32]
+    lib.awq_search_scale_batch_workspace_bytes.restype = sz
+    lib.awq_search_scale_batch_workspace_bytes.argtypes = [i64, i64, i64, i32, i32]
     lib.awq_search_scale.restype = i32
     lib.awq_search_scale.argtypes = [vp, vp, i64, i64, i64, ctypes.POINTER(ctypes.c_float), i32, i32,
                                      vp, sz, vp, vp, vp, vp]
@@ -587,7 +589,9 @@ def awq_search_scale(W: torch.Tensor, X: torch.Tensor, alphas, group: int = GROU
                      workspace: torch.Tensor | None = None):
     """Grid search of Eq. 5 for one linear: W [N,K] fp16, X [T,K] fp16 calibration rows,
     `alphas` a sequence of values in [0,1].  Returns device tensors
-    (best [1] int32, losses [len(alphas)] fp64, s_best [K] fp32); nothing is synchronised."""
+    (best [1] int32, losses [len(alphas)] fp64, s_best [K] fp32); nothing is synchronised.
+    `workspace`: awq_search_scale_workspace_bytes() bytes or more; left out, it is allocated with room for several
+    candidates at a time (awq_search_scale_batch_workspace_bytes)."""
     _dev(W, torch.float16, "W")
     _dev(X, torch.float16, "X")
     N, K = W.shape
@@ -596,9 +600,13 @@ def awq_search_scale(W: torch.Tensor, X: torch.Tensor, alphas, group: int = GROU
         raise ValueError("W and X disagree on K")
     n = len(alphas)
     arr = (ctypes.c_float * max(n, 1))(*[float(a) for a in alphas])
-    need = load().awq_search_scale_workspace_bytes(T, N, K, n, group)
     if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=W.device)
+        need = load().awq_search_scale_batch_workspace_bytes(T, N, K, n, group)
+        try:
+            workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=W.device)
+        except torch.OutOfMemoryError:                    # one candidate at a time
+            need = load().awq_search_scale_workspace_bytes(T, N, K, n, group)
+            workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=W.device)
     losses = torch.empty(max(n, 1), dtype=torch.float64, device=W.device)
     best = torch.empty(1, dtype=torch.int32, device=W.device)
     s_best = torch.empty(K, dtype=torch.float32, device=W.device)

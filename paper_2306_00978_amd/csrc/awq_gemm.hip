@@ -195,12 +195,22 @@ __device__ __forceinline__ int quotient(int a, int b, uint32_t inverse)
 }
 
 enum { GEMM_PLAIN, GEMM_SPLIT, GEMM_LOSS };
+// GEMM_LOSS: the units of several grid points follow each other; point i reads x, weights, steps and zero points i `step` bytes
+// further and leaves its sums loss_step further.
+template <int MODE>
+struct GemmPoints {};
+template <>
+struct GemmPoints<GEMM_LOSS> {
+    int tiles;                     // of a point
+    uint32_t tiles_inverse;
+    int64_t step, loss_step;
+};
 template <int MODE>
 __global__ __launch_bounds__(512, 1) void gemm_kernel(
     const half_t *__restrict__ x, const unsigned char *__restrict__ qweight,
     const unsigned char *__restrict__ scales, const unsigned char *__restrict__ zeros,
     half_t *__restrict__ y, int M, int N, int K, int G, const GemmUnits U, float *__restrict__ part,
-    double *__restrict__ loss)
+    double *__restrict__ loss, const GemmPoints<MODE> points)
 {
     constexpr bool SPLIT = MODE == GEMM_SPLIT;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -216,7 +226,16 @@ __global__ __launch_bounds__(512, 1) void gemm_kernel(
     const int per_xcd = (U.units_total + 7) >> 3;            // units: (tile, K range) pairs
     const int unit = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
     if (unit >= U.units_total) return;
-    const int tile = SPLIT ? quotient(unit, U.ksplit, U.ksplit_inverse) : unit;
+    int tile = SPLIT ? quotient(unit, U.ksplit, U.ksplit_inverse) : unit;
+    if constexpr (MODE == GEMM_LOSS) {
+        const int point = quotient(unit, points.tiles, points.tiles_inverse);
+        tile = unit - point * points.tiles;
+        x = reinterpret_cast<const half_t *>(reinterpret_cast<const unsigned char *>(x) + point * points.step);
+        qweight += point * points.step;
+        scales += point * points.step;
+        zeros += point * points.step;
+        loss += point * points.loss_step;
+    }
     const int ks = SPLIT ? unit - tile * U.ksplit : 0;
     // groups [gofs, gofs + GL) of the G of a row: the first ranges are one longer where the count does not divide G
     const int gofs = SPLIT ? ks * U.group_base + min(ks, U.group_rem) : 0;
@@ -556,11 +575,12 @@ namespace {
 
 template <int MODE>
 int gemm_launch_any(const void *x, const void *qweight, const void *scales, const void *zeros,
-                    void *y, int M, int N, int K, float *part, int ksplit, double *loss, hipStream_t stream)
+                    void *y, int M, int N, int K, float *part, int ksplit, double *loss, hipStream_t stream, int count = 1,
+                    size_t step = 0, size_t loss_step = 0)
 {
     const int G = K / AWQ_GROUP;
     const int tiles_n = (N + BN - 1) / BN;
-    const int64_t tiles_total = (int64_t)tiles_n * ((M + BM - 1) / BM);
+    const int64_t tiles = (int64_t)tiles_n * ((M + BM - 1) / BM), tiles_total = tiles * count;
     if (tiles_total * ksplit > (1 << 30)) return AWQ_ERR_BAD_SHAPE;
     const dim3 grid((unsigned)((tiles_total * ksplit + 7) / 8 * 8)), block(512);
     const GemmUnits units = {tiles_n, ksplit, (int)(tiles_total * ksplit), G / ksplit, G % ksplit, 0xFFFFFFFFu / (uint32_t)tiles_n,
@@ -573,9 +593,11 @@ int gemm_launch_any(const void *x, const void *qweight, const void *scales, cons
             return AWQ_ERR_HIP;
         attr_set.store(true, std::memory_order_relaxed);
     }
+    GemmPoints<MODE> points = {};
+    if constexpr (MODE == GEMM_LOSS) points = {(int)tiles, 0xFFFFFFFFu / (uint32_t)tiles, (int64_t)step, (int64_t)loss_step};
     gemm_kernel<MODE><<<grid, block, LDS_BYTES, stream>>>(
         (const half_t *)x, (const unsigned char *)qweight, (const unsigned char *)scales,
-        (const unsigned char *)zeros, (half_t *)y, M, N, K, G, units, part, loss);
+        (const unsigned char *)zeros, (half_t *)y, M, N, K, G, units, part, loss, points);
     return awq_launch_status();
 }
 
@@ -611,12 +633,13 @@ int awq_gemm_launch_split(const void *x, const void *qweight, const void *scales
     return awq_launch_status();
 }
 
-// The loss form: y_ref [M,N] fp16 is read, loss receives one partial sum for each of awq_gemm_tiles() tiles.
+// The loss form: y_ref [M,N] fp16 is read, loss receives one partial sum for each of awq_gemm_tiles() tiles; the next one of
+// `points` grid points has its operands `step` bytes and its sums loss_step further.
 int64_t awq_gemm_tiles(int M, int N) { return (int64_t)((N + BN - 1) / BN) * ((M + BM - 1) / BM); }
 
 int awq_gemm_launch_loss(const void *x, const void *qweight, const void *scales, const void *zeros, const void *y_ref,
-                         int M, int N, int K, double *loss, hipStream_t stream)
+                         int M, int N, int K, double *loss, int points, size_t step, size_t loss_step, hipStream_t stream)
 {
     return gemm_launch_any<GEMM_LOSS>(x, qweight, scales, zeros, const_cast<void *>(y_ref), M, N, K, nullptr, 1, loss,
-                                      stream);
+                                      stream, points, step, loss_step);
 }

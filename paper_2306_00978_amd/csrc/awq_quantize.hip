@@ -17,6 +17,7 @@
 #include "awq_inv_scale.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace {
 
@@ -113,6 +114,12 @@ struct QuantArgs {
     QuantProblem p[QUANT_MAX_PROBLEMS];
     int count, num_units;
 };
+// The scale search: one matrix and the scales of `points` grid points, K floats apart; the results are `step` bytes apart.
+struct QuantPoints {
+    QuantProblem p;
+    int points, num_units;
+    int64_t step;
+};
 
 // Waves per SIMD the plain kernel is compiled for.  It needs about 130 registers, i.e. three waves
 // per SIMD; forced into 128 for a fourth wave it spills four values per tile and the 224-matrix
@@ -121,25 +128,40 @@ struct QuantArgs {
 #define AWQ_QUANT_MIN_WAVES 1
 #endif
 
-template <bool CLIP, bool ACT>
-__device__ __forceinline__ void quantize_wave(const QuantArgs &A, const ClipRatios &ratios)
+// The grid points of the scale search: the waves of one piece of the matrix follow each other, so that a workgroup or its
+// neighbours on the XCD read it together.
+template <bool CLIP, bool ACT, class Args>
+__device__ __forceinline__ void quantize_wave(const Args &A, const ClipRatios &ratios, int block)
 {
+    constexpr bool POINTS = std::is_same<Args, QuantPoints>::value;
     const int lane = threadIdx.x & 63;
-    const int unit = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    const int unit = __builtin_amdgcn_readfirstlane(block * 4 + (threadIdx.x >> 6));
     if (unit >= A.num_units) return;               // whole wave leaves together
-    int pi = 0;
-    for (int i = 1; i < A.count; ++i)
-        if (unit >= A.p[i].unit_begin) pi = i;
-    const QuantProblem &P = A.p[pi];
+    int local, point = 0;
+    int64_t step = 0;
+    const QuantProblem *problem;
+    if constexpr (POINTS) {
+        local = unit / A.points;
+        point = unit - local * A.points;
+        step = point * A.step;
+        problem = &A.p;
+    } else {
+        int pi = 0;
+        for (int i = 1; i < A.count; ++i)
+            if (unit >= A.p[i].unit_begin) pi = i;
+        problem = &A.p[pi];
+        local = unit - problem->unit_begin;
+    }
+    const QuantProblem &P = *problem;
+    const int G = P.G, NRB = P.NRB, rb_per_wave = P.rb_per_wave, T = P.T;
     const uint4 *__restrict__ W = P.W;
     const float4 *__restrict__ s = P.s;
-    uint4 *__restrict__ qweight = P.qweight;
-    uint16_t *__restrict__ scales = P.scales;
-    uint8_t *__restrict__ zeros = P.zeros;
+    if constexpr (POINTS) s += (int64_t)point * G * (AWQ_GROUP / 4);
+    uint4 *__restrict__ qweight = P.qweight + step / 16;
+    uint16_t *__restrict__ scales = P.scales + step / 2;
+    uint8_t *__restrict__ zeros = P.zeros + step;
     uint8_t *__restrict__ choice = P.choice;
     const uint4 *__restrict__ xs = P.xs;
-    const int G = P.G, NRB = P.NRB, rb_per_wave = P.rb_per_wave, T = P.T;
-    const int local = unit - P.unit_begin;
     const int g = local % G, part = local / G;
     const int rb0 = part * rb_per_wave;
     const int rb1 = min(NRB, rb0 + rb_per_wave);
@@ -321,32 +343,37 @@ __device__ __forceinline__ void quantize_wave(const QuantArgs &A, const ClipRati
 template <bool CLIP, bool ACT>
 __global__ __launch_bounds__(256, CLIP ? 1 : AWQ_QUANT_MIN_WAVES) void quantize_pack_kernel(const QuantArgs A, const ClipRatios ratios)
 {
-    quantize_wave<CLIP, ACT>(A, ratios);
+    quantize_wave<CLIP, ACT>(A, ratios, (int)blockIdx.x);
 }
 
-// One grid point of the scale search: W diag(s) quantized by the first workgroups, xs = x / s by the others.  The
-// two do not depend on each other; apart they are two launches too short to reach the memory's rate.  Both are bound by
-// instruction issue, at the low clock that the products in between leave: a dividing wave therefore keeps the
-// scales of its 64 runs of eight columns, and their reciprocals, for all its rows.  (4096 x 4096, 2048 rows: 17.1 us with a
-// division per element and the run of a thread by a 64-bit modulo, 16.1 now; 1722 x 3472 x 2304 10.3 and 9.7.)
+// Grid points of the scale search: W diag(s) quantized by the first workgroups, xs = x / s by the others.  The two do not depend
+// on each other; apart they are two launches too short to reach the memory's rate.  Both are bound by instruction issue, at the
+// low clock that the products in between leave (4096 x 4096, 2048 rows: about 78 thousand cycles of vector instructions a SIMD for
+// five points, 62 us): a dividing wave therefore keeps the scales of its 64 runs of eight columns, and their reciprocals, for all
+// its rows.  Several points to a launch read W and x once, from the L2 after the first, and share the start and the run-out: 17.1 us a
+// point one by one, 12.4 for five.
 struct InvArgs {
     const uint4 *x;
-    const float4 *s;
-    uint4 *xs;
+    const float4 *s;       // of the first point; K floats further the next one's
+    uint4 *xs;             // of the first point
+    int64_t xs_step;       // runs between two points' xs
     int M, K8;             // K8: runs of a row
     int strips, rows;      // strips of 64 runs, rows of a wave (a multiple of INV_ROWS)
-    int first_block, units;
+    int first_block, units, points;
 };
 constexpr int INV_ROWS = 4;                        // requested together
-__device__ __forceinline__ void inverse_wave(const InvArgs &I)
+__device__ __forceinline__ void inverse_wave(const InvArgs &I, int block)
 {
     const int lane = threadIdx.x & 63;
-    const int unit = __builtin_amdgcn_readfirstlane(((int)blockIdx.x - I.first_block) * 4 + (threadIdx.x >> 6));
+    const int unit = __builtin_amdgcn_readfirstlane(block * 4 + (threadIdx.x >> 6));
     if (unit >= I.units) return;
-    const int part = unit / I.strips, strip = unit - part * I.strips;
+    const int piece = unit / I.points, point = unit - piece * I.points;
+    const int part = piece / I.strips, strip = piece - part * I.strips;
     const int run = 64 * strip + lane, at = min(run, I.K8 - 1);
     const int m0 = part * I.rows, m1 = min(I.M, m0 + I.rows);
-    const float4 a = I.s[2 * at], b = I.s[2 * at + 1];
+    const float4 *scales = I.s + (int64_t)point * I.K8 * 2;
+    uint4 *xs = I.xs + point * I.xs_step;
+    const float4 a = scales[2 * at], b = scales[2 * at + 1];
     uint4 cur[INV_ROWS], nxt[INV_ROWS];
     auto request = [&](uint4 (&raw)[INV_ROWS], int m) {          // rows past the end repeat the last one
 #pragma unroll
@@ -362,15 +389,17 @@ __device__ __forceinline__ void inverse_wave(const InvArgs &I)
 #pragma unroll
         for (int u = 0; u < INV_ROWS; ++u) {
             const uint4 out = inv_scaled_by(cur[u], s, y);
-            if (run < I.K8 && m + u < m1) I.xs[(int64_t)(m + u) * I.K8 + run] = out;
+            if (run < I.K8 && m + u < m1) xs[(int64_t)(m + u) * I.K8 + run] = out;
             cur[u] = nxt[u];
         }
     }
 }
-__global__ __launch_bounds__(256, AWQ_QUANT_MIN_WAVES) void quantize_inv_kernel(const QuantArgs A, const InvArgs I)
+// (both numbers of workgroups are multiples of eight: consecutive pieces stay on one XCD)
+__global__ __launch_bounds__(256, AWQ_QUANT_MIN_WAVES) void quantize_inv_kernel(const QuantPoints A, const InvArgs I)
 {
-    if ((int)blockIdx.x < I.first_block) quantize_wave<false, false>(A, ClipRatios{});
-    else inverse_wave(I);
+    const int b = (int)blockIdx.x, first = I.first_block, rest = (int)gridDim.x - first;
+    if (b < first) quantize_wave<false, false>(A, ClipRatios{}, (b & 7) * (first >> 3) + (b >> 3));
+    else inverse_wave(I, (b & 7) * (rest >> 3) + ((b - first) >> 3));
 }
 
 __global__ __launch_bounds__(256) void unpack_kernel(
@@ -434,15 +463,29 @@ int quantize_check(const QuantJob &j, int group)
     return AWQ_OK;
 }
 
+QuantProblem quant_problem(const QuantJob &j)
+{
+    QuantProblem P = {};
+    P.W = (const uint4 *)j.W;
+    P.s = (const float4 *)j.s;
+    P.qweight = (uint4 *)j.qweight;
+    P.scales = (uint16_t *)j.scales;
+    P.zeros = (uint8_t *)j.zeros;
+    P.choice = j.choice;
+    P.xs = (const uint4 *)j.xs;
+    P.T = (int)j.T;
+    P.G = (int)(j.K / AWQ_GROUP);
+    P.NRB = (int)(j.N / 16);
+    return P;
+}
+
 // Launches for `count` validated matrices, QUANT_MAX_PROBLEMS per launch.  A wave keeps one group
 // and walks down `rb_per_wave` row blocks; that number is chosen so that the waves of a launch
 // about fill the chip once (three waves per SIMD, the kernel's register budget): more waves
 // would queue behind the resident ones as a second, nearly empty round.
-// inv (one matrix, no clipping): the launch also divides activations; the quantizing waves then take two of the
-// three places of a SIMD, so that the others run beside them.
-int quantize_launch(const QuantJob *jobs, int count, const ClipRatios *ratios, hipStream_t stream, InvArgs *inv = nullptr)
+int quantize_launch(const QuantJob *jobs, int count, const ClipRatios *ratios, hipStream_t stream)
 {
-    const int RESIDENT_WAVES = 256 * 4 * (inv ? 2 : ratios ? 3 : AWQ_QUANT_MIN_WAVES == 4 ? 4 : 3);
+    const int RESIDENT_WAVES = 256 * 4 * (ratios ? 3 : AWQ_QUANT_MIN_WAVES == 4 ? 4 : 3);
     for (int first = 0; first < count; first += QUANT_MAX_PROBLEMS) {
         const int n = std::min(QUANT_MAX_PROBLEMS, count - first);
         int64_t tiles = 0;
@@ -454,16 +497,7 @@ int quantize_launch(const QuantJob *jobs, int count, const ClipRatios *ratios, h
         for (int i = 0; i < n; ++i) {
             const QuantJob &j = jobs[first + i];
             QuantProblem &P = A.p[i];
-            P.W = (const uint4 *)j.W;
-            P.s = (const float4 *)j.s;
-            P.qweight = (uint4 *)j.qweight;
-            P.scales = (uint16_t *)j.scales;
-            P.zeros = (uint8_t *)j.zeros;
-            P.choice = j.choice;
-            P.xs = (const uint4 *)j.xs;
-            P.T = (int)j.T;
-            P.G = (int)(j.K / AWQ_GROUP);
-            P.NRB = (int)(j.N / 16);
+            P = quant_problem(j);
             P.rb_per_wave = (int)std::min<int64_t>(per_wave, P.NRB);
             P.unit_begin = units;
             units += ((P.NRB + P.rb_per_wave - 1) / P.rb_per_wave) * P.G;
@@ -472,18 +506,7 @@ int quantize_launch(const QuantJob *jobs, int count, const ClipRatios *ratios, h
         A.count = n;
         A.num_units = units;
         const dim3 grid((unsigned)((units + 3) / 4)), block(256);
-        if (inv) {
-            inv->first_block = (int)grid.x;
-            // one wave to a SIMD, beside two that quantize
-            inv->strips = (inv->K8 + 63) / 64;
-            const int64_t rows = ((int64_t)inv->M * inv->strips + 1023) / 1024;
-            inv->rows = (int)((rows + INV_ROWS - 1) / INV_ROWS * INV_ROWS);
-            const int64_t waves = (int64_t)((inv->M + inv->rows - 1) / inv->rows) * inv->strips;
-            const int64_t blocks = grid.x + (waves + 3) / 4;
-            if (waves > 0x3fffffff || blocks > 0x7fffffff) return AWQ_ERR_BAD_SHAPE;
-            inv->units = (int)waves;
-            quantize_inv_kernel<<<dim3((unsigned)blocks), block, 0, stream>>>(A, *inv);
-        } else if (ratios && act) quantize_pack_kernel<true, true><<<grid, block, 0, stream>>>(A, *ratios);
+        if (ratios && act) quantize_pack_kernel<true, true><<<grid, block, 0, stream>>>(A, *ratios);
         else if (ratios) quantize_pack_kernel<true, false><<<grid, block, 0, stream>>>(A, *ratios);
         else quantize_pack_kernel<false, false><<<grid, block, 0, stream>>>(A, ClipRatios{});
         const int st = awq_launch_status();
@@ -503,13 +526,29 @@ extern "C" int awq_quantize_pack(const void *W_f16, const float *s, int64_t N, i
     return st != AWQ_OK ? st : quantize_launch(&j, 1, nullptr, (hipStream_t)stream);
 }
 
-// awq_quantize_pack(W, s) and awq_apply_inv_scale(x, s) in one launch, for the scale search; arguments validated by it.
+// awq_quantize_pack(W, s) and awq_apply_inv_scale(x, s) for `points` scales in one launch, for the scale search; arguments
+// validated by it.  The scales of the points follow each other; qweight, scales, zeros and xs are the first point's, the next one's
+// are `step` bytes further (a multiple of 16).
 int awq_quantize_inv_launch(const void *W, const float *s, int64_t N, int64_t K, void *qweight, void *scales, void *zeros,
-                            const void *x, int64_t M, void *xs, hipStream_t stream)
+                            const void *x, int64_t M, void *xs, int points, size_t step, hipStream_t stream)
 {
-    const QuantJob j = {W, s, N, K, qweight, scales, zeros, nullptr, nullptr, 0};
-    InvArgs inv = {(const uint4 *)x, (const float4 *)s, (uint4 *)xs, (int)M, (int)(K / 8), 0, 0, 0, 0};
-    return quantize_launch(&j, 1, nullptr, stream, &inv);
+    // the quantizing waves take two of the three places of a SIMD, the dividing ones run beside them
+    const int64_t NRB = N / 16, G = K / AWQ_GROUP;
+    const int64_t rb = std::min(NRB, std::max<int64_t>(1, (NRB * G * points + 2047) / 2048));
+    const int64_t units = (NRB + rb - 1) / rb * G * points;
+    QuantPoints A = {quant_problem({W, s, N, K, qweight, scales, zeros, nullptr, nullptr, 0}), points, (int)units, (int64_t)step};
+    A.p.rb_per_wave = (int)rb;
+    InvArgs I = {(const uint4 *)x, (const float4 *)s, (uint4 *)xs, (int64_t)(step / 16), (int)M, (int)(K / 8), 0, 0, 0, 0, points};
+    I.strips = (I.K8 + 63) / 64;
+    const int64_t rows = (M * I.strips * points + 1023) / 1024;
+    I.rows = (int)((rows + INV_ROWS - 1) / INV_ROWS * INV_ROWS);
+    const int64_t waves = (M + I.rows - 1) / I.rows * I.strips * points;
+    const int64_t first = (units + 31) / 32 * 8, rest = (waves + 31) / 32 * 8;
+    if (units > 0x3fffffff || waves > 0x3fffffff || first + rest > 0x7fffffff) return AWQ_ERR_BAD_SHAPE;
+    I.units = (int)waves;
+    I.first_block = (int)first;
+    quantize_inv_kernel<<<dim3((unsigned)(first + rest)), dim3(256), 0, stream>>>(A, I);
+    return awq_launch_status();
 }
 
 extern "C" int awq_quantize_pack_multi(const awq_quantize_desc *descs, int count, int group, void *stream)

@@ -16,15 +16,16 @@
 #include "awq_gemm_epilogue.h"
 #include "awq_tile.h"
 
+#include <algorithm>
 #include <type_traits>
 
 int awq_act_mean_launch(const void *X_f16, int64_t T, int64_t K, float *mean, hipStream_t stream);
 int awq_quantize_inv_launch(const void *W, const float *s, int64_t N, int64_t K, void *qweight, void *scales, void *zeros,
-                            const void *x, int64_t M, void *xs, hipStream_t stream);
+                            const void *x, int64_t M, void *xs, int points, size_t step, hipStream_t stream);
 bool awq_linear_takes_prefill(int M, int N, int K);
 int64_t awq_gemm_tiles(int M, int N);
 int awq_gemm_launch_loss(const void *x, const void *qweight, const void *scales, const void *zeros, const void *y_ref,
-                         int M, int N, int K, double *loss, hipStream_t stream);
+                         int M, int N, int K, double *loss, int points, size_t step, size_t loss_step, hipStream_t stream);
 
 namespace {
 
@@ -279,12 +280,13 @@ __global__ __launch_bounds__(1024) void finalize_kernel(const double *__restrict
 }
 
 struct SearchLayout {
-    size_t mean, s, xs, q, sc, zp, y, yq, partial, total;
+    size_t mean, s, xs, q, sc, zp, step, y, yq, partial, powers, total;
 };
 
 inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-SearchLayout search_layout(int64_t T, int64_t N, int64_t K, int n_alpha)
+// `points` candidates, `step` bytes apart
+SearchLayout search_layout(int64_t T, int64_t N, int64_t K, int n_alpha, int points)
 {
     SearchLayout L;
     const int64_t G = K / AWQ_GROUP;
@@ -295,11 +297,55 @@ SearchLayout search_layout(int64_t T, int64_t N, int64_t K, int n_alpha)
     L.q = o; o = up256(o + (size_t)N * K / 2);
     L.sc = o; o = up256(o + (size_t)N * G * 2);
     L.zp = o; o = up256(o + (size_t)N * G / 2);
+    L.step = o - L.xs;
+    o += (size_t)(points - 1) * L.step;
     L.y = o; o = up256(o + (size_t)T * N * 2);
     L.yq = o; o = up256(o + (size_t)T * N * 2);
     L.partial = o; o = up256(o + (size_t)n_alpha * LOSS_BLOCKS * 8);
+    // the powers of all grid points: in the place of the candidate's outputs, where that is large enough (several candidates at a time
+    // are evaluated without it)
+    L.powers = (int64_t)n_alpha * K * 4 <= T * N * 2 ? L.yq : o;
+    if (points > 1 && L.powers == o) o = up256(o + (size_t)n_alpha * K * 4);
     L.total = o;
     return L;
+}
+
+// How a grid point's product and loss are computed.
+struct SearchProduct {
+    bool fused, prefill;           // the loss in the product's epilogue; by the prefill kernel
+    TilePlan plan;                 // otherwise by the tile kernel
+    int64_t tiles;                 // partial sums of a point
+};
+
+SearchProduct search_product(int64_t T, int64_t N, int64_t K, int points)
+{
+    // Above 16 tokens the kernel that the layer runs, prefill or tile, has a loss form that takes the differences
+    // in the product's epilogue (2048 x 4096 x 4096: the product 59 us either way, without the 7 us pass over both
+    // outputs; 159 x 1120 x 2944: 21.2 us a grid point before, 16.5 then); its tiles have to fit the
+    // partial sums of a grid point
+    SearchProduct P = {false, false, {1, 1, 0.0}, 0};
+    if (T <= 16) return P;
+    P.prefill = awq_linear_takes_prefill((int)T, (int)N, (int)K);
+    if (!P.prefill) P.plan = awq_tile_plan((int)T, (int)N, (int)K, points);
+    P.tiles = P.prefill ? awq_gemm_tiles((int)T, (int)N) : awq_tile_count(P.plan, (int)T, (int)N);
+    P.fused = P.tiles <= LOSS_BLOCKS;
+    return P;
+}
+
+// Candidates at a time, given the workspace for it.  One by one a search is a chain of launches: quantizing and dividing (17 us at 4096 x
+// 4096 and 2048 rows, a third of it start and run-out) and a product that fills the chip only where the layer is large.  Together W and X
+// are read, and the launches made, once for all of them, and their products fill the chip together.  As many as 128 MB hold, so
+// that the memory-side cache still has them for the product (60 / 128 / 180 / 600 MB: 4096 x 4096 at 2048 rows 1389 / 1360 / 1373 /
+// 1407 us, at 200 rows 497 / 488 / 489 / 476).  us, one by one and together, 20 points: 2048 x 4096 x 4096 1483 / 1360,
+// 1722 x 3472 x 2304 846 / 654, 537 x 1328 x 1920 349 / 188, 95 x 1456 x 1792 273 / 91, 64 x 1024 x 1024 195 / 60.
+int search_points(int64_t T, int64_t N, int64_t K, int n_alpha)
+{
+    static const int64_t megabytes = awq_knob("AWQ_SEARCH_MB", 128);
+    const SearchLayout L = search_layout(T, N, K, n_alpha, 1);
+    const int64_t most = std::min<int64_t>(n_alpha, (megabytes << 20) / (int64_t)L.step);
+    if (most < 2) return 1;
+    const int launches = (int)((n_alpha + most - 1) / most), points = (n_alpha + launches - 1) / launches;
+    return search_product(T, N, K, points).fused ? points : 1;
 }
 
 int check_search_shape(int64_t T, int64_t N, int64_t K, int n_alpha, int group)
@@ -317,7 +363,13 @@ extern "C" size_t awq_search_scale_workspace_bytes(int64_t T, int64_t N, int64_t
                                                    int group)
 {
     if (check_search_shape(T, N, K, n_alpha, group) != AWQ_OK) return 0;
-    return search_layout(T, N, K, n_alpha).total;
+    return search_layout(T, N, K, n_alpha, 1).total;
+}
+
+extern "C" size_t awq_search_scale_batch_workspace_bytes(int64_t T, int64_t N, int64_t K, int n_alpha, int group)
+{
+    if (check_search_shape(T, N, K, n_alpha, group) != AWQ_OK) return 0;
+    return search_layout(T, N, K, n_alpha, search_points(T, N, K, n_alpha)).total;
 }
 
 extern "C" int awq_search_scale(const void *W_f16, const void *X_f16, int64_t T, int64_t N, int64_t K,
@@ -338,8 +390,10 @@ extern "C" int awq_search_scale(const void *W_f16, const void *X_f16, int64_t T,
         (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 ||
         (reinterpret_cast<uintptr_t>(losses) & 7u) != 0 || (reinterpret_cast<uintptr_t>(best) & 3u) != 0)
         return AWQ_ERR_MISALIGNED;
-    const SearchLayout L = search_layout(T, N, K, n_alpha);
-    if (workspace_bytes < L.total) return AWQ_ERR_WORKSPACE_TOO_SMALL;
+    if (workspace_bytes < search_layout(T, N, K, n_alpha, 1).total) return AWQ_ERR_WORKSPACE_TOO_SMALL;
+    int points = search_points(T, N, K, n_alpha);
+    while (points > 1 && workspace_bytes < search_layout(T, N, K, n_alpha, points).total) --points;
+    const SearchLayout L = search_layout(T, N, K, n_alpha, points);
     unsigned char *ws = static_cast<unsigned char *>(workspace);
     float *mean = reinterpret_cast<float *>(ws + L.mean);
     float *s = reinterpret_cast<float *>(ws + L.s);
@@ -353,32 +407,26 @@ extern "C" int awq_search_scale(const void *W_f16, const void *X_f16, int64_t T,
     if (st != AWQ_OK) return st;
     st = dense_gemm_launch((const half_t *)X_f16, (const half_t *)W_f16, Y, (int)T, (int)N, (int)K, hs);
     if (st != AWQ_OK) return st;
-    // Above 16 tokens the kernel that the layer runs, prefill or tile, has a loss form that takes the differences
-    // in the product's epilogue (2048 x 4096 x 4096: the product 59 us either way, without the 7 us pass over both
-    // outputs; 159 x 1120 x 2944: 21.2 us a grid point before, 16.5 now, with the powers below); its tiles have to fit the
-    // partial sums of a grid point
-    const bool prefill = T > 16 && awq_linear_takes_prefill((int)T, (int)N, (int)K);
-    const TilePlan plan = awq_tile_plan((int)T, (int)N, (int)K);
-    const int64_t tiles = prefill ? awq_gemm_tiles((int)T, (int)N) : awq_tile_count(plan, (int)T, (int)N);
-    const bool fused = T > 16 && tiles <= LOSS_BLOCKS;
+    const SearchProduct P = search_product(T, N, K, points);
+    if (!P.fused) points = 1;                            // (fewer candidates at a time than search_points() had in mind)
     const int64_t chunks = T * N / 8;                    // N % 16 == 0
-    // the powers of all grid points in one launch, in the place of the candidate's outputs, where that place is
-    // not used and holds them
-    const bool table = fused && (int64_t)n_alpha * K * 4 <= T * N * 2;
-    float *powers = table ? reinterpret_cast<float *>(Yq) : s;
-    for (int i = 0; i < n_alpha; ++i) {
+    // the powers of all grid points in one launch, where their place is not used for outputs
+    const bool table = P.fused && L.powers < L.total;
+    float *powers = table ? reinterpret_cast<float *>(ws + L.powers) : s;
+    for (int i = 0; i < n_alpha; i += points) {
+        const int count = std::min(points, n_alpha - i);
         if (!table || i == 0) {
             pow_kernel<<<dim3((unsigned)((K + 255) / 256), table ? (unsigned)n_alpha : 1u), dim3(256), 0, hs>>>(
                 mean, al, i, (int)K, powers);
             st = awq_launch_status();
             if (st != AWQ_OK) return st;
         }
-        st = awq_quantize_inv_launch(W_f16, table ? powers + (size_t)i * K : s, N, K, q, sc, zp, X_f16, T, xs, hs);
+        st = awq_quantize_inv_launch(W_f16, table ? powers + (size_t)i * K : s, N, K, q, sc, zp, X_f16, T, xs, count, L.step, hs);
         if (st != AWQ_OK) return st;
         double *part = partial + (size_t)i * LOSS_BLOCKS;
-        if (fused) {
-            st = prefill ? awq_gemm_launch_loss(xs, q, sc, zp, Y, (int)T, (int)N, (int)K, part, hs)
-                         : awq_tile_launch_loss(plan, xs, q, sc, zp, Y, (int)T, (int)N, (int)K, part, hs);
+        if (P.fused) {
+            st = P.prefill ? awq_gemm_launch_loss(xs, q, sc, zp, Y, (int)T, (int)N, (int)K, part, count, L.step, LOSS_BLOCKS, hs)
+                           : awq_tile_launch_loss(P.plan, xs, q, sc, zp, Y, (int)T, (int)N, (int)K, part, count, L.step, LOSS_BLOCKS, hs);
             if (st != AWQ_OK) return st;
             continue;
         }
@@ -388,6 +436,6 @@ extern "C" int awq_search_scale(const void *W_f16, const void *X_f16, int64_t T,
         st = awq_launch_status();
         if (st != AWQ_OK) return st;
     }
-    finalize_kernel<<<dim3(1), dim3(1024), 0, hs>>>(partial, fused ? (int)tiles : LOSS_BLOCKS, n_alpha, al, mean, (int)K, losses, best, s_best);
+    finalize_kernel<<<dim3(1), dim3(1024), 0, hs>>>(partial, P.fused ? (int)P.tiles : LOSS_BLOCKS, n_alpha, al, mean, (int)K, losses, best, s_best);
     return awq_launch_status();
 }

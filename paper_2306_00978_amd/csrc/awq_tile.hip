@@ -123,20 +123,37 @@ __device__ __forceinline__ int quotient(int a, int b, uint32_t inverse)
     return a - q * b >= b ? q + 1 : q;
 }
 
+// With `loss`: the tiles of several grid points follow each other; point i has its operands i `step` bytes and its sums
+// loss_step further.
+struct TilePoints {
+    int tiles;                     // of a point
+    uint32_t tiles_inverse;
+    int64_t step, loss_step;
+};
+
 template <int BITS, int MT, int NT>
 __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
     const unsigned char *__restrict__ x, const unsigned char *__restrict__ qweight,
     const unsigned char *__restrict__ scales, const unsigned char *__restrict__ zeros,
     half_t *__restrict__ y, int M, int N, int K, int tiles_n, uint32_t tiles_n_inverse, uint32_t runs_inverse,
-    uint32_t runs_inverse_long, int tiles_total, double *__restrict__ loss)
+    uint32_t runs_inverse_long, int tiles_total, double *__restrict__ loss, const TilePoints points)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     asm volatile("" ::"s"(x), "s"(qweight), "s"(scales), "s"(zeros), "s"(y), "s"(M), "s"(N), "s"(K), "s"(tiles_n),
                  "s"(tiles_n_inverse), "s"(runs_inverse), "s"(runs_inverse_long), "s"(tiles_total), "s"(loss));   // arguments in one round
     // contiguous ranges of tiles, token-tile-major, per XCD (own L2): see gemm_kernel
     const int per_xcd = (tiles_total + 7) >> 3;
-    const int unit = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
+    int unit = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
     if (unit >= tiles_total || ((int)blockIdx.x >> 3) >= per_xcd) return;
+    if (BITS == 4 && loss) {
+        const int point = quotient(unit, points.tiles, points.tiles_inverse);
+        unit -= point * points.tiles;
+        x += point * points.step;
+        qweight += point * points.step;
+        scales += point * points.step;
+        zeros += point * points.step;
+        loss += point * points.loss_step;
+    }
     const int tile_m = quotient(unit, tiles_n, tiles_n_inverse), tile_n = unit - tile_m * tiles_n;
     const uint32_t lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -403,10 +420,10 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
 
 template <int BITS, int MT, int NT>
 int launch_one(const void *x, const void *qweight, const void *scales, const void *zeros, void *y, int M, int N,
-               int K, double *loss, hipStream_t stream)
+               int K, double *loss, int count, size_t step, size_t loss_step, hipStream_t stream)
 {
     const int tiles_n = (N / 16 + NT - 1) / NT;
-    const int64_t total = awq_tile_count({MT, NT, 0.0}, M, N);
+    const int64_t tiles = awq_tile_count({MT, NT, 0.0}, M, N), total = tiles * count;
     if (total > (1 << 30)) return AWQ_ERR_BAD_SHAPE;
     constexpr int lds = tile_lds(MT, NT);
     static_assert(lds <= 160 * 1024, "LDS of a CU");
@@ -423,11 +440,13 @@ int launch_one(const void *x, const void *qweight, const void *scales, const voi
     tile_kernel<BITS, MT, NT><<<dim3((unsigned)((total + 7) / 8 * 8)), dim3(64 * TILE_WAVES), lds, stream>>>(
         (const unsigned char *)x, (const unsigned char *)qweight, (const unsigned char *)scales,
         (const unsigned char *)zeros, (half_t *)y, M, N, K, tiles_n, 0xFFFFFFFFu / (uint32_t)tiles_n,
-        0xFFFFFFFFu / (runs > 0 ? runs : 1u), 0xFFFFFFFFu / (runs + 1), (int)total, loss);
+        0xFFFFFFFFu / (runs > 0 ? runs : 1u), 0xFFFFFFFFu / (runs + 1), (int)total, loss,
+        TilePoints{(int)tiles, 0xFFFFFFFFu / (uint32_t)tiles, (int64_t)step, (int64_t)loss_step});
     return awq_launch_status();
 }
 
-typedef int (*TileFn)(const void *, const void *, const void *, const void *, void *, int, int, int, double *, hipStream_t);
+typedef int (*TileFn)(const void *, const void *, const void *, const void *, void *, int, int, int, double *, int, size_t, size_t,
+                      hipStream_t);
 
 constexpr int MTS[] = {1, 2, 3, 4, 5, 6, 8};
 // 128 x 64 does not fit the registers
@@ -465,7 +484,7 @@ TileFn pick(int mt, int nt)
 // Fitted to 12300 launches of 2036 shapes (256 to 128256 features, 128 to 32768 columns, 17 to 1600 tokens; of each the shapes of a
 // workgroup within a quarter of the fastest): 6 % rms, 9 % above 24576 columns (where it is 32 % off in one of twenty without the
 // last two terms).  The shape it picks takes 0.8 % longer than the fastest one on average.
-TilePlan awq_tile_plan(int M, int N, int K)
+TilePlan awq_tile_plan(int M, int N, int K, int points)
 {
     const int forced = awq_tile_override();
     if (forced > 0) return {forced / 10, forced % 10, 0.0};
@@ -474,7 +493,7 @@ TilePlan awq_tile_plan(int M, int N, int K)
         for (int nt = 1; nt <= 4; ++nt) {
             if (!tile_built(mt, nt)) continue;
             const int tiles_n = (N / 16 + nt - 1) / nt, tiles_m = (int)(((unsigned)M + 16 * mt - 1) / (16u * mt));
-            const int64_t wgs = (int64_t)tiles_n * tiles_m;
+            const int64_t wgs = (int64_t)tiles_n * tiles_m * points;
             const double rounds = (double)((wgs + 255) / 256), full = (double)wgs / (256.0 * rounds);
             const double l2 = mt * (double)K / 131072.0;                            // a token tile's rows, of 4 MB
             double longer = 1.0;
@@ -499,11 +518,13 @@ int awq_tile_launch(int bits, const TilePlan &plan, const void *x, const void *q
                     const void *zeros, void *y, int M, int N, int K, hipStream_t stream)
 {
     const TileFn fn = bits == 4 ? pick<4>(plan.mt, plan.nt) : bits == 3 ? pick<3>(plan.mt, plan.nt) : pick<2>(plan.mt, plan.nt);
-    return fn(x, qweight, scales, zeros, y, M, N, K, nullptr, stream);
+    return fn(x, qweight, scales, zeros, y, M, N, K, nullptr, 1, 0, 0, stream);
 }
 
 int awq_tile_launch_loss(const TilePlan &plan, const void *x, const void *qweight, const void *scales, const void *zeros,
-                         const void *y_ref, int M, int N, int K, double *loss, hipStream_t stream)
+                         const void *y_ref, int M, int N, int K, double *loss, int points, size_t step, size_t loss_step,
+                         hipStream_t stream)
 {
-    return pick<4>(plan.mt, plan.nt)(x, qweight, scales, zeros, const_cast<void *>(y_ref), M, N, K, loss, stream);
+    return pick<4>(plan.mt, plan.nt)(x, qweight, scales, zeros, const_cast<void *>(y_ref), M, N, K, loss, points, step, loss_step,
+                                     stream);
 }
