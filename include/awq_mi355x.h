@@ -339,7 +339,7 @@ int awq_w4a16_linear_chain(const awq_chain_stage *stages, int n_stages, int64_t 
                            int spin_limit, void *stream);
 
 /* Diagnostic: how the last grouped decode launch of this process (awq_w4a16_linear_multi,
- * awq_w3a16_linear_multi, awq_w4a16_linear_fused_multi through the streaming kernel) laid out its
+ * awq_w3a16_linear_multi, awq_w4a16_linear_fused_multi in one launch) laid out its
  * workgroups: 0 = none yet, 1 = one size of workgroup per linear, 2 = two sizes per linear, paired
  * large with small on every CU.  Not synchronised between threads. */
 int awq_last_grouped_plan(void);

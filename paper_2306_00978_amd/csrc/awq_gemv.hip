@@ -28,8 +28,11 @@
 // The partial sums of the waves are combined through LDS in a fixed order
 // (deterministic output), rounded once to fp16 and stored.
 #include "awq_common.h"
+#include "awq_gemv_stream.h"
 
 #include <stdlib.h>
+
+#include <algorithm>
 
 namespace {
 
@@ -296,6 +299,167 @@ __global__ __launch_bounds__(1024, (MS >= 8 || (U == 4 && (PIPE || MS == 0 || (B
     }
 }
 
+// Several linears in one launch: the same kernel with eight waves to a row block, which divide the groups of a row evenly,
+// whatever their number, and take them two at a time.  A group past the end of a wave's range repeats its last one (loads that
+// hit the cache) and is skipped by a wave-uniform branch.  It starts sooner than the streaming kernel (no plan to read, no
+// activations to stage for a whole row, everything of a wave requested at once) and spends more instructions per weight, so it
+// takes the small launches (awq_linear.hip).  A layer of seven linears at 1 / 4 / 8 tokens, us, before and now: hidden size 1024 (2816)
+// 6.3 / 7.9 / 8.5 and 4.7 / 4.7 / 5.6, 1536 (4608) 7.0 / 8.8 / 10.8 and 5.8 / 5.9 / 7.0, 2048 (5632) 8.6 / 10.9 / 13.1 and 8.0 / 8.2 / 10.0.
+// (Four groups at a time: 4.9 to 6.9, 6.3 to 9.2, 9.3 to 12.5.)
+struct GemvGroupArgs {
+    GemvProblem p[GEMV_GROUP_MAX];
+    int first[GEMV_GROUP_MAX];                     // workgroup of each
+    int count, M;
+};
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+constexpr int GROUP_LOGW = 3, GROUP_U = 2;
+
+template <int BITS, int MS>
+__global__ __launch_bounds__(64 << GROUP_LOGW, MS >= 8 ? 4 : 6) void gemv_group_kernel(const GemvGroupArgs A)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int W = 1 << GROUP_LOGW, U = GROUP_U;
+    constexpr int LPR = U * 16, RPP = 64 / LPR, NS = (MS + RPP - 1) / RPP;
+    constexpr int ROW_BYTES = U * 256 + 16, WAVE_BYTES = MS * ROW_BYTES;
+    int pi = 0;
+#pragma unroll
+    for (int n = 1; n < GEMV_GROUP_MAX; ++n)
+        if (n < A.count && (int)blockIdx.x >= A.first[n]) pi = n;
+    const GemvProblem &P = A.p[pi];
+    const half_t *__restrict__ x = P.x;
+    const uint32_t *__restrict__ qweight = reinterpret_cast<const uint32_t *>(P.q);
+    const int N = P.N, G = P.K / AWQ_GROUP, M = A.M;
+    half_t *y = P.y;
+    asm volatile("" ::"s"(x), "s"(qweight), "s"(P.sc), "s"(P.zp), "s"(y), "s"(N), "s"(G), "s"(M));
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rb = (int)blockIdx.x - A.first[pi];
+    const int r = lane & 15, c = lane >> 4;
+    const int cu = c < U ? c : U - 1;
+    const int g0 = (G * wave) >> GROUP_LOGW, g1 = (G * (wave + 1)) >> GROUP_LOGW;
+    const uint32_t *qt = qweight + ((int64_t)rb * G * 64 + lane) * BITS;
+    const uint16_t *sc = P.sc + (int64_t)rb * G * 16 + r;
+    const uint8_t *zp = P.zp + (int64_t)rb * G * 8 + (r >> 1);
+    const int zshift = (r & 1) * 4;
+    const int mrow = r < M ? r : M - 1;
+    unsigned char *xw = smem + (size_t)wave * WAVE_BYTES;
+    const uint4 *xl = reinterpret_cast<const uint4 *>(xw + mrow * ROW_BYTES) + c;
+    const int srow = lane / LPR, schunk = lane % LPR;
+    const int64_t K8 = (int64_t)G * 16;
+
+    uint32_t q[U][BITS], s_raw = 0, z_raw = 0;
+    u32x4 xs[NS];
+    auto request = [&](int base) {
+        const int last = g1 - 1;
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            const int m = i * RPP + srow;
+            xs[i] = reinterpret_cast<const u32x4 *>(x)[(int64_t)(m < M ? m : M - 1) * K8 + min(base + (schunk >> 4), last) * 16 + (schunk & 15)];
+        }
+        const int gm = min(base + cu, last);
+        s_raw = sc[gm * 16];
+        z_raw = zp[gm * 8];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t *at = qt + min(base + u, last) * (64 * BITS);
+            if (BITS == 4) {
+                const u32x4 v = *reinterpret_cast<const u32x4 *>(at);
+                q[u][0] = v[0]; q[u][1] = v[1]; q[u][2] = v[2]; q[u][BITS - 1] = v[3];
+            } else {
+#pragma unroll
+                for (int i = 0; i < BITS; ++i) q[u][i] = at[i];
+            }
+        }
+    };
+    floatx4 total = {0.f, 0.f, 0.f, 0.f};
+    if (g0 < g1) request(g0);
+    for (int base = g0; base < g1; base += U) {
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            const int m = i * RPP + srow;
+            if (MS % RPP == 0 || m < MS) reinterpret_cast<u32x4 *>(xw + m * ROW_BYTES)[schunk] = xs[i];
+        }
+        uint32_t qc[U][BITS];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < BITS; ++i) qc[u][i] = q[u][i];
+        // codes as subnormals q 2^-24; the zero point leaves in fp32 through S = 2^-24 sum_k x_k (a second chain against the
+        // constant code 1)
+        const float own_zf = (float)((z_raw >> zshift) & 0xFu);
+        const float own_sv = (float)__builtin_bit_cast(half_t, (uint16_t)s_raw) * 16777216.f;
+        if (base + U < g1) request(base + U);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (base + u >= g1) continue;                              // wave-uniform
+            uint4 xa[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) xa[j] = xl[u * 16 + 4 * j];
+            const int src = r + 16 * u;
+            const float sv = __shfl(own_sv, src), zf = __shfl(own_zf, src);
+            const half8_t ones = __builtin_bit_cast(half8_t, make_uint4(0x00010001u, 0x00010001u, 0x00010001u, 0x00010001u));
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f}, xsum = {0.f, 0.f, 0.f, 0.f};
+            const uint32_t *w = qc[u];
+            const uint32_t last = BITS == 3 ? ((w[0] >> 15) & 0x00010001u) | ((w[1] >> 14) & 0x00020002u) | ((w[2] >> 13) & 0x00040004u) : 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const half8_t a = __builtin_bit_cast(half8_t, xa[j]);
+                half8_t b;
+                if constexpr (BITS == 3) {
+                    const uint32_t w3[3] = {w[0], w[1], w[2]};
+                    b = w3_halves(w3, last, j);
+                } else {
+                    const uint32_t v = w[j & (BITS - 1)];
+                    b = __builtin_bit_cast(half8_t, make_uint4(v & 0x000F000Fu, (v >> 4) & 0x000F000Fu, (v >> 8) & 0x000F000Fu,
+                                                               (v >> 12) & 0x000F000Fu));
+                }
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, acc, 0, 0, 0);
+                xsum = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, ones, xsum, 0, 0, 0);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) total[v] += sv * (acc[v] - zf * xsum[v]);
+        }
+    }
+    // the partials of one output are contiguous: red[16 m + n][wave]
+    float *red = reinterpret_cast<float *>(smem + (size_t)W * WAVE_BYTES);
+    if (4 * c < M) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[((4 * c + v) * 16 + r) * W + wave] = total[v];
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < 16 * M; t += 64 * W) {
+        const float4 *p = reinterpret_cast<const float4 *>(red + t * W);
+        const float4 a0 = p[0], a1 = p[1];
+        const float sum = ((((((a0.x + a0.y) + a0.z) + a0.w) + a1.x) + a1.y) + a1.z) + a1.w;
+        y[(int64_t)(t >> 4) * N + rb * 16 + (t & 15)] = (half_t)sum;
+    }
+}
+
+template <int BITS, int MS>
+int gemv_group_one(const GemvGroupArgs &A, int total, hipStream_t stream)
+{
+    const size_t lds = (size_t)(8 * MS * (GROUP_U * 256 + 16)) + (size_t)((A.M + 3) / 4 * 4) * 16 * 8 * 4;
+    static AwqOncePerDevice once;
+    std::atomic<bool> &raised = once.here();
+    if (lds > 64 * 1024 && !raised.load(std::memory_order_relaxed)) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(gemv_group_kernel<BITS, MS>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+            return AWQ_ERR_HIP;
+        raised.store(true, std::memory_order_relaxed);
+    }
+    gemv_group_kernel<BITS, MS><<<dim3((unsigned)total), dim3(64 << GROUP_LOGW), lds, stream>>>(A);
+    return awq_launch_status();
+}
+
+template <int BITS>
+int gemv_group_bits(const GemvGroupArgs &A, int total, hipStream_t stream)
+{
+    const int M = A.M;
+    return M == 1 ? gemv_group_one<BITS, 1>(A, total, stream) : M == 2 ? gemv_group_one<BITS, 2>(A, total, stream)
+         : M <= 4 ? gemv_group_one<BITS, 4>(A, total, stream) : M <= 8 ? gemv_group_one<BITS, 8>(A, total, stream)
+                                                                       : gemv_group_one<BITS, 16>(A, total, stream);
+}
+
 // log2 of the waves per workgroup: about four tiles per wave, 4..16 waves
 int pick_log_waves(int G)
 {
@@ -403,4 +567,58 @@ int awq_gemv_launch_residual(const void *x, const void *qweight, const void *sca
                              void *y, const void *res, int M, int N, int K, hipStream_t stream)
 {
     return gemv_launch_bits<4>(x, qweight, scales, zeros, y, M, N, K, stream, res);
+}
+
+// Linears with the longest rows first: their workgroups run longest.
+int awq_gemv_group_launch(int bits, const GemvProblem *p, int count, int M, hipStream_t stream)
+{
+    if (count < 1 || count > GEMV_GROUP_MAX) return AWQ_ERR_BAD_ARGUMENT;
+    GemvGroupArgs A = {};
+    int order[GEMV_GROUP_MAX];
+    for (int i = 0; i < count; ++i) order[i] = i;
+    std::stable_sort(order, order + count, [&](int a, int b) { return p[a].K > p[b].K; });
+    int64_t total = 0;
+    for (int i = 0; i < count; ++i) {
+        A.p[i] = p[order[i]];
+        A.first[i] = (int)total;
+        total += A.p[i].N / 16;
+    }
+    if (total > (1 << 30)) return AWQ_ERR_BAD_SHAPE;
+    A.count = count;
+    A.M = M;
+    return bits == 4 ? gemv_group_bits<4>(A, (int)total, stream) : gemv_group_bits<3>(A, (int)total, stream);
+}
+
+// us, from the row blocks, the weight tiles (16 x 128) and the batches of the longest row and of all rows.  Fitted to 16000 launches of one
+// to seven linears of 256 to 32768 features and 256 to 28672 columns: 6 to 7 % rms.
+double awq_gemv_group_us(int bits, const GemvProblem *p, int count, int M)
+{
+    double blocks = 0.0, tiles = 0.0, batches = 0.0, longest = 0.0;
+    for (int i = 0; i < count; ++i) {
+        const int rb = p[i].N / 16, G = p[i].K / AWQ_GROUP, per = ((G + 7) / 8 + GROUP_U - 1) / GROUP_U;
+        blocks += rb;
+        tiles += (double)rb * G;
+        batches += (double)rb * per;
+        longest = std::max(longest, (double)per);
+    }
+    static const double fit[2][3][5] = {{{2.116, 0.064, 0.162, 0.443, 0.608}, {2.173, 0.300, 0.209, 0.468, 0.409}, {2.207, 0.446, 0.257, 0.657, 0.373}},
+                                        {{2.111, 0.058, 0.168, 0.434, 0.772}, {2.203, 0.272, 0.225, 0.456, 0.506}, {2.311, 0.450, 0.282, 0.666, 0.402}}};
+    const double *c = fit[bits == 4][M <= 4 ? 0 : M <= 8 ? 1 : 2];
+    return c[0] + c[1] * blocks / 256.0 + c[2] * tiles / 1000.0 + c[3] * longest + c[4] * batches / 1000.0;
+}
+
+// us of the launch of one linear at five tokens and more: tiles that a wave walks (rounds of workgroups, as the LDS admits them), and all
+// tiles.  3700 launches in 4 bits, 3600 in 3: 8 to 9 % rms.
+double awq_gemv_us(int bits, int M, int N, int K)
+{
+    const int G = K / AWQ_GROUP, W = 1 << pick_log_waves(G), MS = M <= 8 ? 8 : 16;
+    int U = pick_unroll(G);
+    if (MS == 16 && U == 4) U = 2;
+    const int lds = (M + 3) / 4 * 4 * 1024 + W * MS * (U * 256 + 16);
+    const int resident = std::max(1, std::min(160 * 1024 / lds, 16 / W));
+    const double rounds = (double)((N / 16 + 256 * resident - 1) / (256 * resident)), walk = rounds * U * ((G / U + W - 1) / W);
+    const double tiles = (double)(N / 16) * G / 1000.0;
+    if (M <= 8) return bits == 4 ? 2.03 + 0.245 * walk + (0.203 + 0.0076 * M) * tiles : 2.08 + 0.257 * walk + (0.185 + 0.006 * M) * tiles;
+    return bits == 4 ? 1.82 + 0.135 * rounds + 0.408 * walk + (0.199 + 0.0094 * M) * tiles
+                     : 2.00 + 0.025 * rounds + 0.381 * walk + (0.166 + 0.0086 * M) * tiles;
 }

@@ -76,3 +76,27 @@ int awq_gemv_stream_launch_fused(const GemvProblem *problems, const GemvFusedExt
                                  int M, hipStream_t stream);
 // whether a linear of this shape can be part of a grouped launch at this M
 bool awq_gemv_stream_fits(int N, int K, int M);
+
+// Up to GEMV_GROUP_MAX linears at up to 16 tokens in one launch of the batch kernel (awq_gemv.hip, 4 and 3 bits) or of the tile kernel
+// (awq_tile.hip, nt row blocks to a workgroup), any K, and their estimated times.
+constexpr int GEMV_GROUP_MAX = 8;
+int awq_gemv_group_launch(int bits, const GemvProblem *p, int count, int M, hipStream_t stream);
+double awq_gemv_group_us(int bits, const GemvProblem *p, int count, int M);
+int awq_tile_group_launch(int bits, int nt, const GemvProblem *p, int count, int M, hipStream_t stream);
+double awq_tile_group_us(int bits, const GemvProblem *p, int count, int M, int *nt);
+double awq_gemv_us(int bits, int M, int N, int K);
+
+// Which calls are looked at at all (weights: of a lone linear).  Up to four tokens a lone linear is the single kernel's, as are small ones beyond, where a
+// call is bound by the host: from five tokens below 16 thousand tiles of 16 x 128, from nine below 4 thousand.  The 2-bit decode kernel
+// is the faster one up to eight tokens.
+inline bool awq_few_considered(int bits, int count, int M, int64_t weights)
+{
+    if (awq_knob("AWQ_FEW", -1) > 0) return count <= GEMV_GROUP_MAX;
+    if (bits == 2 && M <= 8) return false;
+    if (count == 1) return M > 4 && weights >= (M <= 8 ? (int64_t)32 << 20 : (int64_t)8 << 20);
+    return count <= GEMV_GROUP_MAX;
+}
+// The linears of a decode call by one of these two kernels, where that is the faster way; AWQ_GEMV_STREAM_UNFIT, and nothing
+// launched, where it is not.
+void awq_note_plain_plan();          // for awq_last_grouped_plan: one size of workgroup per linear
+int awq_few_launch(int bits, const GemvProblem *p, int count, int M, hipStream_t stream);

@@ -1756,6 +1756,8 @@ int awq_gemv_stream_launch_fused(const GemvProblem *problems, const GemvFusedExt
     return stream_launch_bits<4, true>(problems, extra, count, M, stream);
 }
 
+void awq_note_plain_plan() { g_last_plan.store(1, std::memory_order_relaxed); }
+
 extern "C" int awq_last_grouped_plan(void)
 {
     return g_last_plan.load(std::memory_order_relaxed);

@@ -8,6 +8,7 @@
 #include <stdlib.h>
 #include <algorithm>
 #include <atomic>
+#include <string>
 
 int awq_gemv_launch_residual(const void *x, const void *qweight, const void *scales, const void *zeros,
                              void *y, const void *res, int M, int N, int K, hipStream_t stream);
@@ -62,6 +63,53 @@ bool takes_tile_kernel(const TilePlan &plan, int M, int N, int K, bool split)
 
 }  // namespace
 
+// Which kernel takes the linears of a decode call: the estimated times of the batch kernel (several linears, 4 and 3 bits) and of the
+// tile kernel against one of the kernels that would run otherwise -- for several linears a fit to what those took, of the weight
+// tiles in thousands, the longest row in thousands of columns and the row blocks in 256: the streaming kernel up to four tokens, from five (3 bits:
+// nine) the one that takes the activations through LDS, or several launches; 7 to 14 % rms.  8 % in favour of those, and 15 % from 32
+// thousand tiles (a layer of hidden size 2304), where the estimates' errors are larger than what is to be gained.  Over 1900 calls of two to
+// seven linears in 4 bits and 1800 in 3 (graph replays, eight token counts each) the choice is 1.16, 1.24, 1.35, 1.25, 1.38 and 1.37 times faster at 1, 2, 4,
+// 5, 8 and 9 to 16 tokens -- 1.3 to 1.6 times below 16 thousand tiles -- and more than 3 % slower in one call of a hundred.
+// One linear: from five tokens, 1.03 times faster at 5 to 8 and 1.1 from 9.  2 bits: from nine tokens, 1.07.
+int awq_few_launch(int bits, const GemvProblem *p, int count, int M, hipStream_t stream)
+{
+    // (the tuning build: 0 the kernels that would run otherwise, 1 to 4 the tile kernel, 5 the batch kernel)
+    // (and an override of another decode kernel's plan asks for that kernel)
+    int forced = awq_knob("AWQ_FEW", -1);
+#ifdef AWQ_TUNING_KNOBS
+    for (const char *plan : {"STAGES", "SLOTS", "KSL", "ITERS", "JOBS", "WAVES", "STREAM_SINGLE"})
+        if (getenv((std::string("AWQ_GEMV_") + plan).c_str())) forced = 0;
+#endif
+    if (forced == 0 || !awq_few_considered(bits, count, M, count == 1 ? (int64_t)p[0].N * p[0].K : 0)) return AWQ_GEMV_STREAM_UNFIT;
+    if (forced > 0 && forced < 5) return awq_tile_group_launch(bits, forced, p, count, M, stream);
+    if (forced == 5) return bits == 2 ? AWQ_GEMV_STREAM_UNFIT : awq_gemv_group_launch(bits, p, count, M, stream);
+    double tiles = 0.0, blocks = 0.0, longest = 0.0;
+    for (int i = 0; i < count; ++i) {
+        blocks += p[i].N / 16 / 256.0;
+        tiles += (double)(p[i].N / 16) * (p[i].K / AWQ_GROUP) / 1000.0;
+        longest = std::max(longest, p[i].K / 1024.0);
+    }
+    static const double fit[2][6][4] = {{{3.75, 0.137, 0.239, 0.255}, {4.11, 0.130, 0.282, 0.236}, {4.74, 0.141, 0.333, 0.284},
+                                         {3.76, 0.179, 0.507, 0.174}, {4.26, 0.173, 0.595, 0.280}, {3.75, 0.112, 1.072, 0.431}},
+                                        {{3.60, 0.165, 0.206, 0.194}, {4.03, 0.163, 0.228, 0.167}, {4.64, 0.156, 0.326, 0.289},
+                                         {3.68, 0.174, 0.681, 0.064}, {4.10, 0.122, 1.091, 0.161}, {4.65, 0.121, 1.150, 0.134}}};
+    double present;
+    if (bits == 2) present = 2.9 + (0.165 + 0.0062 * M) * tiles + 0.37 * longest + 0.09 * blocks;
+    else if (count == 1) present = awq_gemv_us(bits, M, p[0].N, p[0].K);
+    else {
+        const double *c = fit[bits == 4][M <= 2 ? M - 1 : M <= 4 ? 2 : M <= 6 ? 3 : M <= 8 ? 4 : 5];
+        present = c[0] + c[1] * tiles + c[2] * longest + c[3] * blocks;
+        if (M == 3) present = 0.5 * (present + fit[bits == 4][1][0] + fit[bits == 4][1][1] * tiles + fit[bits == 4][1][2] * longest +
+                                     fit[bits == 4][1][3] * blocks);
+    }
+    int nt = 1;
+    const double tile = awq_tile_group_us(bits, p, count, M, &nt);
+    const double batch = bits != 2 && count > 1 ? awq_gemv_group_us(bits, p, count, M) : 1e30;
+    if (std::min(tile, batch) * (tiles < 32.8 ? 1.08 : 1.15) > present) return AWQ_GEMV_STREAM_UNFIT;
+    if (count > 1) awq_note_plain_plan();
+    return batch < tile ? awq_gemv_group_launch(bits, p, count, M, stream) : awq_tile_group_launch(bits, nt, p, count, M, stream);
+}
+
 // Whether awq_w4a16_linear without a workspace runs the prefill kernel (whose loss form the scale search uses).
 bool awq_linear_takes_prefill(int M, int N, int K)
 {
@@ -100,6 +148,18 @@ extern "C" int awq_w4a16_linear(const void *x_f16, const void *qweight, const vo
             p.N = (int)N;
             p.K = (int)K;
             st = awq_gemv_stream_launch(&p, 1, (int)M, (hipStream_t)stream);
+            if (st != AWQ_GEMV_STREAM_UNFIT) return st;
+        }
+        if (awq_few_considered(4, 1, (int)M, N * K)) {
+            GemvProblem p = {};
+            p.x = (const half_t *)x_f16;
+            p.q = (const uint4 *)qweight;
+            p.sc = (const uint16_t *)scales;
+            p.zp = (const uint8_t *)zeros;
+            p.y = (half_t *)y_f16;
+            p.N = (int)N;
+            p.K = (int)K;
+            st = awq_few_launch(4, &p, 1, (int)M, (hipStream_t)stream);
             if (st != AWQ_GEMV_STREAM_UNFIT) return st;
         }
         return awq_gemv_launch(x_f16, qweight, scales, zeros, y_f16, (int)M, (int)N, (int)K,
@@ -195,6 +255,8 @@ extern "C" int awq_w4a16_linear_multi(const awq_linear_desc *descs, int count, i
     // enough for every CU (measured at N = 32000, K = 4096, 16 tokens: 21.5 us against 41 us); a
     // smaller one stays with the batch kernel, where everything requested at once is the faster way
     // through a small matrix (N = 4096, K = 11008: 10 us against 20 us).
+    const int st_few = awq_few_launch(4, p, count, (int)M, (hipStream_t)stream);
+    if (st_few != AWQ_GEMV_STREAM_UNFIT) return st_few;
     static const int rows_min_count = awq_knob("AWQ_ROWS_MIN_COUNT", 2);
     // At five and six tokens a small launch is the streaming kernel's still, whose waves request all of it at
     // once (a layer of hidden size 1280 / 3840 at five tokens, 9.4 MB: 7.5 us and 10.1 through LDS; 2048 / 5632, 22 MB: 9.8

@@ -34,6 +34,7 @@
 // step; expanding the next run beside the MFMAs of this one takes 32 more registers per weight tile and was slower at every
 // shape (13.0 -> 14.8 us for 8192 x 4096 at 77 tokens).
 #include "awq_common.h"
+#include "awq_gemv_stream.h"
 #include "awq_tile.h"
 
 #include <algorithm>
@@ -131,30 +132,14 @@ struct TilePoints {
     int64_t step, loss_step;
 };
 
+// The tile (tile_m, tile_n) of one product; `unit` is the workgroup's number among those that read the same x.
 template <int BITS, int MT, int NT>
-__global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
+__device__ __forceinline__ void tile_work(
     const unsigned char *__restrict__ x, const unsigned char *__restrict__ qweight,
     const unsigned char *__restrict__ scales, const unsigned char *__restrict__ zeros,
-    half_t *__restrict__ y, int M, int N, int K, int tiles_n, uint32_t tiles_n_inverse, uint32_t runs_inverse,
-    uint32_t runs_inverse_long, int tiles_total, double *__restrict__ loss, const TilePoints points)
+    half_t *__restrict__ y, int M, int N, int K, int tile_m, int tile_n, int unit, uint32_t runs_inverse,
+    uint32_t runs_inverse_long, double *__restrict__ loss, unsigned char *smem)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
-    asm volatile("" ::"s"(x), "s"(qweight), "s"(scales), "s"(zeros), "s"(y), "s"(M), "s"(N), "s"(K), "s"(tiles_n),
-                 "s"(tiles_n_inverse), "s"(runs_inverse), "s"(runs_inverse_long), "s"(tiles_total), "s"(loss));   // arguments in one round
-    // contiguous ranges of tiles, token-tile-major, per XCD (own L2): see gemm_kernel
-    const int per_xcd = (tiles_total + 7) >> 3;
-    int unit = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
-    if (unit >= tiles_total || ((int)blockIdx.x >> 3) >= per_xcd) return;
-    if (BITS == 4 && loss) {
-        const int point = quotient(unit, points.tiles, points.tiles_inverse);
-        unit -= point * points.tiles;
-        x += point * points.step;
-        qweight += point * points.step;
-        scales += point * points.step;
-        zeros += point * points.step;
-        loss += point * points.loss_step;
-    }
-    const int tile_m = quotient(unit, tiles_n, tiles_n_inverse), tile_n = unit - tile_m * tiles_n;
     const uint32_t lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t r = lane & 15, c = lane >> 4;
@@ -171,9 +156,10 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
     };
     const int m0 = tile_m * (16 * MT), nt0 = tile_n * NT;
 
-    // A token tile that would reach past M is moved back to end there (M >= 16); the rows it shares with
+    // A token tile that would reach past M is moved back to end there (more than one: M >= 16); the rows it shares with
     // its neighbour are computed twice, bit for bit alike, and stored once.
-    auto first_row = [&](int m) { return min(m0 + 16 * m, M - 16); };
+    // (fewer than 16 rows: rows past the end repeat the last one in LDS, and are not stored)
+    auto first_row = [&](int m) { return MT == 1 ? max(min(m0, M - 16), 0) : min(m0 + 16 * m, M - 16); };
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem) + wave * wave_lds(NT);
     // packed words: tile n of the workgroup, wave-uniform; steps and zero points: one load for all tiles, lane
     // (r, c) fetching those of row r of tile c.  Ragged N repeats the last tile.  Counted in runs: K % 256 == 0
@@ -192,7 +178,8 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
     // x: load i (0..3) of a token tile takes its rows 4 i + c, lane r the chunk that belongs at place r
     uint32_t xofs[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) xofs[i] = (4 * i + c) * (uint32_t)(K * 2) + 16 * (r ^ (4 * i + c));
+    for (int i = 0; i < 4; ++i)
+        xofs[i] = (MT == 1 ? min(4 * i + c, (uint32_t)(M - 1)) : 4 * i + c) * (uint32_t)(K * 2) + 16 * (r ^ (4 * i + c));
     auto issue_x = [&](int run, int m, uint32_t slot) {
         const unsigned char *p = x + ((size_t)first_row(m) * K + (size_t)run * RUN) * 2;
 #pragma unroll
@@ -418,6 +405,75 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
     }
 }
 
+struct TileGroupArgs {
+    GemvProblem p[GEMV_GROUP_MAX];
+    int first[GEMV_GROUP_MAX];                     // workgroup of each
+    uint32_t inverse[GEMV_GROUP_MAX][2];
+    int count, M;
+};
+
+template <int BITS, int MT, int NT>
+__global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
+    const unsigned char *__restrict__ x, const unsigned char *__restrict__ qweight,
+    const unsigned char *__restrict__ scales, const unsigned char *__restrict__ zeros,
+    half_t *__restrict__ y, int M, int N, int K, int tiles_n, uint32_t tiles_n_inverse, uint32_t runs_inverse,
+    uint32_t runs_inverse_long, int tiles_total, double *__restrict__ loss, const TilePoints points)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    asm volatile("" ::"s"(x), "s"(qweight), "s"(scales), "s"(zeros), "s"(y), "s"(M), "s"(N), "s"(K), "s"(tiles_n),
+                 "s"(tiles_n_inverse), "s"(runs_inverse), "s"(runs_inverse_long), "s"(tiles_total), "s"(loss));   // arguments in one round
+    // contiguous ranges of tiles, token-tile-major, per XCD (own L2): see gemm_kernel
+    const int per_xcd = (tiles_total + 7) >> 3;
+    int unit = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
+    if (unit >= tiles_total || ((int)blockIdx.x >> 3) >= per_xcd) return;
+    if (BITS == 4 && loss) {
+        const int point = quotient(unit, points.tiles, points.tiles_inverse);
+        unit -= point * points.tiles;
+        x += point * points.step;
+        qweight += point * points.step;
+        scales += point * points.step;
+        zeros += point * points.step;
+        loss += point * points.loss_step;
+    }
+    const int tile_m = quotient(unit, tiles_n, tiles_n_inverse), tile_n = unit - tile_m * tiles_n;
+    tile_work<BITS, MT, NT>(x, qweight, scales, zeros, y, M, N, K, tile_m, tile_n, unit, runs_inverse, runs_inverse_long, loss, smem);
+}
+
+// Several linears at up to 16 tokens in one launch: workgroup b of a linear takes its weight tiles NT b .. + NT - 1.  A token tile
+// costs the same whether it has five rows or sixteen, and a weight is expanded once for all of them, so this takes what lies between the small
+// launches of the batch kernel and the large ones that stream at the memory's rate (awq_linear.hip).  A layer of seven linears at 9 / 16
+// tokens, us, before and now: hidden size 1536 (4608) in 4 bits 11.3 / 11.5 and 7.8 / 8.1, 2304 (7680) 16.6 / 16.9 and 13.1 / 15.1; 4096 (11008) in
+// 3 bits 30.0 / 32.5 and 25.6 / 27.8, in 2 bits 28.2 / 32.6 and 23.8 / 25.8.  One linear of 11008 x 4096 in 4 bits 10.9 / 15.8 and 8.1 / 9.0.
+template <int BITS, int NT>
+__global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_group_kernel(const TileGroupArgs A)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    int i = 0;
+#pragma unroll
+    for (int n = 1; n < GEMV_GROUP_MAX; ++n)
+        if (n < A.count && (int)blockIdx.x >= A.first[n]) i = n;
+    const GemvProblem &P = A.p[i];
+    const int tile_n = (int)blockIdx.x - A.first[i];
+    tile_work<BITS, 1, NT>((const unsigned char *)P.x, (const unsigned char *)P.q, (const unsigned char *)P.sc, (const unsigned char *)P.zp,
+                           (half_t *)P.y, A.M, P.N, P.K, 0, tile_n, tile_n, A.inverse[i][0], A.inverse[i][1], nullptr, smem);
+}
+
+template <int BITS, int NT>
+int launch_group(const TileGroupArgs &A, int total, hipStream_t stream)
+{
+    constexpr int lds = tile_lds(1, NT);
+    static AwqOncePerDevice once;
+    std::atomic<bool> &attr_set = once.here();
+    if (lds > 64 * 1024 && !attr_set.load(std::memory_order_relaxed)) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(tile_group_kernel<BITS, NT>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+            return AWQ_ERR_HIP;
+        attr_set.store(true, std::memory_order_relaxed);
+    }
+    tile_group_kernel<BITS, NT><<<dim3((unsigned)total), dim3(64 * TILE_WAVES), lds, stream>>>(A);
+    return awq_launch_status();
+}
+
 template <int BITS, int MT, int NT>
 int launch_one(const void *x, const void *qweight, const void *scales, const void *zeros, void *y, int M, int N,
                int K, double *loss, int count, size_t step, size_t loss_step, hipStream_t stream)
@@ -527,4 +583,62 @@ int awq_tile_launch_loss(const TilePlan &plan, const void *x, const void *qweigh
 {
     return pick<4>(plan.mt, plan.nt)(x, qweight, scales, zeros, const_cast<void *>(y_ref), M, N, K, loss, points, step, loss_step,
                                      stream);
+}
+
+// Linears with the longest rows first: their workgroups run longest.
+int awq_tile_group_launch(int bits, int nt, const GemvProblem *p, int count, int M, hipStream_t stream)
+{
+    if (count < 1 || count > GEMV_GROUP_MAX) return AWQ_ERR_BAD_ARGUMENT;
+    TileGroupArgs A = {};
+    int order[GEMV_GROUP_MAX];
+    for (int i = 0; i < count; ++i) order[i] = i;
+    std::stable_sort(order, order + count, [&](int a, int b) { return p[a].K > p[b].K; });
+    int64_t total = 0;
+    for (int i = 0; i < count; ++i) {
+        A.p[i] = p[order[i]];
+        A.first[i] = (int)total;
+        total += (A.p[i].N / 16 + nt - 1) / nt;
+        const uint32_t runs = (uint32_t)(A.p[i].K / RUN / TILE_WAVES);
+        A.inverse[i][0] = 0xFFFFFFFFu / (runs > 0 ? runs : 1u);
+        A.inverse[i][1] = 0xFFFFFFFFu / (runs + 1);
+    }
+    if (total > (1 << 30)) return AWQ_ERR_BAD_SHAPE;
+    A.count = count;
+    A.M = M;
+    typedef int (*Fn)(const TileGroupArgs &, int, hipStream_t);
+    static const Fn fn[3][4] = {{launch_group<2, 1>, launch_group<2, 2>, launch_group<2, 3>, launch_group<2, 4>},
+                                {launch_group<3, 1>, launch_group<3, 2>, launch_group<3, 3>, launch_group<3, 4>},
+                                {launch_group<4, 1>, launch_group<4, 2>, launch_group<4, 3>, launch_group<4, 4>}};
+    return fn[bits - 2][nt - 1](A, (int)total, stream);
+}
+
+// us of that launch, and the weight tiles per workgroup that make it shortest: a workgroup takes 1.15 us, 0.18 for each weight tile and,
+// for every run of its waves, 0.30 and 0.145 a weight tile, up to 12 % more as the chip fills; one to a CU, in rounds where all rows are
+// alike, else the longest first with half of a short one's time lost at the end.  40000 launches of one to seven linears, as in awq_gemv_group_us: 7 %
+// rms; its choice takes 0.4 % longer than the best one on average.
+double awq_tile_group_us(int bits, const GemvProblem *p, int count, int M, int *nt)
+{
+    double tiles = 0.0;
+    for (int i = 0; i < count; ++i) tiles += (double)(p[i].N / 16) * (p[i].K / RUN);
+    const double memory = 1e-4 * tiles * (bits == 4 ? 0.75 : bits == 3 ? 0.5 : 0.4) * (M > 8 ? 1.25 : 1.0);
+    double best = 0.0;
+    for (int n = 1; n <= 4; ++n) {
+        double total = 0.0, longest = 0.0, shortest = 1e30;
+        int wgs = 0;
+        for (int i = 0; i < count; ++i) {
+            const int w = (p[i].N / 16 + n - 1) / n;
+            const double d = 1.15 + 0.18 * n + (p[i].K / RUN + TILE_WAVES - 1) / TILE_WAVES * (0.30 + 0.145 * n);
+            wgs += w;
+            total += w * d;
+            longest = std::max(longest, d);
+            shortest = std::min(shortest, d);
+        }
+        const double span = longest == shortest ? (wgs + 255) / 256 * longest : std::max(longest, total / 256.0 + 0.53 * shortest);
+        const double us = 1.27 + span * (1.0 + 0.12 * std::min(1.0, wgs / 256.0)) + memory;
+        if (n == 1 || us < best) {
+            best = us;
+            *nt = n;
+        }
+    }
+    return best;
 }

@@ -32,6 +32,7 @@
 //
 // This file is compiled with -ffp-contract=off (integer decisions in the quantizer).
 #include "awq_common.h"
+#include "awq_gemv_stream.h"
 #include "awq_tile.h"
 
 namespace {
@@ -426,6 +427,25 @@ bool decode_blocks(int64_t blocks, int64_t N, int64_t K)
     return !awq_tile_forced() && blocks <= 6 && K > 512 && K <= 2048 && blocks * N * K <= (int64_t)12 << 20;
 }
 
+// By the tile kernel, where that is the faster way; AWQ_GEMV_STREAM_UNFIT otherwise.  (Not a matrix whose longer prompts run as blocks
+// of 16 rows: their results are those of its calls with 16 rows, bit for bit.)
+int few_w2(const W2Problem *p, int count, int M, hipStream_t stream)
+{
+    if (!awq_few_considered(2, count, M, count == 1 ? (int64_t)p[0].N * p[0].K : 0) || (count == 1 && decode_blocks(2, p[0].N, p[0].K)))
+        return AWQ_GEMV_STREAM_UNFIT;
+    GemvProblem g[GEMV_GROUP_MAX] = {};
+    for (int i = 0; i < count; ++i) {
+        g[i].x = p[i].x;
+        g[i].q = p[i].q;
+        g[i].sc = (const uint16_t *)p[i].sc;
+        g[i].zp = p[i].zp;
+        g[i].y = p[i].y;
+        g[i].N = p[i].N;
+        g[i].K = p[i].K;
+    }
+    return awq_few_launch(2, g, count, M, stream);
+}
+
 int fill_problem(W2Problem &p, const void *x, const void *q, const void *sc, const void *zp, void *y,
                  int64_t N, int64_t K, int group)
 {
@@ -503,7 +523,10 @@ extern "C" int awq_w2a16_linear(const void *x_f16, const void *qweight, const vo
     int st = fill_problem(p, x_f16, qweight, scales, zeros, y_f16, N, K, group);
     if (st != AWQ_OK) return st;
     if (M <= 0 || M > 0x7fffffff) return AWQ_ERR_BAD_SHAPE;
-    if (M <= 16) return launch_w2(&p, 1, (int)M, (hipStream_t)stream);
+    if (M <= 16) {
+        st = few_w2(&p, 1, (int)M, (hipStream_t)stream);
+        return st != AWQ_GEMV_STREAM_UNFIT ? st : launch_w2(&p, 1, (int)M, (hipStream_t)stream);
+    }
     const int64_t blocks = (M + 15) / 16;
     if (decode_blocks(blocks, N, K)) {
         // blocks of 16 rows in one launch; the last one is moved back to end at the last row (the overlap is computed
@@ -536,6 +559,8 @@ extern "C" int awq_w2a16_linear_multi(const awq_linear_desc *descs, int count, i
         int st = fill_problem(p[i], d.x_f16, d.qweight, d.scales, d.zeros, d.y_f16, d.N, d.K, group);
         if (st != AWQ_OK) return st;
     }
+    const int st_few = few_w2(p, count, (int)M, (hipStream_t)stream);
+    if (st_few != AWQ_GEMV_STREAM_UNFIT) return st_few;
     for (int i = 0; i < count; i += W2_MAX_PROBLEMS) {
         const int n = count - i < W2_MAX_PROBLEMS ? count - i : W2_MAX_PROBLEMS;
         int st = launch_w2(p + i, n, (int)M, (hipStream_t)stream);

@@ -316,6 +316,18 @@ extern "C" int awq_w3a16_linear(const void *x_f16, const void *qweight, const vo
     if (!awq_aligned16(x_f16) || !awq_aligned16(qweight) || !awq_aligned16(scales) ||
         !awq_aligned16(zeros) || !awq_aligned16(y_f16))
         return AWQ_ERR_MISALIGNED;
+    if (awq_few_considered(3, 1, (int)M, N * K)) {
+        GemvProblem p = {};
+        p.x = (const half_t *)x_f16;
+        p.q = (const uint4 *)qweight;
+        p.sc = (const uint16_t *)scales;
+        p.zp = (const uint8_t *)zeros;
+        p.y = (half_t *)y_f16;
+        p.N = (int)N;
+        p.K = (int)K;
+        st = awq_few_launch(3, &p, 1, (int)M, (hipStream_t)stream);
+        if (st != AWQ_GEMV_STREAM_UNFIT) return st;
+    }
     return awq_gemv_launch_w3(x_f16, qweight, scales, zeros, y_f16, (int)M, (int)N, (int)K,
                               (hipStream_t)stream);
 }
@@ -344,6 +356,8 @@ extern "C" int awq_w3a16_linear_multi(const awq_linear_desc *descs, int count, i
         p[i].N = (int)d.N;
         p[i].K = (int)d.K;
     }
+    const int st_few = awq_few_launch(3, p, count, (int)M, (hipStream_t)stream);
+    if (st_few != AWQ_GEMV_STREAM_UNFIT) return st_few;
     // From nine tokens the streaming kernel holds one batch of K per wave and takes K up to 4096 only, and not
     // every such K; the linears it does not take would be a launch each.  With two or more of those,
     // and row blocks enough, the kernel that takes the activations through LDS (any K) runs all in one
