@@ -8,22 +8,27 @@
 //
 // The step is bound by reading the caches once (2 * L * Hkv * D * 2 bytes).  They are laid out
 // [kv head][position][D], so the keys of a head are one contiguous stream.  A workgroup handles
-// one query head and one slice of the positions; a wave takes four positions per step: lane
-// l = 16 g + u holds dimensions 8 u .. 8 u + 7 (one 16-byte load) of position 4 i + g, the
-// partial dot products are folded over the 16 lanes of a group with four xor-shuffles, and each
-// group keeps a running (max, sum, weighted values) of its own positions, merged at the end
-// (groups by shuffles, waves through LDS).  Slices are merged by a second, tiny kernel.
+// one query head and one slice of the positions; a wave takes 16 positions at a time: lane
+// l = 16 g + u holds dimensions 8 u .. 8 u + 7 (one 16-byte load) of positions 4 i + g for four i.  The partial
+// dot products of the four are folded over the 16 lanes of a group by rotations within the row, one after the other without
+// waiting, and each group keeps a running (max, sum, weighted values) of its own positions, brought up to date once for the
+// four; merged at the end (groups by shuffles, waves through LDS).  (A position at a time, four xor-shuffles and an update
+// each: a chain of some 300 cycles per position, 7.0 us a call and 6.4 with the batches at 8 heads and 200 positions, 8.7 and 8.1 at 32 heads and
+// 400; 12.2 and 12.4 at 2000, where the loads bound it.)  Slices are merged by a second, tiny kernel; a short context is one slice.
 // The current token's key and value are taken from the inputs, not from the cache row that is
 // written in the same launch, so no workgroup depends on another one's stores.
 #include "awq_common.h"
 
 #include <cmath>
 #include <cstddef>
+#include <type_traits>
 
 namespace {
 
 constexpr int AD = 128;                 // head dimension
-constexpr int ATT_WAVES = 4;
+constexpr int ATT_WAVES = 4, ATT_WHOLE_WAVES = 16;
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // theta^(-2 i / 128), i = 0..63, computed once per call on the host in fp64
 struct RopeTable {
@@ -48,14 +53,16 @@ struct Running {
     float acc[8];        // sum of exp(score - m) * value, this lane's eight dimensions
 };
 
-__device__ __forceinline__ void absorb(Running &r, float score, const float (&val)[8])
+// The sum over the 16 lanes of a group, in every one of them: four rotations within the row.
+__device__ __forceinline__ float row_sum(float s)
 {
-    const float m_new = fmaxf(r.m, score);
-    const float keep = __expf(r.m - m_new), add = __expf(score - m_new);
-    r.l = r.l * keep + add;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) r.acc[e] = r.acc[e] * keep + add * val[e];
-    r.m = m_new;
+    auto turned = [](float v, auto by) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + decltype(by)::value, 0xF, 0xF, false));
+    };
+    s += turned(s, std::integral_constant<int, 8>{});
+    s += turned(s, std::integral_constant<int, 4>{});
+    s += turned(s, std::integral_constant<int, 2>{});
+    return s + turned(s, std::integral_constant<int, 1>{});
 }
 
 __device__ __forceinline__ void merge(Running &r, float m2, float l2, const float (&acc2)[8])
@@ -69,46 +76,54 @@ __device__ __forceinline__ void merge(Running &r, float m2, float l2, const floa
     r.m = m_new;
 }
 
-// grid (H, splits); 256 threads.  partial: [H][splits][AD + 2] floats = (acc[128], m, l).
-__global__ __launch_bounds__(256) void attention_partial_kernel(
+// grid (H, splits); 64 WAVES threads.  partial: [H][splits][AD + 2] floats = (acc[128], m, l).  WHOLE: one slice, finished here (out
+// is [H][AD] halves): a second launch costs more than a short context's rows.
+template <int WAVES, bool WHOLE>
+__global__ __launch_bounds__(64 * WAVES) void attention_partial_kernel(
     const half_t *__restrict__ q, const half_t *__restrict__ k, const half_t *__restrict__ v,
     half_t *__restrict__ k_cache, half_t *__restrict__ v_cache, int H, int Hkv, int Lmax, int pos,
-    RopeTable tab, int chunk, float *__restrict__ partial)
+    RopeTable tab, int chunk, std::conditional_t<WHOLE, half_t, float> *__restrict__ partial)
 {
     __shared__ float qs[AD];                         // rotated query times 1/sqrt(D)
     __shared__ float ks[AD];                         // rotated key of the current token (fp32)
-    __shared__ float wave_state[ATT_WAVES][AD + 2];
+    __shared__ float wave_state[WAVES][AD + 2];
     // all pointer arguments fetched in one round (the compiler would otherwise fetch each where
     // it is first needed, one scalar-cache miss after the other)
     asm volatile("" ::"s"(q), "s"(k), "s"(v), "s"(k_cache), "s"(v_cache), "s"(partial), "s"(H), "s"(Hkv),
                  "s"(Lmax), "s"(pos), "s"(chunk));
     const int h = blockIdx.x, split = blockIdx.y;
     const int g_kv = h / (H / Hkv);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = lane >> 4, u = lane & 15;
     // what the rotary prologue needs (wave 0: the query, wave 1: the key; elements lane and
     // lane + 64), requested before the cache rows so that it is not waited for behind them
     const half_t *rsrc = wave == 1 ? k + (size_t)g_kv * AD : q + (size_t)h * AD;
     const half_t ra_h = rsrc[lane], rb_h = rsrc[lane + 64];
     const double rfreq = tab.inv_freq[lane];
-    const int L = pos + 1;
-    const int p0 = split * chunk, p1 = min(L, p0 + chunk);
-    const uint4 *kbase = reinterpret_cast<const uint4 *>(k_cache + (size_t)g_kv * Lmax * AD) + u;
-    const uint4 *vbase = reinterpret_cast<const uint4 *>(v_cache + (size_t)g_kv * Lmax * AD) + u;
-    // positions of this lane group: p, p + 16, ...; the loads of the next four are in flight while
-    // one is folded in.  The first ones go out before anything else: they do not depend on the
-    // query, and the rotary prologue below runs while they travel.
-    constexpr int AHEAD = 4;
-    uint4 kq[AHEAD + 1], vq[AHEAD + 1];
-    const int first = p0 + 4 * wave + grp;
+    const int p0 = split * chunk, p1 = min(pos, p0 + chunk);             // rows of the caches
+    const u32x4 *kbase = reinterpret_cast<const u32x4 *>(k_cache + (size_t)g_kv * Lmax * AD) + u;
+    const u32x4 *vbase = reinterpret_cast<const u32x4 *>(v_cache + (size_t)g_kv * Lmax * AD) + u;
+    const u32x4 vnow = reinterpret_cast<const u32x4 *>(v + (size_t)g_kv * AD)[u];
+    // A wave takes BATCH x 4 positions at a time, STEP apart; one batch is folded in while the next one travels.  The first ones go
+    // out before anything else: they do not depend on the query, and the rotary prologue below runs meanwhile.  WHOLE: one batch of
+    // up to 512 positions, of which a wave leaves out what is not there.
+    constexpr int BATCH = WHOLE ? 8 : 4, BUFFERS = WHOLE ? 1 : 2, STEP = 4 * WAVES;
+    u32x4 kq[BUFFERS][BATCH], vq[BUFFERS][BATCH];
+    const int first = p0 + 4 * wave;                                     // wave-uniform; lane group: + grp
+    auto request = [&](u32x4 (&kr)[BATCH], u32x4 (&vr)[BATCH], int p) {
+        if (p >= p1) return;                                             // wave-uniform
 #pragma unroll
-    for (int a = 0; a < AHEAD; ++a) {
-        // unconditional (a row that is not needed reads row 0 and is ignored): a predicated
-        // load would be waited for on the spot
-        const int pa = first + 16 * a, pe = pa < p1 ? pa : 0;
-        kq[a] = kbase[(size_t)pe * (AD / 8)];
-        vq[a] = vbase[(size_t)pe * (AD / 8)];
-    }
+        for (int a = 0; a < BATCH; ++a) {
+            if (WHOLE && p + STEP * a >= p1) break;
+            // a row past the end reads the slice's first one and is ignored: a predicated load would be waited for on the spot
+            const int pa = p + STEP * a + grp, pe = pa < p1 ? pa : p0;
+            kr[a] = kbase[(size_t)pe * (AD / 8)];
+            vr[a] = vbase[(size_t)pe * (AD / 8)];
+        }
+    };
+    request(kq[0], vq[0], first);
+    if constexpr (!WHOLE) request(kq[BUFFERS - 1], vq[BUFFERS - 1], first + STEP * BATCH);
 
     {
         // every wave rotates what it fetched (waves 2 and 3 discard the result): a rotation
@@ -143,40 +158,68 @@ __global__ __launch_bounds__(256) void attention_partial_kernel(
 #pragma unroll
     for (int e = 0; e < 8; ++e) r.acc[e] = 0.f;
 
-    for (int p = first; p < p1; p += 16 * (AHEAD + 1)) {
+    auto dot = [&](const u32x4 &row) {
+        const half8_t kh = __builtin_bit_cast(half8_t, row);
+        float s = 0.f;
 #pragma unroll
-        for (int a = 0; a <= AHEAD; ++a) {
-            const int pc = p + 16 * a;                       // position folded in now
-            const int pn = pc + 16 * AHEAD;                  // position requested now
-            const int pne = pn < p1 ? pn : 0;
-            kq[(a + AHEAD) % (AHEAD + 1)] = kbase[(size_t)pne * (AD / 8)];
-            vq[(a + AHEAD) % (AHEAD + 1)] = vbase[(size_t)pne * (AD / 8)];
-            if (pc < p1) {
-                float kf[8], vf[8];
-                if (pc == pos) {                             // the token of this call: from the inputs
+        for (int e = 0; e < 8; ++e) s = __builtin_fmaf(qf[e], (float)kh[e], s);
+        return s;
+    };
+    // the token of this call, from the inputs, with its key in fp32: the initial state of one lane group.  (A score of -inf has the
+    // weight 0; +inf gives NaN, as inf - inf does.)
+    {
+        float s = 0.f;
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        kf[e] = ks[8 * u + e];
-                        vf[e] = (float)v[(size_t)g_kv * AD + 8 * u + e];
-                    }
-                } else {
-                    const half_t *kh = reinterpret_cast<const half_t *>(&kq[a]);
-                    const half_t *vh = reinterpret_cast<const half_t *>(&vq[a]);
+        for (int e = 0; e < 8; ++e) s = __builtin_fmaf(qf[e], ks[8 * u + e], s);
+        s = row_sum(s);
+        if (split == pos / chunk && wave == 0 && grp == 0 && s != -__builtin_inff()) {
+            const half8_t vh = __builtin_bit_cast(half8_t, vnow);
+            r.m = s;
+            r.l = 1.f + (s - s);
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        kf[e] = (float)kh[e];
-                        vf[e] = (float)vh[e];
-                    }
-                }
-                float s = 0.f;
+            for (int e = 0; e < 8; ++e) r.acc[e] = (float)vh[e];
+        }
+    }
+    auto fold = [&](const u32x4 (&kr)[BATCH], u32x4 (&vr)[BATCH], int p) {
+        float s[BATCH], top = r.m;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) s += qf[e] * kf[e];
-                s += __shfl_xor(s, 1);
-                s += __shfl_xor(s, 2);
-                s += __shfl_xor(s, 4);
-                s += __shfl_xor(s, 8);
-                absorb(r, s, vf);
+        for (int a = 0; a < BATCH; ++a) {
+            if (WHOLE && p + STEP * a >= p1) break;
+            s[a] = row_sum(dot(kr[a]));
+        }
+#pragma unroll
+        for (int a = 0; a < BATCH; ++a) {
+            if (WHOLE && p + STEP * a >= p1) break;
+            // a row past the end: weight 0, and values 0, because an infinity times 0 is NaN
+            if (p + STEP * a + grp >= p1) {
+                s[a] = -__builtin_inff();
+                vr[a] = u32x4{0, 0, 0, 0};
             }
+            top = fmaxf(top, s[a]);
+        }
+        const float zero = top == -__builtin_inff() ? 0.f : top;         // all scores so far -inf: all weights 0
+        const float keep = __expf(r.m - zero);
+        r.m = top;
+        r.l *= keep;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) r.acc[e] *= keep;
+#pragma unroll
+        for (int a = 0; a < BATCH; ++a) {
+            if (WHOLE && p + STEP * a >= p1) break;
+            const float w = __expf(s[a] - zero);
+            const half8_t vh = __builtin_bit_cast(half8_t, vr[a]);
+            r.l += w;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) r.acc[e] = __builtin_fmaf(w, (float)vh[e], r.acc[e]);
+        }
+    };
+    for (int p = first; p < p1; p += BUFFERS * STEP * BATCH) {
+        fold(kq[0], vq[0], p);
+        request(kq[0], vq[0], p + BUFFERS * STEP * BATCH);
+        if constexpr (!WHOLE) {
+            if (p + STEP * BATCH >= p1) break;
+            fold(kq[BUFFERS - 1], vq[BUFFERS - 1], p + STEP * BATCH);
+            request(kq[BUFFERS - 1], vq[BUFFERS - 1], p + 3 * STEP * BATCH);
         }
     }
     // the four groups of the wave (lanes u, u+16, u+32, u+48 hold the same dimensions)
@@ -200,20 +243,24 @@ __global__ __launch_bounds__(256) void attention_partial_kernel(
     if (tid < AD) {
         float m = wave_state[0][AD];
 #pragma unroll
-        for (int w = 1; w < ATT_WAVES; ++w) m = fmaxf(m, wave_state[w][AD]);
+        for (int w = 1; w < WAVES; ++w) m = fmaxf(m, wave_state[w][AD]);
         float l = 0.f, a = 0.f;
 #pragma unroll
-        for (int w = 0; w < ATT_WAVES; ++w) {
+        for (int w = 0; w < WAVES; ++w) {
             const float mw = wave_state[w][AD];
             const float kf = mw == m ? 1.0f : __expf(mw - m);
             l += wave_state[w][AD + 1] * kf;
             a += wave_state[w][tid] * kf;
         }
-        float *dst = partial + ((size_t)h * gridDim.y + split) * (AD + 2);
-        dst[tid] = a;
-        if (tid == 0) {
-            dst[AD] = m;
-            dst[AD + 1] = l;
+        if constexpr (WHOLE) {
+            partial[(size_t)h * AD + tid] = (half_t)(a / l);
+        } else {
+            float *dst = partial + ((size_t)h * gridDim.y + split) * (AD + 2);
+            dst[tid] = a;
+            if (tid == 0) {
+                dst[AD] = m;
+                dst[AD + 1] = l;
+            }
         }
     }
 }
@@ -240,7 +287,6 @@ __global__ __launch_bounds__(256) void attention_partial_kernel(
 // rotation 1 us, two rounds of cache rows, two merges), not the 16 MB.
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef const __attribute__((address_space(1))) void gbl_void_t;
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ void dma16(const unsigned char *g, uint32_t lds_addr)
@@ -755,8 +801,15 @@ extern "C" int awq_decode_attention(const void *q_f16, const void *k_f16, const 
     half_t *kc = (half_t *)k_cache_f16, *vc = (half_t *)v_cache_f16;
     float *partial = (float *)workspace;
     int st;
-    // (the tuning build can force the kernel: 0, or the number of workgroups to a slice)
-    const int forced = awq_knob("AWQ_ATTENTION_F", -1);
+    // Up to 320 positions one workgroup takes a head's whole context, in one launch.  us a call from a graph, two launches and one, 8 / 8, 32 / 32 and
+    // 64 / 8 heads: 100 positions 6.2 / 6.5 / 6.6 and 5.3 / 5.5 / 5.4, 200 6.6 / 6.6 / 8.2 and 6.0 / 6.2 / 7.1, 300 6.7 / 7.5 / 8.9 and
+    // 6.7 / 7.4 / 8.1, 400 6.8 / 8.2 / 9.0 and 7.4 / 8.3 / 9.2 (an eager caller saves a launch besides)
+    const int forced = awq_knob("AWQ_ATTENTION_F", -1);      // (the tuning build: the kernel below, 0, or the number of workgroups to a slice)
+    if (forced < 0 && L <= awq_knob("AWQ_ATTENTION_WHOLE", 320)) {
+        attention_partial_kernel<ATT_WHOLE_WAVES, true><<<dim3((unsigned)H, 1), dim3(64 * ATT_WHOLE_WAVES), 0, (hipStream_t)stream>>>(
+            qp, kp, vp, kc, vc, (int)H, (int)Hkv, (int)Lmax, (int)pos, tab, (int)L, (half_t *)out_f16);
+        return awq_launch_status();
+    }
     if (H / Hkv > 2 && (forced < 0 ? attention_grouped(H, Hkv, L) : forced > 0)) {
         GroupedArgs A = {qp, kp, vp, kc, vc, partial, (int)H, (int)Hkv, (int)((H / Hkv + 15) / 16), (int)Lmax, (int)pos,
                          chunk, splits, 0, tab};
@@ -768,7 +821,7 @@ extern "C" int awq_decode_attention(const void *q_f16, const void *k_f16, const 
              : F == 2 ? attention_grouped_launch<2>(A, (hipStream_t)stream)
                       : attention_grouped_launch<4>(A, (hipStream_t)stream);
     } else {
-        attention_partial_kernel<<<dim3((unsigned)H, (unsigned)splits), dim3(256), 0, (hipStream_t)stream>>>(
+        attention_partial_kernel<ATT_WAVES, false><<<dim3((unsigned)H, (unsigned)splits), dim3(64 * ATT_WAVES), 0, (hipStream_t)stream>>>(
             qp, kp, vp, kc, vc, (int)H, (int)Hkv, (int)Lmax, (int)pos, tab, chunk, partial);
         st = awq_launch_status();
     }
