@@ -796,7 +796,13 @@ extern "C" int awq_decode_attention(const void *q_f16, const void *k_f16, const 
     int chunk = (int)((L + splits - 1) / splits);
     chunk = (chunk + 15) / 16 * 16;                  // whole steps of the four waves
     RopeTable tab;
-    for (int i = 0; i < AD / 2; ++i) tab.inv_freq[i] = pow((double)rope_theta, -2.0 * i / AD);
+    // products of 16 powers (one rounding of 2^-53 more) instead of 64: 1.1 us of the host's 6.6 for a call of two launches
+    double coarse[8], fine[8];
+    for (int i = 0; i < 8; ++i) {
+        coarse[i] = pow((double)rope_theta, -16.0 * i / AD);
+        fine[i] = pow((double)rope_theta, -2.0 * i / AD);
+    }
+    for (int i = 0; i < AD / 2; ++i) tab.inv_freq[i] = coarse[i / 8] * fine[i % 8];
     const half_t *qp = (const half_t *)q_f16, *kp = (const half_t *)k_f16, *vp = (const half_t *)v_f16;
     half_t *kc = (half_t *)k_cache_f16, *vc = (half_t *)v_cache_f16;
     float *partial = (float *)workspace;
