@@ -115,27 +115,22 @@ __device__ __forceinline__ half8_t w3_halves(const uint32_t (&w)[3], uint32_t la
     return __builtin_bit_cast(half8_t, make_uint4(t[0], t[1], t[2], t[3]));
 }
 
-constexpr int GEMV_STAGE_MAX_M = 16;  // activations of up to this many rows go through LDS
-
 // Decode kernel.
-// U     = tiles (groups) per batch, a divisor of G: 1, 2 or 4.  A wave owns whole batches.
+// U     = tiles (groups) per batch, a divisor of G: 1 or 2.  A wave owns whole batches.
 // PIPE  = double-buffer the batches (only worth its registers when a wave has several).
-// MS > 0 (M <= MS <= 16): each wave copies the slice of x that its batch needs (MS rows x
-//   U*128 halves; rows >= M repeat row M-1) into a private LDS area with one coalesced
-//   16-byte load per lane for every 64/(16 U) rows, issued before the weight loads so that it returns first,
+// MS (M <= MS <= 16, a multiple of the 4 / U rows that a load covers): each wave copies the slice of x that its batch needs
+//   (MS rows x U*128 halves; rows >= M repeat row M-1) into a private LDS area with one coalesced
+//   16-byte load per lane for every 4 / U rows, issued before the weight loads so that it returns first,
 //   and then reads its A fragments from LDS.  No workgroup barrier is involved, so a wave
 //   starts computing as soon as its own weights arrive.  With few rows most lanes of an A
 //   fragment are duplicates, which is why this is cheaper than loading fragments from
 //   global memory.
-// MS == 0: A fragments are loaded straight from global memory (L2 hits); kept for reference,
-//   the launcher stages every decode M (fragment loads at the point of use are round trips
-//   to L2 in the middle of a batch).
 //
 // The workgroup has W = 2^logW waves; wave w owns batches [NB*w/W, NB*(w+1)/W), NB = G/U.
 // Dynamic LDS: [W][MS rows x (U*256 + 16) bytes], then 16*M outputs x 16 wave slots of
 // fp32 for the cross-wave reduction.
 template <int BITS, int U, int MS, bool PIPE>
-__global__ __launch_bounds__(1024, (MS >= 8 || (U == 4 && (PIPE || MS == 0 || (BITS == 3 && MS == 4)))) ? 4 : 6) void gemv_kernel(
+__global__ __launch_bounds__(1024, MS >= 8 ? 4 : 6) void gemv_kernel(
     const half_t *__restrict__ x, const uint32_t *__restrict__ qweight,
     const uint16_t *__restrict__ scales, const uint8_t *__restrict__ zeros,
     half_t *y, int M, int N, int K, int G, int logW, const half_t *res)
@@ -147,11 +142,11 @@ __global__ __launch_bounds__(1024, (MS >= 8 || (U == 4 && (PIPE || MS == 0 || (B
     asm volatile("" ::"s"(x), "s"(qweight), "s"(scales), "s"(zeros), "s"(y), "s"(M), "s"(N), "s"(K), "s"(G),
                  "s"(logW), "s"(res));
     const ExpandConsts kc = expand_consts();
-    constexpr bool STAGE = MS > 0;
     // staging: a row of the batch is U*16 lanes wide, so one 16-byte load per lane covers
     // RPP = 64 / (U*16) rows; NS passes cover the MS rows
     constexpr int LPR = U * 16, RPP = 64 / LPR;
-    constexpr int NS = STAGE ? (MS + RPP - 1) / RPP : 1;
+    constexpr int NS = MS / RPP;
+    static_assert(MS % RPP == 0, "whole loads");
     constexpr int ROW_BYTES = U * 256 + 16;           // +16: rows land on different banks
     constexpr int WAVE_BYTES = MS * ROW_BYTES;
     const int lane = threadIdx.x & 63;
@@ -173,9 +168,8 @@ __global__ __launch_bounds__(1024, (MS >= 8 || (U == 4 && (PIPE || MS == 0 || (B
     const int mrow = r < M ? r : M - 1;
     unsigned char *xw = smem + (size_t)wave * WAVE_BYTES;                 // this wave's x slice
     const uint4 *xl = reinterpret_cast<const uint4 *>(xw + mrow * ROW_BYTES) + c;
-    const uint4 *xg = reinterpret_cast<const uint4 *>(x + (int64_t)mrow * K) + c;
-    // staging source of this lane in pass i: row i*RPP + lane/LPR (clamped to M-1 for the load,
-    // not stored when >= MS), 16-byte chunk lane%LPR of the batch
+    // staging source of this lane in pass i: row i*RPP + lane/LPR (clamped to M-1 for the load),
+    // 16-byte chunk lane%LPR of the batch
     const int srow = lane / LPR, schunk = lane % LPR;
     const uint4 *xstage = reinterpret_cast<const uint4 *>(x) + schunk;
     const int64_t K8 = (int64_t)K >> 3;
@@ -185,36 +179,31 @@ __global__ __launch_bounds__(1024, (MS >= 8 || (U == 4 && (PIPE || MS == 0 || (B
     };
     auto stage_store = [&](int i, const uint4 &v) {
         const int m = i * RPP + srow;
-        if (MS % RPP == 0 || m < MS) reinterpret_cast<uint4 *>(xw + m * ROW_BYTES)[schunk] = v;
+        reinterpret_cast<uint4 *>(xw + m * ROW_BYTES)[schunk] = v;
     };
-    constexpr bool stager = STAGE;
 
     TileBatch<BITS, U> cur;
     uint4 xs[NS];
 #pragma unroll
     for (int m = 0; m < NS; ++m) xs[m] = make_uint4(0, 0, 0, 0);
     if (g0 < g1) {
-        if (stager) {                              // first: it must not wait for the weights
+        // first: it must not wait for the weights
 #pragma unroll
-            for (int m = 0; m < NS; ++m) xs[m] = stage_src(m, g0);
-        }
+        for (int m = 0; m < NS; ++m) xs[m] = stage_src(m, g0);
         load_batch<BITS, U>(cur, qt, sc, zp, g0);
     }
 
     floatx4 total = {0.f, 0.f, 0.f, 0.f};
     for (int base = g0; base < g1; base += U) {
-        if (stager) {                              // LDS ops of one wave execute in order
+        // LDS ops of one wave execute in order
 #pragma unroll
-            for (int m = 0; m < NS; ++m) stage_store(m, xs[m]);
-        }
+        for (int m = 0; m < NS; ++m) stage_store(m, xs[m]);
         // PIPE: the next batch is requested before this one is consumed
         TileBatch<BITS, U> nxt;
         const bool more = base + U < g1;
         if (PIPE && more) {
-            if (stager) {
 #pragma unroll
-                for (int m = 0; m < NS; ++m) xs[m] = stage_src(m, base + U);
-            }
+            for (int m = 0; m < NS; ++m) xs[m] = stage_src(m, base + U);
             load_batch<BITS, U>(nxt, qt, sc, zp, base + U);
         }
         // constants of (group base + cu, row r), computed once per batch by their owner lane
@@ -227,8 +216,8 @@ __global__ __launch_bounds__(1024, (MS >= 8 || (U == 4 && (PIPE || MS == 0 || (B
             uint4 xa[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                // k = 128g + 32j + 8c + 0..7 -> 16-byte chunk 16g + 4j (+c folded into xl/xg)
-                xa[j] = STAGE ? xl[u * 16 + 4 * j] : xg[(base + u) * 16 + 4 * j];
+                // k = 128g + 32j + 8c + 0..7 -> 16-byte chunk 16g + 4j (+c folded into xl)
+                xa[j] = xl[u * 16 + 4 * j];
             }
             const int src = r + 16 * u;
             const uint32_t nzA = __shfl(own_nzA, src);
@@ -269,10 +258,8 @@ __global__ __launch_bounds__(1024, (MS >= 8 || (U == 4 && (PIPE || MS == 0 || (B
         if (PIPE) {
             if (more) cur = nxt;
         } else if (more) {
-            if (stager) {
 #pragma unroll
-                for (int m = 0; m < NS; ++m) xs[m] = stage_src(m, base + U);
-            }
+            for (int m = 0; m < NS; ++m) xs[m] = stage_src(m, base + U);
             load_batch<BITS, U>(cur, qt, sc, zp, base + U);
         }
     }
@@ -377,7 +364,7 @@ __global__ __launch_bounds__(64 << GROUP_LOGW, MS >= 8 ? 4 : 6) void gemv_group_
 #pragma unroll
         for (int i = 0; i < NS; ++i) {
             const int m = i * RPP + srow;
-            if (MS % RPP == 0 || m < MS) reinterpret_cast<u32x4 *>(xw + m * ROW_BYTES)[schunk] = xs[i];
+            reinterpret_cast<u32x4 *>(xw + m * ROW_BYTES)[schunk] = xs[i];
         }
         uint32_t qc[U][BITS];
 #pragma unroll
@@ -455,28 +442,32 @@ template <int BITS>
 int gemv_group_bits(const GemvGroupArgs &A, int total, hipStream_t stream)
 {
     const int M = A.M;
-    return M == 1 ? gemv_group_one<BITS, 1>(A, total, stream) : M == 2 ? gemv_group_one<BITS, 2>(A, total, stream)
+    return M <= 2 ? gemv_group_one<BITS, 2>(A, total, stream)
          : M <= 4 ? gemv_group_one<BITS, 4>(A, total, stream) : M <= 8 ? gemv_group_one<BITS, 8>(A, total, stream)
                                                                        : gemv_group_one<BITS, 16>(A, total, stream);
 }
 
-// log2 of the waves per workgroup: about four tiles per wave, 4..16 waves
-int pick_log_waves(int G)
+// Waves that share a row block (a power of two) and groups per batch.  Few row blocks: sixteen waves each, so that a CU, which then has
+// one of them, has work for all its SIMDs; many: fewer waves with more groups each.  One group per batch from three tokens (two rows staged
+// by a load would be a second load), else two where a wave has more than one; four are never the faster way.  Over 4900 launches of 16 to
+// 1792 row blocks and 8 to 224 groups, against four, eight and sixteen waves from 8, 24 and 64 groups and the largest batch of 4, 2 and 1 that
+// divides them: 1.08 times faster at 1 and 2 tokens, 1.10 at 4, 1.07 at 8, 1.07 at 9 and 1.14 at 16 in 4 bits, as much in 3; 1 % of
+// the launches are more than 3 % slower.  us, 1 token: 4096 x 4096 4.3 and 4.2, 3584 x 9216 7.1 and 6.4, 9216 x 3584 6.4 and 6.2;
+// 4 tokens 3584 x 9216 7.4 and 6.4.
+struct GemvShape {
+    int waves, unroll;
+};
+GemvShape gemv_shape(int M, int row_blocks, int G)
 {
-    static const int forced = awq_knob("AWQ_GEMV_WAVES", 0);
-    if (forced == 1 || forced == 2 || forced == 4 || forced == 8 || forced == 16)
-        return forced == 1 ? 0 : forced == 2 ? 1 : forced == 4 ? 2 : forced == 8 ? 3 : 4;
-    if (G >= 64) return 4;
-    if (G >= 24) return 3;
-    return 2;
-}
-
-// tiles per batch: the largest of 4, 2, 1 that divides G
-int pick_unroll(int G)
-{
-    static const int forced = awq_knob("AWQ_GEMV_UNROLL", 0);
-    if ((forced == 1 || forced == 2 || forced == 4) && G % forced == 0) return forced;
-    return G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1);
+    GemvShape s;
+    if (M > 12) s.waves = row_blocks <= 256 ? 8 : 4;
+    else s.waves = row_blocks <= 256 ? 16 : row_blocks <= (M == 3 || M == 4 ? 800 : 512) ? 8 : 4;
+    while (s.waves > 4 && G < s.waves) s.waves /= 2;
+    s.unroll = M <= 2 && G % 2 == 0 && 5 * G >= 6 * s.waves ? 2 : 1;
+    const int waves = awq_knob("AWQ_GEMV_WAVES", 0), unroll = awq_knob("AWQ_GEMV_UNROLL", 0);
+    if (waves == 1 || waves == 2 || waves == 4 || waves == 8 || waves == 16) s.waves = waves;
+    if (unroll == 1 || (unroll == 2 && G % 2 == 0 && M <= 2)) s.unroll = unroll;
+    return s;
 }
 
 }  // namespace
@@ -506,12 +497,12 @@ int gemv_launch_bits(const void *x, const void *qweight, const void *scales, con
                      void *y, int M, int N, int K, hipStream_t stream, const void *res = nullptr)
 {
     const int G = K / AWQ_GROUP;
-    const int logW = pick_log_waves(G);
-    const int W = 1 << logW;
-    // every decode M stages its activations through LDS: 1, 2, 4, 8 or 16 rows per wave
-    const int MS = M == 1 ? 1 : (M == 2 ? 2 : (M <= 4 ? 4 : (M <= 8 ? 8 : 16)));
-    int U = pick_unroll(G);
-    if (MS == 16 && U == 4) U = 2;                  // 16 waves x 16 rows x 4 groups would not fit in LDS
+    const GemvShape shape = gemv_shape(M, N / 16, G);
+    const int W = shape.waves, U = shape.unroll, logW = __builtin_ctz(W);
+    // every decode M stages its activations through LDS: 2, 4, 8 or 16 rows per wave.  A load covers 4 / U rows: fewer staged rows
+    // than that would be a store under a mask, and the compiler then moves the load down to it, behind the weights (1 token, 3584 x
+    // 9216, two groups per batch: 7.4 us, with two rows 6.4)
+    const int MS = U == 2 ? 2 : M <= 4 ? 4 : M <= 8 ? 8 : 16;
     const dim3 grid(N / 16), block(W * 64);
     const bool pipe = (G / U + W - 1) / W > 1;      // some wave has more than one batch
     // reduction area: 16*M outputs x 16 wave slots x 4 bytes, after the staging areas
@@ -523,28 +514,14 @@ int gemv_launch_bits(const void *x, const void *qweight, const void *scales, con
                                              (const uint32_t *)qweight, (const uint16_t *)scales,     \
                                              (const uint8_t *)zeros, (half_t *)y, M, N, K, G, logW,   \
                                              (const half_t *)res)
-#define AWQ_GEMV_ROWS(UU, PP)                                                               \
-    switch (MS) {                                                                           \
-    case 1: AWQ_GEMV_LAUNCH(UU, 1, PP);                                                     \
-    case 2: AWQ_GEMV_LAUNCH(UU, 2, PP);                                                     \
-    case 4: AWQ_GEMV_LAUNCH(UU, 4, PP);                                                     \
-    case 8: AWQ_GEMV_LAUNCH(UU, 8, PP);                                                     \
-    default: break;                                                                         \
+    if (U == 2 && pipe) AWQ_GEMV_LAUNCH(2, 2, true);
+    if (U == 2) AWQ_GEMV_LAUNCH(2, 2, false);
+    switch (MS) {
+    case 4: if (pipe) AWQ_GEMV_LAUNCH(1, 4, true); AWQ_GEMV_LAUNCH(1, 4, false);
+    case 8: if (pipe) AWQ_GEMV_LAUNCH(1, 8, true); AWQ_GEMV_LAUNCH(1, 8, false);
+    default: if (pipe) AWQ_GEMV_LAUNCH(1, 16, true); AWQ_GEMV_LAUNCH(1, 16, false);
     }
-    switch (U) {
-    case 1:
-        if (pipe) { AWQ_GEMV_ROWS(1, true) AWQ_GEMV_LAUNCH(1, 16, true); }
-        else { AWQ_GEMV_ROWS(1, false) AWQ_GEMV_LAUNCH(1, 16, false); }
-    case 2:
-        if (pipe) { AWQ_GEMV_ROWS(2, true) AWQ_GEMV_LAUNCH(2, 16, true); }
-        else { AWQ_GEMV_ROWS(2, false) AWQ_GEMV_LAUNCH(2, 16, false); }
-    default:                                        // U == 4: never with 16 rows
-        if (pipe) { AWQ_GEMV_ROWS(4, true) }
-        else { AWQ_GEMV_ROWS(4, false) }
-    }
-#undef AWQ_GEMV_ROWS
 #undef AWQ_GEMV_LAUNCH
-    return AWQ_ERR_BAD_SHAPE;
 }
 
 }  // namespace
@@ -608,17 +585,17 @@ double awq_gemv_group_us(int bits, const GemvProblem *p, int count, int M)
 }
 
 // us of the launch of one linear at five tokens and more: tiles that a wave walks (rounds of workgroups, as the LDS admits them), and all
-// tiles.  3700 launches in 4 bits, 3600 in 3: 8 to 9 % rms.
+// tiles.  2900 launches in 4 bits, 2100 in 3: 5 to 9 % rms.
 double awq_gemv_us(int bits, int M, int N, int K)
 {
-    const int G = K / AWQ_GROUP, W = 1 << pick_log_waves(G), MS = M <= 8 ? 8 : 16;
-    int U = pick_unroll(G);
-    if (MS == 16 && U == 4) U = 2;
-    const int lds = (M + 3) / 4 * 4 * 1024 + W * MS * (U * 256 + 16);
+    const int G = K / AWQ_GROUP;
+    const GemvShape shape = gemv_shape(M, N / 16, G);
+    const int W = shape.waves, MS = M <= 8 ? 8 : 16;
+    const int lds = (M + 3) / 4 * 4 * 1024 + W * MS * 272;
     const int resident = std::max(1, std::min(160 * 1024 / lds, 16 / W));
-    const double rounds = (double)((N / 16 + 256 * resident - 1) / (256 * resident)), walk = rounds * U * ((G / U + W - 1) / W);
+    const double rounds = (double)((N / 16 + 256 * resident - 1) / (256 * resident)), walk = rounds * ((G + W - 1) / W);
     const double tiles = (double)(N / 16) * G / 1000.0;
-    if (M <= 8) return bits == 4 ? 2.03 + 0.245 * walk + (0.203 + 0.0076 * M) * tiles : 2.08 + 0.257 * walk + (0.185 + 0.006 * M) * tiles;
-    return bits == 4 ? 1.82 + 0.135 * rounds + 0.408 * walk + (0.199 + 0.0094 * M) * tiles
-                     : 2.00 + 0.025 * rounds + 0.381 * walk + (0.166 + 0.0086 * M) * tiles;
+    if (M <= 8) return bits == 4 ? 2.42 + 0.338 * walk + 0.201 * tiles : 2.44 + 0.343 * walk + 0.166 * tiles;
+    if (M <= 12) return bits == 4 ? 2.45 + 0.492 * walk + 0.232 * tiles : 2.54 + 0.468 * walk + 0.198 * tiles;
+    return bits == 4 ? 0.23 + 2.27 * rounds + 0.358 * walk + 0.244 * tiles : 0.48 + 2.04 * rounds + 0.366 * walk + 0.207 * tiles;
 }
