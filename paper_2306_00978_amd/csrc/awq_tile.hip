@@ -124,16 +124,23 @@ __device__ __forceinline__ int quotient(int a, int b, uint32_t inverse)
     return a - q * b >= b ? q + 1 : q;
 }
 
-// With `loss`: the tiles of several grid points follow each other; point i has its operands i `step` bytes and its sums
-// loss_step further.
-struct TilePoints {
+// TILE_LOSS (the scale search, 4-bit): the tiles of several grid points follow each other; point i has its operands i `step` bytes
+// and its sums loss_step further.  TILE_FEW: several linears at up to 16 tokens.  (Forms, not arguments: with `loss` tested at
+// run time a 4-bit prompt's workgroup of 80 x 48 has 1268 instructions, 228 in front of its first request, without 1067 and 185; 77 tokens
+// through 11008 x 4096 0.3 to 0.7 %.)
+enum TileForm { TILE_PLAIN, TILE_LOSS, TILE_FEW };
+template <TileForm FORM>
+struct TilePoints {};
+template <>
+struct TilePoints<TILE_LOSS> {
+    double *loss;
     int tiles;                     // of a point
     uint32_t tiles_inverse;
     int64_t step, loss_step;
 };
 
 // The tile (tile_m, tile_n) of one product; `unit` is the workgroup's number among those that read the same x.
-template <int BITS, int MT, int NT>
+template <int BITS, int MT, int NT, TileForm FORM>
 __device__ __forceinline__ void tile_work(
     const unsigned char *__restrict__ x, const unsigned char *__restrict__ qweight,
     const unsigned char *__restrict__ scales, const unsigned char *__restrict__ zeros,
@@ -158,8 +165,8 @@ __device__ __forceinline__ void tile_work(
 
     // A token tile that would reach past M is moved back to end there (more than one: M >= 16); the rows it shares with
     // its neighbour are computed twice, bit for bit alike, and stored once.
-    // (fewer than 16 rows: rows past the end repeat the last one in LDS, and are not stored)
-    auto first_row = [&](int m) { return MT == 1 ? max(min(m0, M - 16), 0) : min(m0 + 16 * m, M - 16); };
+    // (TILE_FEW, one token tile: rows past the end repeat the last one in LDS, and are not stored)
+    auto first_row = [&](int m) { return FORM == TILE_FEW ? 0 : min(m0 + 16 * m, M - 16); };
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem) + wave * wave_lds(NT);
     // packed words: tile n of the workgroup, wave-uniform; steps and zero points: one load for all tiles, lane
     // (r, c) fetching those of row r of tile c.  Ragged N repeats the last tile.  Counted in runs: K % 256 == 0
@@ -179,7 +186,7 @@ __device__ __forceinline__ void tile_work(
     uint32_t xofs[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-        xofs[i] = (MT == 1 ? min(4 * i + c, (uint32_t)(M - 1)) : 4 * i + c) * (uint32_t)(K * 2) + 16 * (r ^ (4 * i + c));
+        xofs[i] = (FORM == TILE_FEW ? min(4 * i + c, (uint32_t)(M - 1)) : 4 * i + c) * (uint32_t)(K * 2) + 16 * (r ^ (4 * i + c));
     auto issue_x = [&](int run, int m, uint32_t slot) {
         const unsigned char *p = x + ((size_t)first_row(m) * K + (size_t)run * RUN) * 2;
 #pragma unroll
@@ -344,9 +351,8 @@ __device__ __forceinline__ void tile_work(
     // Sum over the waves.  Lane (r, c) holds rows 4 c + v, column r of each 16 x 16 tile.  All tiles that fit at once: in passes
     // of three token tiles, each with a nearly empty second round of lanes, this took 3.8 thousand cycles at (5, 3), now 2.8.
     constexpr int MC = tile_pass(MT, NT), TILES = MC * NT;
-    // With `loss` (the scale search, 4-bit): nothing is stored, y holds the layer's reference outputs, and
-    // loss[workgroup] becomes the sum of the squared differences of the outputs, rounded to fp16, to them: four squared
-    // and added in fp32, the rest in fp64, in a fixed order.
+    // TILE_LOSS: nothing is stored, y holds the layer's reference outputs, and loss[workgroup] becomes the sum of the squared
+    // differences of the outputs, rounded to fp16, to them: four squared and added in fp32, the rest in fp64, in a fixed order.
     float *lds = reinterpret_cast<float *>(smem);
     double diff = 0.0;
     float *mine = lds + wave * (TILES * EXCHANGE_TILE) + 80 * c + r;
@@ -378,19 +384,19 @@ __device__ __forceinline__ void tile_work(
                 s.x += b.x; s.y += b.y; s.z += b.z; s.w += b.w;
             }
             const half2_t lo = {(half_t)s.x, (half_t)s.y}, hi = {(half_t)s.z, (half_t)s.w};
-            if (BITS == 4 && loss) {
+            if constexpr (FORM == TILE_LOSS) {
                 const uint2 ref = *reinterpret_cast<const uint2 *>(y + (size_t)m * N + n);
                 const half2_t rlo = __builtin_bit_cast(half2_t, ref.x), rhi = __builtin_bit_cast(half2_t, ref.y);
                 const float d0 = (float)lo[0] - (float)rlo[0], d1 = (float)lo[1] - (float)rlo[1];
                 const float d2 = (float)hi[0] - (float)rhi[0], d3 = (float)hi[1] - (float)rhi[1];
                 diff += (double)(d0 * d0 + d1 * d1 + d2 * d2 + d3 * d3);
-                continue;
+            } else {
+                *reinterpret_cast<uint2 *>(y + (size_t)m * N + n) =
+                    make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
             }
-            *reinterpret_cast<uint2 *>(y + (size_t)m * N + n) =
-                make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
         }
     }
-    if (BITS == 4 && loss) {
+    if constexpr (FORM == TILE_LOSS) {
 #pragma unroll
         for (int d = 1; d <= 32; d <<= 1) diff += __shfl_xor(diff, d);
         __syncthreads();                                   // the last pass has been read
@@ -412,31 +418,32 @@ struct TileGroupArgs {
     int count, M;
 };
 
-template <int BITS, int MT, int NT>
+template <int BITS, int MT, int NT, TileForm FORM>
 __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_kernel(
     const unsigned char *__restrict__ x, const unsigned char *__restrict__ qweight,
     const unsigned char *__restrict__ scales, const unsigned char *__restrict__ zeros,
     half_t *__restrict__ y, int M, int N, int K, int tiles_n, uint32_t tiles_n_inverse, uint32_t runs_inverse,
-    uint32_t runs_inverse_long, int tiles_total, double *__restrict__ loss, const TilePoints points)
+    uint32_t runs_inverse_long, int tiles_total, const TilePoints<FORM> points)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     asm volatile("" ::"s"(x), "s"(qweight), "s"(scales), "s"(zeros), "s"(y), "s"(M), "s"(N), "s"(K), "s"(tiles_n),
-                 "s"(tiles_n_inverse), "s"(runs_inverse), "s"(runs_inverse_long), "s"(tiles_total), "s"(loss));   // arguments in one round
+                 "s"(tiles_n_inverse), "s"(runs_inverse), "s"(runs_inverse_long), "s"(tiles_total));   // arguments in one round
     // contiguous ranges of tiles, token-tile-major, per XCD (own L2): see gemm_kernel
     const int per_xcd = (tiles_total + 7) >> 3;
     int unit = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
     if (unit >= tiles_total || ((int)blockIdx.x >> 3) >= per_xcd) return;
-    if (BITS == 4 && loss) {
+    double *loss = nullptr;
+    if constexpr (FORM == TILE_LOSS) {
         const int point = quotient(unit, points.tiles, points.tiles_inverse);
         unit -= point * points.tiles;
         x += point * points.step;
         qweight += point * points.step;
         scales += point * points.step;
         zeros += point * points.step;
-        loss += point * points.loss_step;
+        loss = points.loss + point * points.loss_step;
     }
     const int tile_m = quotient(unit, tiles_n, tiles_n_inverse), tile_n = unit - tile_m * tiles_n;
-    tile_work<BITS, MT, NT>(x, qweight, scales, zeros, y, M, N, K, tile_m, tile_n, unit, runs_inverse, runs_inverse_long, loss, smem);
+    tile_work<BITS, MT, NT, FORM>(x, qweight, scales, zeros, y, M, N, K, tile_m, tile_n, unit, runs_inverse, runs_inverse_long, loss, smem);
 }
 
 // Several linears at up to 16 tokens in one launch: workgroup b of a linear takes its weight tiles NT b .. + NT - 1.  A token tile
@@ -454,7 +461,7 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void tile_group_kernel(const Ti
         if (n < A.count && (int)blockIdx.x >= A.first[n]) i = n;
     const GemvProblem &P = A.p[i];
     const int tile_n = (int)blockIdx.x - A.first[i];
-    tile_work<BITS, 1, NT>((const unsigned char *)P.x, (const unsigned char *)P.q, (const unsigned char *)P.sc, (const unsigned char *)P.zp,
+    tile_work<BITS, 1, NT, TILE_FEW>((const unsigned char *)P.x, (const unsigned char *)P.q, (const unsigned char *)P.sc, (const unsigned char *)P.zp,
                            (half_t *)P.y, A.M, P.N, P.K, 0, tile_n, tile_n, A.inverse[i][0], A.inverse[i][1], nullptr, smem);
 }
 
@@ -474,7 +481,8 @@ int launch_group(const TileGroupArgs &A, int total, hipStream_t stream)
     return awq_launch_status();
 }
 
-template <int BITS, int MT, int NT>
+// (loss, count, step, loss_step: TILE_LOSS)
+template <int BITS, int MT, int NT, TileForm FORM>
 int launch_one(const void *x, const void *qweight, const void *scales, const void *zeros, void *y, int M, int N,
                int K, double *loss, int count, size_t step, size_t loss_step, hipStream_t stream)
 {
@@ -486,18 +494,19 @@ int launch_one(const void *x, const void *qweight, const void *scales, const voi
     static AwqOncePerDevice once;
     std::atomic<bool> &attr_set = once.here();
     if (lds > 64 * 1024 && !attr_set.load(std::memory_order_relaxed)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(tile_kernel<BITS, MT, NT>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(tile_kernel<BITS, MT, NT, FORM>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
             return AWQ_ERR_HIP;
         attr_set.store(true, std::memory_order_relaxed);
     }
     // a wave has G / 8 runs, or one more
     const uint32_t runs = (uint32_t)(K / RUN / TILE_WAVES);
-    tile_kernel<BITS, MT, NT><<<dim3((unsigned)((total + 7) / 8 * 8)), dim3(64 * TILE_WAVES), lds, stream>>>(
+    TilePoints<FORM> points = {};
+    if constexpr (FORM == TILE_LOSS) points = {loss, (int)tiles, 0xFFFFFFFFu / (uint32_t)tiles, (int64_t)step, (int64_t)loss_step};
+    tile_kernel<BITS, MT, NT, FORM><<<dim3((unsigned)((total + 7) / 8 * 8)), dim3(64 * TILE_WAVES), lds, stream>>>(
         (const unsigned char *)x, (const unsigned char *)qweight, (const unsigned char *)scales,
         (const unsigned char *)zeros, (half_t *)y, M, N, K, tiles_n, 0xFFFFFFFFu / (uint32_t)tiles_n,
-        0xFFFFFFFFu / (runs > 0 ? runs : 1u), 0xFFFFFFFFu / (runs + 1), (int)total, loss,
-        TilePoints{(int)tiles, 0xFFFFFFFFu / (uint32_t)tiles, (int64_t)step, (int64_t)loss_step});
+        0xFFFFFFFFu / (runs > 0 ? runs : 1u), 0xFFFFFFFFu / (runs + 1), (int)total, points);
     return awq_launch_status();
 }
 
@@ -508,25 +517,25 @@ constexpr int MTS[] = {1, 2, 3, 4, 5, 6, 8};
 // 128 x 64 does not fit the registers
 constexpr bool tile_built(int mt, int nt) { return !(mt == 8 && nt == 4); }
 
-template <int BITS, int NT>
+template <int BITS, int NT, TileForm FORM>
 TileFn pick_mt(int mt)
 {
     switch (mt) {
-    case 1: return launch_one<BITS, 1, NT>;
-    case 2: return launch_one<BITS, 2, NT>;
-    case 3: return launch_one<BITS, 3, NT>;
-    case 4: return launch_one<BITS, 4, NT>;
-    case 5: return launch_one<BITS, 5, NT>;
-    case 6: return launch_one<BITS, 6, NT>;
-    default: return launch_one<BITS, 8, NT == 4 ? 3 : NT>;      // (8, 4) is never planned
+    case 1: return launch_one<BITS, 1, NT, FORM>;
+    case 2: return launch_one<BITS, 2, NT, FORM>;
+    case 3: return launch_one<BITS, 3, NT, FORM>;
+    case 4: return launch_one<BITS, 4, NT, FORM>;
+    case 5: return launch_one<BITS, 5, NT, FORM>;
+    case 6: return launch_one<BITS, 6, NT, FORM>;
+    default: return launch_one<BITS, 8, NT == 4 ? 3 : NT, FORM>;      // (8, 4) is never planned
     }
 }
 
-template <int BITS>
+template <int BITS, TileForm FORM = TILE_PLAIN>
 TileFn pick(int mt, int nt)
 {
-    return nt == 1 ? pick_mt<BITS, 1>(mt) : nt == 2 ? pick_mt<BITS, 2>(mt) : nt == 3 ? pick_mt<BITS, 3>(mt)
-                                                                                     : pick_mt<BITS, 4>(mt);
+    return nt == 1 ? pick_mt<BITS, 1, FORM>(mt) : nt == 2 ? pick_mt<BITS, 2, FORM>(mt) : nt == 3 ? pick_mt<BITS, 3, FORM>(mt)
+                                                                                                 : pick_mt<BITS, 4, FORM>(mt);
 }
 
 }  // namespace
@@ -581,8 +590,8 @@ int awq_tile_launch_loss(const TilePlan &plan, const void *x, const void *qweigh
                          const void *y_ref, int M, int N, int K, double *loss, int points, size_t step, size_t loss_step,
                          hipStream_t stream)
 {
-    return pick<4>(plan.mt, plan.nt)(x, qweight, scales, zeros, const_cast<void *>(y_ref), M, N, K, loss, points, step, loss_step,
-                                     stream);
+    return pick<4, TILE_LOSS>(plan.mt, plan.nt)(x, qweight, scales, zeros, const_cast<void *>(y_ref), M, N, K, loss, points, step,
+                                                loss_step, stream);
 }
 
 // Linears with the longest rows first: their workgroups run longest.
