@@ -252,11 +252,16 @@ extern "C" int awq_w4a16_linear_multi(const awq_linear_desc *descs, int count, i
     }
     // More than four tokens: the kernel that takes the activations through LDS (any K) runs all
     // linears of the call in one launch.  A lone linear goes there only when it has row blocks
-    // enough for every CU (measured at N = 32000, K = 4096, 16 tokens: 21.5 us against 41 us); a
-    // smaller one stays with the batch kernel, where everything requested at once is the faster way
-    // through a small matrix (N = 4096, K = 11008: 10 us against 20 us).
-    const int st_few = awq_few_launch(4, p, count, (int)M, (hipStream_t)stream);
-    if (st_few != AWQ_GEMV_STREAM_UNFIT) return st_few;
+    // enough for every CU; a smaller one stays with the batch kernel, where everything requested at once is the faster way
+    // through a small matrix (N = 4096, K = 11008: 10 us against 20 us), or goes to the tile kernel.  Where a row of workgroups of
+    // the tile kernel, four weight tiles each, is more than one round of 256, N > 16384, a lone linear is not looked at: over 107 shapes up to
+    // 152064 features at 5 to 16 tokens the tile kernel takes 0.95 to 2.4 times as long, 1.28 on average (us, through LDS and by tiles, 16 tokens: 32000 x 4096 18.2 / 19.1,
+    // 50304 x 2048 15.6 / 22.5, 128256 x 4096 50.1 / 66.3; 5 tokens, 128256 x 8192 89.9 / 107.7), and at 16384 the faster one
+    // (16384 x 4096 14.3 / 10.9).
+    if (count > 1 || M <= 4 || p[0].N <= 16384) {
+        const int st_few = awq_few_launch(4, p, count, (int)M, (hipStream_t)stream);
+        if (st_few != AWQ_GEMV_STREAM_UNFIT) return st_few;
+    }
     static const int rows_min_count = awq_knob("AWQ_ROWS_MIN_COUNT", 2);
     // At five and six tokens a small launch is the streaming kernel's still, whose waves request all of it at
     // once (a layer of hidden size 1280 / 3840 at five tokens, 9.4 MB: 7.5 us and 10.1 through LDS; 2048 / 5632, 22 MB: 9.8
