@@ -89,6 +89,19 @@ int awq_few_launch(int bits, const GemvProblem *p, int count, int M, hipStream_t
         tiles += (double)(p[i].N / 16) * (p[i].K / AWQ_GROUP) / 1000.0;
         longest = std::max(longest, p[i].K / 1024.0);
     }
+    // Rows of 2048 columns beside longer ones of 4096 and more, all of which the streaming kernel takes, fill its batches at five and six tokens
+    // (3 bits: to eight), and it is up to a quarter faster than the fit below says: from 18 thousand tiles, in 4 bits up to its 32 MB, such a
+    // call is left to it.  us, streaming and as chosen otherwise, 5 tokens: a layer of hidden size 2048 (7936) in 4 bits 10.6 / 14.1, 2048 (5120) 9.6 /
+    // 11.1, in 3 bits 9.8 / 11.5 and, 2048 (7680), 10.2 / 14.3.  (Calls of two to seven linears: 80 above the line 0.91 times as fast on average by the
+    // estimates, 0.72 to 1.22, 36 below 1.29, at least 1.09; all rows 4096 and longer, above, 1.06.)
+    if (count > 1 && bits != 2 && M > 4 && M <= (bits == 4 ? 6 : 8) && tiles > 18.0 && (bits == 3 || tiles <= 32.8)) {
+        bool whole = true, shorter = false;
+        for (int i = 0; i < count; ++i) {
+            shorter = shorter || p[i].K == 2048;
+            whole = whole && (p[i].K == 2048 || p[i].K >= 4096) && awq_gemv_stream_fits(p[i].N, p[i].K, M);
+        }
+        if (whole && shorter && longest > 2.0) return AWQ_GEMV_STREAM_UNFIT;
+    }
     static const double fit[2][6][4] = {{{3.75, 0.137, 0.239, 0.255}, {4.11, 0.130, 0.282, 0.236}, {4.74, 0.141, 0.333, 0.284},
                                          {3.76, 0.179, 0.507, 0.174}, {4.26, 0.173, 0.595, 0.280}, {3.75, 0.112, 1.072, 0.431}},
                                         {{3.60, 0.165, 0.206, 0.194}, {4.03, 0.163, 0.228, 0.167}, {4.64, 0.156, 0.326, 0.289},
@@ -255,7 +268,7 @@ extern "C" int awq_w4a16_linear_multi(const awq_linear_desc *descs, int count, i
     // enough for every CU; a smaller one stays with the batch kernel, where everything requested at once is the faster way
     // through a small matrix (N = 4096, K = 11008: 10 us against 20 us), or goes to the tile kernel.  Where a row of workgroups of
     // the tile kernel, four weight tiles each, is more than one round of 256, N > 16384, a lone linear is not looked at: over 107 shapes up to
-    // 152064 features at 5 to 16 tokens the tile kernel takes 0.95 to 2.4 times as long, 1.28 on average (us, through LDS and by tiles, 16 tokens: 32000 x 4096 18.2 / 19.1,
+    // 152064 features at 5 to 16 tokens the tile kernel takes 0.95 to 2.4 times as long, 1.22 on average (us, through LDS and by tiles, 16 tokens: 32000 x 4096 18.2 / 19.1,
     // 50304 x 2048 15.6 / 22.5, 128256 x 4096 50.1 / 66.3; 5 tokens, 128256 x 8192 89.9 / 107.7), and at 16384 the faster one
     // (16384 x 4096 14.3 / 10.9).
     if (count > 1 || M <= 4 || p[0].N <= 16384) {
