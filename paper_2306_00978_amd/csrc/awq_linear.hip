@@ -83,11 +83,12 @@ int awq_few_launch(int bits, const GemvProblem *p, int count, int M, hipStream_t
     if (forced == 0 || !awq_few_considered(bits, count, M, count == 1 ? (int64_t)p[0].N * p[0].K : 0)) return AWQ_GEMV_STREAM_UNFIT;
     if (forced > 0 && forced < 5) return awq_tile_group_launch(bits, forced, p, count, M, stream);
     if (forced == 5) return bits == 2 ? AWQ_GEMV_STREAM_UNFIT : awq_gemv_group_launch(bits, p, count, M, stream);
-    double tiles = 0.0, blocks = 0.0, longest = 0.0;
+    double tiles = 0.0, blocks = 0.0, longest = 0.0, shortest = 1e30;
     for (int i = 0; i < count; ++i) {
         blocks += p[i].N / 16 / 256.0;
         tiles += (double)(p[i].N / 16) * (p[i].K / AWQ_GROUP) / 1000.0;
         longest = std::max(longest, p[i].K / 1024.0);
+        shortest = std::min(shortest, p[i].K / 1024.0);
     }
     // 2 bits: the estimates of short launches are half a microsecond off; below 4 thousand tiles nothing is gained (23 groups at 9 to 16 tokens 0.89 to 1.04 times
     // as fast: 1024 x 1024 with two of 128 x 1024 3.0 us and 3.4).  A lone linear is larger in any case.
@@ -98,12 +99,10 @@ int awq_few_launch(int bits, const GemvProblem *p, int count, int M, hipStream_t
     // 11.1, in 3 bits 9.8 / 11.5 and, 2048 (7680), 10.2 / 14.3.  (Calls of two to seven linears: 80 above the line 0.91 times as fast on average by the
     // estimates, 0.72 to 1.22, 36 below 1.29, at least 1.09; all rows 4096 and longer, above, 1.06.)
     if (count > 1 && bits != 2 && M > 4 && M <= (bits == 4 ? 6 : 8) && tiles > 18.0 && (bits == 3 || tiles <= 32.8)) {
-        bool whole = true, shorter = false;
-        for (int i = 0; i < count; ++i) {
-            shorter = shorter || p[i].K == 2048;
+        bool whole = shortest == 2.0 && longest > 2.0;
+        for (int i = 0; i < count; ++i)
             whole = whole && (p[i].K == 2048 || p[i].K >= 4096) && awq_gemv_stream_fits(p[i].N, p[i].K, M);
-        }
-        if (whole && shorter && longest > 2.0) return AWQ_GEMV_STREAM_UNFIT;
+        if (whole) return AWQ_GEMV_STREAM_UNFIT;
     }
     static const double fit[2][6][4] = {{{3.75, 0.137, 0.239, 0.255}, {4.11, 0.130, 0.282, 0.236}, {4.74, 0.141, 0.333, 0.284},
                                          {3.76, 0.179, 0.507, 0.174}, {4.26, 0.173, 0.595, 0.280}, {3.75, 0.112, 1.072, 0.431}},
@@ -121,7 +120,10 @@ int awq_few_launch(int bits, const GemvProblem *p, int count, int M, hipStream_t
     int nt = 1;
     const double tile = awq_tile_group_us(bits, p, count, M, &nt);
     const double batch = bits != 2 && count > 1 ? awq_gemv_group_us(bits, p, count, M) : 1e30;
-    if (std::min(tile, batch) * (tiles < 32.8 ? 1.08 : 1.15) > present) return AWQ_GEMV_STREAM_UNFIT;
+    // (2 bits, rows of different lengths: 16 %.  Of 44 such calls between the two lines 12 were slower by the tile kernel, a layer of hidden size 2048
+    // (7168) at 16 tokens 11.5 us and 14.5, of 72 beyond none.)
+    const double margin = bits == 2 && longest != shortest ? 1.16 : tiles < 32.8 ? 1.08 : 1.15;
+    if (std::min(tile, batch) * margin > present) return AWQ_GEMV_STREAM_UNFIT;
     if (count > 1) awq_note_plain_plan();
     return batch < tile ? awq_gemv_group_launch(bits, p, count, M, stream) : awq_tile_group_launch(bits, nt, p, count, M, stream);
 }

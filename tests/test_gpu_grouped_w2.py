@@ -1,4 +1,4 @@
-"""Small grouped 2-bit calls at nine tokens and more stay with the 2-bit decode kernel: as the tuning build runs them with the tile
+"""Grouped 2-bit calls at nine tokens and more that stay with the 2-bit decode kernel, small ones and layers of rows of different lengths: as the tuning build runs them with the tile
 kernel left out, bit for bit."""
 import pytest
 
@@ -7,9 +7,12 @@ from tuning_build import tuning_build
 pytestmark = pytest.mark.gpu
 
 
+LAYER = [(2048, 2048), (512, 2048), (512, 2048), (2048, 2048), (7168, 2048), (7168, 2048), (2048, 7168)]
+
+
 @pytest.mark.parametrize("M", [9, 12, 16])
-@pytest.mark.parametrize("shapes", [[(1024, 1024), (128, 1024), (128, 1024)], [(2560, 1024), (2560, 1024)], [(1792, 1792), (224, 1792), (224, 1792)]])
-def test_small_groups_by_the_decode_kernel(M, shapes):
+@pytest.mark.parametrize("shapes", [[(1024, 1024), (128, 1024), (128, 1024)], [(2560, 1024), (2560, 1024)], [(1792, 1792), (224, 1792), (224, 1792)], LAYER])
+def test_groups_by_the_decode_kernel(M, shapes):
     import torch
     import paper_2306_00978_amd as awq
     g = torch.Generator(device="cuda").manual_seed(M)
