@@ -89,11 +89,12 @@ double awq_gemv_us(int bits, int M, int N, int K);
 // Which calls are looked at at all (weights: of a lone linear).  Up to four tokens a lone linear is the single kernel's, as are small ones beyond, where a
 // call is bound by the host: from five tokens below 16 thousand tiles of 16 x 128, from nine below 4 thousand.  The 2-bit decode kernel
 // is the faster one up to eight tokens.
+constexpr int64_t FEW_LONE_WEIGHTS_5 = (int64_t)32 << 20, FEW_LONE_WEIGHTS_9 = (int64_t)8 << 20;
 inline bool awq_few_considered(int bits, int count, int M, int64_t weights)
 {
     if (awq_knob("AWQ_FEW", -1) > 0) return count <= GEMV_GROUP_MAX;
     if (bits == 2 && M <= 8) return false;
-    if (count == 1) return M > 4 && weights >= (M <= 8 ? (int64_t)32 << 20 : (int64_t)8 << 20);
+    if (count == 1) return M > 4 && weights >= (M <= 8 ? FEW_LONE_WEIGHTS_5 : FEW_LONE_WEIGHTS_9);
     return count <= GEMV_GROUP_MAX;
 }
 // The linears of a decode call by one of these two kernels, where that is the faster way; AWQ_GEMV_STREAM_UNFIT, and nothing

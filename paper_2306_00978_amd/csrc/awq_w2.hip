@@ -422,17 +422,18 @@ int launch_w2(const W2Problem *probs, int count, int M, hipStream_t stream)
 // kernel, graph replays: 1024 x 1024 at 17 / 64 / 96 rows 3.1 / 3.3 / 3.7 and 3.5 / 3.6 / 3.8; 4096 x 1024 at 32 / 48 / 64 3.6 /
 // 4.1 / 5.3 and 3.8 / 4.2 / 4.3; 2048 x 2048 at 32 / 64 3.8 / 4.7 and 4.0 / 4.5.  K of 512 and less: alike up to 33 rows, then the
 // tile kernel; 4096: alike at 17.
+// A matrix that runs so at 17 rows and more keeps the decode kernel at 16 and fewer: its prompts are those calls' results, bit for bit.
+constexpr int64_t BLOCKS_WEIGHTS = (int64_t)12 << 20;      // of all blocks, two or more
+static_assert(BLOCKS_WEIGHTS / 2 < FEW_LONE_WEIGHTS_9, "few_w2 takes such a matrix");
 bool decode_blocks(int64_t blocks, int64_t N, int64_t K)
 {
-    return !awq_tile_forced() && blocks <= 6 && K > 512 && K <= 2048 && blocks * N * K <= (int64_t)12 << 20;
+    return !awq_tile_forced() && blocks <= 6 && K > 512 && K <= 2048 && blocks * N * K <= BLOCKS_WEIGHTS;
 }
 
-// By the tile kernel, where that is the faster way; AWQ_GEMV_STREAM_UNFIT otherwise.  (Not a matrix whose longer prompts run as blocks
-// of 16 rows: their results are those of its calls with 16 rows, bit for bit.)
+// By the tile kernel, where that is the faster way; AWQ_GEMV_STREAM_UNFIT otherwise.
 int few_w2(const W2Problem *p, int count, int M, hipStream_t stream)
 {
-    if (!awq_few_considered(2, count, M, count == 1 ? (int64_t)p[0].N * p[0].K : 0) || (count == 1 && decode_blocks(2, p[0].N, p[0].K)))
-        return AWQ_GEMV_STREAM_UNFIT;
+    if (!awq_few_considered(2, count, M, count == 1 ? (int64_t)p[0].N * p[0].K : 0)) return AWQ_GEMV_STREAM_UNFIT;
     GemvProblem g[GEMV_GROUP_MAX] = {};
     for (int i = 0; i < count; ++i) {
         g[i].x = p[i].x;

@@ -42,3 +42,18 @@ def test_few_tokens(bits, few):
             for y in outs:
                 assert torch.all((y[:M].double() - ref).abs() <= bound), (M, shape)
                 assert torch.all(y[M:] == 7.0), (M, shape)
+
+
+@pytest.mark.parametrize("N,K", [(272, 1280), (80, 2048), (32, 10240)])
+def test_forced_lone_w2_is_the_tile_kernel(N, K):
+    """A lone 2-bit linear forced to the tile kernel gives that kernel's result in a group, bit for bit, whether or not its prompts run
+    as blocks of the decode kernel."""
+    import torch
+    import paper_2306_00978_amd as awq
+    g = torch.Generator(device="cuda").manual_seed(N)
+    packed = awq.awq_quantize_pack_w2((torch.randn((N, K), generator=g, device="cuda") * 0.02).half(), None)
+    x = torch.randn((16, K), generator=g, device="cuda").half()
+    pair = [torch.empty((16, N), dtype=torch.float16, device="cuda") for _ in range(2)]
+    with tuning_build(AWQ_FEW=1):
+        awq.prepare_linear_multi_w2([(x, *packed, y, N) for y in pair])()
+        assert torch.equal(awq.awq_w2a16_linear(x, *packed, N), pair[0])
