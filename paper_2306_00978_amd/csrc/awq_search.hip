@@ -392,7 +392,11 @@ extern "C" int awq_search_scale(const void *W_f16, const void *X_f16, int64_t T,
         return AWQ_ERR_MISALIGNED;
     if (workspace_bytes < search_layout(T, N, K, n_alpha, 1).total) return AWQ_ERR_WORKSPACE_TOO_SMALL;
     int points = search_points(T, N, K, n_alpha);
-    while (points > 1 && workspace_bytes < search_layout(T, N, K, n_alpha, points).total) --points;
+    // (fewer at a time: as many as fit and whose plan has room for its partial sums, as search_points() asks of its own number)
+    if (points > 1 && workspace_bytes < search_layout(T, N, K, n_alpha, points).total) {
+        do --points;
+        while (points > 1 && (workspace_bytes < search_layout(T, N, K, n_alpha, points).total || !search_product(T, N, K, points).fused));
+    }
     const SearchLayout L = search_layout(T, N, K, n_alpha, points);
     unsigned char *ws = static_cast<unsigned char *>(workspace);
     float *mean = reinterpret_cast<float *>(ws + L.mean);
@@ -408,7 +412,6 @@ extern "C" int awq_search_scale(const void *W_f16, const void *X_f16, int64_t T,
     st = dense_gemm_launch((const half_t *)X_f16, (const half_t *)W_f16, Y, (int)T, (int)N, (int)K, hs);
     if (st != AWQ_OK) return st;
     const SearchProduct P = search_product(T, N, K, points);
-    if (!P.fused) points = 1;                            // (fewer candidates at a time than search_points() had in mind)
     const int64_t chunks = T * N / 8;                    // N % 16 == 0
     // the powers of all grid points in one launch, where their place is not used for outputs
     const bool table = P.fused && L.powers < L.total;
