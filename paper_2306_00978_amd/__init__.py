@@ -246,7 +246,18 @@ def status_string(status: int) -> str:
     return load().awq_status_string(int(status)).decode()
 
 
-@functools.lru_cache(maxsize=1024)      # 1.3 us through ctypes, a third of a call that is bound by the host
+def _kept_by_shape(sizes):
+    """Sizes kept for plain ints (1.3 us through ctypes, a third of a call that is bound by the host); anything else, which may be
+    equal to an int or have no hash, is for ctypes to take or refuse."""
+    kept = functools.lru_cache(maxsize=1024)(sizes)
+
+    @functools.wraps(sizes)
+    def wrapper(N, K, group=sizes.__defaults__[0]):
+        return (kept if type(N) is int and type(K) is int and type(group) is int else sizes)(N, K, group)
+    return wrapper
+
+
+@_kept_by_shape
 def awq_packed_sizes(N: int, K: int, group: int = GROUP):
     q, s, z = ctypes.c_size_t(), ctypes.c_size_t(), ctypes.c_size_t()
     _check(load().awq_packed_sizes(N, K, group, ctypes.byref(q), ctypes.byref(s), ctypes.byref(z)),
@@ -656,7 +667,7 @@ def awq_quantize_pack_clip(W: torch.Tensor, s: torch.Tensor | None, ratios, grou
 
 # ---------------------------------------------------------------- INT3-g128 variant
 
-@functools.lru_cache(maxsize=1024)
+@_kept_by_shape
 def awq_packed_sizes_w3(N: int, K: int, group: int = GROUP):
     q, s, z = ctypes.c_size_t(), ctypes.c_size_t(), ctypes.c_size_t()
     _check(load().awq_packed_sizes_w3(N, K, group, ctypes.byref(q), ctypes.byref(s), ctypes.byref(z)),
@@ -737,7 +748,7 @@ def awq_w3a16_linear(x: torch.Tensor, qweight, scales, zeros, N: int, group: int
 GROUP_W2 = 64
 
 
-@functools.lru_cache(maxsize=1024)
+@_kept_by_shape
 def awq_packed_sizes_w2(N: int, K: int, group: int = GROUP_W2):
     q, s, z = ctypes.c_size_t(), ctypes.c_size_t(), ctypes.c_size_t()
     _check(load().awq_packed_sizes_w2(N, K, group, ctypes.byref(q), ctypes.byref(s), ctypes.byref(z)),
