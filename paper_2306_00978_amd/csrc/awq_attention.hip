@@ -126,7 +126,7 @@ __global__ __launch_bounds__(64 * WAVES) void attention_partial_kernel(
     if constexpr (!WHOLE) request(kq[BUFFERS - 1], vq[BUFFERS - 1], first + STEP * BATCH);
 
     {
-        // every wave rotates what it fetched (waves 2 and 3 discard the result): a rotation
+        // every wave rotates what it fetched (all but the first two discard the result): a rotation
         // only some waves need would have its loads moved down behind the cache rows
         float lo, hi;
         rope_pair((float)ra_h, (float)rb_h, rfreq, pos, lo, hi);
@@ -766,6 +766,17 @@ bool attention_grouped(int64_t H, int64_t Hkv, int64_t L)
     return H * L >= (G < 4 ? 110000 : G > 4 && G < 10 ? 20000 : 42000);
 }
 
+// Whether one workgroup takes a head's whole context, in one launch: up to 320 positions.  us a call from a graph, two launches and one, 8 / 8,
+// 32 / 32 and 64 / 8 heads: 100 positions 6.2 / 6.5 / 6.6 and 5.3 / 5.5 / 5.4, 200 6.6 / 6.6 / 8.2 and 6.0 / 6.2 / 7.1, 300 6.7 / 7.5 / 8.9 and
+// 6.7 / 7.4 / 8.1, 400 6.8 / 8.2 / 9.0 and 7.4 / 8.3 / 9.2 (an eager caller saves a launch besides).  Such a workgroup fills a CU: more than 256 heads
+// are a second round (272 / 17 heads at 100 and 300 positions 8.7 / 9.4 and 10.2 / 13.9, 1024 / 64 9.1 / 11.3 and 19.0 / 31.0; 256 / 256
+// 9.6 / 13.4 and 7.7 / 12.0).  Each reads its kv head's rows for itself: with nearly as many heads and 16 kv heads and more, shared by more than two heads
+// each, the grouped kernel is even from 210 positions (256 / 32 at 190 / 210 / 300 8.9 / 8.9 / 9.9 and 8.8 / 9.1 / 11.2, 192 / 16 at 255 / 319 even).
+bool attention_whole(int64_t H, int64_t Hkv, int64_t L)
+{
+    return L <= 320 && H <= 256 && (H <= 192 || Hkv < 16 || H / Hkv <= 2 || L <= 200);
+}
+
 }  // namespace
 
 extern "C" size_t awq_decode_attention_workspace_bytes(int64_t H, int64_t D, int64_t L)
@@ -807,11 +818,9 @@ extern "C" int awq_decode_attention(const void *q_f16, const void *k_f16, const 
     half_t *kc = (half_t *)k_cache_f16, *vc = (half_t *)v_cache_f16;
     float *partial = (float *)workspace;
     int st;
-    // Up to 320 positions one workgroup takes a head's whole context, in one launch.  us a call from a graph, two launches and one, 8 / 8, 32 / 32 and
-    // 64 / 8 heads: 100 positions 6.2 / 6.5 / 6.6 and 5.3 / 5.5 / 5.4, 200 6.6 / 6.6 / 8.2 and 6.0 / 6.2 / 7.1, 300 6.7 / 7.5 / 8.9 and
-    // 6.7 / 7.4 / 8.1, 400 6.8 / 8.2 / 9.0 and 7.4 / 8.3 / 9.2 (an eager caller saves a launch besides)
     const int forced = awq_knob("AWQ_ATTENTION_F", -1);      // (the tuning build: the kernel below, 0, or the number of workgroups to a slice)
-    if (forced < 0 && L <= awq_knob("AWQ_ATTENTION_WHOLE", 320)) {
+    const int whole = awq_knob("AWQ_ATTENTION_WHOLE", -1);   // (the largest L of one launch)
+    if (forced < 0 && (whole < 0 ? attention_whole(H, Hkv, L) : L <= whole)) {
         attention_partial_kernel<ATT_WHOLE_WAVES, true><<<dim3((unsigned)H, 1), dim3(64 * ATT_WHOLE_WAVES), 0, (hipStream_t)stream>>>(
             qp, kp, vp, kc, vc, (int)H, (int)Hkv, (int)Lmax, (int)pos, tab, (int)L, (half_t *)out_f16);
         return awq_launch_status();
