@@ -107,20 +107,32 @@ __global__ __launch_bounds__(64 * WAVES) void attention_partial_kernel(
     const u32x4 vnow = reinterpret_cast<const u32x4 *>(v + (size_t)g_kv * AD)[u];
     // A wave takes BATCH x 4 positions at a time, STEP apart; one batch is folded in while the next one travels.  The first ones go
     // out before anything else: they do not depend on the query, and the rotary prologue below runs meanwhile.  WHOLE: one batch of
-    // up to 512 positions, of which a wave leaves out what is not there.
+    // up to 512 positions.  A wave leaves out what is not there of its last batch, by a branch in front of a form without any for whole
+    // batches; keys travel in front of the values, so that the scores are under way while the values come.  (Slices of 80 to 144 positions with the last batch
+    // made up, keys and values in turn, and now, us: 24 / 24 heads at 1500 10.3 and 9.7, 40 / 40 at 1000 12.4 and 11.8, 48 / 24 at 1500 13.1 and 12.7; one
+    // position at a time before the batches 9.7, 11.8 and 12.5, which 32 / 32 at 511 and 3000 took 8.1 and 15.3 for, now 7.4 and 14.5.)
     constexpr int BATCH = WHOLE ? 8 : 4, BUFFERS = WHOLE ? 1 : 2, STEP = 4 * WAVES;
     u32x4 kq[BUFFERS][BATCH], vq[BUFFERS][BATCH];
     const int first = p0 + 4 * wave;                                     // wave-uniform; lane group: + grp
-    auto request = [&](u32x4 (&kr)[BATCH], u32x4 (&vr)[BATCH], int p) {
-        if (p >= p1) return;                                             // wave-uniform
+    auto request_some = [&](u32x4 (&kr)[BATCH], u32x4 (&vr)[BATCH], int p, auto all) {
+        // a row past the end reads the slice's first one and is ignored: a predicated load would be waited for on the spot
 #pragma unroll
         for (int a = 0; a < BATCH; ++a) {
-            if (WHOLE && p + STEP * a >= p1) break;
-            // a row past the end reads the slice's first one and is ignored: a predicated load would be waited for on the spot
-            const int pa = p + STEP * a + grp, pe = pa < p1 ? pa : p0;
-            kr[a] = kbase[(size_t)pe * (AD / 8)];
-            vr[a] = vbase[(size_t)pe * (AD / 8)];
+            if (!all && p + STEP * a >= p1) break;
+            const int pa = p + STEP * a + grp;
+            kr[a] = kbase[(size_t)(pa < p1 ? pa : p0) * (AD / 8)];
         }
+#pragma unroll
+        for (int a = 0; a < BATCH; ++a) {
+            if (!all && p + STEP * a >= p1) break;
+            const int pa = p + STEP * a + grp;
+            vr[a] = vbase[(size_t)(pa < p1 ? pa : p0) * (AD / 8)];
+        }
+    };
+    auto request = [&](u32x4 (&kr)[BATCH], u32x4 (&vr)[BATCH], int p) {
+        if (p >= p1) return;                                             // wave-uniform
+        if (!WHOLE && p + STEP * (BATCH - 1) < p1) request_some(kr, vr, p, std::true_type{});
+        else request_some(kr, vr, p, std::false_type{});
     };
     request(kq[0], vq[0], first);
     if constexpr (!WHOLE) request(kq[BUFFERS - 1], vq[BUFFERS - 1], first + STEP * BATCH);
@@ -180,16 +192,16 @@ __global__ __launch_bounds__(64 * WAVES) void attention_partial_kernel(
             for (int e = 0; e < 8; ++e) r.acc[e] = (float)vh[e];
         }
     }
-    auto fold = [&](const u32x4 (&kr)[BATCH], u32x4 (&vr)[BATCH], int p) {
+    auto fold_some = [&](const u32x4 (&kr)[BATCH], u32x4 (&vr)[BATCH], int p, auto all) {
         float s[BATCH], top = r.m;
 #pragma unroll
         for (int a = 0; a < BATCH; ++a) {
-            if (WHOLE && p + STEP * a >= p1) break;
+            if (!all && p + STEP * a >= p1) break;
             s[a] = row_sum(dot(kr[a]));
         }
 #pragma unroll
         for (int a = 0; a < BATCH; ++a) {
-            if (WHOLE && p + STEP * a >= p1) break;
+            if (!all && p + STEP * a >= p1) break;
             // a row past the end: weight 0, and values 0, because an infinity times 0 is NaN
             if (p + STEP * a + grp >= p1) {
                 s[a] = -__builtin_inff();
@@ -205,13 +217,17 @@ __global__ __launch_bounds__(64 * WAVES) void attention_partial_kernel(
         for (int e = 0; e < 8; ++e) r.acc[e] *= keep;
 #pragma unroll
         for (int a = 0; a < BATCH; ++a) {
-            if (WHOLE && p + STEP * a >= p1) break;
+            if (!all && p + STEP * a >= p1) break;
             const float w = __expf(s[a] - zero);
             const half8_t vh = __builtin_bit_cast(half8_t, vr[a]);
             r.l += w;
 #pragma unroll
             for (int e = 0; e < 8; ++e) r.acc[e] = __builtin_fmaf(w, (float)vh[e], r.acc[e]);
         }
+    };
+    auto fold = [&](const u32x4 (&kr)[BATCH], u32x4 (&vr)[BATCH], int p) {
+        if (!WHOLE && p + STEP * (BATCH - 1) < p1) fold_some(kr, vr, p, std::true_type{});
+        else fold_some(kr, vr, p, std::false_type{});
     };
     for (int p = first; p < p1; p += BUFFERS * STEP * BATCH) {
         fold(kq[0], vq[0], p);
