@@ -223,7 +223,7 @@ __device__ __forceinline__ void tile_work(
         issue_x(run_at(1 / MT), 1 % MT, UNIT_BYTES);
         issue_x(run_at(2 / MT), 2 % MT, 2 * UNIT_BYTES);
         uint32_t slot = 0;                                 // of the token tile being multiplied
-        u32x4 a[4];
+        uint32_t a[4][4];
         // Counting: behind a token tile that is waited for, the two after it have been requested (8 loads)
         // and, if it was itself requested before the run's weights, those as well.  A smaller count only waits longer.
         for (int i = 0; i < cnt; ++i) {
@@ -249,9 +249,14 @@ __device__ __forceinline__ void tile_work(
             issue_raw(run_at(i + 1));
             if (i == 0) {
                 wait_loads<8 + RAW_LOADS>();
+                u32x4 a0[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) a[j] = lds_read16(frag[j]);
-                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]));
+                for (int j = 0; j < 4; ++j) a0[j] = lds_read16(frag[j]);
+                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a0[0]), "+v"(a0[1]), "+v"(a0[2]), "+v"(a0[3]));
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) a[j][e] = a0[j][e];
             }
             half8_t bf[NT][4];
             float s0[NT], s1[NT];
@@ -322,7 +327,7 @@ __device__ __forceinline__ void tile_work(
                 floatx4 acc[NT];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const half8_t av = __builtin_bit_cast(half8_t, a[j]);
+                    const half8_t av = __builtin_bit_cast(half8_t, u32x4{a[j][0], a[j][1], a[j][2], a[j][3]});
 #pragma unroll
                     for (int n = 0; n < NT; ++n) {
                         if (j == 0 || (BITS == 2 && j == 2)) acc[n] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -338,8 +343,12 @@ __device__ __forceinline__ void tile_work(
                 }
                 __builtin_amdgcn_sched_barrier(0);         // the wait stays behind the multiplications
                 asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(an[0]), "+v"(an[1]), "+v"(an[2]), "+v"(an[3]));
+                // (dwords, not vectors: those the compiler copies with v_mov_b64, which one token tile cannot hide: 43 tokens through
+                // 1616 x 9472 8.9 us and 9.4 so)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) a[j] = an[j];
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) a[j][e] = an[j][e];
                 slot = next;
                 __builtin_amdgcn_sched_barrier(0);
             }
