@@ -103,7 +103,7 @@ __device__ __forceinline__ void load_batch(TileBatch<BITS, U> &b, const uint32_t
 
 // INT3 slot: pair p = 0..14 of the 16 code pairs sits in word p/5 at bits [3f, 3f+3), f = p%5,
 // of both halves; pair 15 in the top bits of the six halves.  (word >> 3f) & 0x00070007 is the
-// pair as two fp16 subnormals q * 2^-24, which the matrix core takes at full precision.
+// pair as two fp16 subnormals q * 2^-24, exactly (raised_halves below: what the matrix core makes of them).
 __device__ __forceinline__ half8_t w3_halves(const uint32_t (&w)[3], uint32_t last_pair, int j)
 {
     uint32_t t[4];
