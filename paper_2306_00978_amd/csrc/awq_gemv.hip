@@ -464,7 +464,8 @@ int gemv_group_bits(const GemvGroupArgs &A, int total, hipStream_t stream)
 
 // Waves that share a row block (a power of two) and groups per batch.  Few row blocks: sixteen waves each, so that a CU, which then has
 // one of them, has work for all its SIMDs; many: fewer waves with more groups each.  One group per batch from three tokens (two rows staged
-// by a load would be a second load), else two where a wave has more than one; four are never the faster way.  Over 4900 launches of 16 to
+// by a load would be a second load), else two where a wave has more than one; four are faster at single shapes only (sixteen waves with four groups
+// each, 3392 x 8192 at one token 5.3 us and 5.6).  Over 4900 launches of 16 to
 // 1792 row blocks and 8 to 224 groups, against four, eight and sixteen waves from 8, 24 and 64 groups and the largest batch of 4, 2 and 1 that
 // divides them: 1.08 times faster at 1 and 2 tokens, 1.10 at 4, 1.07 at 8, 1.07 at 9 and 1.14 at 16 in 4 bits, as much in 3; 1 % of
 // the launches are more than 3 % slower.  us, 1 token: 4096 x 4096 4.3 and 4.2, 3584 x 9216 7.1 and 6.4, 9216 x 3584 6.4 and 6.2;

@@ -91,8 +91,9 @@ int awq_few_launch(int bits, const GemvProblem *p, int count, int M, hipStream_t
         shortest = std::min(shortest, p[i].K / 1024.0);
     }
     // 2 bits: the estimates of short launches are half a microsecond off; below 4 thousand tiles nothing is gained (23 groups at 9 to 16 tokens 0.89 to 1.04 times
-    // as fast: 1024 x 1024 with two of 128 x 1024 3.0 us and 3.4).  A lone linear is larger in any case.
-    if (bits == 2 && tiles < 4.0) return AWQ_GEMV_STREAM_UNFIT;
+    // as fast: 1024 x 1024 with two of 128 x 1024 3.0 us and 3.4), nor by a lone linear of up to 2048 columns (10 of 5728 to 27616 features 0.93 to 1.02: 9952 x
+    // 1024 4.2 and 4.5).  A lone linear has 4 thousand tiles in any case.
+    if (bits == 2 && (tiles < 4.0 || (count == 1 && longest <= 2.0))) return AWQ_GEMV_STREAM_UNFIT;
     // Rows of 2048 columns beside longer ones of 4096 and more, all of which the streaming kernel takes, fill its batches at five and six tokens
     // (3 bits: to eight), and it is up to a quarter faster than the fit below says: from 18 thousand tiles, in 4 bits up to its 32 MB, such a
     // call is left to it.  us, streaming and as chosen otherwise, 5 tokens: a layer of hidden size 2048 (7936) in 4 bits 10.6 / 14.1, 2048 (5120) 9.6 /

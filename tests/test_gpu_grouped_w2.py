@@ -1,4 +1,4 @@
-"""Grouped 2-bit calls at nine tokens and more that stay with the 2-bit decode kernel, small ones and layers of rows of different lengths: as the tuning build runs them with the tile
+"""Grouped 2-bit calls at nine tokens and more that stay with the 2-bit decode kernel, small ones, lone linears of short rows and layers of rows of different lengths: as the tuning build runs them with the tile
 kernel left out, bit for bit."""
 import pytest
 
@@ -11,7 +11,7 @@ LAYER = [(2048, 2048), (512, 2048), (512, 2048), (2048, 2048), (7168, 2048), (71
 
 
 @pytest.mark.parametrize("M", [9, 12, 16])
-@pytest.mark.parametrize("shapes", [[(1024, 1024), (128, 1024), (128, 1024)], [(2560, 1024), (2560, 1024)], [(1792, 1792), (224, 1792), (224, 1792)], LAYER])
+@pytest.mark.parametrize("shapes", [[(1024, 1024), (128, 1024), (128, 1024)], [(2560, 1024), (2560, 1024)], [(1792, 1792), (224, 1792), (224, 1792)], [(9952, 1024)], [(7696, 1792)], LAYER])
 def test_groups_by_the_decode_kernel(M, shapes):
     import torch
     import paper_2306_00978_amd as awq
